@@ -254,6 +254,75 @@ def work(case):
     return {"bytes": b, "flops": f}
 
 
+# ---- the same in 64 bits --------------------------------------------------------------------------------------------------
+def _gram64(A, B):
+    """2 A^T B in 64 bits."""
+    G = torch.zeros((A.shape[1], B.shape[1]), dtype=torch.float64, device=DEV)
+    for t in range(0, A.shape[0], 8192):
+        a = A[t:t + 8192].double()
+        G.addmm_(a.t(), a if A is B else B[t:t + 8192].double(), alpha=2.0)
+    return G
+
+
+def _factor64(case, H):
+    """(perm, R, U) in 64 bits: R R^T is the damped matrix in sweep order with R upper triangular, U = 1 / R."""
+    d = H.shape[0]
+    diag = torch.diagonal(H)
+    perm = torch.argsort(diag, descending=True, stable=True) if case["act_order"] else torch.arange(d, device=DEV)
+    A = H.to(torch.float64, copy=True)
+    torch.diagonal(A).add_((torch.diagonal(A) == 0).double())   # a dead channel
+    torch.diagonal(A).add_(float(torch.tensor(DAMP)) * torch.diagonal(A).mean())
+    R = torch.linalg.cholesky(A[perm][:, perm].flip(0, 1)).flip(0, 1).contiguous()
+    return perm, R, torch.linalg.solve_triangular(R, torch.eye(d, dtype=torch.float64, device=DEV), upper=True)
+
+
+def _block_form(R, U):
+    """The factor in block form: U on the 128 x 128 diagonal blocks, -U_jj R_jk / R_kk behind them."""
+    F = -R / torch.diagonal(R)[None, :] * torch.diagonal(U)[:, None]
+    for b in range(0, R.shape[0], 128):
+        F[b:b + 128, b:b + 128] = U[b:b + 128, b:b + 128]
+    return F
+
+
+def _proxy64(W, a, bits, group):
+    """1/2 sum a_c (w^ - w)^2 with every group of a row rounded to its own min-max grid."""
+    top, err = 2 ** bits - 1, torch.zeros((), dtype=torch.float64, device=DEV)
+    for r in range(0, W.shape[0], 2048):
+        w = W[r:r + 2048].double().reshape(-1, W.shape[1] // group, group)
+        lo, hi = w.amin(2, keepdim=True), w.amax(2, keepdim=True)
+        s = (hi - lo) / top
+        s = torch.where(s == 0, torch.ones_like(s), s)
+        z = torch.round(-lo / s).clamp(0, top)
+        e = s * ((torch.round(w / s) + z).clamp(0, top) - z) - w
+        err += 0.5 * (e.square() * a.double().reshape(1, -1, group)).sum()
+    return err.reshape(1)
+
+
+def exact(case, seed):
+    """Gram matrices, factors, corrected targets and the proxy.  Codes, grids and what follows from them hang on how ties
+    of the rounding fall: no 64-bit value.  The factor of the widest layers takes too long."""
+    s = prepare(case, seed)
+    kind = case["kind"]
+    if kind == "sens":
+        return [_proxy64(s["W"], s["a"], bits, group) for bits, group in CANDIDATES]
+    if kind == "gram":
+        return _gram64(s["X"], s["X"])
+    if case["d_in"] > 14336 or kind == "jointq":
+        return None
+    res = {}
+    H = s["H"]
+    if kind in ("layer", "qep"):
+        X = s["X_hat"] if kind == "qep" else s["X"]
+        H = res["H"] = _gram64(X, X)
+    _, R, U = _factor64(case, H)
+    res["U"] = _block_form(R, U) if case["form"] == "block" else U
+    if kind == "qep":   # perm is the identity here
+        G = res["G"] = _gram64(s["X_hat"], s["X"])
+        W = s["W"].double()
+        res["W_star"] = W + 0.5 * (((W @ (G - H).t()) @ U.t()) @ U)
+    return res
+
+
 def tolerance(case):
     """Gram matrices and the proxy are fp32 sums (measured against 64 bits and between tile shapes: up to 4e-6; the
     proxy 7e-8).  What lies behind a column sweep also holds what a rounding tie that falls the other way does: one code
