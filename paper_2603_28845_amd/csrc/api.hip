@@ -74,11 +74,10 @@ ONECOMP_API onecomp_status onecomp_accumulate_describe(onecomp_dtype x_dtype, in
     if (!out3 || d_in <= 0 || n_tokens < 0 || ldx < d_in) return ONECOMP_ERR_INVALID_ARG;
     if (d_in % 16 != 0 || d_in > (1 << 20)) return ONECOMP_ERR_INVALID_ARG;
     GramPlanInfo info{128, 128, 1};
-    if (x_dtype == ONECOMP_BF16) {
-        const onecomp_status st = gram_accumulate_bf16(nullptr, n_tokens, d_in, ldx, nullptr, nullptr, workspace_bytes,
-                                                       nullptr, &info);
-        if (st != ONECOMP_OK) return st;
-    }
+    const onecomp_status st = x_dtype == ONECOMP_BF16 ? gram_accumulate_bf16(nullptr, n_tokens, d_in, ldx, nullptr, nullptr,
+                                                                             workspace_bytes, nullptr, &info)
+                                                      : gram_accumulate_f32(nullptr, n_tokens, d_in, ldx, nullptr, nullptr, &info);
+    if (st != ONECOMP_OK) return st;
     out3[0] = info.tile_rows;
     out3[1] = info.tile_cols;
     out3[2] = info.launches;

@@ -130,7 +130,7 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
                                     float* H, void* ws, size_t ws_bytes, hipStream_t stream,
                                     GramPlanInfo* info = nullptr);
 onecomp_status gram_accumulate_f32(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx,
-                                   float* H, hipStream_t stream);
+                                   float* H, hipStream_t stream, GramPlanInfo* info = nullptr);
 
 onecomp_status gram_cross_accumulate_bf16(const void* Xh, const void* X, int64_t n_tokens, int64_t d_in, int64_t ldxh,
                                           int64_t ldx, float* G, hipStream_t stream);

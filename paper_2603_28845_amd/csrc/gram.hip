@@ -16,7 +16,8 @@
 //     order that walks bands of 4 tile rows column by column.  The 32 workgroups that share an
 //     XCD's L2 at any time then cover a compact 4 x 8 patch of tiles (12 X panels, not 64).  A wide layer is
 //     launched one round of tiles (one per CU) at a time, so that those 32 also stay together along the tokens.
-//   * fp32 path (small layers): 128-wide tiles on v_mfma_f32_32x32x2_f32, products in fp32.
+//   * fp32 path (small layers): v_mfma_f32_32x32x2_f32, products in fp32; 32- or 64-wide tiles whose tokens eight waves
+//     share out, 128-wide tiles for wide layers with few tokens (f32_tile).
 #include "common.hpp"
 #include "planner.hpp"
 #include <stdlib.h>
@@ -733,6 +734,150 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_f32_kernel(const float* __r
     }
 }
 
+// -------------------------------------------------------------------------------------------
+// fp32 kernel for few tiles: a (32 MT) x (32 MT) tile per workgroup, its tokens cut into eight runs, one per wave.
+// Every wave accumulates the whole tile over its own tokens, so no two waves share an operand: the operands go from
+// global memory straight to registers in MFMA order (lane l: channel l % 32, token l / 32; a load reads two rows of
+// 128 bytes), no LDS and no barrier until the eight partial sums meet, added in wave order.
+// Bound by the fp32 matrix rate (157 TFLOP/s) once every CU has a tile: 253 tiles at d_in 1360 with 3001 tokens take 59 us
+// (94 TFLOP/s of the triangle; 278 us in 66 tiles of 128 x 128, each on a CU of its own), d_in 5792 with 8192 tokens
+// 129 TFLOP/s.  With the loads left to the compiler's schedule they sank to their use: 87 us instead of 59.
+// -------------------------------------------------------------------------------------------
+constexpr int F32S_WAVES = 8;
+template <int MT>
+struct F32Split {
+    static constexpr int TS = 32 * MT, PITCH = TS + 1;
+    static constexpr int KT = MT == 2 ? 16 : 32;   // tokens per load batch: 32 registers of operands, two batches
+    static constexpr size_t LDS_BYTES = size_t(F32S_WAVES) * TS * PITCH * sizeof(float);
+};
+template <int MT, bool DIAG>
+__device__ __forceinline__ void gram_f32_run(const float* __restrict__ X, int64_t t_begin, int64_t t_end, int64_t ldx,
+                                             int d_in, int i0, int k0, int lane, float16v (&acc)[MT][MT]) {
+    constexpr int STEPS = F32Split<MT>::KT / 2;
+    const int tl = lane >> 5, cl = lane & 31;
+    // byte offsets of this lane's channels in a pair of tokens; channels past the last one read it again (their sums
+    // are not stored)
+    int oa[MT], ob[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        oa[m] = int(tl * ldx + min(i0 + m * 32 + cl, d_in - 1)) * 4;
+        ob[m] = int(tl * ldx + min(k0 + m * 32 + cl, d_in - 1)) * 4;
+    }
+    struct Batch {
+        float a[STEPS][MT], b[DIAG ? 1 : STEPS][MT];
+    };
+    // A batch's address is scalar (descriptor base and offset), so the loads take no vector arithmetic; the descriptor
+    // ends with the run's last token and what lies behind reads as zero.
+    auto desc = [&](int64_t t0) __attribute__((always_inline)) {
+        const int64_t left = t0 < t_end ? ((t_end - t0 - 1) * ldx + d_in) * 4 : 0;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + (left > 0 ? t0 : 0) * ldx), 0,
+                                                 int(min(left, int64_t(0x7FFFFFFF))), 0x00020000);
+    };
+    auto load = [&](Batch& f, __amdgpu_buffer_rsrc_t rs, int s) __attribute__((always_inline)) {   // tokens 2 s, 2 s + 1
+        const int so = 2 * s * int(ldx) * 4;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            f.a[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, oa[m], so, 0));
+            if constexpr (!DIAG) f.b[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ob[m], so, 0));
+        }
+    };
+    // the products of batch f with the loads of batch `next` (tokens from t0 on) between them, a whole batch ahead of
+    // their use; the fences keep the compiler from moving the loads down to it
+    auto step = [&](const Batch& f, Batch& next, int64_t t0) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rs = desc(t0);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            load(next, rs, s);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int n = 0; n < MT; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[s][m], DIAG ? f.a[s][n] : f.b[s][n], acc[m][n], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    Batch f0, f1;
+    const __amdgpu_buffer_rsrc_t r0 = desc(t_begin);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) load(f0, r0, s);
+#pragma unroll 1
+    for (int64_t t = t_begin; t < t_end; t += 4 * STEPS) {
+        step(f0, f1, t + 2 * STEPS);
+        step(f1, f0, t + 4 * STEPS);
+    }
+}
+template <int MT>
+__global__ __launch_bounds__(64 * F32S_WAVES) void gram_f32_split_kernel(const float* __restrict__ X, int64_t n_tokens,
+                                                                         int d_in, int64_t ldx, float* __restrict__ H,
+                                                                         int n_t, int n_tiles, int chunk) {
+    extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
+    using F = F32Split<MT>;
+    float* part = reinterpret_cast<float*>(dyn_lds);   // [wave][TS][PITCH]
+    const int v = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+    if (v >= n_tiles) return;
+    int ti, tk;
+    tile_from_rank(v, n_t, ti, tk);
+    const bool diag = ti == tk;
+    const int i0 = ti * F::TS, k0 = tk * F::TS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t run = (n_tokens + 2 * F32S_WAVES - 1) / (2 * F32S_WAVES) * 2;
+    const int64_t t0 = min(n_tokens, wave * run), t1 = min(n_tokens, t0 + run);
+    float16v acc[MT][MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < MT; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
+    if (diag) gram_f32_run<MT, true>(X, t0, t1, ldx, d_in, i0, k0, lane, acc);
+    else gram_f32_run<MT, false>(X, t0, t1, ldx, d_in, i0, k0, lane, acc);
+    // register r of lane l: row (r/4)*8 + (l/32)*4 + r%4, column l%32 of a 32 x 32 tile
+    const int lr = (lane >> 5) * 4, lc = lane & 31;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < MT; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                part[(wave * F::TS + m * 32 + (r / 4) * 8 + lr + (r % 4)) * F::PITCH + n * 32 + lc] = acc[m][n][r];
+    __syncthreads();
+    // H += 2 sum along its rows, then the mirror positions along theirs, from the values kept in the first partial
+    for (int e = tid; e < F::TS * F::TS; e += 64 * F32S_WAVES) {
+        const int r = e / F::TS, c = e % F::TS, i = i0 + r, k = k0 + c;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < F32S_WAVES; ++w) sum += part[(w * F::TS + r) * F::PITCH + c];
+        if (i >= d_in || k >= d_in || (diag && i > k)) continue;
+        float* p = H + int64_t(i) * d_in + k;
+        const float nv = *p + 2.0f * sum;
+        *p = nv;
+        part[r * F::PITCH + c] = nv;
+    }
+    __syncthreads();
+    for (int e = tid; e < F::TS * F::TS; e += 64 * F32S_WAVES) {
+        const int c = e / F::TS, r = e % F::TS, i = i0 + r, k = k0 + c;
+        if (i >= d_in || k >= d_in || (diag && i >= k)) continue;
+        H[int64_t(k) * d_in + i] = part[r * F::PITCH + c];
+    }
+}
+
+template <int MT>
+onecomp_status launch_f32_split(const float* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H, hipStream_t stream) {
+    using F = F32Split<MT>;
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&gram_f32_split_kernel<MT>), int(F::LDS_BYTES), lds_ok) != ONECOMP_OK)
+        return ONECOMP_ERR_HIP;
+    const int n_t = int(ceil_div(d_in, F::TS));
+    const int n_tiles = n_t * (n_t + 1) / 2;
+    const int chunk = int(ceil_div(n_tiles, 8));
+    hipLaunchKernelGGL(gram_f32_split_kernel<MT>, dim3(unsigned(chunk * 8)), dim3(64 * F32S_WAVES), F::LDS_BYTES, stream, X,
+                       n_tokens, int(d_in), ldx, H, n_t, n_tiles, chunk);
+    ONECOMP_CHECK_LAUNCH();
+    return ONECOMP_OK;
+}
+
 template <int WT>
 onecomp_status launch_bf16(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H,
                            hipStream_t stream) {
@@ -953,8 +1098,29 @@ onecomp_status gram_cross_accumulate_bf16(const void* Xh, const void* X, int64_t
     return launch_bf16_ring<RingMid, true>(Xh, X, n_tokens, d_in, ldxh, ldx, G, nullptr, 0, stream);
 }
 
+// Which fp32 kernel a call takes, by measurement (us of a call, 128 x 128 tiles / 64 x 64 / 32 x 32 over eight token runs):
+//   d_in   512, 1024 tokens:  102 /  20 /   9      d_in 1360, 3001 tokens:  278 /  59 /  62
+//   d_in  2048, 3001 tokens:  276 / 160 / 129      d_in 2896, 8192 tokens: 1220 / 642 / 626
+//   d_in  4096, 1024 tokens:  243 / 194 / 212      d_in 4096, 8192 tokens: 1715 / 1175 / 1171
+//   d_in  8192, 1024 tokens:  712 / 765 / 840      d_in 8192, 3001 tokens: 1897 / 1826 / 1831
+// Below d_in 3072 the 32-wide tiles fill the CUs best; wide layers take 64-wide ones, which move half the operand
+// bytes; where the layer is wide and the tokens are few, reading and writing H is most of the call, and there the
+// 128-wide tiles (three workgroups per CU instead of one) are the better ones.
+static int f32_tile(int64_t n_tokens, int64_t d_in, int64_t ldx) {
+    // the token-run kernel addresses a batch of 32 tokens with 32-bit byte offsets
+    if (ldx >= (int64_t(1) << 23) || (d_in >= 8192 && n_tokens < d_in / 4)) return F32_TS;
+    return d_in < 3072 ? 32 : 64;
+}
+
 onecomp_status gram_accumulate_f32(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H,
-                                   hipStream_t stream) {
+                                   hipStream_t stream, GramPlanInfo* info) {
+    const int tile = f32_tile(n_tokens, d_in, ldx);
+    if (info) {
+        *info = GramPlanInfo{tile, tile, 1};
+        return ONECOMP_OK;
+    }
+    if (tile == 32) return launch_f32_split<1>(static_cast<const float*>(X), n_tokens, d_in, ldx, H, stream);
+    if (tile == 64) return launch_f32_split<2>(static_cast<const float*>(X), n_tokens, d_in, ldx, H, stream);
     const int n_t = int(ceil_div(d_in, F32_TS));
     const int n_tiles = n_t * (n_t + 1) / 2;
     const int chunk = int(ceil_div(n_tiles, 8));

@@ -134,6 +134,34 @@ def test_gram_ragged_shapes(d_in, n_tok, dtype):
     assert np.array_equal(Hn, Hn.T)
 
 
+@pytest.mark.parametrize("d_in,n_tok,pad,tile", [
+    # 32-wide tiles: one ragged tile, a ragged last tile, token counts around the eight runs and their batches of 32
+    (16, 1, 0, 32), (48, 7, 0, 32), (80, 255, 4, 32), (512, 257, 0, 32), (1360, 3001, 16, 32), (3056, 33, 0, 32),
+    # 64-wide tiles, batches of 16
+    (3072, 2, 0, 64), (3088, 385, 16, 64), (4112, 127, 0, 64), (8192, 2049, 0, 64),
+    # few tokens of a wide layer
+    (8208, 100, 0, 128),
+])
+def test_gram_f32_tiles(d_in, n_tok, pad, tile):
+    _announce(f"gram fp32 d_in={d_in} n_tok={n_tok} pad={pad}")
+    assert og.onecomp_accumulate_describe(torch.float32, n_tok, d_in, 0)["tile_rows"] == tile
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    # what lies between the rows and behind the last one must not be read into the sums
+    wide = torch.full((n_tok + 1, d_in + pad), float("nan"), device=DEV)
+    wide[:n_tok, :d_in] = torch.randn((n_tok, d_in), generator=g, device=DEV)
+    X = wide[:n_tok, :d_in]
+    H = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H)
+    H2 = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H2)
+    assert torch.equal(H, H2) and torch.equal(H, H.t())
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd) + 0.5
+    # n_tok fp32 additions of terms of one size: their rounding errors add up like a random walk, 2^-24 sqrt(n) of the
+    # sum's own spread; six times that, and the last rounding
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
 def test_gram_big_tiles_bf16():
     # d_in large enough for the direct-to-LDS tile kernels, several stages and a ragged token tail
     _announce("gram d_in=8192 n_tok=1055 bf16 (direct-to-LDS tiles)")
