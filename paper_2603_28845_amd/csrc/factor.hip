@@ -443,45 +443,46 @@ __device__ __forceinline__ double* wg_lds() {
 }
 
 // ------------------------------------------------------------------------------------------
-// One 128 x 128 tile (tm, tn) of batch entry z with NW waves: 4 (2 x 2 waves of 64 x 64) or 8 (2 x 4 waves of
-// 64 x 32: half the accumulators per lane, so that four waves share a SIMD and cover each other's waits).
-// tri_out: the finished tile is also left in LDS (from its start, over the dead operand slots) in the layout of
-// potrf_body (lower sub-blocks, identity beyond the matrix edge), for a diagonal tile that the same workgroup
-// factors next.
-// The operands are streamed global -> LDS directly (buffer_load ... lds) through a ring of RNS slots
-// of RK inner steps each, three stages ahead of the MFMAs: no staging registers, no LDS stores, no multiplication by
+// One T x T tile (tm, tn) of batch entry z with NW waves in two rows of NW / 2.  T = 128: 4 waves of 64 x 64, or 8 of
+// 64 x 32 (half the accumulators per lane, so that four waves share a SIMD and cover each other's waits).  T = 64: 4
+// waves of 32 x 32, for launches whose 128-wide tiles would leave CUs idle.
+// The operands are streamed global -> LDS directly (buffer_load ... lds) through a ring of NS slots
+// of RK inner steps each, NS - 1 stages ahead of the MFMAs: no staging registers, no LDS stores, no multiplication by
 // alpha on the way (alpha = +-1 is folded into the accumulators: they start as (beta / alpha) C and the result is
 // alpha acc, both exact), one barrier per stage.  A direct load deposits lane l at slot + 16 l, so rows cannot be
 // padded; the 16-byte chunks (two doubles) are permuted instead, which costs nothing on the global side because
 // every lane supplies its own address:
-//   A-form part (128 rows x RK k, a row is 64 B = 4 chunks): chunk c of row r sits at position c ^ ((r >> 2) & 3);
+//   A-form part (T rows x RK k, a row is 64 B = 4 chunks): chunk c of row r sits at position c ^ ((r >> 2) & 3);
 //     the 16 rows x 2 k that one half-wave reads for an MFMA operand then fall into 64 different banks.
-//   NN B part (RK k-rows x 128 columns, a k-row is 1 KB = 64 chunks): chunk c of k-row kr sits at c ^ ((kr & 1) << 3).
+//   NN B part (RK k-rows x T columns, a k-row is T / 2 chunks): chunk c of k-row kr sits at c ^ ((kr & 1) << 3).
 // ------------------------------------------------------------------------------------------
 
-template <bool bt, int NW>
-__device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn, const int tm, const int z,
-                                                const bool tri_out) {
-    constexpr int NJ = 16 / NW;    // 16-column MFMA tiles per wave
-    constexpr int LPW = 16 / NW;   // 1 KB loads per wave and stage: 8 for the A part, 8 for the B part
-    double* lds = wg_lds();
+template <bool bt, int NW, int T, int NS>
+__device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn, const int tm, const int z, double* lds) {
+    constexpr int NI = T / 32;          // 16-row MFMA tiles per wave (two waves share the rows)
+    constexpr int NJ = T / (8 * NW);    // 16-column MFMA tiles per wave
+    constexpr int PART_LOADS = T / 16;  // 1 KB loads of a stage's A part, and of its B part
+    constexpr int LPW = 2 * PART_LOADS / NW;
+    constexpr int PART_BYTES = T * RK * 8, STAGE_BYTES = 2 * PART_BYTES;
+    constexpr int KROW = T * 8;         // bytes of a k-row of a row-major B part
+    static_assert(PART_LOADS % NW == 0 && LPW >= 2, "a load belongs to one operand in every wave");
     const bool last = (z == g.batch - 1);
     const int m = last ? g.m_last : g.m;
     const int kdim = last ? g.k_last : g.k;
-    if (tm * GT >= m) return;
+    if (tm * T >= m) return;
     if ((g.flags & G_CLOWER) && tn > tm) return;
     const double* __restrict__ A = g.A + z * g.sa;
     const double* __restrict__ B = g.B + z * g.sb;
     double* __restrict__ C = g.C + z * g.sc;
     int k_lo = 0, k_hi = kdim;
-    if (g.flags & G_BLOWER) k_lo = tn * GT;
-    if (g.flags & G_ALOWER) k_hi = min(kdim, (tm + 1) * GT);
+    if (g.flags & G_BLOWER) k_lo = tn * T;
+    if (g.flags & G_ALOWER) k_hi = min(kdim, (tm + 1) * T);
     const int n_st = k_hi > k_lo ? (k_hi - k_lo) / RK : 0;   // inner ranges are multiples of 16
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave / (NW / 2), wc = wave % (NW / 2);
-    const int m0 = tm * GT, n0 = tn * GT;
+    const int m0 = tm * T, n0 = tn * T;
     const int cw = wc * (NJ * 16);
     const int l16 = lane & 15, lk = lane >> 4;
     const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)lds));
@@ -495,23 +496,24 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     uint32_t voff[LPW], ldst[LPW];
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
-        const int j = wave + NW * q;            // load of the stage: 0 .. 7 A part, 8 .. 15 B part (uniform per q)
-        const bool is_a = q * NW < 8;
-        const int jj = is_a ? j : j - 8;
+        const int j = wave + NW * q;            // load of the stage: first the A part, then the B part (uniform per q)
+        const bool is_a = q * NW < PART_LOADS;
+        const int jj = is_a ? j : j - PART_LOADS;
         if (is_a || bt) {
             const int row = 16 * jj + (lane >> 2);
             const int c = (lane & 3) ^ ((row >> 2) & 3);
             const bool ok = is_a ? (m0 + row < m) : (n0 + row < g.n);
             voff[q] = ok ? uint32_t((int64_t(row) * (is_a ? g.lda : g.ldb) + 2 * c) * 8) : LDS_DMA_OOB;
         } else {
-            const int kr = jj;
-            const int c = lane ^ ((kr & 1) << 3);
+            const int e = jj * 64 + lane;       // 16-byte chunk of the part
+            const int kr = e / (KROW / 16), c = (e % (KROW / 16)) ^ ((kr & 1) << 3);
             voff[q] = (n0 + 2 * c < g.n) ? uint32_t((int64_t(kr) * g.ldb + 2 * c) * 8) : LDS_DMA_OOB;
         }
-        ldst[q] = (is_a ? 0 : R_PART_BYTES) + jj * 1024;
+        ldst[q] = (is_a ? 0 : PART_BYTES) + jj * 1024;
     }
-    auto issue = [&](int st) __attribute__((always_inline)) {   // loads of stage st into its slot; past the end: zeros
-        const uint32_t slot = lds0 + uint32_t(st % RNS) * R_STAGE_BYTES;
+    // loads of stage st into a slot; past the end: zeros
+    auto issue = [&](int st, int slot_no) __attribute__((always_inline)) {
+        const uint32_t slot = lds0 + uint32_t(slot_no) * STAGE_BYTES;
         const bool live = st < n_st;
         const int64_t sk = live ? int64_t(st) : 0;
         const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
@@ -520,38 +522,38 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
             const_cast<double*>(bbase + sk * step_b), 0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
         for (int q = 0; q < LPW; ++q)
-            lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, (q * NW < 8) ? ra : rb);
+            lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, (q * NW < PART_LOADS) ? ra : rb);
     };
-    for (int st = 0; st < RNS - 1; ++st) issue(st);
+    for (int st = 0; st < NS - 1; ++st) issue(st, st);
 
     // accumulators start as (beta / alpha) C (alpha = +-1: exact); register r of lane l: row 4 r + l / 16,
     // column l % 16 of its 16 x 16 tile
     const double binit = g.beta * g.alpha;   // beta / alpha for alpha = +-1
-    double4v acc[4][NJ];
-    const bool full = (m0 + GT <= m) && (n0 + GT <= g.n);
-    double* __restrict__ ct = C + int64_t(m0 + wr * 64 + lk) * g.ldc + n0 + cw + l16;
+    double4v acc[NI][NJ];
+    const bool full = (m0 + T <= m) && (n0 + T <= g.n);
+    double* __restrict__ ct = C + int64_t(m0 + wr * (T / 2) + lk) * g.ldc + n0 + cw + l16;
     if (g.beta == 0.0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0;
     } else if (full) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = binit * ct[int64_t(i * 16 + 4 * r) * g.ldc + j * 16];
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wr * 64 + i * 16 + 4 * r + lk;
+                    const int row = m0 + wr * (T / 2) + i * 16 + 4 * r + lk;
                     const int col = n0 + cw + j * 16 + l16;
                     double c = 0.0;
                     if (row < m && col < g.n) c = binit * C[int64_t(row) * g.ldc + col];
@@ -560,37 +562,40 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     }
 
     // fragment addresses inside a stage (bytes), inner steps 0 .. 3; steps 4 .. 7: A-form ^ 32, NN + 4 KB
-    int fa[4], fb[NJ];
+    int fa[NI], fb[NJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = wr * 64 + i * 16 + l16;
+    for (int i = 0; i < NI; ++i) {
+        const int row = wr * (T / 2) + i * 16 + l16;
         fa[i] = row * 64 + (((lk >> 1) ^ ((row >> 2) & 3)) << 4) + (lk & 1) * 8;
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int col = cw + j * 16 + l16;
-        if (bt) fb[j] = R_PART_BYTES + col * 64 + (((lk >> 1) ^ ((col >> 2) & 3)) << 4) + (lk & 1) * 8;
-        else fb[j] = R_PART_BYTES + lk * 1024 + (((col >> 1) ^ ((lk & 1) << 3)) << 4) + (col & 1) * 8;
+        if (bt) fb[j] = PART_BYTES + col * 64 + (((lk >> 1) ^ ((col >> 2) & 3)) << 4) + (lk & 1) * 8;
+        else fb[j] = PART_BYTES + lk * KROW + (((col >> 1) ^ ((lk & 1) << 3)) << 4) + (col & 1) * 8;
     }
     const char* ldsc = reinterpret_cast<const char*>(lds);
 
+    int cur = 0, fill = NS - 1;   // slots of stage st and of the stage NS - 1 further on
     for (int st = 0; st < n_st; ++st) {
         // the loads of stages st + 1 and st + 2 may still be in flight: wait for those of stage st, publish them,
         // and refill the slot every wave has finished reading (stage st - 1)
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (RNS - 2)));
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NS - 2)));
         __syncthreads();
-        issue(st + RNS - 1);
-        const char* sp = ldsc + (st % RNS) * R_STAGE_BYTES;
+        issue(st + NS - 1, fill);
+        const char* sp = ldsc + cur * STAGE_BYTES;
+        fill = cur;
+        cur = cur == NS - 1 ? 0 : cur + 1;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            double a[4], b[NJ];
+            double a[NI], b[NJ];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const double*>(sp + (h ? fa[i] ^ 32 : fa[i]));
+            for (int i = 0; i < NI; ++i) a[i] = *reinterpret_cast<const double*>(sp + (h ? fa[i] ^ 32 : fa[i]));
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                b[j] = *reinterpret_cast<const double*>(sp + (bt ? (h ? fb[j] ^ 32 : fb[j]) : fb[j] + h * 4096));
+                b[j] = *reinterpret_cast<const double*>(sp + (bt ? (h ? fb[j] ^ 32 : fb[j]) : fb[j] + h * 4 * KROW));
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
@@ -601,35 +606,21 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     const double aout = g.alpha;
     if (full) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) ct[int64_t(i * 16 + 4 * r) * g.ldc + j * 16] = aout * acc[i][j][r];
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wr * 64 + i * 16 + 4 * r + lk;
+                    const int row = m0 + wr * (T / 2) + i * 16 + 4 * r + lk;
                     const int col = n0 + cw + j * 16 + l16;
                     if (row < m && col < g.n) C[int64_t(row) * g.ldc + col] = aout * acc[i][j][r];
-                }
-    }
-    if (tri_out) {   // uniform; every wave must be done with the last stage before the operand slots are overwritten
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int lrow = wr * 64 + i * 16 + 4 * r + lk, lcol = cw + j * 16 + l16;
-                    if ((lcol >> 4) > (lrow >> 4)) continue;
-                    const bool inside = (m0 + lrow < m) && (n0 + lcol < g.n);
-                    lds[tri(lrow, lcol)] = inside ? aout * acc[i][j][r] : (lrow == lcol ? 1.0 : 0.0);
                 }
     }
 }
@@ -763,15 +754,6 @@ __device__ __forceinline__ void dgemm_diag_tile(const GemmArgs& g) {
     }
 }
 
-// Tile (tm, tn), tn <= tm, of rank v in the row-major enumeration of a lower triangle of tiles.
-__device__ __forceinline__ void lower_tile_from_rank(int v, int& tm, int& tn) {
-    int r = int((__fsqrt_rn(8.0f * float(v) + 1.0f) - 1.0f) * 0.5f);
-    while (r * (r + 1) / 2 > v) --r;
-    while ((r + 1) * (r + 2) / 2 <= v) ++r;
-    tm = r;
-    tn = v - r * (r + 1) / 2;
-}
-
 // Work map of a GEMM launch: one workgroup per tile that has work, in a one-dimensional grid (workgroups that return
 // at once are not free: each still waits for its turn at a CU, and a quarter of such workgroups in a launch cost a
 // quarter of its time).  Workgroups are dispatched in rank order; with a triangular operand the tiles differ in
@@ -782,23 +764,20 @@ __device__ __forceinline__ void lower_tile_from_rank(int v, int& tm, int& tn) {
 struct GemmGrid {
     int tn_cnt, tm_full, tm_last, per_full, per_last, total;
 };
+template <int T>
 __host__ __device__ inline GemmGrid gemm_grid(const GemmArgs& g) {
     GemmGrid q;
-    q.tn_cnt = (g.n + GT - 1) / GT;
-    q.tm_full = (g.m + GT - 1) / GT;
-    q.tm_last = (g.m_last + GT - 1) / GT;
-    if (g.flags & G_CLOWER) {   // square C, lower tiles only
-        q.per_full = q.tm_full * (q.tm_full + 1) / 2;
-        q.per_last = q.tm_last * (q.tm_last + 1) / 2;
-    } else {
-        q.per_full = q.tm_full * q.tn_cnt;
-        q.per_last = q.tm_last * q.tn_cnt;
-    }
+    q.tn_cnt = (g.n + T - 1) / T;
+    q.tm_full = (g.m + T - 1) / T;
+    q.tm_last = (g.m_last + T - 1) / T;
+    q.per_full = q.tm_full * q.tn_cnt;
+    q.per_last = q.tm_last * q.tn_cnt;
     q.total = q.per_last + (g.batch - 1) * q.per_full;
     return q;
 }
+template <int T>
 __device__ __forceinline__ void gemm_tile_from_rank(const GemmArgs& g, int v, int& tm, int& tn, int& z) {
-    const GemmGrid q = gemm_grid(g);
+    const GemmGrid q = gemm_grid<T>(g);
     int rem, tm_cnt;
     if (v < q.per_last) {
         z = g.batch - 1;
@@ -810,9 +789,7 @@ __device__ __forceinline__ void gemm_tile_from_rank(const GemmArgs& g, int v, in
         rem = v / (g.batch - 1);
         tm_cnt = q.tm_full;
     }
-    if (g.flags & G_CLOWER) {
-        lower_tile_from_rank(rem, tm, tn);
-    } else if (g.flags & G_BLOWER) {   // tile columns left to right, rows fastest
+    if (g.flags & G_BLOWER) {   // tile columns left to right, rows fastest
         tn = rem / tm_cnt;
         tm = rem % tm_cnt;
     } else if (g.flags & G_ALOWER) {   // tile rows from the bottom
@@ -824,14 +801,28 @@ __device__ __forceinline__ void gemm_tile_from_rank(const GemmArgs& g, int v, in
     }
 }
 
-// Stand-alone GEMM launches run eight waves per workgroup (64 x 32 per wave, under 128 registers): four waves share a
-// SIMD and cover each other's waits (k = 128 updates: 46 -> 51 TFLOP/s; large GEMMs 64 -> 66).
-constexpr int GEMM_WAVES = 8;
-template <bool bt>
-__global__ __launch_bounds__(64 * GEMM_WAVES, 2) void dgemm_kernel(GemmArgs g) {
+// The launches of the inverse.  128-wide tiles run eight waves per workgroup (64 x 32 per wave, under 128 registers):
+// four waves share a SIMD and cover each other's waits (64 -> 66 TFLOP/s on large products against four waves).
+template <int T>
+struct GemmShape;
+template <>
+struct GemmShape<128> {
+    static constexpr int WAVES = 8, SLOTS = RNS;
+};
+template <>
+struct GemmShape<64> {
+    static constexpr int WAVES = 4, SLOTS = 6;
+};
+template <int T>
+__global__ __launch_bounds__(64 * GemmShape<T>::WAVES, 2) void dgemm_kernel(GemmArgs g) {
+    using S = GemmShape<T>;
+    __shared__ double lds[S::SLOTS * 2 * T * RK];
     int tm, tn, z;
-    gemm_tile_from_rank(g, blockIdx.x, tm, tn, z);
-    dgemm_tile_ring<bt, GEMM_WAVES>(g, tn, tm, z, false);
+    gemm_tile_from_rank<T>(g, blockIdx.x, tm, tn, z);
+    tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
+    tn = __builtin_amdgcn_readfirstlane(tn);
+    z = __builtin_amdgcn_readfirstlane(z);
+    dgemm_tile_ring<false, S::WAVES, T, S::SLOTS>(g, tn, tm, z, lds);
 }
 
 __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, double* __restrict__ V, int n,
@@ -866,7 +857,7 @@ __global__ __launch_bounds__(256, 2) void syrk_potrf_kernel(GemmArgs g, double* 
         __syncthreads();
         potrf_body(A, V, n, off, bs, info, wg_lds(), true);
     } else {
-        dgemm_tile_ring<true, 4>(g, tn, tm, 0, false);
+        dgemm_tile_ring<true, 4, GT, RNS>(g, tn, tm, 0, wg_lds());
     }
 }
 
@@ -937,9 +928,16 @@ __global__ __launch_bounds__(256) void trsm_kernel(double* __restrict__ P, int64
 
 onecomp_status dgemm(const GemmArgs& g, hipStream_t stream) {
     if (g.m <= 0 || g.n <= 0 || g.batch <= 0 || g.m_last <= 0) return ONECOMP_OK;
-    const dim3 grid(unsigned(gemm_grid(g).total), 1, 1);
-    if (g.flags & G_BTRANS) hipLaunchKernelGGL(dgemm_kernel<true>, grid, dim3(64 * GEMM_WAVES), 0, stream, g);
-    else hipLaunchKernelGGL(dgemm_kernel<false>, grid, dim3(64 * GEMM_WAVES), 0, stream, g);
+    // 128-wide tiles move half the operand bytes per flop of 64-wide ones, but a launch of few of them leaves CUs idle
+    // and ends with its longest tile (the triangular operand makes the inner ranges differ).  Whole factor, us, with
+    // 64-wide tiles in no launch / in launches of up to 256 / 1024 128-wide tiles: d_in 512: 336 / 262 / 262;
+    // 2048: 1423 / 1071 / 1070; 4096: 3103 / 2570 / 2555; 8192: 10234 / 9953 / 9602; 14336: 38.2 ms each way.
+    const int t128 = gemm_grid<128>(g).total;
+    if (t128 > 4 * device_cus()) {
+        hipLaunchKernelGGL(dgemm_kernel<128>, dim3(unsigned(t128)), dim3(64 * GemmShape<128>::WAVES), 0, stream, g);
+    } else {
+        hipLaunchKernelGGL(dgemm_kernel<64>, dim3(unsigned(gemm_grid<64>(g).total)), dim3(64 * GemmShape<64>::WAVES), 0, stream, g);
+    }
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
 }

@@ -406,6 +406,30 @@ def test_factor_against_oracle(d_in, act):
     np.testing.assert_allclose(Un @ Hp @ Un.T, np.eye(d_in), atol=2e-5)
 
 
+@pytest.mark.parametrize("d_in", [
+    144, 192, 464, 1104, 3088,   # 64-wide tiles at every level of the inverse, ragged last tiles, a short last pair
+    12304,                       # 128-wide tiles at the top level, 64-wide below
+])
+def test_factor_inverse_levels(d_in):
+    _announce(f"factor d_in={d_in}: every level of the triangular inverse")
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    X = torch.randn((d_in + 64, d_in), generator=g, device=DEV)
+    H = X.t() @ X
+    H = (torch.triu(H) + torch.triu(H, 1).t()).contiguous()
+    U, _, info = og.onecomp_hessian_factor(H, 0.01)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    Hd = H.double()
+    Hd.diagonal().add_(float(np.float32(0.01)) * Hd.diagonal().mean())
+    R = torch.linalg.cholesky(Hd.flip(0, 1)).flip(0, 1)   # Hd = R R^T, U = 1 / R
+    E = U.double() @ R
+    E.diagonal().sub_(1.0)
+    # U is rounded once to fp32: an entry of U R - 1 is a sum of products of rounding errors 2^-24 |U_ij| |R_jk|, in the
+    # norm at most 2^-24 |U| |R|; the fp64 work before it is six orders below
+    assert float(E.norm()) <= 2.0 ** -24 * float(U.double().norm() * torch.linalg.matrix_norm(R, 2 if d_in < 4000 else "fro"))
+    assert torch.all(torch.tril(U, -1) == 0.0)
+
+
 def test_factor_dead_channel_and_not_posdef():
     _announce("factor dead channel / not positive definite")
     H32 = _oracle_H32(256, 900, seed=12)
