@@ -416,7 +416,7 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
 // ------------------------------------------------------------------------------------------
 constexpr int GT = 128;  // tile side
 
-enum : int { G_BTRANS = 1, G_ALOWER = 2, G_BLOWER = 4, G_CLOWER = 8 };
+enum : int { G_BTRANS = 1, G_ALOWER = 2, G_BLOWER = 4 };
 
 struct GemmArgs {
     const double* A; int64_t lda, sa;
@@ -470,7 +470,6 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     const int m = last ? g.m_last : g.m;
     const int kdim = last ? g.k_last : g.k;
     if (tm * T >= m) return;
-    if ((g.flags & G_CLOWER) && tn > tm) return;
     const double* __restrict__ A = g.A + z * g.sa;
     const double* __restrict__ B = g.B + z * g.sb;
     double* __restrict__ C = g.C + z * g.sc;
@@ -831,31 +830,31 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A,
 }
 
 // Trailing update of one step of the blocked Cholesky together with the factorization of the next diagonal block:
-// workgroup (0, 0), the first of the grid and therefore resident from the start, computes the updated diagonal
-// tile, keeps it in LDS and factors / inverts it while the other workgroups update the rest of the trailing
-// matrix.  Takes the single-workgroup factorization off the critical path of every step whose update is longer.
-__global__ __launch_bounds__(256, 2) void syrk_potrf_kernel(GemmArgs g, double* __restrict__ A, double* __restrict__ V,
-                                                           int n, int off, int bs, int32_t* __restrict__ info) {
-    const bool first = blockIdx.x == 0;
+// workgroup 0, the first of the grid and therefore resident from the start, computes the updated diagonal
+// tile, keeps it in LDS and factors / inverts it while the other workgroups update the columns that are due.  Takes the
+// single-workgroup factorization off the critical path of every step whose update is longer.
+// A: the whole matrix; the trailing matrix begins at block row and column step + 1 and has `rest` rows.
+__global__ __launch_bounds__(256, 2) void syrk_potrf_kernel(double* __restrict__ A, double* __restrict__ V, int n,
+                                                           int step, int rest, int stride, int lag, int base,
+                                                           int32_t* __restrict__ info) {
+    const int off = (step + 1) * NB;
     int tm, tn;
-    if (g.flags & G_CLOWER) {
-        // Workgroup b runs on XCD b % 8; each XCD takes a run of consecutive ranks of the banded order (bands of eight
-        // tile columns walked row by row), so that the 64 tiles resident on an XCD at one time form a patch of about
-        // 8 x 8 and find the 16 operand panels they share in its L2 (in row-major order of the ranks the tiles of an XCD
-        // were every eighth of five tile rows; 38.4 -> 38.0 ms at d_in 14336, 265 -> 261.5 at 28672).  Rank 0 is
-        // tile (0, 0).
-        const int nt = (g.m + GT - 1) / GT, total = nt * (nt + 1) / 2, chunk = (total + 7) >> 3;
-        const int v = (int(blockIdx.x) & 7) * chunk + (int(blockIdx.x) >> 3);
-        if (v >= total) return;
-        plan::tile_from_rank_band<plan::SYRK_BAND>(v, nt, tn, tm);
-    } else {   // one block column whose first tile lies on the diagonal: one workgroup per tile row
-        tm = blockIdx.x;
-        tn = 0;
-    }
-    if (first) {
+    if (!plan::syrk_tile(blockIdx.x, plan::syrk_grid((rest + GT - 1) / GT, stride), tm, tn)) return;
+    tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
+    tn = __builtin_amdgcn_readfirstlane(tn);
+    const int k0 = __builtin_amdgcn_readfirstlane(tn == 0 ? step : plan::syrk_first_panel(tn, step, lag, base));
+    GemmArgs g{};   // C -= P P^T with P the panels k0 .. step below the diagonal block
+    g.A = A + int64_t(off) * n + k0 * NB; g.lda = n;
+    g.B = g.A; g.ldb = n;
+    g.C = A + int64_t(off) * n + off; g.ldc = n;
+    g.m = g.m_last = g.n = rest;
+    g.k = g.k_last = (step + 1 - k0) * NB;
+    g.batch = 1;
+    g.alpha = -1.0; g.beta = 1.0; g.flags = G_BTRANS;
+    if (blockIdx.x == 0) {
         dgemm_diag_tile(g);
         __syncthreads();
-        potrf_body(A, V, n, off, bs, info, wg_lds(), true);
+        potrf_body(A, V, n, off, min(NB, rest), info, wg_lds(), true);
     } else {
         dgemm_tile_ring<true, 4, GT, RNS>(g, tn, tm, 0, wg_lds());
     }
@@ -994,53 +993,27 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     const int nblk = int(ceil_div(n, NB));
     hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, stream, w.A, w.V, n, 0, min(NB, n), info);
     ONECOMP_CHECK_LAUNCH();
-    // One step: panel solve below diagonal block kb, then the trailing update fused with the factorization of the
-    // next diagonal block.  While the trailing matrix is large the steps go in pairs: the first block's update is
-    // applied to the next block column only (enough to factor and solve that one), and both blocks update everything
-    // behind the pair in one pass with k = 256: the rank-128 update is bound by reading and writing the trailing
-    // matrix (52 TFLOP/s at best, 60 with k = 256), and the additions happen in the same order, so the factor is
-    // bit-equal.  The price is the second block's factorization, which now has only a short launch to hide behind
-    // (about 70 us per pair): below PAIR_MIN_BLOCKS tile rows the saving no longer covers it.
-    auto panel_solve = [&](int off, int rest) -> onecomp_status {
+    // One step: panel solve below diagonal block s, then a trailing update fused with the factorization of diagonal
+    // block s + 1.  The next step needs block column s + 1 only, so that one is updated at once and the others every
+    // `lag` steps, by all panels solved since, in turn: a launch updates every lag-th column with k = 128 lag.  A rank-128
+    // update of everything is bound by reading and writing the trailing matrix; the lag divides these bytes while
+    // every launch keeps the same work to hide the next diagonal block behind.  The additions to a tile happen in
+    // the same order whatever the lag, so the factor is bit-equal.
+    int base = 0, lag = plan::syrk_lag(nblk);
+    for (int s = 0; s + 1 < nblk; ++s) {
+        const int off = s * NB, rest = n - off - NB;
         // A[off+NB:, off:off+NB] <- A[off+NB:, off:off+NB] * Linv_kk^T   (in place)
         hipLaunchKernelGGL(trsm_kernel, dim3(unsigned(ceil_div(rest, TR))), dim3(256), 0, stream,
                            w.A + int64_t(off + NB) * n + off, int64_t(n), rest, w.V + int64_t(off) * n + off, int64_t(n));
         ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
-    };
-    // C[c_off:, c_off : c_off + cols) -= P P^T with P = A[c_off:, k_off : k_off + k), lower tiles when cols covers the
-    // whole remainder; the first tile is the next diagonal block, factored by the same workgroup
-    auto update = [&](int c_off, int cols, int k_off, int k, bool lower) -> onecomp_status {
-        const int rows = n - c_off;
-        GemmArgs s{};
-        s.A = w.A + int64_t(c_off) * n + k_off; s.lda = n; s.sa = 0;
-        s.B = s.A; s.ldb = n; s.sb = 0;
-        s.C = w.A + int64_t(c_off) * n + c_off; s.ldc = n; s.sc = 0;
-        s.m = rows; s.m_last = rows; s.n = cols; s.k = k; s.k_last = k; s.batch = 1;
-        s.alpha = -1.0; s.beta = 1.0; s.flags = G_BTRANS | (lower ? G_CLOWER : 0);
-        const unsigned nt = unsigned(ceil_div(rows, GT));
-        const dim3 grid(lower ? 8 * ((nt * (nt + 1) / 2 + 7) / 8) : nt, 1, 1);   // tile (0, 0) first
-        hipLaunchKernelGGL(syrk_potrf_kernel, grid, dim3(256), 0, stream, s, w.A, w.V, n, c_off, min(NB, n - c_off),
-                           info);
+        const int next_lag = plan::syrk_lag(nblk - 2 - s);
+        const int stride = next_lag == lag ? lag : 1;   // where the lag changes every column is brought up to date
+        const plan::SyrkGrid q = plan::syrk_grid(nblk - 1 - s, stride);
+        hipLaunchKernelGGL(syrk_potrf_kernel, dim3(unsigned(q.total)), dim3(256), 0, stream, w.A, w.V, n, s, rest, stride,
+                           lag, base, info);
         ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
-    };
-    constexpr int PAIR_MIN_BLOCKS = 60;
-    for (int kb = 0; kb < nblk;) {
-        const int off = kb * NB;
-        const int rest = n - off - NB;     // rows below this block (only the last block can be shorter than NB,
-        if (rest <= 0) break;              // and it has nothing below it)
-        if ((st = panel_solve(off, rest)) != ONECOMP_OK) return st;
-        const int rest2 = rest - NB;       // rows below the next block
-        if (rest2 >= PAIR_MIN_BLOCKS * NB) {
-            if ((st = update(off + NB, NB, off, NB, false)) != ONECOMP_OK) return st;       // next block column only
-            if ((st = panel_solve(off + NB, rest2)) != ONECOMP_OK) return st;
-            if ((st = update(off + 2 * NB, rest2, off, 2 * NB, true)) != ONECOMP_OK) return st;   // both blocks, k = 256
-            kb += 2;
-        } else {
-            if ((st = update(off + NB, rest, off, NB, true)) != ONECOMP_OK) return st;
-            kb += 1;
-        }
+        if (stride != lag) base = s + 1;
+        lag = next_lag;
     }
 
     if (form == ONECOMP_FACTOR_BLOCK) {   // diagonal blocks of L^-1 are in V already; the rest comes from L itself

@@ -47,10 +47,73 @@ ONECOMP_HD void tile_from_rank_band(int v, int n_t, int& ti, int& tk) {
     }
 }
 ONECOMP_HD void tile_from_rank(int v, int n_t, int& ti, int& tk) { tile_from_rank_band<GRAM_BAND>(v, n_t, ti, tk); }
-// ---- factor: the lower tiles of a trailing update go through the same banded order with bands of SYRK_BAND tile
-// columns ((tn, tm) = tile_from_rank_band<SYRK_BAND>): two workgroups per CU, 64 tiles of an XCD in flight, an 8 x 8
-// patch of them shares 16 operand panels.
+// ---- factor: the tiles of a trailing update.  The trailing matrix has n_t block columns; a launch updates column 0 (its
+// first tile is the next diagonal block) and the columns 1, 1 + stride, 1 + 2 stride, ...: tiles (tm, tn), tn <= tm < n_t.
+// Workgroup 0 owns tile (0, 0), the next ones the strided columns, dealt to the XCDs in runs of consecutive ranks (bands
+// of SYRK_BAND of these columns walked row by row: two workgroups per CU, 64 tiles of an XCD in flight, an 8 x 8 patch
+// of them shares 16 operand panels), the last ones the rest of column 0.
 constexpr int SYRK_BAND = 8;
+struct SyrkGrid {
+    int n_t, stride, n_c, n_s, chunk, total;   // strided columns and their tiles, ranks per XCD, workgroups
+};
+ONECOMP_HD SyrkGrid syrk_grid(int n_t, int stride) {
+    SyrkGrid q;
+    q.n_t = n_t;
+    q.stride = stride;
+    q.n_c = n_t > 1 ? (n_t - 2) / stride + 1 : 0;
+    q.n_s = q.n_c * (n_t - 1) - stride * (q.n_c * (q.n_c - 1) / 2);
+    q.chunk = (q.n_s + 7) >> 3;
+    q.total = 1 + 8 * q.chunk + (n_t - 1);
+    return q;
+}
+// Returns false for a workgroup with nothing to do.
+ONECOMP_HD bool syrk_tile(int bid, const SyrkGrid& q, int& tm, int& tn) {
+    tn = 0;
+    tm = 0;
+    if (bid == 0) return true;
+    const int u = bid - 1;
+    if (u >= 8 * q.chunk) {
+        tm = u - 8 * q.chunk + 1;
+        return tm < q.n_t;
+    }
+    int v = (u & 7) * q.chunk + (u >> 3);
+    if (v >= q.n_s) return false;
+    for (int c0 = 0;; c0 += SYRK_BAND) {
+        const int cols = imin(SYRK_BAND, q.n_c - c0), first = 1 + q.stride * c0, rows = q.n_t - first;
+        const int steps = (cols - 1) * q.stride;   // rows that do not reach every column of the band
+        const int head = q.stride * (cols * (cols - 1) / 2), cnt = head + (rows - steps) * cols;
+        if (v >= cnt) {
+            v -= cnt;
+            continue;
+        }
+        int r, c;
+        if (v < head) {
+            int i = 1;   // columns that the row reaches
+            while (v >= q.stride * i) v -= q.stride * i++;
+            r = (i - 1) * q.stride + v / i;
+            c = v % i;
+        } else {
+            r = steps + (v - head) / cols;
+            c = (v - head) % cols;
+        }
+        tm = first + r;
+        tn = first + q.stride * c;
+        return true;
+    }
+}
+// Every column but the next one is brought up to date in every lag-th launch only, by all panels solved since: column
+// tn of the trailing matrix behind block `step` still lacks the panels [syrk_first_panel, step] (`base`: the first
+// panel after the last launch that updated every column).
+ONECOMP_HD int syrk_first_panel(int tn, int step, int lag, int base) {
+    const int k = step - (lag - tn % lag) % lag;
+    return k > base ? k : base;
+}
+// Lag while n_t block columns trail: 4 halves the bytes once more, but a launch has half as many tiles, twice as long, and
+// its last round of them costs more the fewer there are.  Per step, us, with lag 1 / 2 / 4 (d_in 28672, mean over 24
+// steps): 223 - 200 trailing: 1906 / 1618 / 1470; 151 - 128: 810 / 725 / 700; 103 - 80: 367 / 334 / 334; 79 - 56: 211 / 197 /
+// 207; 31 - 8: 48 / 46 / 50.  Lag 8: 1341, 725, 375 and 242.
+constexpr int SYRK_LAG4_MIN = 80;
+ONECOMP_HD int syrk_lag(int n_t) { return n_t >= SYRK_LAG4_MIN ? 4 : 2; }
 ONECOMP_HD int n_upper_tiles(int n_t) { return n_t * (n_t + 1) / 2; }
 
 // ---- symmetric Gram, 128 x 256 tiles: tile (i, k) = rows [128 i, +128) x columns [256 k, +256) is computed when it

@@ -38,21 +38,33 @@ static void check_simple_upper(int d_in, int ts) {
     REQUIRE(int(seen.size()) == n_tiles, "d_in %d ts %d: %zu of %d tiles owned", d_in, ts, seen.size(), n_tiles);
 }
 
-// trailing update of the blocked Cholesky: the lower tiles of a matrix of n_t tile rows through the banded order with
-// bands of SYRK_BAND, (tn, tm) = tile_from_rank_band(v), rank 0 = tile (0, 0), grid rounded up to a multiple of 8
-static void check_syrk_lower(int n_t) {
-    const int n_tiles = n_upper_tiles(n_t), chunk = int(cdiv(n_tiles, 8));
-    std::set<std::pair<int, int>> seen;
-    for (int b = 0; b < chunk * 8; ++b) {
-        const int v = (b & 7) * chunk + (b >> 3);
-        if (v >= n_tiles) continue;
-        int tn, tm;
-        tile_from_rank_band<SYRK_BAND>(v, n_t, tn, tm);
-        REQUIRE(0 <= tn && tn <= tm && tm < n_t, "syrk n_t %d rank %d -> (%d, %d)", n_t, v, tm, tn);
-        REQUIRE(b != 0 || (tm == 0 && tn == 0), "syrk n_t %d: workgroup 0 owns (%d, %d), not the diagonal tile", n_t, tm, tn);
-        REQUIRE(seen.insert({tm, tn}).second, "syrk n_t %d tile (%d, %d) owned twice", n_t, tm, tn);
+// trailing updates of the blocked Cholesky of n_blk blocks: every launch's tiles are owned once and workgroup 0 owns the
+// diagonal tile; over the steps every tile receives the panels 0 .. (its column - 1) once each and in order, and a column
+// is complete when its diagonal block and its panel solve need it
+static void check_syrk_schedule(int n_blk) {
+    std::vector<std::vector<int>> done(n_blk);   // done[i][j]: panels that tile (i, j) has received
+    for (int i = 0; i < n_blk; ++i) done[i].assign(i + 1, 0);
+    int base = 0, lag = syrk_lag(n_blk);
+    for (int s = 0; s + 1 < n_blk; ++s) {
+        const int next_lag = syrk_lag(n_blk - 2 - s), stride = next_lag == lag ? lag : 1, n_t = n_blk - 1 - s;
+        const SyrkGrid q = syrk_grid(n_t, stride);
+        std::set<std::pair<int, int>> seen;
+        for (int b = 0; b < q.total; ++b) {
+            int tm = -1, tn = -1;
+            if (!syrk_tile(b, q, tm, tn)) continue;
+            REQUIRE(0 <= tn && tn <= tm && tm < n_t, "syrk %d step %d workgroup %d -> (%d, %d)", n_blk, s, b, tm, tn);
+            REQUIRE(b != 0 || (tm == 0 && tn == 0), "syrk %d step %d: workgroup 0 owns (%d, %d)", n_blk, s, tm, tn);
+            REQUIRE(seen.insert({tm, tn}).second, "syrk %d step %d tile (%d, %d) owned twice", n_blk, s, tm, tn);
+            const int k0 = tn == 0 ? s : syrk_first_panel(tn, s, lag, base);
+            int& d = done[s + 1 + tm][s + 1 + tn];
+            REQUIRE(d == k0 && k0 <= s, "syrk %d step %d tile (%d, %d): has %d panels, next %d", n_blk, s, tm, tn, d, k0);
+            d = s + 1;
+        }
+        for (int i = s + 1; i < n_blk; ++i)
+            REQUIRE(done[i][s + 1] == s + 1, "syrk %d step %d: tile (%d, %d) incomplete", n_blk, s, i, s + 1);
+        if (stride != lag) base = s + 1;
+        lag = next_lag;
     }
-    REQUIRE(int(seen.size()) == n_tiles, "syrk n_t %d: %zu of %d tiles owned", n_t, seen.size(), n_tiles);
 }
 
 // ring kernel, symmetric: 256 x 256 tiles with the split plan, 128 x 256 tiles, or 384 x 256 tiles with the
@@ -199,7 +211,10 @@ int main() {
 #else
     const int step = 16;
 #endif
-    for (int n_t = 1; n_t <= 512; ++n_t) check_syrk_lower(n_t);   // every trailing matrix up to d_in 65536
+    for (int n_blk = 1; n_blk <= 80; ++n_blk) check_syrk_schedule(n_blk);
+#ifndef PLANNER_CHECK_THIN
+    for (int n_blk : {96, 112, 113, 160, 224, 256}) check_syrk_schedule(n_blk);   // up to d_in 32768
+#endif
     for (int d_in = 16; d_in <= 32768; d_in += step) {
         if (d_in <= 4096 || d_in % 256 == 0) {            // every width up to 4096, then every multiple of 256 (set-based checks)
             check_simple_upper(d_in, 128);
