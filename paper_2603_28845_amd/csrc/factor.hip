@@ -131,14 +131,17 @@ __global__ __launch_bounds__(256) void output_block_kernel(const double* __restr
 // The block lives in LDS as 16 x 16 sub-blocks (only those on and below the diagonal, 36 of them, row pitch 17
 // doubles, 76.5 KB: small enough for two workgroups per CU, so the factorization can share a launch with GEMM
 // tiles).  Everything but the 16 x 16 leaves runs on v_mfma_f64_16x16x4_f64 with sub-blocks as operands:
-//   Cholesky, block column J:  leaf factorization of (J,J) by wave 0 in registers (pivot and column broadcasts
-//     by DPP row_newbcast, reciprocal square roots from v_rsq_f64 + a Newton step), which leaves T = L_JJ^-1 in the
+//   Cholesky, block column J:  leaf factorization of (J,J) by wave 0 in registers, which leaves T = L_JJ^-1 in the
 //     sub-block's place;  L_IJ = A_IJ T^T for the sub-blocks below;  A_IK -= L_IJ L_KJ^T for J < K <= I, of which
 //     wave 0 takes (J+1, J+1) alone and goes straight on to the next leaf while the other waves do the rest.
-//   Inverse:  the diagonal sub-blocks hold their inverses already; recursive doubling over aligned pairs of
-//     s = 16, 32, 64:  X[C,A] = -X[C,C] (L[C,A] X[A,A]), both products in place: the first by sub-block rows
-//     (a wave holds its row of L[C,A] in registers while it overwrites it), the second by sub-block columns.
-//     Every level has exactly four row / column tasks: one per wave.
+//   Inverse X = L^-1, beside it: once column K of L is behind the updates, P_IC += L_IK X_KC (C < K) and
+//     P_IK = L_IK X_KK in place of L_IK, for the rows I > K;  when all columns left of row R are in,
+//     X_RC = -T_R P_RC.  Row by row this runs one column behind the Cholesky on the waves that are not in a leaf, and
+//     every finished row goes to V at once; only the last two rows are left when the last leaf is done.
+// The whole is a chain of latencies on one CU, exposed in every step with a short trailing update (d_in 4096: most of
+// them), so what counts is what stands between two pivots.  Leaves with square roots on that chain (and two moves per
+// broadcast), with the inverse behind the last column: leaf 2.3 -> 1.2 us, a block alone in its launch 49.7 ->
+// 31 us.
 // MFMA operand layouts (lane l): A[i][k]: i = l % 16, k = l / 16;  B[k][j]: k = l / 16, j = l % 16;
 // C/D register r: row 4 r + l / 16, column l % 16.
 // ------------------------------------------------------------------------------------------
@@ -153,23 +156,37 @@ __device__ __forceinline__ int tri(int r, int c) {   // element (r, c), c / 16 <
 }
 __device__ __forceinline__ int sub(int I, int J) { return ((I * (I + 1)) / 2 + J) * SBS; }   // J <= I
 
-// 1 / sqrt(p): v_rsq_f64 is good to 5e-8 relative (measured over 120 binades), one Newton step brings it to 4e-15.
-// That is what scales a column of the factor; the diagonal entry itself gets a further correction step where it is
-// computed.  The step sits on the dependency chain of every pivot, so there is exactly one.
+// 1 / sqrt(p): v_rsq_f64 is good to 5e-8 relative (measured over 120 binades), the first Newton step brings it to 4e-15,
+// the second to rounding.
 __device__ inline double rsqrt_refined(double p) {
     double y = __builtin_amdgcn_rsq(p);
     const double h = 0.5 * p;
     y = y * __builtin_fma(-h * y, y, 1.5);
+    y = y * __builtin_fma(-h * y, y, 1.5);
     return y;
 }
 
+// DPP row_newbcast:J (lane J of every 16-lane row) is the one DPP form of 64-bit instructions; hipcc's builtin offers it
+// for 32 bits only, which costs two moves per broadcast instead of none.  A DPP operand must not have been written by
+// the two instructions before: the compiler does not look into these statements, so they keep that distance themselves
+// (s_nop 1) where the operand is fresh, and are volatile, that is, stay in order.
+// c += (lane J of b) * m.  FRESH: b may come from the instruction before.
+template <int J, bool FRESH>
+__device__ __forceinline__ void fma_bcast16(double& c, double b, double m) {
+    if constexpr (FRESH)
+        asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                     : "+v"(c) : "v"(b), "v"(m), "n"(J));
+    else
+        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                     : "+v"(c) : "v"(b), "v"(m), "n"(J));
+}
 // value of lane J of every 16-lane row, in all lanes of the row
 template <int J>
 __device__ __forceinline__ double bcast16(double v) {
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_update_dpp(0, lo, 0x150 + J, 0xF, 0xF, true);   // row_newbcast:J
-    hi = __builtin_amdgcn_update_dpp(0, hi, 0x150 + J, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
+    double o;
+    asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+                 : "=v"(o) : "v"(v), "n"(J));
+    return o;
 }
 
 template <int I, int N, typename F>
@@ -180,32 +197,22 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-// Inverse of a 16 x 16 lower-triangular block by one wave, all in registers.  Every 16-lane row of the wave holds
-// the block (lane i of each row: row i of L in r[], entries above the diagonal arbitrary, 1 / L_ii in rdi); row q
-// of lanes computes the columns c = 4 k + q of L^-1, so lane (q, i) returns X[i][4 k + q] in x[k], k = 0 .. 3.
-// With L = Lh D (Lh = columns of L divided by their diagonal entries, unit diagonal) L^-1 = D^-1 Lh^-1: the rows of
-// Z = Lh^-1 follow without divisions, z_m = e_m - sum_{k<m} Lh[m][k] z_k, row m being final once rows 0 .. m-1 have
-// been eliminated from it and then broadcast inside each 16-lane row (DPP row_newbcast) to the lanes below; the
-// scaling by 1 / L_ii at the end is local to the lane.  Entries of Lh on and above the diagonal are set to zero
-// beforehand, so the elimination needs no per-step predicates: 40 broadcast + FMA pairs, no memory traffic.
-__device__ __forceinline__ void tri_inverse16(const double (&r)[SBW], const double rdi, const int i, const int q,
+// D^-1/2 Lh^-1 for a 16 x 16 unit lower-triangular Lh by one wave, all in registers.  Lane i of each 16-lane row of the
+// wave holds row i of -Lh in nlh[] (zero on and above the diagonal) and D_i^-1/2 in rdi; row q of lanes computes the
+// columns c = 4 k + q, so lane (q, i) returns X[i][4 k + q] in x[k], k = 0 .. 3.  The rows of Z = Lh^-1 follow without
+// divisions, z_m = e_m - sum_{k<m} Lh[m][k] z_k: row m is final once rows 0 .. m-1 have been eliminated from it and is
+// then broadcast inside each 16-lane row to the lanes below.
+__device__ __forceinline__ void tri_inverse16(const double (&nlh)[SBW], const double rdi, const int i, const int q,
                                               double (&x)[4]) {
-    double lh[SBW];
-    static_for<0, SBW>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        const double rdm = bcast16<m>(rdi);
-        lh[m] = (i > m) ? r[m] * rdm : 0.0;
-    });
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = (4 * k + q == i) ? 1.0 : 0.0;
     static_for<0, SBW - 1>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
-        static_for<0, m / 4 + 1>([&](auto kc) {   // columns beyond m are still zero in row m: harmless
+        // columns beyond m are still zero in row m; the first statement keeps the distance for all of them
+        static_for<0, m / 4 + 1>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
-            const double zm = bcast16<m>(x[k]);
-            x[k] = __builtin_fma(-lh[m], zm, x[k]);
+            fma_bcast16<m, k == 0>(x[k], x[k], nlh[m]);
         });
-        __builtin_amdgcn_sched_barrier(0);   // keeps the scheduler from issuing later rows' broadcasts early (registers)
     });
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] *= rdi;
@@ -213,7 +220,7 @@ __device__ __forceinline__ void tri_inverse16(const double (&r)[SBW], const doub
 
 // S: POTRF_LDS_DOUBLES doubles of LDS.  preloaded: the block (lower sub-blocks, identity padding beyond bs) is
 // already in S and a barrier has been passed.
-__device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __restrict__ V, int n, int off, int bs,
+__device__ __forceinline__ void potrf_body(const double* __restrict__ A, double* __restrict__ V, int n, int off, int bs,
                                            int32_t* __restrict__ info, double* S, bool preloaded) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -232,9 +239,7 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
     auto frag_rowk = [&](const double* M, int q) __attribute__((always_inline)) {   // M[l%16][4q + l/16]
         return M[l16 * SBP + 4 * q + lk];
     };
-    auto frag_krow = [&](const double* M, int q) __attribute__((always_inline)) {   // M[4q + l/16][l%16]
-        return M[(4 * q + lk) * SBP + l16];
-    };
+    // M[4 r + l/16][l%16], r = 0..3: the accumulator layout and, register r for k-step r, also that of a B operand
     auto load_c = [&](const double* M) __attribute__((always_inline)) {
         double4v c;
 #pragma unroll
@@ -245,170 +250,222 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
 #pragma unroll
         for (int r = 0; r < 4; ++r) M[(4 * r + lk) * SBP + l16] = c[r];
     };
+    // c + sign A B, A by its row fragments, B in accumulator layout
+    auto mul_add = [&](const double* MA, const double4v& b, double4v c, double sign) __attribute__((always_inline)) {
+        double a[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = sign * frag_rowk(MA, q);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
+        return c;
+    };
+    const double4v zero4 = {0.0, 0.0, 0.0, 0.0};
+    // sub-block (I, J) of the inverse to V: a store instruction writes four 128-byte row segments
+    auto out = [&](int I, int J, const double4v& c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
+            if (row < bs && col < bs) V[int64_t(off + row) * n + off + col] = c[r];
+        }
+    };
 
     // ---------------- Cholesky, 8 block columns of 16 ----------------
     // Leaf of block column J: wave 0 factors the diagonal sub-block in registers (lane i (mod 16) = row i; lanes
-    // 16..63 shadow lanes 0..15) and leaves its INVERSE in the sub-block's place: the panel solves below and the
-    // inversion of the whole block need T = L_JJ^-1, nothing reads L_JJ itself.
+    // 16..63 shadow lanes 0..15) as Lh D Lh^T and leaves its inverse factor T = D^-1/2 Lh^-1 in the sub-block's place: the
+    // panel solves below and the inversion of the whole block need that, nothing reads L_JJ itself.
+    // From one pivot to the next: one update, its broadcast, v_rcp_f64 with a Newton step (the raw column is
+    // broadcast, not the scaled one, so nothing else waits for the reciprocal), the scaling.  The updates of the other
+    // columns are issued behind the instructions of that chain.
     auto leaf = [&](int J) __attribute__((always_inline)) {
         double* DJ = S + sub(J, J);
         const int i = l16;
         // Entries above the diagonal (c > i) are carried along unmasked: they never reach a valid entry (a
         // broadcast of column j takes lane c >= j).  The first bad pivot is remembered in a register, so the 16
         // steps form one straight-line block.
-        double r[SBW];
-        double my_dinv = 1.0;
+        double r[SBW], nlh[SBW];
+        double my_d = 1.0;
         int bad_at = -1;
 #pragma unroll
         for (int c = 0; c < SBW; ++c) r[c] = DJ[i * SBP + c];
+        double p = bcast16<0>(r[0]);           // pivot, the same in every lane
+        double y = __builtin_amdgcn_rcp(p);
+        y = __builtin_fma(y, __builtin_fma(-p, y, 1.0), y);
         static_for<0, SBW>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            double p = bcast16<j>(r[j]);           // pivot, the same in every lane
-            const bool bad = !(p > 0.0);
-            if (bad) p = 1.0;
+            const bool bad = !(p > 0.0);       // replaced by 1
             bad_at = (bad && bad_at < 0) ? j : bad_at;
-            const double ri = rsqrt_refined(p);
-            double sq = p * ri;
-            sq = __builtin_fma(0.5 * ri, __builtin_fma(-sq, sq, p), sq);
-            const double lij = (i == j) ? sq : r[j] * ri;   // column j on and below the pivot
-            r[j] = lij;
-            if (i == j) my_dinv = ri;
-            static_for<j + 1, SBW>([&](auto cc) {
-                constexpr int c = decltype(cc)::value;
-                const double lcj = bcast16<c>(lij);
-                r[c] = __builtin_fma(-lij, lcj, r[c]);
-            });
+            my_d = (i == j && !bad) ? p : my_d;
+            const double nm = bad ? -r[j] : -(r[j] * y);
+            nlh[j] = (i > j) ? nm : 0.0;
+            if constexpr (j + 1 < SBW) {
+                fma_bcast16<j + 1, false>(r[j + 1], r[j], nm);   // r[j] was last written before p was broadcast
+                p = bcast16<j + 1>(r[j + 1]);
+                y = __builtin_amdgcn_rcp(p);
+                constexpr int rest = SBW - 2 - j, third = (rest + 2) / 3;
+                auto updates = [&](auto lo, auto hi) __attribute__((always_inline)) {
+                    static_for<decltype(lo)::value, decltype(hi)::value>([&](auto cc) {
+                        constexpr int c = decltype(cc)::value;
+                        fma_bcast16<c, false>(r[c], r[j], nm);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                constexpr int c0 = j + 2, c1 = c0 + third < SBW ? c0 + third : SBW, c2 = c1 + third < SBW ? c1 + third : SBW;
+                __builtin_amdgcn_sched_barrier(0);
+                updates(std::integral_constant<int, c0>{}, std::integral_constant<int, c1>{});
+                const double e = __builtin_fma(-p, y, 1.0);
+                updates(std::integral_constant<int, c1>{}, std::integral_constant<int, c2>{});
+                y = __builtin_fma(y, e, y);
+                updates(std::integral_constant<int, c2>{}, std::integral_constant<int, SBW>{});
+            }
         });
         if (bad_at >= 0 && tid == 0 && *info == 0) *info = off + J * SBW + bad_at + 1;
-        // T = L_JJ^-1 from the rows still in registers (all four 16-lane rows hold them); every lane has read its
-        // row before any lane overwrites the sub-block (one wave: program order); zeros above the diagonal
+        // every lane has read its row before any lane overwrites the sub-block (one wave: program order); zeros above
+        // the diagonal
         double x[4];
-        tri_inverse16(r, my_dinv, i, lk, x);
+        tri_inverse16(nlh, rsqrt_refined(my_d), i, lk, x);
 #pragma unroll
         for (int k = 0; k < 4; ++k) DJ[i * SBP + 4 * k + lk] = x[k];
     };
-    // A_IK -= L_IJ L_KJ^T for the pair p of the sub-blocks below J (row-major over the triangle, kk <= ii)
-    auto update_pair = [&](int J, int p) __attribute__((always_inline)) {
-        int ii = 0;
-        while ((ii + 1) * (ii + 2) / 2 <= p) ++ii;
-        const int kk = p - ii * (ii + 1) / 2;
-        const int I = J + 1 + ii, K = J + 1 + kk;
-        double* M = S + sub(I, K);
-        const double* LI = S + sub(I, J);
-        const double* LK = S + sub(K, J);
-        double4v c = load_c(M);
+    // N products with the same left operand, side by side: one after the other a product is a chain of LDS reads, four
+    // dependent MFMAs and an LDS write.
+    // A_IK -= L_IJ L_KJ^T for K = K0 .. K0 + N - 1
+    auto update_row = [&](auto nc, int I, int J, int K0) __attribute__((always_inline)) {
+        constexpr int N = decltype(nc)::value;
+        double a[4], b[N][4];
+        double4v c[N];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = -frag_rowk(S + sub(I, J), q);
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[u][q] = frag_rowk(S + sub(K0 + u, J), q);
+            c[u] = load_c(S + sub(I, K0 + u));
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            c = __builtin_amdgcn_mfma_f64_16x16x4f64(-frag_rowk(LI, q), frag_rowk(LK, q), c, 0, 0, 0);
-        store_c(M, c);
+#pragma unroll
+            for (int u = 0; u < N; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[u][q], c[u], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < N; ++u) store_c(S + sub(I, K0 + u), c[u]);
+    };
+    // P_IC += L_IK X_KC for C = C0 .. C0 + N - 1; a = L_IK, in whose place P_IK = L_IK X_KK comes last
+    auto inverse_row = [&](auto nc, int I, int K, int C0, const double (&a)[4]) __attribute__((always_inline)) {
+        constexpr int N = decltype(nc)::value;
+        double4v b[N], c[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            b[u] = load_c(S + sub(K, C0 + u));
+            c[u] = load_c(S + sub(I, C0 + u));
+            if (u == N - 1 && C0 + u == K) c[u] = zero4;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int u = 0; u < N; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[u][q], c[u], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < N; ++u) store_c(S + sub(I, C0 + u), c[u]);
+    };
+    auto in_fours = [&](int n, auto&& f) __attribute__((always_inline)) {   // f(count, first) over 0 .. n - 1
+        int k = 0;
+        for (; k + 4 <= n; k += 4) f(std::integral_constant<int, 4>{}, k);
+        switch (n - k) {
+            case 3: f(std::integral_constant<int, 3>{}, k); break;
+            case 2: f(std::integral_constant<int, 2>{}, k); break;
+            case 1: f(std::integral_constant<int, 1>{}, k); break;
+            default: break;
+        }
     };
     // The leaves are a chain of latencies on one wave (16 dependent pivots each, then the 16 x 16 inverse), so the
-    // next leaf runs beside the update it does not depend on: after the panel solve of column J, wave 0 updates the
-    // next diagonal sub-block alone and factors it at once, while the other three waves update the rest.
-    if (wave == 0) leaf(0);
+    // next leaf runs beside the updates it does not depend on: after the panel solve of column J, wave 0 updates the
+    // next diagonal sub-block alone and factors it at once, while the other three waves do the rest.
+    if (wave == 0) {
+        leaf(0);
+    } else {   // what the inverse has above its diagonal sub-blocks: nobody waits for these stores
+        for (int t = wave - 1; t < NSB * (NSB - 1) / 2; t += 3) {
+            int J = 1;
+            while (J * (J + 1) / 2 <= t) ++J;
+            out(t - J * (J - 1) / 2, J, zero4);
+        }
+    }
     __syncthreads();
 #pragma unroll 1
     for (int J = 0; J < NSB - 1; ++J) {
         const double* TJ = S + sub(J, J);
-        // L_IJ = A_IJ T^T for I > J (in place: the wave holds A_IJ's fragments before it writes)
-        for (int I = J + 1 + wave; I < NSB; I += 4) {
-            double* M = S + sub(I, J);
-            double a[4];
+        // L_IJ = A_IJ T^T for I > J, then row R = J - 1 of the inverse: seven products, two per wave side by side (both
+        // in place: the operands are in registers before anything is written)
+        {
+            double a[2][4];
+            double4v b[2], c[2] = {zero4, zero4};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = frag_rowk(M, q);
-            double4v c = {0.0, 0.0, 0.0, 0.0};
+            for (int u = 0; u < 2; ++u) {
+                const int I = J + 1 + min(wave + 4 * u, NSB - 2), R = J - 1, C = I - NSB;
+                if (I < NSB) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], frag_rowk(TJ, q), c, 0, 0, 0);
-            store_c(M, c);
+                    for (int q = 0; q < 4; ++q) {
+                        a[u][q] = frag_rowk(S + sub(I, J), q);
+                        b[u][q] = frag_rowk(TJ, q);
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) a[u][q] = -frag_rowk(S + sub(R, R), q);
+                    b[u] = load_c(S + sub(R, C));
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][q], b[u][q], c[u], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int t = wave + 4 * u, I = J + 1 + t, R = J - 1, C = I - NSB;
+                if (t > NSB - 2) continue;
+                if (I < NSB) {
+                    store_c(S + sub(I, J), c[u]);
+                } else if (C < R) {
+                    store_c(S + sub(R, C), c[u]);
+                    out(R, C, c[u]);
+                } else {
+                    out(R, R, b[u]);
+                }
+            }
         }
         __syncthreads();
-        const int nr = NSB - 1 - J;                 // sub-block rows below J
-        const int np = nr * (nr + 1) / 2;
         if (wave == 0) {
-            update_pair(J, 0);                      // the next diagonal sub-block
+            update_row(std::integral_constant<int, 1>{}, J + 1, J, J + 1);   // the next diagonal sub-block
             leaf(J + 1);
         } else {
-            for (int p = wave; p < np; p += 3) update_pair(J, p);
-        }
-        __syncthreads();
-    }
-    // L_kk itself is not written back to A: nothing reads the diagonal blocks of L afterwards (the panel solve, the
-    // triangular inverse and the block-form output take L_kk^-1 from V; the trailing updates and the off-diagonal
-    // blocks of the inverse and of the block form read only blocks below the block diagonal).
-    (void)A;
-
-    // ---------------- X = L^-1 in place ----------------
-    // the diagonal sub-blocks hold their inverses already
-    // recursive doubling: ns = sub-blocks per side of a pair
-    static_for<0, 3>([&](auto lc) {
-        constexpr int ns = 1 << decltype(lc)::value;     // 1, 2, 4
-        const int pr = wave / ns, t = wave % ns;         // pair and row / column task of this wave
-        const int a0 = pr * 2 * ns, c0 = a0 + ns;        // first sub-block of A and of C
-        {   // T = L[C,A] X[A,A], sub-block row I = c0 + t, in place
-            const int I = c0 + t;
-            double a[ns][4];
+            // Rows dealt from the last one back and forth over the three waves: row I has I products (I - J updates, J of
+            // the inverse; the first two rows have fewer), at most nine a wave.
+            for (int m = 0; m < NSB - J; ++m) {
+                const int I = NSB - 1 - m, turn = m % 6;
+                if ((turn < 3 ? turn : 5 - turn) != wave - 1) continue;
+                if (I > J + 1)
+                    in_fours(I - J, [&](auto nc, int k) __attribute__((always_inline)) { update_row(nc, I, J, J + 1 + k); });
+                if (J > 0) {
+                    double a[4];
 #pragma unroll
-            for (int kb = 0; kb < ns; ++kb)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) a[kb][q] = frag_rowk(S + sub(I, a0 + kb), q);
-#pragma unroll
-            for (int jb = 0; jb < ns; ++jb) {
-                double4v c = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int kb = jb; kb < ns; ++kb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kb][q], frag_krow(S + sub(a0 + kb, a0 + jb), q), c, 0,
-                                                                 0, 0);
-                store_c(S + sub(I, a0 + jb), c);
-            }
-        }
-        __syncthreads();
-        {   // X[C,A] = -X[C,C] T, sub-block column a0 + t, in place
-            const int Jc = a0 + t;
-            double b[ns][4];
-#pragma unroll
-            for (int kb = 0; kb < ns; ++kb)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) b[kb][q] = frag_krow(S + sub(c0 + kb, Jc), q);
-#pragma unroll
-            for (int ib = 0; ib < ns; ++ib) {
-                double4v c = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int kb = 0; kb <= ib; ++kb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        c = __builtin_amdgcn_mfma_f64_16x16x4f64(-frag_rowk(S + sub(c0 + ib, c0 + kb), q), b[kb][q], c, 0,
-                                                                 0, 0);
-                store_c(S + sub(c0 + ib, Jc), c);
-            }
-        }
-        __syncthreads();
-    });
-    // L_kk^-1 to V (zeros above the diagonal), sub-block by sub-block: wave w takes the sub-block rows w and 7 - w
-    // (eight sub-blocks each), a lane four rows of one column, so that addresses step by constants and a store
-    // instruction writes four 128-byte row segments
-    {
-        const int rows2[2] = {wave, NSB - 1 - wave};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int I = rows2[h];
-#pragma unroll 2
-            for (int J = 0; J < NSB; ++J) {
-                double v[4] = {0.0, 0.0, 0.0, 0.0};
-                if (J <= I) {   // uniform
-                    const double* M = S + sub(I, J);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = M[(4 * r + lk) * SBP + l16];
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
-                    if (row < bs && col < bs) V[int64_t(off + row) * n + off + col] = v[r];
+                    for (int q = 0; q < 4; ++q) a[q] = frag_rowk(S + sub(I, J - 1), q);
+                    in_fours(J, [&](auto nc, int k) __attribute__((always_inline)) { inverse_row(nc, I, J - 1, k, a); });
                 }
             }
         }
+        __syncthreads();
     }
+    // rows NSB - 2 and NSB - 1 of the inverse, by columns: nothing but registers between the products
+    constexpr int R0 = NSB - 2, R1 = NSB - 1;
+    for (int C = wave; C <= R0; C += 4) {
+        double4v x0 = load_c(S + sub(R0, C));
+        double4v c = zero4;
+        if (C < R0) {
+            x0 = mul_add(S + sub(R0, R0), x0, zero4, -1.0);
+            c = load_c(S + sub(R1, C));
+        }
+        c = mul_add(S + sub(R1, R0), x0, c, 1.0);
+        c = mul_add(S + sub(R1, R1), c, zero4, -1.0);
+        out(R0, C, x0);
+        out(R1, C, c);
+    }
+    if (wave == 3) out(R1, R1, load_c(S + sub(R1, R1)));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -707,24 +764,40 @@ __device__ __forceinline__ void dgemm_diag_tile_wave(const GemmArgs& g, double* 
     for (int c = 0; c < NB_COLS; ++c) fr[c] = frag(c);
     const int faA = frag(RA), faB = frag(RB);
     const char* ldsc = reinterpret_cast<const char*>(lds);
-    for (int st = 0; st < n_st; ++st) {
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (DNS - 2)));   // stage st has landed
-        __syncthreads();
-        issue(st + DNS - 1);                                        // into the slot every wave has finished reading
+    // One wave per SIMD has nothing beside it to cover its LDS reads, so the fragments of a half-stage are read while the
+    // MFMAs of the half before it run
+    // (12.3 -> 11.6 us a tile).
+    struct Frags {
+        double b[NB_COLS], aA, aB;
+    };
+    auto read = [&](Frags& f, int st, int h) __attribute__((always_inline)) {
         const char* sp = ldsc + (st % DNS) * R_PART_BYTES;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            double b[NB_COLS];
+        for (int c = 0; c < NB_COLS; ++c) f.b[c] = *reinterpret_cast<const double*>(sp + (h ? fr[c] ^ 32 : fr[c]));
+        f.aA = *reinterpret_cast<const double*>(sp + (h ? faA ^ 32 : faA));
+        f.aB = *reinterpret_cast<const double*>(sp + (h ? faB ^ 32 : faB));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](const Frags& f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c = 0; c < NB_COLS; ++c) b[c] = *reinterpret_cast<const double*>(sp + (h ? fr[c] ^ 32 : fr[c]));
-            const double aA = *reinterpret_cast<const double*>(sp + (h ? faA ^ 32 : faA));
-            const double aB = *reinterpret_cast<const double*>(sp + (h ? faB ^ 32 : faB));
-#pragma unroll
-            for (int c = 0; c <= RB; ++c) {
-                accB[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(aB, b[c], accB[c], 0, 0, 0);
-                if (c <= RA) accA[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(aA, b[c], accA[c], 0, 0, 0);
-            }
+        for (int c = 0; c <= RB; ++c) {
+            accB[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.aB, f.b[c], accB[c], 0, 0, 0);
+            if (c <= RA) accA[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.aA, f.b[c], accA[c], 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Frags f0, f1;
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (DNS - 2)));   // stage 0 has landed
+    __syncthreads();
+    read(f0, 0, 0);
+    for (int st = 0; st < n_st; ++st) {
+        read(f1, st, 1);
+        multiply(f0);
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (DNS - 3)));   // stage st + 1 has landed
+        __syncthreads();
+        issue(st + DNS - 1);                                        // into the slot of stage st - 1, which every wave has read
+        read(f0, st + 1, 0);                                        // past the last stage: zeros nobody uses
+        multiply(f1);
     }
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the slots are reused
     __syncthreads();   // every wave is done with the last stage before the operand slots are overwritten
