@@ -227,3 +227,26 @@ def test_rtn_sensitivity(bits, G, d_out, d_in, dtype, grid):
         ref = oc.rtn_sensitivity(to_f64(W), to_f64(a), None if bd is None else to_f64(bd), bits, G, grid=og_grid)
         assert abs(float(e.item()) - ref) <= 1e-3 * ref
         assert torch.equal(e, e2)        # reproducible bit for bit
+
+
+@pytest.mark.parametrize("bits,G,d_out,d_in,dtype", [
+    (4, 16, 5, 48, torch.bfloat16),          # one load per lane, fewer groups than teams
+    (3, 48, 1, 48, torch.float32),           # two loads per lane, the second one ragged; a single group
+    (2, 48, 2777, 336, torch.bfloat16),      # the same, odd numbers of rows and of groups per row
+    (8, 512, 33, 1536, torch.bfloat16),      # one load of a whole wave
+    (4, 1008, 9, 3024, torch.bfloat16),      # two loads of a whole wave, ragged
+    (4, 528, 21, 1584, torch.float32),       # three loads: the group is read twice
+    (3, 16, 300, 32848, torch.bfloat16),     # 2053 groups per row (a prime): teams change their slice of a
+])
+def test_rtn_sensitivity_group_widths(bits, G, d_out, d_in, dtype):
+    """Group widths around the lane counts of the kernel.  Bar as above."""
+    _announce(f"RTN sensitivity b{bits} g{G} {d_out}x{d_in} {dtype}")
+    gen = torch.Generator(device=DEV).manual_seed(d_in + G)
+    W = torch.randn((d_out, d_in), generator=gen, device=DEV).to(dtype)
+    a = (0.5 + 3.0 * torch.rand(d_in, generator=gen, device=DEV)).to(torch.float32)
+    b = (0.5 + torch.rand(d_out, generator=gen, device=DEV)).to(torch.float32)
+    for grid, og_grid in (("minmax", "asym"), ("symmetric", "sym")):
+        e = og.onecomp_rtn_sensitivity(W, a, bits, G, b_diag=b, grid=grid)
+        torch.cuda.synchronize()
+        ref = oc.rtn_sensitivity(to_f64(W), to_f64(a), to_f64(b), bits, G, grid=og_grid)
+        assert abs(float(e.item()) - ref) <= 1e-3 * ref
