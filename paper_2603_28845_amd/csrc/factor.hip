@@ -36,7 +36,7 @@ __global__ __launch_bounds__(1024) void prep_diag_kernel(const float* __restrict
     double s = 0.0;
     for (int i = threadIdx.x; i < n; i += 1024) {
         float h = H[int64_t(i) * n + i];
-        keys[i] = h;
+        keys[i] = h == h ? h : -__builtin_inff();   // a NaN goes last: every position of the order is taken once
         double d = (h == 0.0f) ? 1.0 : double(h);
         dfix[i] = d;
         s += d;  // fixed order per thread
@@ -53,20 +53,36 @@ __global__ __launch_bounds__(1024) void prep_diag_kernel(const float* __restrict
     }
 }
 
-// perm: act_order ? stable descending order of keys : identity.  rank by counting.
-__global__ __launch_bounds__(256) void order_kernel(const float* __restrict__ keys, int n, int act_order,
-                                                   int32_t* __restrict__ perm, int32_t* __restrict__ perm_out) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
+// perm: act_order ? stable descending order of keys : identity.  rank by counting: n^2 comparisons, two operations each.
+// A lane owns a key and the 16 waves of a workgroup share out the keys it is compared with, which arrive as scalar
+// loads; a thread per key that walked through all of them left the chip to 56 workgroups at d_in 14336 and waited for
+// one load after the other: 805 -> 26 us.
+constexpr int ORDER_KEYS = 64, ORDER_WAVES = 16;
+__global__ __launch_bounds__(64 * ORDER_WAVES) void order_kernel(const float* __restrict__ keys, int n, int act_order,
+                                                                int32_t* __restrict__ perm,
+                                                                int32_t* __restrict__ perm_out) {
+    __shared__ int part[ORDER_WAVES][ORDER_KEYS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i0 = blockIdx.x * ORDER_KEYS, i = i0 + lane;
+    if (act_order) {
+        const float ki = keys[min(i, n - 1)];
+        const int each = (n + ORDER_WAVES - 1) / ORDER_WAVES;
+        const int k0 = min(wave * each, n), k1 = min(k0 + each, n);
+        const int b0 = max(k0, min(k1, i0)), b1 = max(k0, min(k1, i0 + ORDER_KEYS));   // this workgroup's own keys
+        int rank = 0;
+#pragma unroll 16
+        for (int k = k0; k < b0; ++k) rank += keys[k] >= ki;
+        for (int k = b0; k < b1; ++k) rank += (keys[k] > ki) || (keys[k] == ki && k < i);
+#pragma unroll 16
+        for (int k = b1; k < k1; ++k) rank += keys[k] > ki;
+        part[wave][lane] = rank;
+        __syncthreads();
+    }
+    if (wave != 0 || i >= n) return;
     int pos = i;
     if (act_order) {
-        const float ki = keys[i];
-        int rank = 0;
-        for (int k = 0; k < n; ++k) {
-            const float kk = keys[k];
-            rank += (kk > ki) || (kk == ki && k < i);
-        }
-        pos = rank;
+        pos = 0;
+        for (int w = 0; w < ORDER_WAVES; ++w) pos += part[w][lane];
     }
     perm[pos] = i;
     if (perm_out) perm_out[pos] = i;
@@ -74,19 +90,71 @@ __global__ __launch_bounds__(256) void order_kernel(const float* __restrict__ ke
 
 // A[r][c] = Hd[p[n-1-r]][p[n-1-c]] in fp64 (reversed, permuted, damped); upper triangle of H is read.  Only the
 // 128 x 128 blocks on and below the diagonal are written: the factorization never reads the others, and in natural
-// order those are the ones whose source rows are read along the row.
+// order (this kernel) those are the ones whose source rows are read along the row.
 __global__ __launch_bounds__(256) void build_kernel(const float* __restrict__ H, int n,
-                                                   const int32_t* __restrict__ perm,
                                                    const double* __restrict__ dfix, const double* __restrict__ lam,
                                                    double* __restrict__ A) {
     const int c = blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (c >= n || c / NB > r / NB) return;
-    const int i = perm[n - 1 - r], k = perm[n - 1 - c];
+    const int i = n - 1 - r, k = n - 1 - c;
     double v;
     if (i == k) v = dfix[i] + *lam;
     else v = double(H[int64_t(min(i, k)) * n + max(i, k)]);
     A[int64_t(r) * n + c] = v;
+}
+
+// The same under a column order.  H's upper triangle then comes in at scattered places, half of them along columns: 64
+// bytes fetched for 4.  So the triangle is mirrored into a full matrix S first, 64 x 64 tiles at a time, and every row
+// of A takes its values from one row of S, read along the row into LDS and gathered there.  d_in 14336: 1362 us in one
+// pass of gathers -> 257 + 405 us in the two.
+__global__ __launch_bounds__(256) void mirror_kernel(const float* __restrict__ H, int n, float* __restrict__ S) {
+    __shared__ float tile[64][65];
+    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+    if (c0 < r0) return;
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = r0 + ty + 4 * q, c = c0 + tx;
+        float v = 0.f;
+        if (r < n && c < n && r <= c) v = H[int64_t(r) * n + c];
+        tile[ty + 4 * q][tx] = v;
+        if (r < n && c < n && r <= c) S[int64_t(r) * n + c] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = c0 + ty + 4 * q, c = r0 + tx;   // below the diagonal
+        if (r < n && c < r) S[int64_t(r) * n + c] = tile[tx][ty + 4 * q];
+    }
+}
+
+constexpr int GATHER_COLS = 16384;   // columns of S in LDS at a time: two workgroups per CU
+__global__ __launch_bounds__(512) void build_order_kernel(const float* __restrict__ S, int n,
+                                                         const int32_t* __restrict__ perm,
+                                                         const double* __restrict__ dfix,
+                                                         const double* __restrict__ lam, double* __restrict__ A) {
+    extern __shared__ float srow[];
+    const int r = n - 1 - int(blockIdx.x);   // the longest rows first
+    const int i = perm[n - 1 - r];
+    const int c_end = min(n, (r / NB + 1) * NB);
+    for (int b = 0; b < n; b += GATHER_COLS) {
+        const int cols = min(GATHER_COLS, n - b);
+        const float* src = S + int64_t(i) * n + b;
+        if (b > 0) __syncthreads();
+        if (n % 4 == 0) {
+            for (int c = threadIdx.x * 4; c < cols; c += 512 * 4)
+                *reinterpret_cast<float4v*>(srow + c) = *reinterpret_cast<const float4v*>(src + c);
+        } else {
+            for (int c = threadIdx.x; c < cols; c += 512) srow[c] = src[c];
+        }
+        __syncthreads();
+        for (int c = threadIdx.x; c < c_end; c += 512) {
+            const int k = perm[n - 1 - c];
+            if (unsigned(k - b) >= unsigned(cols)) continue;
+            A[int64_t(r) * n + c] = k == i ? dfix[i] + *lam : double(srow[k - b]);
+        }
+    }
 }
 
 // U[i][k] = float(V[n-1-i][n-1-k]) for k >= i, 0 below the diagonal.
@@ -1054,11 +1122,20 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     hipLaunchKernelGGL(prep_diag_kernel, dim3(1), dim3(1024), 0, stream, H, n, double(damp), w.keys, w.dfix, w.lam,
                        info);
     ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(order_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, stream, w.keys, n, act_order,
-                       w.perm, perm_out);
+    hipLaunchKernelGGL(order_kernel, dim3(unsigned(ceil_div(n, ORDER_KEYS))), dim3(64 * ORDER_WAVES), 0, stream, w.keys, n,
+                       act_order, w.perm, perm_out);
     ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(build_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, H, n,
-                       w.perm, w.dfix, w.lam, w.A);
+    if (act_order) {   // w.T is free until the triangular inverse
+        float* S = reinterpret_cast<float*>(w.T);
+        const unsigned tiles = unsigned(ceil_div(n, 64));
+        hipLaunchKernelGGL(mirror_kernel, dim3(tiles, tiles), dim3(256), 0, stream, H, n, S);
+        ONECOMP_CHECK_LAUNCH();
+        hipLaunchKernelGGL(build_order_kernel, dim3(unsigned(n)), dim3(512), min(n, GATHER_COLS) * sizeof(float), stream,
+                           S, n, w.perm, w.dfix, w.lam, w.A);
+    } else {
+        hipLaunchKernelGGL(build_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, H, n,
+                           w.dfix, w.lam, w.A);
+    }
     ONECOMP_CHECK_LAUNCH();
 
     // ---- blocked right-looking Cholesky of A (lower) ----

@@ -855,3 +855,34 @@ def test_largest_layer_properties():
     rows_equal = (outs["inverse"] == outs["block"]).all(dim=1).float().mean().item()
     _announce(f"   codes, inverse form vs block form: {agree:.6f} of the entries equal, {rows_equal:.4f} of the rows")
     assert agree >= 0.99 and rows_equal >= 0.9
+
+
+@pytest.mark.parametrize("d_in,form", [(592, "inverse"), (16512, "block")])   # ragged tiles; two chunks of gathered columns
+def test_factor_order_with_ties_and_upper_triangle(d_in, form):
+    """The column order is the stable descending one of the diagonal (many equal entries here), only H's upper triangle
+    is read, and the factor is that of the explicitly ordered matrix.  The two differ by the rounding of the damping's
+    mean (summed in another order, 1e-15) times the condition number, and by one fp32 rounding: <= 1e-6."""
+    _announce(f"factor, order with ties, d_in={d_in} {form}")
+    gen = torch.Generator(device=DEV).manual_seed(d_in)
+    X = torch.randn((256, d_in), generator=gen, device=DEV)
+    H = X.t() @ X
+    H = torch.triu(H) + torch.triu(H, 1).t()
+    H.diagonal().copy_(300.0 + 10.0 * torch.randint(0, 40, (d_in,), generator=gen, device=DEV).float())
+    want = torch.argsort(H.diagonal(), descending=True, stable=True)
+    F, perm, info = og.onecomp_hessian_factor(torch.triu(H) + torch.tril(torch.full_like(H, 7.0), -1), 4.0, act_order=True,
+                                              form=form)
+    R, _, info2 = og.onecomp_hessian_factor(H[want][:, want].contiguous(), 4.0, form=form)
+    torch.cuda.synchronize()
+    assert torch.equal(perm.long(), want) and int(info.item()) == 0 and int(info2.item()) == 0
+    assert (torch.linalg.norm((F - R).double()) / torch.linalg.norm(R.double())).item() <= 1e-6
+
+
+def test_factor_order_of_nan_diagonal():
+    """A NaN on the diagonal goes last; every column keeps a place in the order."""
+    d_in = 320
+    H = torch.eye(d_in, device=DEV) * torch.arange(1, d_in + 1, device=DEV).float()
+    H[5, 5] = H[200, 200] = float("nan")
+    _, perm, _ = og.onecomp_hessian_factor(H, 0.01, act_order=True)
+    torch.cuda.synchronize()
+    keys = torch.nan_to_num(H.diagonal(), nan=-1.0)
+    assert torch.equal(perm.long(), torch.argsort(keys, descending=True, stable=True))
