@@ -1105,17 +1105,27 @@ __global__ __launch_bounds__(256) void panel_far_kernel(PanelArgs pa, TrailArgs 
     else trailing_tile<3, true>(ta, blockIdx.x - n_panel, dyn_lds);
 }
 
-// Scale and zero-point of one wide group (columns g0 .. g0 + G - 1 of every row) from its current values
-// w0 + c in fp64: W0 the weights in sweep order, C the working copy (accumulated feedback; nullptr = none, the
+// Scale and zero-point of one wide group (columns g0 .. g0 + G - 1 of every row, G a multiple of 128) from its current
+// values w0 + c in fp64: W0 the weights in sweep order, C the working copy (accumulated feedback; nullptr = none, the
 // first group of a row or one group per row), which the caller guarantees to be complete for these columns: the far
 // updates of all earlier super-blocks have run.  One workgroup per row; the fp64 scale goes to s64[row].
+//
+// The scale search is bound by its VALU operations, five per value and candidate.  A thread owns a candidate and a
+// quarter of the values, which every lane reads from LDS at the same address, so that a candidate's grid (fp64
+// divisions) is formed once per thread and nothing is reduced before the end; with the values spread over the threads
+// every one of the 80 candidates had its divisions in all threads and a workgroup sum.  The sums are kept short (32
+// values, four accumulators; 4096 values; the row).  1999 rows of 2048: 260 -> 49 us.
+constexpr int GP_SLICES = 4, GP_THREADS = GP_SLICES * MSE_CANDIDATES, GP_CHUNK = 4096;
 template <typename T>
-__global__ __launch_bounds__(256) void group_params_kernel(const T* __restrict__ W0, const float* __restrict__ C, int d_out,
-                                                          int d_in, int g0, int G, float qmax, float qs, int mse, int n_g,
-                                                          int g_idx, float* __restrict__ scales, float* __restrict__ zeros,
-                                                          double* __restrict__ s64) {
-    __shared__ double smn[256], smx[256];
-    __shared__ float sred[256];
+__global__ __launch_bounds__(GP_THREADS) void group_params_kernel(const T* __restrict__ W0, const float* __restrict__ C,
+                                                                 int d_out, int d_in, int g0, int G, float qmax, float qs,
+                                                                 int mse, int n_g, int g_idx, float* __restrict__ scales,
+                                                                 float* __restrict__ zeros, double* __restrict__ s64) {
+    constexpr int WAVES = GP_THREADS / 64;
+    __shared__ double smn[WAVES], smx[WAVES];
+    __shared__ float part[GP_SLICES][MSE_CANDIDATES];
+    __shared__ __attribute__((aligned(16))) float val[GP_CHUNK];
+    const int tid = threadIdx.x;
     for (int64_t r = blockIdx.x; r < d_out; r += gridDim.x) {
         const T* row = W0 + r * d_in + g0;
         const float* crow = C ? C + r * d_in + g0 : nullptr;
@@ -1123,47 +1133,82 @@ __global__ __launch_bounds__(256) void group_params_kernel(const T* __restrict__
             return double(to_f32<T>(row[c])) + (crow ? double(crow[c]) : 0.0);
         };
         double mn = value(0), mx = mn;
-        for (int c = threadIdx.x; c < G; c += 256) {
+        const bool keep = mse && G <= GP_CHUNK;
+        for (int c = tid; c < G; c += GP_THREADS) {
             const double v = value(c);
             mn = fmin(mn, v); mx = fmax(mx, v);
+            if (keep) val[c] = float(v);
         }
-        smn[threadIdx.x] = mn; smx[threadIdx.x] = mx;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (int(threadIdx.x) < w) {
-                smn[threadIdx.x] = fmin(smn[threadIdx.x], smn[threadIdx.x + w]);
-                smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + w]);
-            }
-            __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            mn = fmin(mn, __shfl_xor(mn, off, 64));
+            mx = fmax(mx, __shfl_xor(mx, off, 64));
         }
-        mn = smn[0]; mx = smx[0];
+        if ((tid & 63) == 0) { smn[tid >> 6] = mn; smx[tid >> 6] = mx; }
         __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) { mn = fmin(mn, smn[w]); mx = fmax(mx, smx[w]); }
         int cand = 0;
-        if (mse) {   // uniform; the row's values are re-read from cache for every candidate
-            cand = mse_search(mn, mx, double(qmax), double(qs),
-                       [&](float zi, float rsi) __attribute__((always_inline)) {
-                           float e = 0.f;
-                           for (int c = threadIdx.x; c < G; c += 256) e += mse_term(float(value(c)), zi, rsi, qmax);
-                           return e;
-                       },
-                       [&](float x) __attribute__((always_inline)) {   // workgroup sum, the same value in every thread
-                           x += dpp_quad<QUAD_SWAP1>(x);
-                           x += dpp_quad<QUAD_SWAP2>(x);
-                           sred[threadIdx.x] = x;
-                           __syncthreads();
-                           float t = 0.f;
-                           for (int w = 0; w < 256; w += 4) t += sred[w];
-                           __syncthreads();
-                           return t;
-                       });
+        if (mse) {   // uniform
+            const int slice = tid / MSE_CANDIDATES, i = tid % MSE_CANDIDATES;
+            double sd, zd;
+            grid_params(mn, mx, i, double(qmax), double(qs), sd, zd);
+            const float si = float(sd), zi = float(zd), rsi = 1.0f / si;
+            float err = 0.f;
+            for (int b = 0; b < G; b += GP_CHUNK) {
+                const int cols = min(GP_CHUNK, G - b);
+                if (!keep) {
+                    __syncthreads();
+                    for (int c = tid; c < cols; c += GP_THREADS) val[c] = float(value(b + c));
+                    __syncthreads();
+                }
+                const float4v* src = reinterpret_cast<const float4v*>(val) + slice * (cols / (4 * GP_SLICES));
+                float e_chunk = 0.f;
+                for (int c = 0; c < cols / (4 * GP_SLICES); c += 8) {
+                    float4v e4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float4v x = src[c + j];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float t = fmaf(x[e], rsi, zi);
+                            const float d = t - __builtin_amdgcn_fmed3f(rintf(t), 0.f, qmax);   // see mse_term
+                            e4[e] = fmaf(d, d, e4[e]);
+                        }
+                    }
+                    e_chunk += (e4[0] + e4[1]) + (e4[2] + e4[3]);
+                }
+                err += e_chunk;
+            }
+            part[slice][i] = err;
+            __syncthreads();
+            if (tid < 64) {   // the first smallest error, as mse_search takes it
+                auto total = [&](int k) __attribute__((always_inline)) {
+                    return (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
+                };
+                float best = 3.0e38f;
+                auto offer = [&](float x, int k) __attribute__((always_inline)) {
+                    if (x < best || (x == best && k < cand)) { best = x; cand = k; }
+                };
+                offer(si * si * total(tid), tid);
+                if (tid < MSE_CANDIDATES - 64) {
+                    const int k = tid + 64;
+                    double s2, z2;
+                    grid_params(mn, mx, k, double(qmax), double(qs), s2, z2);
+                    offer(float(s2) * float(s2) * total(k), k);
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) offer(__shfl_xor(best, off, 64), __shfl_xor(cand, off, 64));
+            }
         }
         double s, z;
-        grid_params(mn, mx, cand, double(qmax), double(qs), s, z);
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
+            grid_params(mn, mx, cand, double(qmax), double(qs), s, z);
             scales[r * n_g + g_idx] = float(s);
             zeros[r * n_g + g_idx] = float(z);
             s64[r] = s;
         }
+        __syncthreads();   // the next row's values and partial results go to the same LDS
     }
 }
 
@@ -1411,11 +1456,11 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
                 // group per row, whose grid comes from the original weights)
                 const float* cur = (direct || s0 == 0) ? nullptr : w.Wf;
                 if (pa.w0_bf16)
-                    hipLaunchKernelGGL(group_params_kernel<uint16_t>, pgrid, dim3(256), 0, stream,
+                    hipLaunchKernelGGL(group_params_kernel<uint16_t>, pgrid, dim3(GP_THREADS), 0, stream,
                                        static_cast<const uint16_t*>(pa.W0), cur, int(d_out), int(d_in), s0, group_size,
                                        pa.qmax, pa.qs, pa.mse, pa.n_g, g_idx, scales, zeros, w.s64);
                 else
-                    hipLaunchKernelGGL(group_params_kernel<float>, pgrid, dim3(256), 0, stream,
+                    hipLaunchKernelGGL(group_params_kernel<float>, pgrid, dim3(GP_THREADS), 0, stream,
                                        static_cast<const float*>(pa.W0), cur, int(d_out), int(d_in), s0, group_size,
                                        pa.qmax, pa.qs, pa.mse, pa.n_g, g_idx, scales, zeros, w.s64);
                 ONECOMP_CHECK_LAUNCH();

@@ -886,3 +886,17 @@ def test_factor_order_of_nan_diagonal():
     torch.cuda.synchronize()
     keys = torch.nan_to_num(H.diagonal(), nan=-1.0)
     assert torch.equal(perm.long(), torch.argsort(keys, descending=True, stable=True))
+
+
+@pytest.mark.parametrize("bits,G,d_out,d_in,dtype,grid", [
+    (4, 4224, 5, 4224, torch.float32, "symmetric_mse"),     # one group per row, two chunks of values in LDS
+    (3, 640, 37, 1280, torch.bfloat16, "minmax_mse"),       # groups of five blocks, the second one on compensated values
+])
+def test_scale_search_wide_groups(bits, G, d_out, d_in, dtype, grid):
+    _announce(f"scale search b{bits} g{G} {d_out}x{d_in} {dtype} {grid}")
+    cfg = synth.scaled(synth.CONFIGS["c2"], d_out=d_out, d_in=d_in, n_tokens=16, seed=91, dtype=dtype)
+    W = synth.make_weight(cfg, DEV)
+    H = torch.from_numpy(_oracle_H32(d_in, 512, seed=92)).to(DEV)
+    U, _, info = og.onecomp_hessian_factor(H, 0.1)
+    assert int(info.item()) == 0
+    _check_sweep(W, U, bits, G, grid=grid)
