@@ -1098,18 +1098,31 @@ onecomp_status gram_cross_accumulate_bf16(const void* Xh, const void* X, int64_t
     return launch_bf16_ring<RingMid, true>(Xh, X, n_tokens, d_in, ldxh, ldx, G, nullptr, 0, stream);
 }
 
-// Which fp32 kernel a call takes, by measurement (us of a call, 128 x 128 tiles / 64 x 64 / 32 x 32 over eight token runs):
-//   d_in   512, 1024 tokens:  102 /  20 /   9      d_in 1360, 3001 tokens:  278 /  59 /  62
-//   d_in  2048, 3001 tokens:  276 / 160 / 129      d_in 2896, 8192 tokens: 1220 / 642 / 626
-//   d_in  4096, 1024 tokens:  243 / 194 / 212      d_in 4096, 8192 tokens: 1715 / 1175 / 1171
-//   d_in  8192, 1024 tokens:  712 / 765 / 840      d_in 8192, 3001 tokens: 1897 / 1826 / 1831
-// Below d_in 3072 the 32-wide tiles fill the CUs best; wide layers take 64-wide ones, which move half the operand
-// bytes; where the layer is wide and the tokens are few, reading and writing H is most of the call, and there the
-// 128-wide tiles (three workgroups per CU instead of one) are the better ones.
+// Which fp32 kernel a call takes, by measurement (us of a call, 128 x 128 tiles / 64 x 64 / 32 x 32 over eight token runs).
+// Many tokens: the 32-wide tiles fill the CUs best in narrow layers, the 64-wide ones move half the operand bytes; up to
+// 256 tokens a wave of a 64-wide tile has one pair of batches, and there these win from d_in 2048 on:
+//   d_in   512, 1024 tokens:  102 /   20 /   9     d_in 1360, 3001 tokens:  278 /   59 /  62
+//   d_in  2048,  256 tokens:   42 /   27 /  37     d_in 2048, 1024 tokens:  112 /   63 /  53
+//   d_in  2560,  256 tokens:   51 /   41 /  55     d_in 2560, 1024 tokens:  116 /   85 /  80
+//   d_in  2816,  512 tokens:   73 /   56 /  66     d_in 2816, 4096 tokens:  370 /  262 / 280
+//   d_in  4096, 1024 tokens:  243 /  194 / 212     d_in 4096, 8192 tokens: 1715 / 1175 / 1171
+// Few tokens for the width: reading and writing H is most of the call, and the 128-wide tiles (three workgroups per CU
+// instead of one) are the better ones.  On both sides of the crossing, 128-wide : the other tile:
+//   d_in  1536,   32 /  100:    24 /   31 :   23 /   24    d_in  1792,   64 /  128:   27 /   33 :   29 /   30
+//   d_in  2048,   64 /  128:    26 /   32 :   28 /   27    d_in  2816,   64 /  192:   33 /   45 :   40 /   42
+//   d_in  3072,  100 /  192:    51 /   61 :   53 /   53    d_in  4096,  256 /  512:   90 /  138 :   92 /  125
+//   d_in  5120,  512 /  768:   181 /  249 :  185 /  231    d_in  6144, 1024 / 2048:  391 /  747 :  411 /  690
+//   d_in  7168, 1024 / 2048:   534 / 1023 :  549 /  916    d_in  8192, 1024 / 2048:  712 / 1316 :  765 / 1255
+//   d_in 10240, 2560 / 4096:  2326 / 3659 : 2343 / 3468    d_in 14336, 3584 / 4608: 6125 / 7830 : 6112 / 7579
 static int f32_tile(int64_t n_tokens, int64_t d_in, int64_t ldx) {
     // the token-run kernel addresses a batch of 32 tokens with 32-bit byte offsets
-    if (ldx >= (int64_t(1) << 23) || (d_in >= 8192 && n_tokens < d_in / 4)) return F32_TS;
-    return d_in < 3072 ? 32 : 64;
+    if (ldx >= (int64_t(1) << 23)) return F32_TS;
+    const int64_t few = d_in < 2048   ? (d_in - 1408) / 4
+                        : d_in < 3072 ? d_in / 24
+                        : d_in < 8192 ? d_in * d_in / 1000 * d_in / 180000
+                                      : d_in / 4;
+    if (n_tokens < few && n_tokens < d_in / 4) return F32_TS;
+    return d_in < 2048 || (d_in < 2688 && n_tokens > 256) ? 32 : 64;
 }
 
 onecomp_status gram_accumulate_f32(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H,
