@@ -16,6 +16,7 @@
 //     order that walks bands of 4 tile rows column by column.  The 32 workgroups that share an
 //     XCD's L2 at any time then cover a compact 4 x 8 patch of tiles (12 X panels, not 64).  A wide layer is
 //     launched one round of tiles (one per CU) at a time, so that those 32 also stay together along the tokens.
+//   * calls of few tokens and narrow layers: register-staged 128 x 128 tiles (few_tokens_bf16).
 //   * fp32 path (small layers): v_mfma_f32_32x32x2_f32, products in fp32; 32- or 64-wide tiles whose tokens eight waves
 //     share out, 128-wide tiles for wide layers with few tokens (f32_tile).
 #include "common.hpp"
@@ -1034,6 +1035,20 @@ GramShape choose_shape(int64_t d_in, int64_t n_tokens, int n_cus, size_t ws_byte
     return cost_big <= cost_mid ? GramShape::Big : GramShape::Mid;
 }
 
+// Calls whose time is the start and end of a tile rather than its tokens: the ring kernels fill eight slots first, and
+// their 256-wide tiles (one per CU) leave little in flight while H is read and written; the 128 x 128 kernel has four
+// times the workgroups, several per CU.  It is the slower one per token, by more the wider the layer (operand bytes).
+// us of a call, ring (best shape) : 128 x 128:
+//   d_in 1024,  128 tokens: 33 : 17;  2048: 56 : 43;  4096: 96 : 86;  4900: 99 : 101 (8192: 147 : 157)
+//   d_in 2048,  128 tokens: 41 : 19;  2048: 72 : 57;  4096: 97 : 90;  4900: 102 : 102 (8192: 146 : 158)
+//   d_in 3072,  128 tokens: 51 : 32;  2048: 77 : 67;  3115: 88 : 87 (4096: 102 : 104)
+//   d_in 4096,  128 tokens: 61 : 40;  1024: 79 : 68;  1752: 92 : 92 (2048: 99 : 102)
+//   d_in 6144,  128 tokens: 78 : 56;   512: 91 : 76;   778: 100 : 90 (1024: 97 : 102)
+//   d_in 8192,  128 tokens: 110 : 88;  438: 128 : 113     d_in 14336, 128 tokens: 354 : 307
+bool few_tokens_bf16(int64_t n_tokens, int64_t d_in) {
+    return n_tokens <= 4096 && n_tokens * d_in * d_in < 30000000000;
+}
+
 }  // namespace
 
 // bytes of workspace that let gram_accumulate_bf16 cut tiles into pieces (0: this width never does): the larger of
@@ -1055,9 +1070,9 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
                                     size_t ws_bytes, hipStream_t stream, GramPlanInfo* info) {
     float* ws = static_cast<float*>(wsv);
     if (info) *info = GramPlanInfo{128, 128, 0};
-    // The direct-to-LDS kernels need 32-bit byte offsets inside a step of tokens; narrow layers take the
-    // register-staged 128 x 128 kernel.
-    if (ldx * 64 >= (int64_t(1) << 31) || d_in < 1024) {
+    // The direct-to-LDS kernels need 32-bit byte offsets inside a step of tokens; narrow layers and calls of few tokens
+    // take the register-staged 128 x 128 kernel.
+    if (ldx * 64 >= (int64_t(1) << 31) || d_in < 1024 || (few_tokens_bf16(n_tokens, d_in) && forced_shape() < 0)) {
         if (info) {
             info->launches = 1;
             return ONECOMP_OK;

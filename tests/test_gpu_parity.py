@@ -162,6 +162,27 @@ def test_gram_f32_tiles(d_in, n_tok, pad, tile):
     assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
 
 
+@pytest.mark.parametrize("d_in,n_tok,pad,tile", [
+    (1024, 1, 0, 128), (1040, 33, 16, 128), (2064, 4096, 0, 128), (2048, 4097, 0, 256), (4096, 1788, 0, 128), (4096, 1789, 0, 256),
+    (8208, 65, 8, 128),
+])
+def test_gram_bf16_few_tokens(monkeypatch, d_in, n_tok, pad, tile):
+    monkeypatch.delenv("ONECOMP_GRAM_SHAPE", raising=False)
+    _announce(f"gram bf16 of few tokens d_in={d_in} n_tok={n_tok} pad={pad}")
+    assert og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, 0)["tile_cols"] == tile
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    wide = torch.full((n_tok + 1, d_in + pad), float("nan"), device=DEV, dtype=torch.bfloat16)
+    wide[:n_tok, :d_in] = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    X = wide[:n_tok, :d_in]
+    H = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H)
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd) + 0.5
+    assert torch.equal(H, H.t())
+    # products of bf16 are exact; n_tok fp32 additions whose rounding errors add up like a random walk (see the fp32 tiles)
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
 def test_gram_big_tiles_bf16():
     # d_in large enough for the direct-to-LDS tile kernels, several stages and a ragged token tail
     _announce("gram d_in=8192 n_tok=1055 bf16 (direct-to-LDS tiles)")
