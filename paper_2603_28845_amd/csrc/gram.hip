@@ -767,28 +767,47 @@ __device__ __forceinline__ void gram_f32_run(const float* __restrict__ X, int64_
     struct Batch {
         float a[STEPS][MT], b[DIAG ? 1 : STEPS][MT];
     };
-    // A batch's address is scalar (descriptor base and offset), so the loads take no vector arithmetic; the descriptor
-    // ends with the run's last token and what lies behind reads as zero.
-    auto desc = [&](int64_t t0) __attribute__((always_inline)) {
-        const int64_t left = t0 < t_end ? ((t_end - t0 - 1) * ldx + d_in) * 4 : 0;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + (left > 0 ? t0 : 0) * ldx), 0,
-                                                 int(min(left, int64_t(0x7FFFFFFF))), 0x00020000);
+    // A batch's address is scalar (descriptor base, and the instruction's scalar offset for the token), so the loads take
+    // no vector arithmetic.  The scalar offset is no part of the bounds check: a batch that reaches past the run's last
+    // token steps its vector offsets instead, and what lies behind that token reads as zero.
+    struct Source {
+        __amdgpu_buffer_rsrc_t rs;
+        int a[MT], b[MT];
     };
-    auto load = [&](Batch& f, __amdgpu_buffer_rsrc_t rs, int s) __attribute__((always_inline)) {   // tokens 2 s, 2 s + 1
-        const int so = 2 * s * int(ldx) * 4;
+    const int pair = 2 * int(ldx) * 4;   // bytes from one pair of tokens to the next
+    auto source = [&](int64_t t0, auto inside) __attribute__((always_inline)) {
+        Source s;
+        const int64_t left = t0 < t_end ? ((t_end - t0 - 1) * ldx + d_in) * 4 : 0;
+        s.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + (left > 0 ? t0 : 0) * ldx), 0,
+                                                 int(min(left, int64_t(0x7FFFFFFF))), 0x00020000);
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-            f.a[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, oa[m], so, 0));
-            if constexpr (!DIAG) f.b[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ob[m], so, 0));
+            s.a[m] = oa[m];
+            s.b[m] = ob[m];
+            // unknown to the compiler, or it keeps the stepped offsets of a whole batch in registers of their own
+            if constexpr (!decltype(inside)::value) asm volatile("" : "+v"(s.a[m]), "+v"(s.b[m]));
+        }
+        return s;
+    };
+    auto load = [&](Batch& f, Source& src, int s, auto inside) __attribute__((always_inline)) {   // tokens 2 s, 2 s + 1
+        const int so = decltype(inside)::value ? s * pair : 0;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            f.a[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src.rs, src.a[m], so, 0));
+            if constexpr (!DIAG) f.b[s][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src.rs, src.b[m], so, 0));
+            if constexpr (!decltype(inside)::value) {
+                src.a[m] += pair;
+                src.b[m] += pair;
+            }
         }
     };
     // the products of batch f with the loads of batch `next` (tokens from t0 on) between them, a whole batch ahead of
     // their use; the fences keep the compiler from moving the loads down to it
-    auto step = [&](const Batch& f, Batch& next, int64_t t0) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rs = desc(t0);
+    auto step = [&](const Batch& f, Batch& next, int64_t t0, auto inside) __attribute__((always_inline)) {
+        Source src = source(t0, inside);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
-            load(next, rs, s);
+            load(next, src, s, inside);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int m = 0; m < MT; ++m)
@@ -798,14 +817,22 @@ __device__ __forceinline__ void gram_f32_run(const float* __restrict__ X, int64_
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    constexpr std::false_type checked{};
+    constexpr std::true_type inside{};
     Batch f0, f1;
-    const __amdgpu_buffer_rsrc_t r0 = desc(t_begin);
+    Source src = source(t_begin, checked);
 #pragma unroll
-    for (int s = 0; s < STEPS; ++s) load(f0, r0, s);
+    for (int s = 0; s < STEPS; ++s) load(f0, src, s, checked);
+    int64_t t = t_begin;
 #pragma unroll 1
-    for (int64_t t = t_begin; t < t_end; t += 4 * STEPS) {
-        step(f0, f1, t + 2 * STEPS);
-        step(f1, f0, t + 4 * STEPS);
+    for (; t + 6 * STEPS <= t_end; t += 4 * STEPS) {   // both batches to load lie inside the run
+        step(f0, f1, t + 2 * STEPS, inside);
+        step(f1, f0, t + 4 * STEPS, inside);
+    }
+#pragma unroll 1
+    for (; t < t_end; t += 4 * STEPS) {
+        step(f0, f1, t + 2 * STEPS, checked);
+        step(f1, f0, t + 4 * STEPS, checked);
     }
 }
 template <int MT>

@@ -1,6 +1,12 @@
-"""The 384 x 256 Gram kernel pins its accumulator tiles through inline-assembly MFMAs, which the compiler's hazard
-handling cannot see: the loop is only correct while the compiler neither spills nor copies an accumulator inside it.
-This test compiles the kernel the way the build does and checks exactly that in the generated ISA (CPU only)."""
+"""Properties of the Gram kernels that only the generated code shows.  These tests compile gram.hip the way the build does
+and look at the ISA (CPU only).
+
+The 384 x 256 kernel pins its accumulator tiles through inline-assembly MFMAs, which the compiler's hazard handling
+cannot see: the loop is only correct while the compiler neither spills nor copies an accumulator inside it.
+
+The fp32 kernel whose waves share out the tokens takes what lies behind a run's last token as zero, from the bounds check
+of its buffer loads.  An instruction's scalar offset is no part of that check, so only batches that lie inside the run may
+use one."""
 import os
 import re
 import shutil
@@ -43,3 +49,29 @@ def test_wide_gram_loop_is_straight_line(tmp_path):
             "no wait states after the last MFMA of the loop"
         found += 1
     assert found == 3        # the symmetric kernel, its paced form and the cross kernel
+
+
+@pytest.fixture(scope="module")
+def isa(tmp_path_factory):
+    return _isa(tmp_path_factory.mktemp("isa"))
+
+
+@pytest.mark.parametrize("mt,steps", [(1, 16), (2, 8)])   # 32 x 32 tiles per side, loads of a batch per operand tile
+def test_f32_runs_check_every_offset_past_the_run(isa, mt, steps):
+    body = re.search(r"^_ZN\S*gram_f32_split_kernelILi%dE\S*:[^\n]*\n(.*?)^\.Lfunc_end" % mt, isa, re.S | re.M).group(1)
+    loads = [m.group(1) for m in re.finditer(r"buffer_load_dword v\d+, v\d+, s\[\d+:\d+\], (\S+) offen", body)]
+    operands = mt + 2 * mt                                    # diagonal tiles load one operand, the others two
+    # per kind of tile: the first batch, two batches inside the run, two that may reach past its end
+    assert len(loads) == 5 * steps * operands
+    # the first pair of tokens of a batch has offset 0; every other load of the two inside batches has a scalar offset
+    assert sum(o != "0" for o in loads) == 2 * (steps - 1) * operands
+    # kinds of tile one after the other: the first batch and the last two of each carry no scalar offset
+    sizes = sorted((mt, 2 * mt), reverse=loads.index(next(o for o in loads if o != "0")) > steps * mt + mt)
+    pos = 0
+    for per_step in sizes:
+        n = steps * per_step
+        first, inside, past = loads[pos:pos + n], loads[pos + n:pos + 3 * n], loads[pos + 3 * n:pos + 5 * n]
+        assert all(o == "0" for o in first) and all(o == "0" for o in past)
+        assert sum(o != "0" for o in inside) == 2 * (steps - 1) * per_step
+        pos += 5 * n
+    assert pos == len(loads)
