@@ -1115,16 +1115,19 @@ __global__ __launch_bounds__(256) void panel_far_kernel(PanelArgs pa, TrailArgs 
 // divisions) is formed once per thread and nothing is reduced before the end; with the values spread over the threads
 // every one of the 80 candidates had its divisions in all threads and a workgroup sum.  The sums are kept short (32
 // values, four accumulators; 4096 values; the row).  1999 rows of 2048: 260 -> 49 us.
+// Without the search (MSE false) the row's range is all there is: no values kept and four waves, so that eight workgroups
+// share a CU.  14336 x 4096 bf16 in groups of 256, whole sweep: 2.79 ms when the search's workgroup of five waves with its
+// values' LDS did this as well, 2.60 like this.
 constexpr int GP_SLICES = 4, GP_THREADS = GP_SLICES * MSE_CANDIDATES, GP_CHUNK = 4096;
-template <typename T>
-__global__ __launch_bounds__(GP_THREADS) void group_params_kernel(const T* __restrict__ W0, const float* __restrict__ C,
-                                                                 int d_out, int d_in, int g0, int G, float qmax, float qs,
-                                                                 int mse, int n_g, int g_idx, float* __restrict__ scales,
-                                                                 float* __restrict__ zeros, double* __restrict__ s64) {
-    constexpr int WAVES = GP_THREADS / 64;
+constexpr int gp_threads(bool mse) { return mse ? GP_THREADS : 256; }
+template <typename T, bool MSE>
+__global__ __launch_bounds__(gp_threads(MSE), 8) void group_params_kernel(   // 8: waves per SIMD
+    const T* __restrict__ W0, const float* __restrict__ C, int d_out, int d_in, int g0, int G, float qmax, float qs, int n_g,
+    int g_idx, float* __restrict__ scales, float* __restrict__ zeros, double* __restrict__ s64) {
+    constexpr int THREADS = gp_threads(MSE), WAVES = THREADS / 64;
     __shared__ double smn[WAVES], smx[WAVES];
-    __shared__ float part[GP_SLICES][MSE_CANDIDATES];
-    __shared__ __attribute__((aligned(16))) float val[GP_CHUNK];
+    __shared__ float part[MSE ? GP_SLICES : 1][MSE ? MSE_CANDIDATES : 1];
+    __shared__ __attribute__((aligned(16))) float val[MSE ? GP_CHUNK : 4];
     const int tid = threadIdx.x;
     for (int64_t r = blockIdx.x; r < d_out; r += gridDim.x) {
         const T* row = W0 + r * d_in + g0;
@@ -1133,8 +1136,8 @@ __global__ __launch_bounds__(GP_THREADS) void group_params_kernel(const T* __res
             return double(to_f32<T>(row[c])) + (crow ? double(crow[c]) : 0.0);
         };
         double mn = value(0), mx = mn;
-        const bool keep = mse && G <= GP_CHUNK;
-        for (int c = tid; c < G; c += GP_THREADS) {
+        const bool keep = MSE && G <= GP_CHUNK;
+        for (int c = tid; c < G; c += THREADS) {
             const double v = value(c);
             mn = fmin(mn, v); mx = fmax(mx, v);
             if (keep) val[c] = float(v);
@@ -1149,7 +1152,7 @@ __global__ __launch_bounds__(GP_THREADS) void group_params_kernel(const T* __res
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) { mn = fmin(mn, smn[w]); mx = fmax(mx, smx[w]); }
         int cand = 0;
-        if (mse) {   // uniform
+        if constexpr (MSE) {
             const int slice = tid / MSE_CANDIDATES, i = tid % MSE_CANDIDATES;
             double sd, zd;
             grid_params(mn, mx, i, double(qmax), double(qs), sd, zd);
@@ -1455,14 +1458,19 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
                 // the feedback of the earlier columns (none before the first group; the block form only takes one
                 // group per row, whose grid comes from the original weights)
                 const float* cur = (direct || s0 == 0) ? nullptr : w.Wf;
-                if (pa.w0_bf16)
-                    hipLaunchKernelGGL(group_params_kernel<uint16_t>, pgrid, dim3(GP_THREADS), 0, stream,
-                                       static_cast<const uint16_t*>(pa.W0), cur, int(d_out), int(d_in), s0, group_size,
-                                       pa.qmax, pa.qs, pa.mse, pa.n_g, g_idx, scales, zeros, w.s64);
-                else
-                    hipLaunchKernelGGL(group_params_kernel<float>, pgrid, dim3(GP_THREADS), 0, stream,
-                                       static_cast<const float*>(pa.W0), cur, int(d_out), int(d_in), s0, group_size,
-                                       pa.qmax, pa.qs, pa.mse, pa.n_g, g_idx, scales, zeros, w.s64);
+                auto params = [&](auto kernel, auto* W0) {
+                    hipLaunchKernelGGL(kernel, pgrid, dim3(gp_threads(pa.mse)), 0, stream, W0, cur, int(d_out), int(d_in), s0,
+                                       group_size, pa.qmax, pa.qs, pa.n_g, g_idx, scales, zeros, w.s64);
+                };
+                if (pa.w0_bf16) {
+                    const uint16_t* W0 = static_cast<const uint16_t*>(pa.W0);
+                    if (pa.mse) params(group_params_kernel<uint16_t, true>, W0);
+                    else params(group_params_kernel<uint16_t, false>, W0);
+                } else {
+                    const float* W0 = static_cast<const float*>(pa.W0);
+                    if (pa.mse) params(group_params_kernel<float, true>, W0);
+                    else params(group_params_kernel<float, false>, W0);
+                }
                 ONECOMP_CHECK_LAUNCH();
             }
             if (wide_static) pa.wide_g = s0 / group_size;
