@@ -740,9 +740,9 @@ __global__ __launch_bounds__(GRAM_THREADS) void gram_f32_kernel(const float* __r
 // Every wave accumulates the whole tile over its own tokens, so no two waves share an operand: the operands go from
 // global memory straight to registers in MFMA order (lane l: channel l % 32, token l / 32; a load reads two rows of
 // 128 bytes), no LDS and no barrier until the eight partial sums meet, added in wave order.
-// Bound by the fp32 matrix rate (157 TFLOP/s) once every CU has a tile: 253 tiles at d_in 1360 with 3001 tokens take 59 us
-// (94 TFLOP/s of the triangle; 278 us in 66 tiles of 128 x 128, each on a CU of its own), d_in 5792 with 8192 tokens
-// 129 TFLOP/s.  With the loads left to the compiler's schedule they sank to their use: 87 us instead of 59.
+// Bound by the fp32 matrix rate (157 TFLOP/s) once every CU has a tile: 253 tiles of 64 x 64 at d_in 1360 with 3001 tokens
+// take 52 us (107 TFLOP/s of the triangle; 278 us in 66 tiles of 128 x 128, each on a CU of its own), d_in 5792 with 8192
+// tokens 129 TFLOP/s.  With the loads left to the compiler's schedule they sank to their use: 1.5 times as long.
 // -------------------------------------------------------------------------------------------
 constexpr int F32S_WAVES = 8;
 template <int MT>
@@ -827,6 +827,10 @@ __device__ __forceinline__ void gram_f32_run(const float* __restrict__ X, int64_
 #pragma unroll 1
     for (; t + 6 * STEPS <= t_end; t += 4 * STEPS) {   // both batches to load lie inside the run
         step(f0, f1, t + 2 * STEPS, inside);
+        // All of f1 before its first product.  Left to wait load by load the eight waves drift apart along their runs, and
+        // where X just outgrows the cache the 32-wide tiles of a row of tiles then share less of it (d_in 1424, 24576
+        // tokens: 608 us instead of 545; d_in 896, 98304 tokens: 1070 instead of 1000; equal or 1 % apart elsewhere).
+        if constexpr (MT == 1) __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
         step(f1, f0, t + 4 * STEPS, inside);
     }
 #pragma unroll 1
@@ -1141,13 +1145,23 @@ onecomp_status gram_cross_accumulate_bf16(const void* Xh, const void* X, int64_t
 }
 
 // Which fp32 kernel a call takes, by measurement (us of a call, 128 x 128 tiles / 64 x 64 / 32 x 32 over eight token runs).
-// Many tokens: the 32-wide tiles fill the CUs best in narrow layers, the 64-wide ones move half the operand bytes; up to
-// 256 tokens a wave of a 64-wide tile has one pair of batches, and there these win from d_in 2048 on:
-//   d_in   512, 1024 tokens:  102 /   20 /   9     d_in 1360, 3001 tokens:  278 /   59 /  62
-//   d_in  2048,  256 tokens:   42 /   27 /  37     d_in 2048, 1024 tokens:  112 /   63 /  53
-//   d_in  2560,  256 tokens:   51 /   41 /  55     d_in 2560, 1024 tokens:  116 /   85 /  80
-//   d_in  2816,  512 tokens:   73 /   56 /  66     d_in 2816, 4096 tokens:  370 /  262 / 280
-//   d_in  4096, 1024 tokens:  243 /  194 / 212     d_in 4096, 8192 tokens: 1715 / 1175 / 1171
+// Many tokens: the 32-wide tiles fill the CUs best in narrow layers, the 64-wide ones move half the operand bytes, and one
+// of them is a round of a CU.  So the 64-wide tiles win where they fill their last round of 256, or wherever X is too
+// large for the 256 MB of cache behind the L2s (the operand bytes are then what a call takes); both from the width on where
+// there are enough of them:
+//   d_in   512, 1024 tokens:  102 /   20 /   9     d_in  768, 262144 tokens: 21650 / 4120 / 3700 (1.0 GB of X)
+//   d_in  1024, 8192 tokens:  705 /  124 /  97     d_in 1024, 131072 tokens: 10860 / 1890 / 2090 (0.5 GB)
+//   d_in  1360, 3001 tokens:  278 /   52 /  58     (253 tiles)    65536 tokens:  5450 /  961 / 1970
+//   d_in  1424, 8192 tokens:    -  /  245 / 164     (276 tiles)    65536 tokens:     - / 1990 / 2310
+//   d_in  1792, 16384 tokens:   -  /  478 / 440     (406 tiles)    65536 tokens:     - / 1900 / 2940
+//   d_in  1920, 16384 tokens:   -  /  481 / 501     (465 tiles)    65536 tokens:     - / 1900 / 3750
+//   d_in  2048, 16384 tokens: 1390 /  718 / 570     (528 tiles)    65536 tokens:  5470 / 2950 / 3790
+//   d_in  2304, 16384 tokens:   -  /  720 / 708     (666 tiles)    32768 tokens:     - / 1440 / 2200
+//   d_in  2432, 16384 tokens:   -  /  724 / 775     (741 tiles)    32768 tokens:     - / 1440 / 2620
+//   d_in  2560, 16384 tokens: 1390 /  960 / 867     (820 tiles)    32768 tokens:  2760 / 1950 / 3020
+//   d_in  2816,  512 tokens:   73 /   56 /  66     d_in 4096, 8192 / 65536 tokens: 1707 / 1109 / 1099, 13780 / 9240 / 15150
+// Up to 256 tokens a wave of a 64-wide tile has one pair of batches, and there these win from d_in 2048 on:
+//   d_in  2048,  256 tokens:   42 /   27 /  31     d_in 2560,  256 tokens:   49 /   41 /  46
 // Few tokens for the width: reading and writing H is most of the call, and the 128-wide tiles (three workgroups per CU
 // instead of one) are the better ones.  On both sides of the crossing, 128-wide : the other tile:
 //   d_in  1536,   32 /  100:    24 /   31 :   23 /   24    d_in  1792,   64 /  128:   27 /   33 :   29 /   30
@@ -1164,7 +1178,11 @@ static int f32_tile(int64_t n_tokens, int64_t d_in, int64_t ldx) {
                         : d_in < 8192 ? d_in * d_in / 1000 * d_in / 180000
                                       : d_in / 4;
     if (n_tokens < few && n_tokens < d_in / 4) return F32_TS;
-    return d_in < 2048 || (d_in < 2688 && n_tokens > 256) ? 32 : 64;
+    if (d_in >= 2688 || (d_in >= 2048 && n_tokens <= 256)) return 64;
+    const int64_t n_t = ceil_div(d_in, 64), tiles = n_t * (n_t + 1) / 2;
+    const bool full = ceil_div(tiles, 256) * 256 * 100 <= tiles * 114;
+    const bool out_of_cache = d_in >= 1024 && n_tokens * d_in > (int64_t(1) << 26);
+    return (full && n_tokens >= 2048) || out_of_cache ? 64 : 32;
 }
 
 onecomp_status gram_accumulate_f32(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H,

@@ -136,9 +136,12 @@ def test_gram_ragged_shapes(d_in, n_tok, dtype):
 
 @pytest.mark.parametrize("d_in,n_tok,pad,tile", [
     # 32-wide tiles: one ragged tile, a ragged last tile, token counts around the eight runs and their batches of 32
-    (16, 1, 0, 32), (48, 7, 0, 32), (80, 255, 4, 32), (512, 257, 0, 32), (1360, 3001, 16, 32), (2672, 257, 0, 32),
+    (16, 1, 0, 32), (48, 7, 0, 32), (80, 255, 4, 32), (512, 257, 0, 32), (1424, 3001, 16, 32), (2672, 257, 0, 32),
+    (1360, 2047, 0, 32), (2560, 2049, 0, 32),
     # 64-wide tiles, batches of 16; a last run of one token, an odd last pair
     (2064, 86, 0, 64), (2560, 256, 0, 64), (3072, 161, 0, 64), (3088, 385, 16, 64), (4112, 401, 0, 64), (8192, 2049, 0, 64),
+    # 64-wide tiles that fill their last round of CUs; X larger than the cache
+    (1360, 2048, 0, 64), (1360, 3001, 16, 64), (1040, 64545, 0, 64), (2560, 26241, 0, 64),
     # few tokens for the width
     (1552, 1, 0, 128), (3056, 33, 0, 128), (4112, 127, 16, 128), (8208, 100, 0, 128),
 ])
