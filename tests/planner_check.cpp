@@ -48,13 +48,14 @@ static void check_syrk_schedule(int n_blk) {
     for (int s = 0; s + 1 < n_blk; ++s) {
         const int next_lag = syrk_lag(n_blk - 2 - s), stride = next_lag == lag ? lag : 1, n_t = n_blk - 1 - s;
         const SyrkGrid q = syrk_grid(n_t, stride);
-        std::set<std::pair<int, int>> seen;
+        std::vector<char> seen(size_t(n_t) * n_t, 0);
         for (int b = 0; b < q.total; ++b) {
             int tm = -1, tn = -1;
             if (!syrk_tile(b, q, tm, tn)) continue;
             REQUIRE(0 <= tn && tn <= tm && tm < n_t, "syrk %d step %d workgroup %d -> (%d, %d)", n_blk, s, b, tm, tn);
             REQUIRE(b != 0 || (tm == 0 && tn == 0), "syrk %d step %d: workgroup 0 owns (%d, %d)", n_blk, s, tm, tn);
-            REQUIRE(seen.insert({tm, tn}).second, "syrk %d step %d tile (%d, %d) owned twice", n_blk, s, tm, tn);
+            REQUIRE(!seen[size_t(tm) * n_t + tn], "syrk %d step %d tile (%d, %d) owned twice", n_blk, s, tm, tn);
+            seen[size_t(tm) * n_t + tn] = 1;
             const int k0 = tn == 0 ? s : syrk_first_panel(tn, s, lag, base);
             int& d = done[s + 1 + tm][s + 1 + tn];
             REQUIRE(d == k0 && k0 <= s, "syrk %d step %d tile (%d, %d): has %d panels, next %d", n_blk, s, tm, tn, d, k0);
@@ -211,9 +212,12 @@ int main() {
 #else
     const int step = 16;
 #endif
-    for (int n_blk = 1; n_blk <= 80; ++n_blk) check_syrk_schedule(n_blk);
-#ifndef PLANNER_CHECK_THIN
-    for (int n_blk : {96, 112, 113, 160, 224, 256}) check_syrk_schedule(n_blk);   // up to d_in 32768
+    // up to the 362 blocks of the widest factor (d_in 46336); in the thinned build a few of those that begin with lag 4
+    for (int n_blk = 1; n_blk <= 82; ++n_blk) check_syrk_schedule(n_blk);
+#ifdef PLANNER_CHECK_THIN
+    for (int n_blk : {83, 84, 85, 113, 224, 362}) check_syrk_schedule(n_blk);
+#else
+    for (int n_blk = 83; n_blk <= 362; n_blk += n_blk < 130 || n_blk > 300 ? 1 : 7) check_syrk_schedule(n_blk);
 #endif
     for (int d_in = 16; d_in <= 32768; d_in += step) {
         if (d_in <= 4096 || d_in % 256 == 0) {            // every width up to 4096, then every multiple of 256 (set-based checks)
