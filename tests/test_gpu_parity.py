@@ -120,7 +120,7 @@ def test_gram_c1_fp32():
 @pytest.mark.parametrize("d_in,n_tok,dtype", [
     (128, 77, torch.bfloat16), (384, 1000, torch.bfloat16), (528, 333, torch.bfloat16),
     (1024, 4099, torch.bfloat16), (144, 50, torch.float32), (384, 1001, torch.float32),
-    # 128 x 256 direct-to-LDS tiles: ragged channel edge, fewer tokens than the ring holds, odd number of steps
+    # few tokens for a wide layer: ragged channel edge, odd number of steps
     (1040, 333, torch.bfloat16), (1536, 17, torch.bfloat16), (2304, 1000, torch.bfloat16), (4096, 515, torch.bfloat16),
 ])
 def test_gram_ragged_shapes(d_in, n_tok, dtype):
@@ -132,6 +132,28 @@ def test_gram_ragged_shapes(d_in, n_tok, dtype):
     Hn = H.cpu().numpy()
     assert rel_fro(Hn.astype(np.float64), Ho) <= 1e-4
     assert np.array_equal(Hn, Hn.T)
+
+
+@pytest.mark.parametrize("shape", ["wide", "big", "mid"])
+@pytest.mark.parametrize("d_in,n_tok", [(1040, 333), (1536, 17), (2304, 1), (4096, 515)])
+def test_gram_ring_of_few_tokens(monkeypatch, shape, d_in, n_tok):
+    """The direct-to-LDS kernels where a call ends before their ring of slots is full: ragged channel edge, fewer tokens
+    than the ring holds, odd number of steps.  (Left to itself the library takes them for such calls in wider layers.)"""
+    _announce(f"gram ring {shape} d_in={d_in} n_tok={n_tok}")
+    monkeypatch.setenv("ONECOMP_GRAM_SHAPE", shape)
+    plan = og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, 0)
+    assert (plan["tile_rows"], plan["tile_cols"]) == ({"wide": 384, "big": 256, "mid": 128}[shape], 256)
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    wide = torch.full((n_tok + 1, d_in), float("nan"), device=DEV, dtype=torch.bfloat16)   # the row behind is not read
+    wide[:n_tok] = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    X = wide[:n_tok]
+    H = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H)
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd) + 0.5
+    assert torch.equal(H, H.t())
+    # exact products, n_tok fp32 additions whose rounding errors add up like a random walk (see the fp32 tiles)
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
 
 
 @pytest.mark.parametrize("d_in,n_tok,pad,tile", [

@@ -237,16 +237,33 @@ def test_rtn_sensitivity(bits, G, d_out, d_in, dtype, grid):
     (4, 1008, 9, 3024, torch.bfloat16),      # two loads of a whole wave, ragged
     (4, 528, 21, 1584, torch.float32),       # three loads: the group is read twice
     (3, 16, 300, 32848, torch.bfloat16),     # 2053 groups per row (a prime): teams change their slice of a
+    # more groups than the grid's teams, a last step that not every team takes: one load per lane, two, three; both widths
+    (4, 16, 6300, 336, torch.float32), (2, 48, 18800, 336, torch.bfloat16), (3, 48, 9400, 336, torch.float32),
+    (4, 1040, 2750, 3120, torch.bfloat16), (4, 528, 2760, 1584, torch.float32),
 ])
 def test_rtn_sensitivity_group_widths(bits, G, d_out, d_in, dtype):
-    """Group widths around the lane counts of the kernel.  Bar as above."""
+    """Group widths around the lane counts of the kernel.  Bar: relative error <= 1e-5: grids, squares
+    and sums in fp32, errors of 2^-24 that do not add up in one direction (up to 1.4e-7 here), and a rounding tie costs the
+    same on both sides.  The weights of channels and rows differ so much that a wrong slice of a, a wrong row or a lost
+    last group moves the sum by more than a hundred times the bar, which the oracle confirms."""
     _announce(f"RTN sensitivity b{bits} g{G} {d_out}x{d_in} {dtype}")
     gen = torch.Generator(device=DEV).manual_seed(d_in + G)
     W = torch.randn((d_out, d_in), generator=gen, device=DEV).to(dtype)
-    a = (0.5 + 3.0 * torch.rand(d_in, generator=gen, device=DEV)).to(torch.float32)
+    slope = 10.0 ** (3.0 * torch.arange(d_in, device=DEV) / d_in)
+    a = ((0.5 + 3.0 * torch.rand(d_in, generator=gen, device=DEV)) * slope).to(torch.float32)
     b = (0.5 + torch.rand(d_out, generator=gen, device=DEV)).to(torch.float32)
+    b[0] *= 1e3
+    b[-1] *= 1e4
+    bar = 1e-5
     for grid, og_grid in (("minmax", "asym"), ("symmetric", "sym")):
         e = og.onecomp_rtn_sensitivity(W, a, bits, G, b_diag=b, grid=grid)
         torch.cuda.synchronize()
-        ref = oc.rtn_sensitivity(to_f64(W), to_f64(a), to_f64(b), bits, G, grid=og_grid)
-        assert abs(float(e.item()) - ref) <= 1e-3 * ref
+        Wn, an, bn = to_f64(W), to_f64(a), to_f64(b)
+        ref = oc.rtn_sensitivity(Wn, an, bn, bits, G, grid=og_grid)
+        _announce(f"   {grid}: relative error {abs(float(e.item()) - ref) / ref:.2e}")
+        assert abs(float(e.item()) - ref) <= bar * ref
+        if d_in > G:
+            assert abs(oc.rtn_sensitivity(Wn, np.roll(an, G), bn, bits, G, grid=og_grid) - ref) > 100 * bar * ref
+        if d_out > 1:
+            assert abs(oc.rtn_sensitivity(Wn, an, np.roll(bn, 1), bits, G, grid=og_grid) - ref) > 100 * bar * ref
+        assert oc.rtn_sensitivity(Wn[-1:, -G:], an[-G:], bn[-1:], bits, G, grid=og_grid) > 100 * bar * ref
