@@ -7,11 +7,13 @@
 //
 // gfx950: W is read once from HBM.  A team of TS <= 64 lanes of one wave owns a group at a time, 16 bytes per lane and
 // load.  Per-workgroup partial sums are combined in a fixed order: bit-wise reproducible.
-// Once W comes in at full width the kernel is bound by its VALU operations, so the work beside the nine operations per
-// weight is kept small: a group of up to two loads per lane stays in registers between the pass for min / max and the
-// one that rounds (wider groups read it again, from cache), the lanes of a row of 16 meet through DPP operands, the
-// position in the matrix advances by additions (a 64-bit division per group cost more than the group's arithmetic), and
-// the grid is a multiple of the groups of a row where it can be, so that a team keeps its slice of `a`.
+// Once W comes in at full width the kernel is bound by its VALU operations: 24 per weight at 4096 x 4096 bf16 in groups of
+// 64 and 128 (counted by SQ_INSTS_VALU), nine of them the weight's own (unpacking, range, rounding, sum), the rest what a
+// group costs every lane of its team for eight weights: the reduction of the range, two divisions and a reciprocal,
+// addresses.  That rest is kept small: a group of up to two loads per lane stays in registers between the pass for min / max
+// and the one that rounds (wider groups read it again, from cache), the lanes of a row of 16 meet through DPP operands,
+// the position in the matrix advances by additions (a 64-bit division per group cost more than the group's arithmetic),
+// and the grid is a multiple of the groups of a row where it can be, so that a team keeps its slice of `a`.
 // 4096 x 4096 bf16, G 64 / 128: 16.2 -> 13.5 us per candidate.
 #include "common.hpp"
 
