@@ -148,7 +148,7 @@ onecomp_status onecomp_accumulate_describe(onecomp_dtype x_dtype, int64_t n_toke
  *   damp      eta >= 0.  A zero diagonal entry of H (dead input channel) is replaced by 1
  *             before lambda is computed.
  *   act_order 0: natural column order.  non-zero: perm = indices of diag(H) in decreasing
- *             order (equal keys: lower index first) and the matrix factored is
+ *             order (equal keys: lower index first; a NaN goes last) and the matrix factored is
  *             (H + lambda I)[perm][:, perm].
  *   perm_out  int32[d_in]; the order used (identity when act_order == 0).  May be NULL when
  *             act_order == 0.

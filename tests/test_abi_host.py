@@ -91,7 +91,7 @@ def test_accumulate_describe_argument_checks(lib):
     assert fn(1, i64(-1), i64(512), i64(512), sz(0), out) == INVALID
     assert fn(1, i64(100), i64(512), i64(256), sz(0), out) == INVALID           # row stride below d_in
     assert list(out) == [-1, -1, -1]
-    # narrow layers and fp32 inputs: one launch of a 128 x 128 kernel, known without asking the device
+    # narrow layers, and fp32 inputs of few tokens: one launch of a 128 x 128 kernel, known without asking the device
     assert fn(1, i64(100), i64(512), i64(512), sz(0), out) == OK and list(out) == [128, 128, 1]
     assert fn(0, i64(100), i64(4096), i64(4096), sz(0), out) == OK and list(out) == [128, 128, 1]
 
