@@ -8,13 +8,13 @@
 // One Cholesky plus one triangular inverse (2 n^3 / 3 flops), all in fp64; U is rounded once to fp32.
 //
 // gfx950 design
-//   * blocked right-looking Cholesky, block 128: diagonal block factored (and inverted) inside one
+//   * blocked right-looking Cholesky, block 128: diagonal block factored (and its halves inverted) inside one
 //     workgroup's LDS; panel solve and trailing update are fp64 MFMA GEMMs (v_mfma_f64_16x16x4_f64),
-//     128 x 128 tile per workgroup, operands streamed global -> LDS directly through a four-slot ring; a launch
+//     128 x 128 or 128 x 64 tile per workgroup, operands streamed global -> LDS directly through a ring of slots; a launch
 //     has one workgroup per tile that has work, the longest tiles first.
-//   * triangular inverse by recursive doubling over aligned block pairs: for block size s = 128 * 2^l,
+//   * triangular inverse by recursive doubling over aligned block pairs: for block size s = 64 * 2^l,
 //     V[C,A] = -V[C,C] (L[C,A] V[A,A]); every level is two batched GEMMs, so the whole inverse is
-//     ~2 log2(n/128) large launches instead of n/128 skinny ones.
+//     ~2 log2(n/64) large launches instead of n/128 skinny ones.
 //   * ordering by rank counting (stable, deterministic), no floating-point atomics anywhere.
 #include "common.hpp"
 #include "planner.hpp"
@@ -90,10 +90,12 @@ __global__ __launch_bounds__(64 * ORDER_WAVES) void order_kernel(const float* __
 
 // A[r][c] = Hd[p[n-1-r]][p[n-1-c]] in fp64 (reversed, permuted, damped); upper triangle of H is read.  Only the
 // 128 x 128 blocks on and below the diagonal are written: the factorization never reads the others, and in natural
-// order (this kernel) those are the ones whose source rows are read along the row.
+// order (this kernel) those are the ones whose source rows are read along the row.  Also: V's zeros above the diagonal
+// of its diagonal blocks, and the copy of block (1, 0) that the first panel solve takes (panel_kernel).
 __global__ __launch_bounds__(256) void build_kernel(const float* __restrict__ H, int n,
                                                    const double* __restrict__ dfix, const double* __restrict__ lam,
-                                                   double* __restrict__ A) {
+                                                   double* __restrict__ A, double* __restrict__ V,
+                                                   double* __restrict__ Pn) {
     const int c = blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (c >= n || c / NB > r / NB) return;
@@ -102,6 +104,8 @@ __global__ __launch_bounds__(256) void build_kernel(const float* __restrict__ H,
     if (i == k) v = dfix[i] + *lam;
     else v = double(H[int64_t(min(i, k)) * n + max(i, k)]);
     A[int64_t(r) * n + c] = v;
+    if (c > r) V[int64_t(r) * n + c] = 0.0;
+    if (c < NB && r / NB == 1) Pn[(r - NB) * NB + c] = v;
 }
 
 // The same under a column order.  H's upper triangle then comes in at scattered places, half of them along columns: 64
@@ -133,7 +137,8 @@ constexpr int GATHER_COLS = 16384;   // columns of S in LDS at a time: two workg
 __global__ __launch_bounds__(512) void build_order_kernel(const float* __restrict__ S, int n,
                                                          const int32_t* __restrict__ perm,
                                                          const double* __restrict__ dfix,
-                                                         const double* __restrict__ lam, double* __restrict__ A) {
+                                                         const double* __restrict__ lam, double* __restrict__ A,
+                                                         double* __restrict__ V, double* __restrict__ Pn) {
     extern __shared__ float srow[];
     const int r = n - 1 - int(blockIdx.x);   // the longest rows first
     const int i = perm[n - 1 - r];
@@ -152,7 +157,10 @@ __global__ __launch_bounds__(512) void build_order_kernel(const float* __restric
         for (int c = threadIdx.x; c < c_end; c += 512) {
             const int k = perm[n - 1 - c];
             if (unsigned(k - b) >= unsigned(cols)) continue;
-            A[int64_t(r) * n + c] = k == i ? dfix[i] + *lam : double(srow[k - b]);
+            const double v = k == i ? dfix[i] + *lam : double(srow[k - b]);
+            A[int64_t(r) * n + c] = v;
+            if (c > r) V[int64_t(r) * n + c] = 0.0;
+            if (c < NB && r / NB == 1) Pn[(r - NB) * NB + c] = v;
         }
     }
 }
@@ -192,24 +200,26 @@ __global__ __launch_bounds__(256) void output_block_kernel(const double* __restr
 }
 
 // ------------------------------------------------------------------------------------------
-// diagonal block: Cholesky in LDS, then in-place triangular inverse.  One workgroup of 256 threads (4 waves).
-// A block (bs x bs, bs <= 128) at A + off*(n+1); L^-1 is written to V (full block, zeros above the diagonal); the
-// factor L_kk of the block itself stays in LDS (nothing downstream reads it).  A non-positive pivot sets *info (first one wins) and is replaced by 1.
+// diagonal block: Cholesky and the inverses of its two 64 x 64 diagonal halves.  One workgroup of 512 threads (8 waves).
+// A block (bs x bs, bs <= 128) at A + off*(n+1).  The inverses of the halves of L_kk go to V (zeros above the diagonal are
+// there already), the quarter of L_kk between them to A's place: the panel solve needs these three, and V's lower left
+// quarter is completed for all blocks at once at the end.  Nothing else of L_kk leaves the workgroup.  A non-positive
+// pivot sets *info (first one wins) and is replaced by 1.
 //
-// The block lives in LDS as 16 x 16 sub-blocks (only those on and below the diagonal, 36 of them, row pitch 17
-// doubles, 76.5 KB: small enough for two workgroups per CU, so the factorization can share a launch with GEMM
-// tiles).  Everything but the 16 x 16 leaves runs on v_mfma_f64_16x16x4_f64 with sub-blocks as operands:
-//   Cholesky, block column J:  leaf factorization of (J,J) by wave 0 in registers, which leaves T = L_JJ^-1 in the
-//     sub-block's place;  L_IJ = A_IJ T^T for the sub-blocks below;  A_IK -= L_IJ L_KJ^T for J < K <= I, of which
-//     wave 0 takes (J+1, J+1) alone and goes straight on to the next leaf while the other waves do the rest.
-//   Inverse X = L^-1, beside it: once column K of L is behind the updates, P_IC += L_IK X_KC (C < K) and
-//     P_IK = L_IK X_KK in place of L_IK, for the rows I > K;  when all columns left of row R are in,
-//     X_RC = -T_R P_RC.  Row by row this runs one column behind the Cholesky on the waves that are not in a leaf, and
-//     every finished row goes to V at once; only the last two rows are left when the last leaf is done.
-// The whole is a chain of latencies on one CU, exposed in every step with a short trailing update (d_in 4096: most of
-// them), so what counts is what stands between two pivots.  Leaves with square roots on that chain (and two moves per
-// broadcast), with the inverse behind the last column: leaf 2.3 -> 1.2 us, a block alone in its launch 49.7 ->
-// 31 us.
+// The block is 36 sub-blocks of 16 x 16 (on and below the diagonal); finished ones live in LDS (row pitch 17 doubles,
+// 76.5 KB: small enough for two workgroups per CU, so the factorization can share a launch with GEMM tiles), those that
+// still take updates in the accumulators of the wave that owns them.  Everything but the 16 x 16 leaves runs on
+// v_mfma_f64_16x16x4_f64 with sub-blocks as operands.  The whole is a chain of latencies on one CU, exposed in every step
+// with a short trailing update (d_in 4096: all of them), so what counts is what stands between two pivots:
+//   wave 0: the leaf of (J,J) in registers, which leaves T = L_JJ^-1; from T, still in the registers in operand layout,
+//     L_J+1,J = A_J+1,J T^T and A_J+1,J+1 -= L L^T (computed transposed, so that one product's result is the next one's
+//     operand), then the next leaf.
+//   waves 1-3 and 5-7 (SIMDs 1-3, two waves each to cover each other's waits): L_IJ = A_IJ T^T for I > J + 1 while wave 0
+//     does its two products, then, beside the next leaf, A_IK -= L_IJ L_KJ^T and, on three of the waves, a column each of
+//     the halves' inverses, X_J = -T_J P_J, P_J+1 = sum_K L_J+1,K X_K.
+//   wave 4 (SIMD 0, next to the leaves): sends what is finished to memory.
+// Before: the inverse of the whole 128-wide block here, all products on four waves and through LDS, the trailing update of
+// the block in front of it in the same workgroup: 37 us a launch, now 18.
 // MFMA operand layouts (lane l): A[i][k]: i = l % 16, k = l / 16;  B[k][j]: k = l / 16, j = l % 16;
 // C/D register r: row 4 r + l / 16, column l % 16.
 // ------------------------------------------------------------------------------------------
@@ -217,11 +227,9 @@ constexpr int SBW = 16;      // sub-block width
 constexpr int SBP = SBW + 1;
 constexpr int SBS = SBW * SBP;
 constexpr int NSB = NB / SBW;
+constexpr int HALF = NB / 2;   // the block's diagonal is inverted in halves
+constexpr int POTRF_THREADS = 512;
 constexpr int POTRF_LDS_DOUBLES = NSB * (NSB + 1) / 2 * SBS;   // the lower sub-blocks
-__device__ __forceinline__ int tri(int r, int c) {   // element (r, c), c / 16 <= r / 16
-    const int rb = r >> 4, cb = c >> 4;
-    return ((rb * (rb + 1)) / 2 + cb) * SBS + (r & 15) * SBP + (c & 15);
-}
 __device__ __forceinline__ int sub(int I, int J) { return ((I * (I + 1)) / 2 + J) * SBS; }   // J <= I
 
 // 1 / sqrt(p): v_rsq_f64 is good to 5e-8 relative (measured over 120 binades), the first Newton step brings it to 4e-15,
@@ -287,23 +295,14 @@ __device__ __forceinline__ void tri_inverse16(const double (&nlh)[SBW], const do
     for (int k = 0; k < 4; ++k) x[k] *= rdi;
 }
 
-// S: POTRF_LDS_DOUBLES doubles of LDS.  preloaded: the block (lower sub-blocks, identity padding beyond bs) is
-// already in S and a barrier has been passed.
-__device__ __forceinline__ void potrf_body(const double* __restrict__ A, double* __restrict__ V, int n, int off, int bs,
-                                           int32_t* __restrict__ info, double* S, bool preloaded) {
+// S: POTRF_LDS_DOUBLES doubles of LDS
+__device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __restrict__ V, int n, int off, int bs,
+                                           int32_t* __restrict__ info, double* S) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lk = lane >> 4;
-    if (!preloaded) {
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int r = e / NB, c = e % NB;
-            if ((c >> 4) > (r >> 4)) continue;
-            double v = (r == c) ? 1.0 : 0.0;   // identity padding for a short last block
-            if (r < bs && c < bs) v = A[int64_t(off + r) * n + off + c];
-            S[tri(r, c)] = v;
-        }
-        __syncthreads();
-    }
+    double* __restrict__ const Ab = A + int64_t(off) * (n + 1);
+    double* __restrict__ const Vb = V + int64_t(off) * (n + 1);
     // operand fragments of a sub-block M (pointer to its first element), k-step q = 0..3
     auto frag_rowk = [&](const double* M, int q) __attribute__((always_inline)) {   // M[l%16][4q + l/16]
         return M[l16 * SBP + 4 * q + lk];
@@ -328,17 +327,46 @@ __device__ __forceinline__ void potrf_body(const double* __restrict__ A, double*
         for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
         return c;
     };
+    // c + A B^T, both by their row fragments
+    auto mul_add_t = [&](const double* MA, const double* MB, double4v c) __attribute__((always_inline)) {
+        double a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = frag_rowk(MA, q);
+            b[q] = frag_rowk(MB, q);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
+        return c;
+    };
     const double4v zero4 = {0.0, 0.0, 0.0, 0.0};
-    // sub-block (I, J) of the inverse to V: a store instruction writes four 128-byte row segments
-    auto out = [&](int I, int J, const double4v& c) __attribute__((always_inline)) {
+    // sub-block (I, J) of the matrix, identity padding for a short last block
+    auto fetch = [&](int I, int J) __attribute__((always_inline)) {
+        double4v c;
+        const double* p = Ab + int64_t(I * SBW + lk) * n + J * SBW + l16;
+        if (bs == NB) {   // unconditional loads: all in flight together
+#pragma unroll
+            for (int r = 0; r < 4; ++r) c[r] = p[int64_t(4 * r) * n];
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
+                double v = row == col ? 1.0 : 0.0;
+                if (row < bs && col < bs) v = p[int64_t(4 * r) * n];
+                c[r] = v;
+            }
+        }
+        return c;
+    };
+    // sub-block (I, J) to memory: a store instruction writes four 128-byte row segments
+    auto out = [&](double* __restrict__ M, int I, int J, const double4v& c) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
-            if (row < bs && col < bs) V[int64_t(off + row) * n + off + col] = c[r];
+            if (row < bs && col < bs) M[int64_t(row) * n + col] = c[r];
         }
     };
 
-    // ---------------- Cholesky, 8 block columns of 16 ----------------
     // Leaf of block column J: wave 0 factors the diagonal sub-block in registers (lane i (mod 16) = row i; lanes
     // 16..63 shadow lanes 0..15) as Lh D Lh^T and leaves its inverse factor T = D^-1/2 Lh^-1 in the sub-block's place: the
     // panel solves below and the inversion of the whole block need that, nothing reads L_JJ itself.
@@ -348,6 +376,7 @@ __device__ __forceinline__ void potrf_body(const double* __restrict__ A, double*
     // with the step (4 million values over 400 binades), and that is an update's relative error; columns scaled by
     // reciprocal square roots with one step each had 8e-15.  U of a rank-deficient H with damping 1e-6, d_in 1024:
     // 1.545e-3 of its entries are not the rounded exact value (extended precision); with those square roots 1.566e-3.
+    double x[4];   // wave 0: T of the last leaf, k-step q of its row fragments in x[q]
     auto leaf = [&](int J) __attribute__((always_inline)) {
         double* DJ = S + sub(J, J);
         const int i = l16;
@@ -393,151 +422,102 @@ __device__ __forceinline__ void potrf_body(const double* __restrict__ A, double*
         if (bad_at >= 0 && tid == 0 && *info == 0) *info = off + J * SBW + bad_at + 1;
         // every lane has read its row before any lane overwrites the sub-block (one wave: program order); zeros above
         // the diagonal
-        double x[4];
         tri_inverse16(nlh, rsqrt_refined(my_d), i, lk, x);
 #pragma unroll
         for (int k = 0; k < 4; ++k) DJ[i * SBP + 4 * k + lk] = x[k];
     };
-    // N products with the same left operand, side by side: one after the other a product is a chain of LDS reads, four
-    // dependent MFMAs and an LDS write.
-    // A_IK -= L_IJ L_KJ^T for K = K0 .. K0 + N - 1
-    auto update_row = [&](auto nc, int I, int J, int K0) __attribute__((always_inline)) {
-        constexpr int N = decltype(nc)::value;
-        double a[4], b[N][4];
-        double4v c[N];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) a[q] = -frag_rowk(S + sub(I, J), q);
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) b[u][q] = frag_rowk(S + sub(K0 + u, J), q);
-            c[u] = load_c(S + sub(I, K0 + u));
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int u = 0; u < N; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[u][q], c[u], 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < N; ++u) store_c(S + sub(I, K0 + u), c[u]);
-    };
-    // P_IC += L_IK X_KC for C = C0 .. C0 + N - 1; a = L_IK, in whose place P_IK = L_IK X_KK comes last
-    auto inverse_row = [&](auto nc, int I, int K, int C0, const double (&a)[4]) __attribute__((always_inline)) {
-        constexpr int N = decltype(nc)::value;
-        double4v b[N], c[N];
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            b[u] = load_c(S + sub(K, C0 + u));
-            c[u] = load_c(S + sub(I, C0 + u));
-            if (u == N - 1 && C0 + u == K) c[u] = zero4;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int u = 0; u < N; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[u][q], c[u], 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < N; ++u) store_c(S + sub(I, C0 + u), c[u]);
-    };
-    auto in_fours = [&](int n, auto&& f) __attribute__((always_inline)) {   // f(count, first) over 0 .. n - 1
-        int k = 0;
-        for (; k + 4 <= n; k += 4) f(std::integral_constant<int, 4>{}, k);
-        switch (n - k) {
-            case 3: f(std::integral_constant<int, 3>{}, k); break;
-            case 2: f(std::integral_constant<int, 2>{}, k); break;
-            case 1: f(std::integral_constant<int, 1>{}, k); break;
-            default: break;
-        }
-    };
-    // The leaves are a chain of latencies on one wave (16 dependent pivots each, then the 16 x 16 inverse), so the
-    // next leaf runs beside the updates it does not depend on: after the panel solve of column J, wave 0 updates the
-    // next diagonal sub-block alone and factors it at once, while the other three waves do the rest.
+    store_c(S + sub(wave, 0), fetch(wave, 0));
+    // The three roles pass the same barriers: one before the first leaf, then two per column, behind its leaf and behind
+    // its solve.
     if (wave == 0) {
+        __syncthreads();
         leaf(0);
-    } else {   // what the inverse has above its diagonal sub-blocks: nobody waits for these stores
-        for (int t = wave - 1; t < NSB * (NSB - 1) / 2; t += 3) {
-            int J = 1;
-            while (J * (J + 1) / 2 <= t) ++J;
-            out(t - J * (J - 1) / 2, J, zero4);
-        }
-    }
-    __syncthreads();
 #pragma unroll 1
-    for (int J = 0; J < NSB - 1; ++J) {
-        const double* TJ = S + sub(J, J);
-        // L_IJ = A_IJ T^T for I > J, then row R = J - 1 of the inverse: seven products, two per wave side by side (both
-        // in place: the operands are in registers before anything is written)
-        {
-            double a[2][4];
-            double4v b[2], c[2] = {zero4, zero4};
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int I = J + 1 + min(wave + 4 * u, NSB - 2), R = J - 1, C = I - NSB;
-                if (I < NSB) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        a[u][q] = frag_rowk(S + sub(I, J), q);
-                        b[u][q] = frag_rowk(TJ, q);
-                    }
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) a[u][q] = -frag_rowk(S + sub(R, R), q);
-                    b[u] = load_c(S + sub(R, C));
-                }
-            }
+        for (int J = 0; J < NSB - 1; ++J) {
+            __syncthreads();
+            // L_J+1,J, transposed: register r of the result is L_J+1,J[l%16][4 r + l/16], a row fragment
+            double4v lt = zero4;
+            double* const D = S + sub(J + 1, J + 1);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
+                lt = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q], frag_rowk(S + sub(J + 1, J), q), lt, 0, 0, 0);
+            double4v c = load_c(D);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) c[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][q], b[u][q], c[u], 0, 0, 0);
+            for (int q = 0; q < 4; ++q) S[sub(J + 1, J) + l16 * SBP + 4 * q + lk] = lt[q];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int t = wave + 4 * u, I = J + 1 + t, R = J - 1, C = I - NSB;
-                if (t > NSB - 2) continue;
-                if (I < NSB) {
-                    store_c(S + sub(I, J), c[u]);
-                } else if (C < R) {
-                    store_c(S + sub(R, C), c[u]);
-                    out(R, C, c[u]);
-                } else {
-                    out(R, R, b[u]);
-                }
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            update_row(std::integral_constant<int, 1>{}, J + 1, J, J + 1);   // the next diagonal sub-block
+            for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-lt[q], lt[q], c, 0, 0, 0);
+            store_c(D, c);
+            __syncthreads();
             leaf(J + 1);
-        } else {
-            // Rows dealt from the last one back and forth over the three waves: row I has I products (I - J updates, J of
-            // the inverse; the first two rows have fewer), at most nine a wave.
-            for (int m = 0; m < NSB - J; ++m) {
-                const int I = NSB - 1 - m, turn = m % 6;
-                if ((turn < 3 ? turn : 5 - turn) != wave - 1) continue;
-                if (I > J + 1)
-                    in_fours(I - J, [&](auto nc, int k) __attribute__((always_inline)) { update_row(nc, I, J, J + 1 + k); });
-                if (J > 0) {
-                    double a[4];
+        }
+        __syncthreads();
+    } else if (wave == 4) {
+        __syncthreads();
+#pragma unroll 1
+        for (int J = 0; J < NSB - 1; ++J) {
+            __syncthreads();
+            __syncthreads();
+            out(Vb, J, J, load_c(S + sub(J, J)));
+            if (J < NSB / 2)
+                for (int I = NSB / 2; I < NSB; ++I) out(Ab, I, J, load_c(S + sub(I, J)));
+        }
+        __syncthreads();
+        out(Vb, NSB - 1, NSB - 1, load_c(S + sub(NSB - 1, NSB - 1)));
+    } else {
+        // The sub-blocks right of column 0 in column order, dealt to the six waves: whatever column the factorization has
+        // reached, those that still take updates are spread evenly.  They are held with the sign reversed, so that the
+        // products need no negated operand.
+        constexpr int OWNERS = 6, N_OWNED = NSB * (NSB - 1) / 2, SLOTS = (N_OWNED + OWNERS - 1) / OWNERS;
+        const int ow = wave - 1 - (wave >> 2);
+        int si[SLOTS], sk[SLOTS];
+        double4v acc[SLOTS];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) a[q] = frag_rowk(S + sub(I, J - 1), q);
-                    in_fours(J, [&](auto nc, int k) __attribute__((always_inline)) { inverse_row(nc, I, J - 1, k, a); });
+        for (int u = 0; u < SLOTS; ++u) {
+            int rem = ow + OWNERS * u, K = 1;
+            while (K < NSB && rem >= NSB - K) rem -= NSB - K++;
+            sk[u] = K < NSB ? K : 0;   // 0: no sub-block
+            si[u] = K + rem;
+            if (sk[u] > 0) acc[u] = -fetch(si[u], K);
+        }
+        if (ow == 0) store_c(S + sub(1, 1), -acc[0]);
+        const int inv_c = OWNERS - 1 - ow;   // column of the halves' inverses of this wave (the waves of fewest updates)
+        const bool inv = inv_c < NSB / 2 - 1;
+        double4v pc = zero4;                 // and that column's next P
+        __syncthreads();
+#pragma unroll 1
+        for (int J = 0; J < NSB - 1; ++J) {
+            __syncthreads();
+            if (J + 2 + ow < NSB) {   // L_IJ = A_IJ T^T, in place
+                double* const M = S + sub(J + 2 + ow, J);
+                store_c(M, mul_add_t(M, S + sub(J, J), zero4));
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < SLOTS; ++u) {
+                const int I = si[u], K = sk[u];
+                if (K <= J || (I == K && K == J + 1)) continue;   // finished; or wave 0's
+                acc[u] = mul_add_t(S + sub(I, J), S + sub(K, J), acc[u]);
+                // to LDS before the solve of its column, a diagonal one before wave 0 takes over its last update
+                if (I == K ? K == J + 2 : K == J + 1) store_c(S + sub(I, K), -acc[u]);
+            }
+            const int C = (J & (NSB / 2)) + inv_c;
+            if (inv && C <= J) {
+                double4v xj = load_c(S + sub(J, J));
+                if (C < J) {
+                    xj = mul_add(S + sub(J, J), pc, zero4, -1.0);
+                    store_c(S + sub(J, C), xj);   // in place of L_JC, which only this column's earlier products needed
+                    out(Vb, J, C, xj);
+                }
+                if ((J + 1) % (NSB / 2) != 0) {
+                    pc = zero4;
+                    for (int K = C; K < J; ++K) pc = mul_add(S + sub(J + 1, K), load_c(S + sub(K, C)), pc, 1.0);
+                    pc = mul_add(S + sub(J + 1, J), xj, pc, 1.0);
                 }
             }
         }
         __syncthreads();
+        if (inv) out(Vb, NSB - 1, NSB / 2 + inv_c, mul_add(S + sub(NSB - 1, NSB - 1), pc, zero4, -1.0));
     }
-    // rows NSB - 2 and NSB - 1 of the inverse, by columns: nothing but registers between the products
-    constexpr int R0 = NSB - 2, R1 = NSB - 1;
-    for (int C = wave; C <= R0; C += 4) {
-        double4v x0 = load_c(S + sub(R0, C));
-        double4v c = zero4;
-        if (C < R0) {
-            x0 = mul_add(S + sub(R0, R0), x0, zero4, -1.0);
-            c = load_c(S + sub(R1, C));
-        }
-        c = mul_add(S + sub(R1, R0), x0, c, 1.0);
-        c = mul_add(S + sub(R1, R1), c, zero4, -1.0);
-        out(R0, C, x0);
-        out(R1, C, c);
-    }
-    if (wave == 3) out(R1, R1, load_c(S + sub(R1, R1)));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -557,6 +537,7 @@ struct GemmArgs {
     int batch;
     double alpha, beta;
     int flags;
+    double* copy;      // where block (1, 0) also goes, rows of NB (nullptr: nowhere)
 };
 
 constexpr int RK = 8, RNS = 4;                      // inner steps per ring slot, ring slots of the GEMM tile
@@ -572,72 +553,73 @@ __device__ __forceinline__ double* wg_lds() {
 }
 
 // ------------------------------------------------------------------------------------------
-// One T x T tile (tm, tn) of batch entry z with NW waves in two rows of NW / 2.  T = 128: 4 waves of 64 x 64, or 8 of
-// 64 x 32 (half the accumulators per lane, so that four waves share a SIMD and cover each other's waits).  T = 64: 4
-// waves of 32 x 32, for launches whose 128-wide tiles would leave CUs idle.
+// One TM x TN tile (tm, tn) of batch entry z with WR x WC waves.  128 x 128: 2 x 4 waves of 64 x 32, so that with two
+// workgroups per CU four waves share a SIMD and cover each other's waits.  64 x 64 (2 x 2 waves of 32 x 32) and 128 x 64
+// (4 x 2 of 32 x 32): for launches whose 128-wide tiles would leave CUs idle.
 // The operands are streamed global -> LDS directly (buffer_load ... lds) through a ring of NS slots
-// of RK inner steps each, NS - 1 stages ahead of the MFMAs: no staging registers, no LDS stores, no multiplication by
-// alpha on the way (alpha = +-1 is folded into the accumulators: they start as (beta / alpha) C and the result is
-// alpha acc, both exact), one barrier per stage.  A direct load deposits lane l at slot + 16 l, so rows cannot be
+// of SUB parts of RK inner steps each, NS - 1 stages ahead of the MFMAs: no staging registers, no LDS stores, no
+// multiplication by alpha on the way (alpha = +-1 is folded into the accumulators: they start as (beta / alpha) C and the
+// result is alpha acc, both exact), one barrier per stage.  A direct load deposits lane l at slot + 16 l, so rows cannot be
 // padded; the 16-byte chunks (two doubles) are permuted instead, which costs nothing on the global side because
 // every lane supplies its own address:
-//   A-form part (T rows x RK k, a row is 64 B = 4 chunks): chunk c of row r sits at position c ^ ((r >> 2) & 3);
+//   A-form part (rows x RK k, a row is 64 B = 4 chunks): chunk c of row r sits at position c ^ ((r >> 2) & 3);
 //     the 16 rows x 2 k that one half-wave reads for an MFMA operand then fall into 64 different banks.
-//   NN B part (RK k-rows x T columns, a k-row is T / 2 chunks): chunk c of k-row kr sits at c ^ ((kr & 1) << 3).
+//   NN B part (RK k-rows x TN columns, a k-row is TN / 2 chunks): chunk c of k-row kr sits at c ^ ((kr & 1) << 3).
 // ------------------------------------------------------------------------------------------
 
-template <bool bt, int NW, int T, int NS>
+template <bool bt, int WR, int WC, int TM, int TN, int SUB, int NS>
 __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn, const int tm, const int z, double* lds) {
-    constexpr int NI = T / 32;          // 16-row MFMA tiles per wave (two waves share the rows)
-    constexpr int NJ = T / (8 * NW);    // 16-column MFMA tiles per wave
-    constexpr int PART_LOADS = T / 16;  // 1 KB loads of a stage's A part, and of its B part
-    constexpr int LPW = 2 * PART_LOADS / NW;
-    constexpr int PART_BYTES = T * RK * 8, STAGE_BYTES = 2 * PART_BYTES;
-    constexpr int KROW = T * 8;         // bytes of a k-row of a row-major B part
-    static_assert(PART_LOADS % NW == 0 && LPW >= 2, "a load belongs to one operand in every wave");
+    constexpr int NW = WR * WC;
+    constexpr int NI = TM / (16 * WR), NJ = TN / (16 * WC);       // 16 x 16 MFMA tiles per wave
+    constexpr int A_LOADS = TM / 16, B_LOADS = TN / 16;           // 1 KB loads of a part
+    constexpr int LA = SUB * A_LOADS / NW, LPW = LA + SUB * B_LOADS / NW;   // loads per wave and stage: A's come first
+    constexpr int A_BYTES = TM * RK * 8, PART_BYTES = A_BYTES + TN * RK * 8, STAGE_BYTES = SUB * PART_BYTES;
+    constexpr int KROW = TN * 8;        // bytes of a k-row of a row-major B part
+    static_assert(SUB * A_LOADS % NW == 0 && SUB * B_LOADS % NW == 0, "a load belongs to one operand in every wave");
     const bool last = (z == g.batch - 1);
     const int m = last ? g.m_last : g.m;
     const int kdim = last ? g.k_last : g.k;
-    if (tm * T >= m) return;
+    if (tm * TM >= m) return;
     const double* __restrict__ A = g.A + z * g.sa;
     const double* __restrict__ B = g.B + z * g.sb;
     double* __restrict__ C = g.C + z * g.sc;
     int k_lo = 0, k_hi = kdim;
-    if (g.flags & G_BLOWER) k_lo = tn * T;
-    if (g.flags & G_ALOWER) k_hi = min(kdim, (tm + 1) * T);
-    const int n_st = k_hi > k_lo ? (k_hi - k_lo) / RK : 0;   // inner ranges are multiples of 16
+    if (g.flags & G_BLOWER) k_lo = tn * TN;
+    if (g.flags & G_ALOWER) k_hi = min(kdim, (tm + 1) * TM);
+    const int n_st = k_hi > k_lo ? (k_hi - k_lo) / (SUB * RK) : 0;   // inner ranges are multiples of 16
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave / (NW / 2), wc = wave % (NW / 2);
-    const int m0 = tm * T, n0 = tn * T;
+    const int wr = wave / WC, wc = wave % WC;
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int rw = wr * (NI * 16);
     const int cw = wc * (NJ * 16);
     const int l16 = lane & 15, lk = lane >> 4;
     const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)lds));
 
     // descriptor bases: the tile's first operand row / column at the start of the inner range; a stage's descriptor
-    // starts RK inner steps further on (64-bit scalar arithmetic), so that the 32-bit offsets of the lanes stay
+    // starts SUB * RK inner steps further on (64-bit scalar arithmetic), so that the 32-bit offsets of the lanes stay
     // below 128 rows x ld
     const double* const abase = A + int64_t(m0) * g.lda + k_lo;
     const double* const bbase = bt ? B + int64_t(n0) * g.ldb + k_lo : B + int64_t(k_lo) * g.ldb + n0;
-    const int64_t step_b = bt ? int64_t(RK) : int64_t(RK) * g.ldb;   // doubles along k per stage
+    const int64_t step_b = bt ? int64_t(SUB * RK) : int64_t(SUB * RK) * g.ldb;   // doubles along k per stage
     uint32_t voff[LPW], ldst[LPW];
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
-        const int j = wave + NW * q;            // load of the stage: first the A part, then the B part (uniform per q)
-        const bool is_a = q * NW < PART_LOADS;
-        const int jj = is_a ? j : j - PART_LOADS;
+        const bool is_a = q < LA;
+        const int j = wave + NW * (is_a ? q : q - LA);
+        const int sp = j / (is_a ? A_LOADS : B_LOADS), jj = j % (is_a ? A_LOADS : B_LOADS);   // part, load of the part
         if (is_a || bt) {
             const int row = 16 * jj + (lane >> 2);
             const int c = (lane & 3) ^ ((row >> 2) & 3);
             const bool ok = is_a ? (m0 + row < m) : (n0 + row < g.n);
-            voff[q] = ok ? uint32_t((int64_t(row) * (is_a ? g.lda : g.ldb) + 2 * c) * 8) : LDS_DMA_OOB;
+            voff[q] = ok ? uint32_t((int64_t(row) * (is_a ? g.lda : g.ldb) + sp * RK + 2 * c) * 8) : LDS_DMA_OOB;
         } else {
             const int e = jj * 64 + lane;       // 16-byte chunk of the part
             const int kr = e / (KROW / 16), c = (e % (KROW / 16)) ^ ((kr & 1) << 3);
-            voff[q] = (n0 + 2 * c < g.n) ? uint32_t((int64_t(kr) * g.ldb + 2 * c) * 8) : LDS_DMA_OOB;
+            voff[q] = (n0 + 2 * c < g.n) ? uint32_t((int64_t(sp * RK + kr) * g.ldb + 2 * c) * 8) : LDS_DMA_OOB;
         }
-        ldst[q] = (is_a ? 0 : PART_BYTES) + jj * 1024;
+        ldst[q] = sp * PART_BYTES + (is_a ? 0 : A_BYTES) + jj * 1024;
     }
     // loads of stage st into a slot; past the end: zeros
     auto issue = [&](int st, int slot_no) __attribute__((always_inline)) {
@@ -645,12 +627,11 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
         const bool live = st < n_st;
         const int64_t sk = live ? int64_t(st) : 0;
         const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<double*>(abase + sk * RK), 0, 0x7FFFFFFF, 0x00020000);
+            const_cast<double*>(abase + sk * (SUB * RK)), 0, 0x7FFFFFFF, 0x00020000);
         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<double*>(bbase + sk * step_b), 0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
-        for (int q = 0; q < LPW; ++q)
-            lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, (q * NW < PART_LOADS) ? ra : rb);
+        for (int q = 0; q < LPW; ++q) lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, q < LA ? ra : rb);
     };
     for (int st = 0; st < NS - 1; ++st) issue(st, st);
 
@@ -658,8 +639,8 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     // column l % 16 of its 16 x 16 tile
     const double binit = g.beta * g.alpha;   // beta / alpha for alpha = +-1
     double4v acc[NI][NJ];
-    const bool full = (m0 + T <= m) && (n0 + T <= g.n);
-    double* __restrict__ ct = C + int64_t(m0 + wr * (T / 2) + lk) * g.ldc + n0 + cw + l16;
+    const bool full = (m0 + TM <= m) && (n0 + TN <= g.n);
+    double* __restrict__ ct = C + int64_t(m0 + rw + lk) * g.ldc + n0 + cw + l16;
     if (g.beta == 0.0) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -681,7 +662,7 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wr * (T / 2) + i * 16 + 4 * r + lk;
+                    const int row = m0 + rw + i * 16 + 4 * r + lk;
                     const int col = n0 + cw + j * 16 + l16;
                     double c = 0.0;
                     if (row < m && col < g.n) c = binit * C[int64_t(row) * g.ldc + col];
@@ -693,14 +674,14 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     int fa[NI], fb[NJ];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int row = wr * (T / 2) + i * 16 + l16;
+        const int row = rw + i * 16 + l16;
         fa[i] = row * 64 + (((lk >> 1) ^ ((row >> 2) & 3)) << 4) + (lk & 1) * 8;
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int col = cw + j * 16 + l16;
-        if (bt) fb[j] = PART_BYTES + col * 64 + (((lk >> 1) ^ ((col >> 2) & 3)) << 4) + (lk & 1) * 8;
-        else fb[j] = PART_BYTES + lk * KROW + (((col >> 1) ^ ((lk & 1) << 3)) << 4) + (col & 1) * 8;
+        if (bt) fb[j] = A_BYTES + col * 64 + (((lk >> 1) ^ ((col >> 2) & 3)) << 4) + (lk & 1) * 8;
+        else fb[j] = A_BYTES + lk * KROW + (((col >> 1) ^ ((lk & 1) << 3)) << 4) + (col & 1) * 8;
     }
     const char* ldsc = reinterpret_cast<const char*>(lds);
 
@@ -715,13 +696,15 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
         fill = cur;
         cur = cur == NS - 1 ? 0 : cur + 1;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int e = 0; e < 2 * SUB; ++e) {   // four inner steps each
+            const char* pp = sp + (e >> 1) * PART_BYTES;
+            const int h = e & 1;
             double a[NI], b[NJ];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) a[i] = *reinterpret_cast<const double*>(sp + (h ? fa[i] ^ 32 : fa[i]));
+            for (int i = 0; i < NI; ++i) a[i] = *reinterpret_cast<const double*>(pp + (h ? fa[i] ^ 32 : fa[i]));
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                b[j] = *reinterpret_cast<const double*>(sp + (bt ? (h ? fb[j] ^ 32 : fb[j]) : fb[j] + h * 4 * KROW));
+                b[j] = *reinterpret_cast<const double*>(pp + (bt ? (h ? fb[j] ^ 32 : fb[j]) : fb[j] + h * 4 * KROW));
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -732,6 +715,17 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the slots are reused or the workgroup ends
 
     const double aout = g.alpha;
+    if (bt && g.copy && m0 == NB && n0 < NB) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = rw + i * 16 + 4 * r + lk;
+                    if (m0 + row < m) g.copy[row * NB + n0 + cw + j * 16 + l16] = aout * acc[i][j][r];
+                }
+    }
     if (full) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -746,155 +740,10 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wr * (T / 2) + i * 16 + 4 * r + lk;
+                    const int row = m0 + rw + i * 16 + 4 * r + lk;
                     const int col = n0 + cw + j * 16 + l16;
                     if (row < m && col < g.n) C[int64_t(row) * g.ldc + col] = aout * acc[i][j][r];
                 }
-    }
-}
-
-// Tile (0, 0) of a trailing update C -= P P^T whose first tile lies on the diagonal: the tile the next diagonal block
-// is waiting for.  Its workgroup is the first of the launch and what counts is how soon it is done, not throughput.
-// A 128 x 128 x 128 tile is 512 fp64 MFMAs per wave, 64 cycles each: 17 us on a CU to itself, twice that next to a
-// second workgroup.  Only the 36 sub-blocks of 16 x 16 on and below the diagonal are needed (potrf_body takes
-// nothing else), so wave w computes the sub-block rows w and 7 - w: (w + 1) + (8 - w) = 9 sub-blocks each instead
-// of 16.  Both operands are the same 128 rows, so a stage holds that one 8 KB part only and the same LDS takes a
-// ring of eight slots.  Every sub-block sees the MFMAs of dgemm_tile_ring<true, 4> in the same order: bit-equal
-// results.  The updated tile goes, as lower 16 x 16 sub-blocks (identity beyond the matrix edge), to the LDS layout
-// of potrf_body and nowhere else: the block column it heads is finished with this step and nothing reads the tile
-// from C again.
-constexpr int DNS = 2 * RNS;   // slots of the diagonal tile's ring
-static_assert(DNS * R_PART_BYTES <= LDS_DOUBLES * 8, "the diagonal tile's ring fits into the workgroup's LDS");
-template <int W>
-__device__ __forceinline__ void dgemm_diag_tile_wave(const GemmArgs& g, double* lds) {
-    constexpr int NW = 4, LPW = 2;           // waves; 1 KB loads per wave and stage
-    constexpr int RA = W, RB = 7 - W;        // this wave's sub-block rows; row R needs the sub-block columns 0 .. R
-    constexpr int NB_COLS = RB + 1;          // operand fragments of the second kind: sub-block columns 0 .. RB
-    const int m = g.m_last, nc = g.n;        // rows and columns of C that exist (the last block may be short)
-    const int n_st = g.k_last / RK;
-    const double* __restrict__ A = g.A;
-    const double* __restrict__ C = g.C;
-    const int lane = threadIdx.x & 63;
-    const int l16 = lane & 15, lk = lane >> 4;
-    const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)lds));
-    uint32_t voff[LPW], ldst[LPW];
-#pragma unroll
-    for (int q = 0; q < LPW; ++q) {
-        const int j = W + NW * q;               // load 0 .. 7 of the stage: rows 16 j .. 16 j + 15
-        const int row = 16 * j + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
-        voff[q] = (row < m) ? uint32_t((int64_t(row) * g.lda + 2 * c) * 8) : LDS_DMA_OOB;
-        ldst[q] = j * 1024;
-    }
-    auto issue = [&](int st) __attribute__((always_inline)) {   // loads of stage st into its slot; past the end: zeros
-        const uint32_t slot = lds0 + uint32_t(st % DNS) * R_PART_BYTES;
-        const bool live = st < n_st;
-        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<double*>(A + (live ? int64_t(st) : 0) * RK), 0, 0x7FFFFFFF, 0x00020000);
-#pragma unroll
-        for (int q = 0; q < LPW; ++q) lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, ra);
-    };
-    for (int st = 0; st < DNS - 1; ++st) issue(st);
-
-    // accumulators start as (beta / alpha) C (alpha = +-1: exact); register r of lane l: row 4 r + l / 16,
-    // column l % 16 of its sub-block
-    const double binit = g.beta * g.alpha;
-    double4v accA[RA + 1], accB[RB + 1];
-    const bool full = m >= GT && nc >= GT;
-    auto init = [&](double4v& acc, int R, int c, auto whole) __attribute__((always_inline)) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = R * 16 + 4 * r + lk, col = c * 16 + l16;
-            if constexpr (decltype(whole)::value) {   // unconditional loads: all in flight together
-                acc[r] = binit * C[int64_t(row) * g.ldc + col];
-            } else {
-                double v = 0.0;
-                if (row < m && col < nc) v = binit * C[int64_t(row) * g.ldc + col];
-                acc[r] = v;
-            }
-        }
-    };
-    if (full) {
-#pragma unroll
-        for (int c = 0; c <= RA; ++c) init(accA[c], RA, c, std::true_type{});
-#pragma unroll
-        for (int c = 0; c <= RB; ++c) init(accB[c], RB, c, std::true_type{});
-    } else {
-#pragma unroll
-        for (int c = 0; c <= RA; ++c) init(accA[c], RA, c, std::false_type{});
-#pragma unroll
-        for (int c = 0; c <= RB; ++c) init(accB[c], RB, c, std::false_type{});
-    }
-
-    // fragment addresses inside a stage (bytes), inner steps 0 .. 3; steps 4 .. 7: ^ 32
-    auto frag = [&](int sb) __attribute__((always_inline)) {
-        const int row = sb * 16 + l16;
-        return row * 64 + (((lk >> 1) ^ ((row >> 2) & 3)) << 4) + (lk & 1) * 8;
-    };
-    int fr[NB_COLS];
-#pragma unroll
-    for (int c = 0; c < NB_COLS; ++c) fr[c] = frag(c);
-    const int faA = frag(RA), faB = frag(RB);
-    const char* ldsc = reinterpret_cast<const char*>(lds);
-    // One wave per SIMD has nothing beside it to cover its LDS reads, so the fragments of a half-stage are read while the
-    // MFMAs of the half before it run
-    // (12.3 -> 11.6 us a tile).
-    struct Frags {
-        double b[NB_COLS], aA, aB;
-    };
-    auto read = [&](Frags& f, int st, int h) __attribute__((always_inline)) {
-        const char* sp = ldsc + (st % DNS) * R_PART_BYTES;
-#pragma unroll
-        for (int c = 0; c < NB_COLS; ++c) f.b[c] = *reinterpret_cast<const double*>(sp + (h ? fr[c] ^ 32 : fr[c]));
-        f.aA = *reinterpret_cast<const double*>(sp + (h ? faA ^ 32 : faA));
-        f.aB = *reinterpret_cast<const double*>(sp + (h ? faB ^ 32 : faB));
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto multiply = [&](const Frags& f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int c = 0; c <= RB; ++c) {
-            accB[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.aB, f.b[c], accB[c], 0, 0, 0);
-            if (c <= RA) accA[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.aA, f.b[c], accA[c], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    Frags f0, f1;
-    __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (DNS - 2)));   // stage 0 has landed
-    __syncthreads();
-    read(f0, 0, 0);
-    for (int st = 0; st < n_st; ++st) {
-        read(f1, st, 1);
-        multiply(f0);
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (DNS - 3)));   // stage st + 1 has landed
-        __syncthreads();
-        issue(st + DNS - 1);                                        // into the slot of stage st - 1, which every wave has read
-        read(f0, st + 1, 0);                                        // past the last stage: zeros nobody uses
-        multiply(f1);
-    }
-    __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the slots are reused
-    __syncthreads();   // every wave is done with the last stage before the operand slots are overwritten
-    const double aout = g.alpha;
-    auto put = [&](const double4v& acc, int R, int c) __attribute__((always_inline)) {
-        double* M = lds + sub(R, c);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int lrow = R * 16 + 4 * r + lk, lcol = c * 16 + l16;
-            const bool inside = full || ((lrow < m) && (lcol < nc));
-            M[(4 * r + lk) * SBP + l16] = inside ? aout * acc[r] : (lrow == lcol ? 1.0 : 0.0);
-        }
-    };
-#pragma unroll
-    for (int c = 0; c <= RA; ++c) put(accA[c], RA, c);
-#pragma unroll
-    for (int c = 0; c <= RB; ++c) put(accB[c], RB, c);
-}
-__device__ __forceinline__ void dgemm_diag_tile(const GemmArgs& g) {
-    double* lds = wg_lds();
-    switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-        case 0: dgemm_diag_tile_wave<0>(g, lds); break;
-        case 1: dgemm_diag_tile_wave<1>(g, lds); break;
-        case 2: dgemm_diag_tile_wave<2>(g, lds); break;
-        default: dgemm_diag_tile_wave<3>(g, lds); break;
     }
 }
 
@@ -951,11 +800,11 @@ template <int T>
 struct GemmShape;
 template <>
 struct GemmShape<128> {
-    static constexpr int WAVES = 8, SLOTS = RNS;
+    static constexpr int WR = 2, WC = 4, WAVES = WR * WC, SLOTS = RNS;
 };
 template <>
 struct GemmShape<64> {
-    static constexpr int WAVES = 4, SLOTS = 6;
+    static constexpr int WR = 2, WC = 2, WAVES = WR * WC, SLOTS = 6;
 };
 template <int T>
 __global__ __launch_bounds__(64 * GemmShape<T>::WAVES, 2) void dgemm_kernel(GemmArgs g) {
@@ -966,28 +815,32 @@ __global__ __launch_bounds__(64 * GemmShape<T>::WAVES, 2) void dgemm_kernel(Gemm
     tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
     tn = __builtin_amdgcn_readfirstlane(tn);
     z = __builtin_amdgcn_readfirstlane(z);
-    dgemm_tile_ring<false, S::WAVES, T, S::SLOTS>(g, tn, tm, z, lds);
-}
-
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, double* __restrict__ V, int n,
-                                                        int off, int bs, int32_t* __restrict__ info) {
-    potrf_body(A, V, n, off, bs, info, wg_lds(), false);
+    dgemm_tile_ring<false, S::WR, S::WC, T, T, 1, S::SLOTS>(g, tn, tm, z, lds);
 }
 
 // Trailing update of one step of the blocked Cholesky together with the factorization of the next diagonal block:
-// workgroup 0, the first of the grid and therefore resident from the start, computes the updated diagonal
-// tile, keeps it in LDS and factors / inverts it while the other workgroups update the columns that are due.  Takes the
+// workgroup 0, the first of the grid and therefore resident from the start, factors the block (the panel solve's launch
+// has brought it up to date) while the other workgroups update the columns that are due.  Takes the
 // single-workgroup factorization off the critical path of every step whose update is longer.
-// A: the whole matrix; the trailing matrix begins at block row and column step + 1 and has `rest` rows.
-__global__ __launch_bounds__(256, 2) void syrk_potrf_kernel(double* __restrict__ A, double* __restrict__ V, int n,
-                                                           int step, int rest, int stride, int lag, int base,
-                                                           int32_t* __restrict__ info) {
+// A: the whole matrix; the trailing matrix begins at block row and column step + 1 and has `rest` rows.  Step -1, a launch
+// of one workgroup: the first diagonal block.  NARROW: few columns, see plan::syrk_lag.
+template <bool NARROW>
+__global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __restrict__ A, double* __restrict__ V,
+                                                                     double* __restrict__ Pn, int n, int step, int rest,
+                                                                     int stride, int lag, int base,
+                                                                     int32_t* __restrict__ info) {
     const int off = (step + 1) * NB;
-    int tm, tn;
-    if (!plan::syrk_tile(blockIdx.x, plan::syrk_grid((rest + GT - 1) / GT, stride), tm, tn)) return;
+    if (blockIdx.x == 0) {
+        potrf_body(A, V, n, off, min(NB, rest), info, wg_lds());
+        return;
+    }
+    int tm, tn;   // NARROW: tn counts columns of 64
+    if (!(NARROW ? plan::syrk_narrow_tile(blockIdx.x, (rest + GT - 1) / GT, tm, tn)
+                 : plan::syrk_tile(blockIdx.x, plan::syrk_grid((rest + GT - 1) / GT, stride), tm, tn)))
+        return;
     tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
     tn = __builtin_amdgcn_readfirstlane(tn);
-    const int k0 = __builtin_amdgcn_readfirstlane(tn == 0 ? step : plan::syrk_first_panel(tn, step, lag, base));
+    const int k0 = NARROW || tn == 0 ? step : __builtin_amdgcn_readfirstlane(plan::syrk_first_panel(tn, step, lag, base));
     GemmArgs g{};   // C -= P P^T with P the panels k0 .. step below the diagonal block
     g.A = A + int64_t(off) * n + k0 * NB; g.lda = n;
     g.B = g.A; g.ldb = n;
@@ -996,78 +849,150 @@ __global__ __launch_bounds__(256, 2) void syrk_potrf_kernel(double* __restrict__
     g.k = g.k_last = (step + 1 - k0) * NB;
     g.batch = 1;
     g.alpha = -1.0; g.beta = 1.0; g.flags = G_BTRANS;
-    if (blockIdx.x == 0) {
-        dgemm_diag_tile(g);
-        __syncthreads();
-        potrf_body(A, V, n, off, min(NB, rest), info, wg_lds(), true);
-    } else {
-        dgemm_tile_ring<true, 4, GT, RNS>(g, tn, tm, 0, wg_lds());
-    }
+    g.copy = Pn;   // the next step's block below the diagonal, unsolved
+    if constexpr (NARROW) dgemm_tile_ring<true, 4, 2, GT, 64, 2, 3>(g, tn, tm, 0, wg_lds());
+    else dgemm_tile_ring<true, 2, 4, GT, GT, 1, RNS>(g, tn, tm, 0, wg_lds());
 }
 
 // ------------------------------------------------------------------------------------------
-// Panel solve of the blocked Cholesky:  P <- P Linv^T  for the m x 128 panel below a 128 x 128 diagonal block whose
-// inverse Linv (lower triangular, zeros above the diagonal) is known.  A 128 x 128 GEMM tile per workgroup would
-// occupy only m / 128 of the CUs for about 23 us (fp64 MFMA bound), on the critical path of every block step; here
-// a workgroup takes 32 rows and only the non-zero half of Linv:  wave w computes the 16-column tiles 7 - w and w
-// (k < 16 (c + 1) for tile c: 9 units of 16 k per wave).  The rows go through LDS (read once, written in place);
-// the Linv operands, shared by all workgroups and resident in L2, are read from global memory straight in MFMA
-// operand order.  Layouts as in potrf_body: A[i][k]: i = l % 16, k = l / 16; B[k][j]: k = l / 16, j = l % 16;
+// Panel solve of the blocked Cholesky, P <- P L_kk^-T for the panel of `rest` rows below diagonal block `step`, and the
+// update of the next diagonal block, A -= P P^T, which the chain of diagonal blocks waits for.
+// With V1, V2 the inverses of the halves of L_kk and L21 the quarter between them, columns 0 .. 63 and 64 .. 127 are
+//     X1 = P1 V1^T,   X2 = (P2 - X1 L21^T) V2^T :
+// 36 products of 16 x 16 sub-blocks per 16 rows, as many as with the inverse of the whole block, which would lengthen
+// the chain by 64 products and their waits.  A 128 x 128 GEMM tile per workgroup would occupy only rest / 128 of the
+// CUs for about 23 us; here a workgroup takes two groups of 16 rows, and its four waves share out each group's column
+// tiles (c and 3 - c: equal lengths of the triangular inner range).  Rows and results go through LDS; the operands, shared
+// by all workgroups and resident in L2, are read from global memory straight in MFMA operand order and requested before
+// the rows have arrived.
+// Workgroups 0 .. n_pairs - 1: a sub-block (I, J) of the next diagonal block each.  They solve the row groups I and J of the
+// next block row (from Pn, the copy of its unsolved values: its place in A is being overwritten by the workgroups
+// that solve it) and multiply them: 36 short products side by side.  One workgroup for the whole 128 x 128 x 128 update
+// took 12 us of every step; here the launch takes 12.5 us where it took 9.5 without the update.
+// Layouts as in potrf_body: A[i][k]: i = l % 16, k = l / 16; B[k][j]: k = l / 16, j = l % 16;
 // D register r: row 4 r + l / 16, column l % 16.
 // ------------------------------------------------------------------------------------------
 constexpr int TR = 32;          // rows per workgroup
-constexpr int TRP = NB + 1;     // LDS pitch in doubles
+constexpr int TRP = NB + 2;     // LDS pitch in doubles: the 16 rows x 2 k of a half-wave fall into 64 different banks
+constexpr int PANEL_PAIRS = NSB * (NSB + 1) / 2;
 
-__global__ __launch_bounds__(256) void trsm_kernel(double* __restrict__ P, int64_t ldp, int m,
-                                                  const double* __restrict__ Linv, int64_t ldl) {
-    __shared__ double sA[TR * TRP];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.x * TR;
-    {
-        const int r = tid >> 3, c0 = (tid & 7) * 16;
-        const bool ok = m0 + r < m;
-        const double2* src = reinterpret_cast<const double2*>(P + int64_t(ok ? m0 + r : 0) * ldp + c0);
+template <int H>   // waves of column tiles H and 3 - H of each half
+__device__ __forceinline__ void panel_body(const double* __restrict__ V1, const double* __restrict__ L21,
+                                           const double* __restrict__ V2, int n, int rt, double* sP, double* sX) {
+    constexpr int C[2] = {H, 3 - H};
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    double b1[2][16], b2[2][16], b3[2][16];   // operands of the three products
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const double2 v = ok ? src[e] : make_double2(0.0, 0.0);
-            sA[r * TRP + c0 + 2 * e] = v.x;
-            sA[r * TRP + c0 + 2 * e + 1] = v.y;
-        }
+    for (int u = 0; u < 2; ++u) {
+        const int64_t row = int64_t(C[u] * 16 + li) * n + lk;
+#pragma unroll
+        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) b1[u][ks] = V1[row + 4 * ks];
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) b2[u][ks] = L21[row + 4 * ks];
+#pragma unroll
+        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) b3[u][ks] = V2[row + 4 * ks];
     }
-    const int li = lane & 15, lk = lane >> 4;
-    // the Linv operands of both passes are requested before the rows arrive: one memory latency instead of three
-    double bvs[2][32];
+    double* const p = sP + (rt * 16 + li) * TRP + lk;    // row fragments of the row group
+    double* const x = sX + (rt * 16 + li) * TRP + lk;
+    double* const pc = sP + (rt * 16 + lk) * TRP + li;   // its accumulator layout
+    double* const xc = sX + (rt * 16 + lk) * TRP + li;
+    __syncthreads();
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int c = pass == 0 ? NB / 16 - 1 - wave : wave;
-        const int nk = 4 * (c + 1);
-        const double* bp = Linv + int64_t(c * 16 + li) * ldl + lk;
+    for (int u = 0; u < 2; ++u) {
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < 32; ++ks) bvs[pass][ks] = ks < nk ? bp[4 * ks] : 0.0;
+        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[4 * ks], b1[u][ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xc[4 * r * TRP + C[u] * 16] = acc[r];
+    }
+    __syncthreads();
+    {
+        double4v acc[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[u][r] = -pc[4 * r * TRP + HALF + C[u] * 16];
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) {
+            const double a = x[4 * ks];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b2[u][ks], acc[u], 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pc[4 * r * TRP + HALF + C[u] * 16] = -acc[u][r];
     }
     __syncthreads();
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int c = pass == 0 ? NB / 16 - 1 - wave : wave;   // column tile
-        const int nk = 4 * (c + 1);                             // MFMA steps of 4 k
-        const double (&bv)[32] = bvs[pass];
-        const double* ap0 = sA + li * TRP + lk;
-        const double* ap1 = sA + (16 + li) * TRP + lk;
-        double4v acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < 2; ++u) {
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < 32; ++ks) {
-            if (ks < nk) {   // uniform per wave
-                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(ap0[4 * ks], bv[ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(ap1[4 * ks], bv[ks], acc1, 0, 0, 0);
-            }
-        }
+        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[HALF + 4 * ks], b3[u][ks], acc, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row0 = m0 + 4 * r + lk, row1 = row0 + 16;
-            if (row0 < m) P[int64_t(row0) * ldp + c * 16 + li] = acc0[r];
-            if (row1 < m) P[int64_t(row1) * ldp + c * 16 + li] = acc1[r];
-        }
+        for (int r = 0; r < 4; ++r) xc[4 * r * TRP + HALF + C[u] * 16] = acc[r];
     }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, const double* __restrict__ V,
+                                                   const double* __restrict__ Pn, int n, int step, int rest) {
+    __shared__ __align__(16) double sP[TR * TRP];
+    __shared__ __align__(16) double sX[TR * TRP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t off = int64_t(step) * NB;
+    double* __restrict__ const P = A + (off + NB) * n + off;
+    const bool pair = blockIdx.x < PANEL_PAIRS;
+    int I = 0, J = 0, m0 = 0;
+    if (pair) {
+        while ((I + 1) * (I + 2) / 2 <= int(blockIdx.x)) ++I;
+        J = int(blockIdx.x) - I * (I + 1) / 2;
+        if (I * SBW >= rest) return;
+    } else {
+        m0 = (int(blockIdx.x) - PANEL_PAIRS) * TR;
+    }
+    // thread t: 16-byte pieces t % 8, t % 8 + 8, .. of row t / 8
+    const int r = tid >> 3, c0 = (tid & 7) * 2;
+    const int row = pair ? (r < SBW ? I : J) * SBW + (r & (SBW - 1)) : m0 + r;   // of the panel
+    const double* const src = pair ? Pn + row * NB + c0 : P + int64_t(row) * n + c0;
+    double2 v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = row < rest ? *reinterpret_cast<const double2*>(src + 16 * e) : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) *reinterpret_cast<double2*>(sP + r * TRP + c0 + 16 * e) = v[e];
+    const double* const V1 = V + off * (n + 1);
+    const double* const L21 = A + (off + HALF) * n + off;
+    const double* const V2 = V + (off + HALF) * (n + 1);
+    if (wave < 2) panel_body<0>(V1, L21, V2, n, wave & 1, sP, sX);
+    else panel_body<1>(V1, L21, V2, n, wave & 1, sP, sX);
+    if (!pair) {
+        if (row < rest) {
+            double* const dst = P + int64_t(row) * n + c0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                *reinterpret_cast<double2*>(dst + 16 * e) = *reinterpret_cast<const double2*>(sX + r * TRP + c0 + 16 * e);
+        }
+        return;
+    }
+    // a quarter of the inner range per wave, the four partial products added in order
+    const int li = lane & 15, lk = lane >> 4;
+    double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        const int k = wave * 32 + 4 * ks + lk;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sX[li * TRP + k], sX[(SBW + li) * TRP + k], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sP[wave * (SBW * SBW) + (4 * q + lk) * SBW + li] = acc[q];   // P has been read
+    const int er = I * SBW + (tid >> 4), ec = J * SBW + (tid & 15);
+    double* const D = A + (off + NB + er) * n + off + NB + ec;
+    const bool inside = er < rest && ec < rest;
+    double d = inside ? *D : 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) d -= sP[w * (SBW * SBW) + tid];
+    if (inside) *D = d;
 }
 
 onecomp_status dgemm(const GemmArgs& g, hipStream_t stream) {
@@ -1090,6 +1015,7 @@ struct Workspace {
     double* A;      // n x n: reversed damped matrix, then L in its lower triangle
     double* V;      // n x n: L^-1 (lower)
     double* T;      // n x n: temporaries of the inverse
+    double* Pn;     // up to 128 x 128, in T's second half: the block below a diagonal block before its panel is solved
     double* dfix;   // n
     double* lam;    // 1
     float* keys;    // n
@@ -1103,6 +1029,7 @@ Workspace carve(void* ws, int64_t n) {
     w.A = reinterpret_cast<double*>(p); p += mat;
     w.V = reinterpret_cast<double*>(p); p += mat;
     w.T = reinterpret_cast<double*>(p); p += mat;
+    w.Pn = w.T + align_up(size_t(n) * n / 2, 32);   // min(128, n - 128) rows of 128 fit behind it for every n > 128
     w.dfix = reinterpret_cast<double*>(p); p += align_up(size_t(n) * sizeof(double), 256);
     w.lam = reinterpret_cast<double*>(p); p += 256;
     w.keys = reinterpret_cast<float*>(p); p += align_up(size_t(n) * sizeof(float), 256);
@@ -1135,17 +1062,18 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
         hipLaunchKernelGGL(mirror_kernel, dim3(tiles, tiles), dim3(256), 0, stream, H, n, S);
         ONECOMP_CHECK_LAUNCH();
         hipLaunchKernelGGL(build_order_kernel, dim3(unsigned(n)), dim3(512), min(n, GATHER_COLS) * sizeof(float), stream,
-                           S, n, w.perm, w.dfix, w.lam, w.A);
+                           S, n, w.perm, w.dfix, w.lam, w.A, w.V, w.Pn);
     } else {
         hipLaunchKernelGGL(build_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, H, n,
-                           w.dfix, w.lam, w.A);
+                           w.dfix, w.lam, w.A, w.V, w.Pn);
     }
     ONECOMP_CHECK_LAUNCH();
 
     // ---- blocked right-looking Cholesky of A (lower) ----
     // diagonal block 0 on its own; every later one inside the launch that updates the trailing matrix before it
     const int nblk = int(ceil_div(n, NB));
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, stream, w.A, w.V, n, 0, min(NB, n), info);
+    hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, -1, n, 1, 1, 0,
+                       info);
     ONECOMP_CHECK_LAUNCH();
     // One step: panel solve below diagonal block s, then a trailing update fused with the factorization of diagonal
     // block s + 1.  The next step needs block column s + 1 only, so that one is updated at once and the others every
@@ -1155,32 +1083,27 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     // the same order whatever the lag, so the factor is bit-equal.
     int base = 0, lag = plan::syrk_lag(nblk);
     for (int s = 0; s + 1 < nblk; ++s) {
-        const int off = s * NB, rest = n - off - NB;
-        // A[off+NB:, off:off+NB] <- A[off+NB:, off:off+NB] * Linv_kk^T   (in place)
-        hipLaunchKernelGGL(trsm_kernel, dim3(unsigned(ceil_div(rest, TR))), dim3(256), 0, stream,
-                           w.A + int64_t(off + NB) * n + off, int64_t(n), rest, w.V + int64_t(off) * n + off, int64_t(n));
+        const int rest = n - (s + 1) * NB;
+        hipLaunchKernelGGL(panel_kernel, dim3(PANEL_PAIRS + unsigned(ceil_div(rest, TR))), dim3(256), 0, stream, w.A, w.V,
+                           w.Pn, n, s, rest);
         ONECOMP_CHECK_LAUNCH();
         const int next_lag = plan::syrk_lag(nblk - 2 - s);
         const int stride = next_lag == lag ? lag : 1;   // where the lag changes every column is brought up to date
-        const plan::SyrkGrid q = plan::syrk_grid(nblk - 1 - s, stride);
-        hipLaunchKernelGGL(syrk_potrf_kernel, dim3(unsigned(q.total)), dim3(256), 0, stream, w.A, w.V, n, s, rest, stride,
-                           lag, base, info);
+        if (lag == 1) {
+            hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(unsigned(plan::syrk_narrow_grid(nblk - 1 - s))),
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, s, rest, 1, 1, s, info);
+        } else {
+            hipLaunchKernelGGL(syrk_potrf_kernel<false>, dim3(unsigned(plan::syrk_grid(nblk - 1 - s, stride).total)),
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, s, rest, stride, lag, base, info);
+        }
         ONECOMP_CHECK_LAUNCH();
         if (stride != lag) base = s + 1;
         lag = next_lag;
     }
 
-    if (form == ONECOMP_FACTOR_BLOCK) {   // diagonal blocks of L^-1 are in V already; the rest comes from L itself
-        hipLaunchKernelGGL(rdiag_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, stream, w.V, n, w.dfix);
-        ONECOMP_CHECK_LAUNCH();
-        hipLaunchKernelGGL(output_block_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, w.A,
-                           w.V, w.dfix, n, U);
-        ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
-    }
-
-    // ---- V = L^-1 by recursive doubling over aligned block pairs ----
-    for (int64_t s = NB; s < n; s *= 2) {
+    // ---- V = L^-1 by recursive doubling over aligned block pairs, from the halves of the diagonal blocks; the block form
+    // needs the diagonal blocks only ----
+    for (int64_t s = HALF; s < (form == ONECOMP_FACTOR_BLOCK ? NB : n); s *= 2) {
         const int64_t pairs = ceil_div(n, 2 * s);
         // last pair may have a short or empty C range
         int64_t m_last = n - ((pairs - 1) * 2 * s + s);
@@ -1205,6 +1128,15 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
         b.m = int(s); b.m_last = int(m_last); b.n = int(s); b.k = int(s); b.k_last = int(m_last); b.batch = int(batch);
         b.alpha = -1.0; b.beta = 0.0; b.flags = G_ALOWER;
         if ((st = dgemm(b, stream)) != ONECOMP_OK) return st;
+    }
+
+    if (form == ONECOMP_FACTOR_BLOCK) {   // the rest comes from L itself
+        hipLaunchKernelGGL(rdiag_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, stream, w.V, n, w.dfix);
+        ONECOMP_CHECK_LAUNCH();
+        hipLaunchKernelGGL(output_block_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, w.A,
+                           w.V, w.dfix, n, U);
+        ONECOMP_CHECK_LAUNCH();
+        return ONECOMP_OK;
     }
 
     hipLaunchKernelGGL(output_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, w.V, n, U);

@@ -49,7 +49,7 @@ ONECOMP_HD void tile_from_rank_band(int v, int n_t, int& ti, int& tk) {
 ONECOMP_HD void tile_from_rank(int v, int n_t, int& ti, int& tk) { tile_from_rank_band<GRAM_BAND>(v, n_t, ti, tk); }
 // ---- factor: the tiles of a trailing update.  The trailing matrix has n_t block columns; a launch updates column 0 (its
 // first tile is the next diagonal block) and the columns 1, 1 + stride, 1 + 2 stride, ...: tiles (tm, tn), tn <= tm < n_t.
-// Workgroup 0 owns tile (0, 0), the next ones the strided columns, dealt to the XCDs in runs of consecutive ranks (bands
+// Workgroup 0 owns tile (0, 0) (and factors it: it has been brought up to date before the launch), the next ones the strided columns, dealt to the XCDs in runs of consecutive ranks (bands
 // of SYRK_BAND of these columns walked row by row: two workgroups per CU, 64 tiles of an XCD in flight, an 8 x 8 patch
 // of them shares 16 operand panels), the last ones the rest of column 0.
 constexpr int SYRK_BAND = 8;
@@ -113,7 +113,25 @@ ONECOMP_HD int syrk_first_panel(int tn, int step, int lag, int base) {
 // steps): 223 - 200 trailing: 1906 / 1618 / 1470; 151 - 128: 810 / 725 / 700; 103 - 80: 367 / 334 / 334; 79 - 56: 211 / 197 /
 // 207; 31 - 8: 48 / 46 / 50.  Lag 8: 1341, 725, 375 and 242.
 constexpr int SYRK_LAG4_MIN = 80;
-ONECOMP_HD int syrk_lag(int n_t) { return n_t >= SYRK_LAG4_MIN ? 4 : 2; }
+// With few columns a launch is as long as its longest workgroup: a tile of k = 256 is 40 us on its CU, the next diagonal
+// block 18, so every column is updated in every step and the tiles are half as wide (syrk_narrow_tile).  Cholesky alone,
+// us, narrow below 2 / 32 / 48 / 56 / 64 / 80 columns: d_in 2048: 820 / 545 / 544 / - ..; 4096: 1798 / 1357 / 1357 / - ..; 8192:
+// 6027 / 5598 / 5387 / 5386 / 5528 / 5600; 14336: 21957 / - / 21270 / 21226 / 21346 / 21822.
+constexpr int SYRK_LAG2_MIN = 56;
+ONECOMP_HD int syrk_lag(int n_t) { return n_t >= SYRK_LAG4_MIN ? 4 : n_t >= SYRK_LAG2_MIN ? 2 : 1; }
+// Launches with lag 1: tiles of 128 rows x 64 columns, tile (tm, tc) with tc < 2 (tm + 1), 1 <= tm < n_t (block (0, 0) has
+// been brought up to date before), row by row, a run of consecutive ranks per XCD; workgroup 0 has the diagonal block.
+ONECOMP_HD int syrk_narrow_tiles(int n_t) { return n_t * (n_t + 1) - 2; }
+ONECOMP_HD int syrk_narrow_grid(int n_t) { return 1 + ((syrk_narrow_tiles(n_t) + 7) & ~7); }
+ONECOMP_HD bool syrk_narrow_tile(int bid, int n_t, int& tm, int& tc) {
+    const int n = syrk_narrow_tiles(n_t), chunk = (n + 7) >> 3, u = bid - 1;
+    int v = (u & 7) * chunk + (u >> 3);
+    if (v >= n) return false;
+    tm = 1;
+    while (v >= 2 * (tm + 1)) v -= 2 * (tm++ + 1);
+    tc = v;
+    return true;
+}
 ONECOMP_HD int n_upper_tiles(int n_t) { return n_t * (n_t + 1) / 2; }
 
 // ---- symmetric Gram, 128 x 256 tiles: tile (i, k) = rows [128 i, +128) x columns [256 k, +256) is computed when it

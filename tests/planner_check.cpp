@@ -68,6 +68,21 @@ static void check_syrk_schedule(int n_blk) {
     }
 }
 
+// trailing updates of few columns: the 128 x 64 tiles on and below the diagonal but those of the first block, once each
+static void check_syrk_narrow(int n_t) {
+    std::vector<char> seen(size_t(n_t) * 2 * n_t, 0);
+    long n = 0;
+    for (int b = 1; b < syrk_narrow_grid(n_t); ++b) {
+        int tm = -1, tc = -1;
+        if (!syrk_narrow_tile(b, n_t, tm, tc)) continue;
+        REQUIRE(1 <= tm && tm < n_t && 0 <= tc && tc < 2 * (tm + 1), "syrk narrow %d workgroup %d -> (%d, %d)", n_t, b, tm, tc);
+        REQUIRE(!seen[size_t(tm) * 2 * n_t + tc], "syrk narrow %d tile (%d, %d) owned twice", n_t, tm, tc);
+        seen[size_t(tm) * 2 * n_t + tc] = 1;
+        ++n;
+    }
+    REQUIRE(n == long(n_t) * (n_t + 1) - 2, "syrk narrow %d: %ld tiles", n_t, n);
+}
+
 // ring kernel, symmetric: 256 x 256 tiles with the split plan, 128 x 256 tiles, or 384 x 256 tiles with the
 // workspace-only split plan
 enum Shape { BIG, MID, WIDE };
@@ -214,6 +229,7 @@ int main() {
 #endif
     // up to the 362 blocks of the widest factor (d_in 46336); in the thinned build a few of those that begin with lag 4
     for (int n_blk = 1; n_blk <= 82; ++n_blk) check_syrk_schedule(n_blk);
+    for (int n_t = 1; n_t < SYRK_LAG2_MIN; ++n_t) check_syrk_narrow(n_t);
 #ifdef PLANNER_CHECK_THIN
     for (int n_blk : {83, 84, 85, 113, 224, 362}) check_syrk_schedule(n_blk);
 #else
