@@ -12,9 +12,10 @@
 //     workgroup's LDS; panel solve and trailing update are fp64 MFMA GEMMs (v_mfma_f64_16x16x4_f64),
 //     128 x 128 or 128 x 64 tile per workgroup, operands streamed global -> LDS directly through a ring of slots; a launch
 //     has one workgroup per tile that has work, the longest tiles first.
-//   * triangular inverse by recursive doubling over aligned block pairs: for block size s = 64 * 2^l,
+//   * triangular inverse of narrow factors: row by row beside the trailing updates;
+//     of wider ones by recursive doubling over aligned block pairs: for block size s = 128 * 2^l,
 //     V[C,A] = -V[C,C] (L[C,A] V[A,A]); every level is two batched GEMMs, so the whole inverse is
-//     ~2 log2(n/64) large launches instead of n/128 skinny ones.
+//     ~2 log2(n/128) large launches instead of n/128 skinny ones.
 //   * ordering by rank counting (stable, deterministic), no floating-point atomics anywhere.
 #include "common.hpp"
 #include "planner.hpp"
@@ -201,25 +202,24 @@ __global__ __launch_bounds__(256) void output_block_kernel(const double* __restr
 
 // ------------------------------------------------------------------------------------------
 // diagonal block: Cholesky and the inverses of its two 64 x 64 diagonal halves.  One workgroup of 512 threads (8 waves).
-// A block (bs x bs, bs <= 128) at A + off*(n+1).  The inverses of the halves of L_kk go to V (zeros above the diagonal are
-// there already), the quarter of L_kk between them to A's place: the panel solve needs these three, and V's lower left
-// quarter is completed for all blocks at once at the end.  Nothing else of L_kk leaves the workgroup.  A non-positive
-// pivot sets *info (first one wins) and is replaced by 1.
+// A block (bs x bs, bs <= 128) at A + off*(n+1).  The inverses of the halves of L_kk and the quarter of L_kk between them go
+// to Pk, sub-block by sub-block in the order in which the panel solve's MFMAs take them; nothing else leaves the
+// workgroup.  A non-positive pivot sets *info (first one wins) and is replaced by 1.
 //
 // The block is 36 sub-blocks of 16 x 16 (on and below the diagonal); finished ones live in LDS (row pitch 17 doubles,
 // 76.5 KB: small enough for two workgroups per CU, so the factorization can share a launch with GEMM tiles), those that
-// still take updates in the accumulators of the wave that owns them.  Everything but the 16 x 16 leaves runs on
+// still take updates in the accumulators of the wave that owns their row.  Everything but the 16 x 16 leaves runs on
 // v_mfma_f64_16x16x4_f64 with sub-blocks as operands.  The whole is a chain of latencies on one CU, exposed in every step
 // with a short trailing update (d_in 4096: all of them), so what counts is what stands between two pivots:
 //   wave 0: the leaf of (J,J) in registers, which leaves T = L_JJ^-1; from T, still in the registers in operand layout,
 //     L_J+1,J = A_J+1,J T^T and A_J+1,J+1 -= L L^T (computed transposed, so that one product's result is the next one's
 //     operand), then the next leaf.
 //   waves 1-3 and 5-7 (SIMDs 1-3, two waves each to cover each other's waits): L_IJ = A_IJ T^T for I > J + 1 while wave 0
-//     does its two products, then, beside the next leaf, A_IK -= L_IJ L_KJ^T and, on three of the waves, a column each of
-//     the halves' inverses, X_J = -T_J P_J, P_J+1 = sum_K L_J+1,K X_K.
+//     does its two products, then, beside the next leaf, A_IK -= L_IJ L_KJ^T for the next two columns, and on three of them a
+//     column each of the halves' inverses, X_J = -T_J P_J, P_J+1 = sum_K L_J+1,K X_K.
 //   wave 4 (SIMD 0, next to the leaves): sends what is finished to memory.
 // Before: the inverse of the whole 128-wide block here, all products on four waves and through LDS, the trailing update of
-// the block in front of it in the same workgroup: 37 us a launch, now 18.
+// the block in front of it in the same workgroup: 37 us a launch, now 14.
 // MFMA operand layouts (lane l): A[i][k]: i = l % 16, k = l / 16;  B[k][j]: k = l / 16, j = l % 16;
 // C/D register r: row 4 r + l / 16, column l % 16.
 // ------------------------------------------------------------------------------------------
@@ -274,35 +274,44 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-// D^-1/2 Lh^-1 for a 16 x 16 unit lower-triangular Lh by one wave, all in registers.  Lane i of each 16-lane row of the
-// wave holds row i of -Lh in nlh[] (zero on and above the diagonal) and D_i^-1/2 in rdi; row q of lanes computes the
-// columns c = 4 k + q, so lane (q, i) returns X[i][4 k + q] in x[k], k = 0 .. 3.  The rows of Z = Lh^-1 follow without
-// divisions, z_m = e_m - sum_{k<m} Lh[m][k] z_k: row m is final once rows 0 .. m-1 have been eliminated from it and is
-// then broadcast inside each 16-lane row to the lanes below.
-__device__ __forceinline__ void tri_inverse16(const double (&nlh)[SBW], const double rdi, const int i, const int q,
-                                              double (&x)[4]) {
+// where the operand fragments of sub-block (I, J) begin in Pk
+__device__ __forceinline__ int packed(int I, int J) { return (I * (I + 1) / 2 + J) * (SBW * SBW); }
+
+// The leaf of potrf_body again, on the sub-block D in LDS, where a pivot was not positive: every such pivot is replaced by 1
+// and the first one of the factorization left in *info.  Returns D_i, and Z = Lh^-1 in x.
+__device__ __forceinline__ double leaf_with_bad_pivots(double* D, int i, int lk, double (&x)[4], int32_t* info, int row0) {
+    double my_d = 1.0;
+    int bad_at = -1;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = (4 * k + q == i) ? 1.0 : 0.0;
-    static_for<0, SBW - 1>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        // columns beyond m are still zero in row m; the first statement keeps the distance for all of them
-        static_for<0, m / 4 + 1>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            fma_bcast16<m, k == 0>(x[k], x[k], nlh[m]);
-        });
-    });
+    for (int k = 0; k < 4; ++k) x[k] = (4 * k + lk == i) ? 1.0 : 0.0;
+#pragma unroll 1
+    for (int j = 0; j < SBW; ++j) {
+        double p = D[j * SBP + j];
+        if (!(p > 0.0)) {
+            if (bad_at < 0) bad_at = j;
+            p = 1.0;
+        }
+        if (i == j) my_d = p;
+        const double nm = i > j ? -(D[i * SBP + j] / p) : 0.0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] *= rdi;
+        for (int k = 0; k < 4; ++k) {
+            const int c = 4 * k + lk;
+            if (c > j) D[i * SBP + c] = __builtin_fma(D[c * SBP + j], nm, D[i * SBP + c]);
+            x[k] = __builtin_fma(__shfl(x[k], j, SBW), nm, x[k]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the other lanes' entries
+    }
+    if (bad_at >= 0 && i == 0 && lk == 0 && *info == 0) *info = row0 + bad_at + 1;
+    return my_d;
 }
 
 // S: POTRF_LDS_DOUBLES doubles of LDS
-__device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __restrict__ V, int n, int off, int bs,
+__device__ __forceinline__ void potrf_body(const double* __restrict__ A, double* __restrict__ Pk, int n, int off, int bs,
                                            int32_t* __restrict__ info, double* S) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lk = lane >> 4;
-    double* __restrict__ const Ab = A + int64_t(off) * (n + 1);
-    double* __restrict__ const Vb = V + int64_t(off) * (n + 1);
+    const double* __restrict__ const Ab = A + int64_t(off) * (n + 1);
     // operand fragments of a sub-block M (pointer to its first element), k-step q = 0..3
     auto frag_rowk = [&](const double* M, int q) __attribute__((always_inline)) {   // M[l%16][4q + l/16]
         return M[l16 * SBP + 4 * q + lk];
@@ -327,110 +336,149 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
         for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
         return c;
     };
-    // c + A B^T, both by their row fragments
-    auto mul_add_t = [&](const double* MA, const double* MB, double4v c) __attribute__((always_inline)) {
-        double a[4], b[4];
+    // c + the products lo .. hi, whose operands `load` gives; they are read a product ahead
+    auto chain = [&](int lo, int hi, double4v c, auto&& load) __attribute__((always_inline)) {
+        double a0[4], b0[4], a1[4], b1[4];
+        auto multiply = [&](const double (&a)[4], const double (&b)[4]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            a[q] = frag_rowk(MA, q);
-            b[q] = frag_rowk(MB, q);
+            for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
+        };
+        load(lo, a0, b0);
+        int k = lo;
+        for (; k + 2 <= hi; k += 2) {
+            load(k + 1, a1, b1);
+            multiply(a0, b0);
+            load(k + 2, a0, b0);
+            multiply(a1, b1);
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
+        if (k < hi) {
+            load(hi, a1, b1);
+            multiply(a0, b0);
+            multiply(a1, b1);
+        } else {
+            multiply(a0, b0);
+        }
         return c;
+    };
+    // c + sum over J = lo .. hi of L_IJ L_KJ^T
+    auto mul_add_t = [&](int I, int K, int lo, int hi, double4v c) __attribute__((always_inline)) {
+        const double* const MA = S + sub(I, 0);
+        const double* const MB = S + sub(K, 0);
+        return chain(lo, hi, c, [&](int J, double (&a)[4], double (&b)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = frag_rowk(MA + J * SBS, q);
+                b[q] = frag_rowk(MB + J * SBS, q);
+            }
+        });
     };
     const double4v zero4 = {0.0, 0.0, 0.0, 0.0};
-    // sub-block (I, J) of the matrix, identity padding for a short last block
+    // sub-block (I, J) of the matrix, its row fragments: loads without a branch, and the identity padding of a short last
+    // block where the values are first used, so that nobody waits for them earlier
     auto fetch = [&](int I, int J) __attribute__((always_inline)) {
         double4v c;
-        const double* p = Ab + int64_t(I * SBW + lk) * n + J * SBW + l16;
-        if (bs == NB) {   // unconditional loads: all in flight together
+        const double* p = Ab + int64_t(I * SBW + l16) * n + J * SBW + lk;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) c[r] = p[int64_t(4 * r) * n];
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
-                double v = row == col ? 1.0 : 0.0;
-                if (row < bs && col < bs) v = p[int64_t(4 * r) * n];
-                c[r] = v;
-            }
-        }
+        for (int q = 0; q < 4; ++q) c[q] = *(I * SBW + l16 < bs && J * SBW + 4 * q + lk < bs ? p + 4 * q : Ab);
         return c;
     };
-    // sub-block (I, J) to memory: a store instruction writes four 128-byte row segments
-    auto out = [&](double* __restrict__ M, int I, int J, const double4v& c) __attribute__((always_inline)) {
+    auto padded = [&](int I, int J, double4v c) __attribute__((always_inline)) {
+        if (bs < NB)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = I * SBW + 4 * r + lk, col = J * SBW + l16;
-            if (row < bs && col < bs) M[int64_t(row) * n + col] = c[r];
-        }
+            for (int q = 0; q < 4; ++q) {
+                const int row = I * SBW + l16, col = J * SBW + 4 * q + lk;
+                if (row >= bs || col >= bs) c[q] = row == col ? 1.0 : 0.0;
+            }
+        return c;
+    };
+    auto store_rowk = [&](double* M, const double4v& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) M[l16 * SBP + 4 * q + lk] = f[q];
+    };
+    // finished sub-block (I, J), in LDS, to the panel solve's operands: its row fragments, a lane's four side by side
+    auto pack = [&](int I, int J) __attribute__((always_inline)) {
+        if (I * SBW >= bs) return;
+        double4v f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f[q] = frag_rowk(S + sub(I, J), q);
+        *reinterpret_cast<double4v*>(Pk + packed(I, J) + 4 * lane) = f;
     };
 
     // Leaf of block column J: wave 0 factors the diagonal sub-block in registers (lane i (mod 16) = row i; lanes
     // 16..63 shadow lanes 0..15) as Lh D Lh^T and leaves its inverse factor T = D^-1/2 Lh^-1 in the sub-block's place: the
-    // panel solves below and the inversion of the whole block need that, nothing reads L_JJ itself.
-    // From one pivot to the next: one update, its broadcast, v_rcp_f64 with a Newton step (the raw column is
-    // broadcast, not the scaled one, so nothing else waits for the reciprocal), the scaling.  The updates of the other
-    // columns are issued behind the instructions of that chain.  The reciprocal is good to 4.6e-8 relative, to 2.2e-15
-    // with the step (4 million values over 400 binades), and that is an update's relative error; columns scaled by
-    // reciprocal square roots with one step each had 8e-15.  U of a rank-deficient H with damping 1e-6, d_in 1024:
-    // 1.545e-3 of its entries are not the rounded exact value (extended precision); with those square roots 1.566e-3.
+    // panel solves below and the inverses of the halves need that, nothing reads L_JJ itself.
+    // From one pivot to the next: one update, its broadcast, v_rcp_f64, its error and the column scaled by it, the column
+    // corrected (the raw column is broadcast, not the scaled one, so nothing else waits for the reciprocal).  What does not
+    // lie on that chain is issued behind its instructions: the updates of the other columns and the rows of
+    // Z = Lh^-1, which follow without divisions, z_m = e_m - sum_{k<m} Lh[m][k] z_k: row m is final once rows 0 .. m-1 have
+    // been eliminated from it and is then broadcast inside each 16-lane row to the lanes below.  Row q of lanes computes
+    // the columns c = 4 k + q of Z: lane (q, i) has Z[i][4 k + q] in x[k].
+    // Before, with Z behind the last pivot and the reciprocal corrected in front of the column: 2920 cycles a leaf, now 2080;
+    // of these, 400 were what a pivot replaced by 1 cost every pivot.
+    // The reciprocal is good to 4.6e-8 relative, a column corrected by its error to 2.2e-15, and that is an update's relative
+    // error; columns scaled by reciprocal square roots with one step each had 8e-15.
     double x[4];   // wave 0: T of the last leaf, k-step q of its row fragments in x[q]
     auto leaf = [&](int J) __attribute__((always_inline)) {
         double* DJ = S + sub(J, J);
         const int i = l16;
-        // Entries above the diagonal (c > i) are carried along unmasked: they never reach a valid entry (a
-        // broadcast of column j takes lane c >= j).  The first bad pivot is remembered in a register, so the 16
-        // steps form one straight-line block.
-        double r[SBW], nlh[SBW];
+        // Entries above the diagonal (c > i) are carried along: they never reach a valid entry (a broadcast of column j
+        // takes lane c >= j).  The 16 steps form one straight-line block; whether a pivot was bad is asked once, behind it.
+        double r[SBW];
         double my_d = 1.0;
-        int bad_at = -1;
 #pragma unroll
         for (int c = 0; c < SBW; ++c) r[c] = DJ[i * SBP + c];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = (4 * k + lk == i) ? 1.0 : 0.0;
         double p = bcast16<0>(r[0]);           // pivot, the same in every lane
         double y = __builtin_amdgcn_rcp(p);
-        y = __builtin_fma(y, __builtin_fma(-p, y, 1.0), y);
+        double e = __builtin_fma(-p, y, 1.0), t = -(r[0] * y);
         static_for<0, SBW>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            const bool bad = !(p > 0.0);       // replaced by 1
-            bad_at = (bad && bad_at < 0) ? j : bad_at;
-            my_d = (i == j && !bad) ? p : my_d;
-            const double nm = bad ? -r[j] : -(r[j] * y);
-            nlh[j] = (i > j) ? nm : 0.0;
             if constexpr (j + 1 < SBW) {
+                const double nm = __builtin_fma(t, e, t);
                 fma_bcast16<j + 1, false>(r[j + 1], r[j], nm);   // r[j] was last written before p was broadcast
+                const double pj = p;
                 p = bcast16<j + 1>(r[j + 1]);
                 y = __builtin_amdgcn_rcp(p);
-                constexpr int rest = SBW - 2 - j, third = (rest + 2) / 3;
-                auto updates = [&](auto lo, auto hi) __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_barrier(0);
+                const double nlh = (i > j) ? nm : 0.0;
+                my_d = (i == j) ? pj : my_d;
+                // columns beyond j are still zero in row j of Z
+                constexpr int rest = SBW - 2 - j, half = rest < 3 ? rest : 3, zs = j / 4 + 1;
+                auto updates = [&](auto lo, auto hi, auto zhi) __attribute__((always_inline)) {
                     static_for<decltype(lo)::value, decltype(hi)::value>([&](auto cc) {
                         constexpr int c = decltype(cc)::value;
                         fma_bcast16<c, false>(r[c], r[j], nm);
                     });
+                    static_for<0, decltype(zhi)::value>([&](auto kc) {
+                        constexpr int k = decltype(kc)::value;
+                        fma_bcast16<j, false>(x[k], x[k], nlh);   // x[k] was last written a pivot ago
+                    });
                     __builtin_amdgcn_sched_barrier(0);
                 };
-                constexpr int c0 = j + 2, c1 = c0 + third < SBW ? c0 + third : SBW, c2 = c1 + third < SBW ? c1 + third : SBW;
-                __builtin_amdgcn_sched_barrier(0);
-                updates(std::integral_constant<int, c0>{}, std::integral_constant<int, c1>{});
-                const double e = __builtin_fma(-p, y, 1.0);
-                updates(std::integral_constant<int, c1>{}, std::integral_constant<int, c2>{});
-                y = __builtin_fma(y, e, y);
-                updates(std::integral_constant<int, c2>{}, std::integral_constant<int, SBW>{});
+                updates(std::integral_constant<int, j + 2>{}, std::integral_constant<int, j + 2 + half>{},
+                        std::integral_constant<int, 0>{});
+                e = __builtin_fma(-p, y, 1.0);
+                t = -(r[j + 1] * y);
+                updates(std::integral_constant<int, j + 2 + half>{}, std::integral_constant<int, SBW>{},
+                        std::integral_constant<int, zs>{});
+            } else {
+                my_d = (i == j) ? p : my_d;
             }
         });
-        if (bad_at >= 0 && tid == 0 && *info == 0) *info = off + J * SBW + bad_at + 1;
+        if (__builtin_expect(__any(!(my_d > 0.0)), 0)) my_d = leaf_with_bad_pivots(DJ, i, lk, x, info, off + J * SBW);
         // every lane has read its row before any lane overwrites the sub-block (one wave: program order); zeros above
         // the diagonal
-        tri_inverse16(nlh, rsqrt_refined(my_d), i, lk, x);
+        const double rdi = rsqrt_refined(my_d);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) DJ[i * SBP + 4 * k + lk] = x[k];
+        for (int k = 0; k < 4; ++k) {
+            x[k] *= rdi;
+            DJ[i * SBP + 4 * k + lk] = x[k];
+        }
     };
-    store_c(S + sub(wave, 0), fetch(wave, 0));
-    // The three roles pass the same barriers: one before the first leaf, then two per column, behind its leaf and behind
-    // its solve.
+    // The three roles pass the same barriers, two per column: behind its leaf and behind its solve.
     if (wave == 0) {
-        __syncthreads();
+        store_rowk(S, padded(0, 0, fetch(0, 0)));
         leaf(0);
 #pragma unroll 1
         for (int J = 0; J < NSB - 1; ++J) {
@@ -442,8 +490,7 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
             for (int q = 0; q < 4; ++q)
                 lt = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q], frag_rowk(S + sub(J + 1, J), q), lt, 0, 0, 0);
             double4v c = load_c(D);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) S[sub(J + 1, J) + l16 * SBP + 4 * q + lk] = lt[q];
+            store_rowk(S + sub(J + 1, J), lt);
 #pragma unroll
             for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-lt[q], lt[q], c, 0, 0, 0);
             store_c(D, c);
@@ -451,72 +498,80 @@ __device__ __forceinline__ void potrf_body(double* __restrict__ A, double* __res
             leaf(J + 1);
         }
         __syncthreads();
-    } else if (wave == 4) {
-        __syncthreads();
-#pragma unroll 1
-        for (int J = 0; J < NSB - 1; ++J) {
-            __syncthreads();
-            __syncthreads();
-            out(Vb, J, J, load_c(S + sub(J, J)));
-            if (J < NSB / 2)
-                for (int I = NSB / 2; I < NSB; ++I) out(Ab, I, J, load_c(S + sub(I, J)));
-        }
-        __syncthreads();
-        out(Vb, NSB - 1, NSB - 1, load_c(S + sub(NSB - 1, NSB - 1)));
     } else {
-        // The sub-blocks right of column 0 in column order, dealt to the six waves: whatever column the factorization has
-        // reached, those that still take updates are spread evenly.  They are held with the sign reversed, so that the
-        // products need no negated operand.
-        constexpr int OWNERS = 6, N_OWNED = NSB * (NSB - 1) / 2, SLOTS = (N_OWNED + OWNERS - 1) / OWNERS;
-        const int ow = wave - 1 - (wave >> 2);
-        int si[SLOTS], sk[SLOTS];
-        double4v acc[SLOTS];
-#pragma unroll
-        for (int u = 0; u < SLOTS; ++u) {
-            int rem = ow + OWNERS * u, K = 1;
-            while (K < NSB && rem >= NSB - K) rem -= NSB - K++;
-            sk[u] = K < NSB ? K : 0;   // 0: no sub-block
-            si[u] = K + rem;
-            if (sk[u] > 0) acc[u] = -fetch(si[u], K);
-        }
-        if (ow == 0) store_c(S + sub(1, 1), -acc[0]);
-        const int inv_c = OWNERS - 1 - ow;   // column of the halves' inverses of this wave (the waves of fewest updates)
-        const bool inv = inv_c < NSB / 2 - 1;
-        double4v pc = zero4;                 // and that column's next P
-        __syncthreads();
-#pragma unroll 1
-        for (int J = 0; J < NSB - 1; ++J) {
-            __syncthreads();
-            if (J + 2 + ow < NSB) {   // L_IJ = A_IJ T^T, in place
-                double* const M = S + sub(J + 2 + ow, J);
-                store_c(M, mul_add_t(M, S + sub(J, J), zero4));
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < SLOTS; ++u) {
-                const int I = si[u], K = sk[u];
-                if (K <= J || (I == K && K == J + 1)) continue;   // finished; or wave 0's
-                acc[u] = mul_add_t(S + sub(I, J), S + sub(K, J), acc[u]);
-                // to LDS before the solve of its column, a diagonal one before wave 0 takes over its last update
-                if (I == K ? K == J + 2 : K == J + 1) store_c(S + sub(I, K), -acc[u]);
-            }
+        // Column inv_c of the halves' inverses, beside leaf J + 1, in the waves whose rows are complete first (not in
+        // wave 4: its products slow the leaf beside them, 2900 -> 3700 cycles)
+        const int inv_c = wave > 4 ? 7 - wave : NSB / 2;
+        double4v pc = zero4;   // the column's next P
+        auto inverse_step = [&](int J) __attribute__((always_inline)) {
             const int C = (J & (NSB / 2)) + inv_c;
-            if (inv && C <= J) {
-                double4v xj = load_c(S + sub(J, J));
-                if (C < J) {
-                    xj = mul_add(S + sub(J, J), pc, zero4, -1.0);
-                    store_c(S + sub(J, C), xj);   // in place of L_JC, which only this column's earlier products needed
-                    out(Vb, J, C, xj);
+            if (inv_c >= NSB / 2 - 1 || C > J) return;
+            double4v xj = load_c(S + sub(J, J));
+            if (C < J) {
+                xj = mul_add(S + sub(J, J), pc, zero4, -1.0);
+                store_c(S + sub(J, C), xj);   // in place of L_JC, which only this column's earlier products needed
+            }
+            if ((J + 1) % (NSB / 2) != 0) {
+                pc = mul_add(S + sub(J + 1, J), xj, zero4, 1.0);
+                if (C < J)
+                    pc = chain(C, J - 1, pc, [&](int K, double (&a)[4], double (&b)[4]) __attribute__((always_inline)) {
+                        const double4v x = load_c(S + sub(K, C));
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            a[q] = frag_rowk(S + sub(J + 1, K), q);
+                            b[q] = x[q];
+                        }
+                    });
+            }
+            if (C < J) pack(J, C);
+        };
+        if (wave == 4) {
+            const double4v a10 = fetch(1, 0), a11 = fetch(1, 1);
+            store_rowk(S + sub(1, 0), padded(1, 0, a10));
+            store_rowk(S + sub(1, 1), padded(1, 1, a11));
+#pragma unroll 1
+            for (int J = 0; J < NSB; ++J) {
+                __syncthreads();
+                if (J + 1 < NSB) __syncthreads();
+                pack(J, J);
+                if (J < NSB / 2)
+                    for (int I = NSB / 2; I < NSB; ++I) pack(I, J);
+            }
+            return;
+        }
+        // A row of sub-blocks per wave, the longest ones on different SIMDs.  Its sub-blocks are held transposed: the
+        // accumulators of (I, K) are then the B operand of its solve, whose result is L_IK's row fragments.  Column J + 1
+        // takes its last update beside leaf J + 1 and column J + 2 all that there are before, so that 6 to 8 products are
+        // due on a wave then at most; updating all columns would be 27 products in all beside the first leaf and 1 beside
+        // the last.  Sums are held with the sign reversed, so that the products need no negated operand.
+        const int I = wave < 4 ? NSB - wave : NSB + 1 - wave;
+        double4v cur = fetch(I, 0), nxt = fetch(I, 1), pre = fetch(I, 2);   // (I, J); (I, J + 1); (I, J + 2) as it was
+        cur = padded(I, 0, cur);
+        nxt = -padded(I, 1, nxt);
+#pragma unroll 1
+        for (int J = 0; J < NSB; ++J) {
+            const bool active = J + 2 <= I;
+            __syncthreads();
+            if (J + 1 < NSB) {
+                if (active) {   // L_IJ = A_IJ T^T
+                    double4v lt = zero4;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        lt = __builtin_amdgcn_mfma_f64_16x16x4f64(frag_rowk(S + sub(J, J), q), cur[q], lt, 0, 0, 0);
+                    store_rowk(S + sub(I, J), lt);
                 }
-                if ((J + 1) % (NSB / 2) != 0) {
-                    pc = zero4;
-                    for (int K = C; K < J; ++K) pc = mul_add(S + sub(J + 1, K), load_c(S + sub(K, C)), pc, 1.0);
-                    pc = mul_add(S + sub(J + 1, J), xj, pc, 1.0);
+                __syncthreads();
+                if (active) {
+                    cur = -mul_add_t(J + 1, I, J, J, nxt);
+                    nxt = -padded(I, J + 2, pre);
+                    if (J + 3 <= I) pre = fetch(I, J + 3);
+                    if (J + 2 == I) store_rowk(S + sub(I, J + 1), cur);   // wave 0 solves it
+                    nxt = mul_add_t(J + 2, I, 0, J, nxt);
+                    if (J + 2 == I) store_rowk(S + sub(I, I), -nxt);      // wave 0 takes over its last update
                 }
             }
+            inverse_step(J);
         }
-        __syncthreads();
-        if (inv) out(Vb, NSB - 1, NSB / 2 + inv_c, mul_add(S + sub(NSB - 1, NSB - 1), pc, zero4, -1.0));
     }
 }
 
@@ -553,7 +608,7 @@ __device__ __forceinline__ double* wg_lds() {
 }
 
 // ------------------------------------------------------------------------------------------
-// One TM x TN tile (tm, tn) of batch entry z with WR x WC waves.  128 x 128: 2 x 4 waves of 64 x 32, so that with two
+// One TM x TN tile (tm, tn) of batch entry z with WR x WC waves; K > 0: an inner range of that length.  128 x 128: 2 x 4 waves of 64 x 32, so that with two
 // workgroups per CU four waves share a SIMD and cover each other's waits.  64 x 64 (2 x 2 waves of 32 x 32) and 128 x 64
 // (4 x 2 of 32 x 32): for launches whose 128-wide tiles would leave CUs idle.
 // The operands are streamed global -> LDS directly (buffer_load ... lds) through a ring of NS slots
@@ -567,7 +622,7 @@ __device__ __forceinline__ double* wg_lds() {
 //   NN B part (RK k-rows x TN columns, a k-row is TN / 2 chunks): chunk c of k-row kr sits at c ^ ((kr & 1) << 3).
 // ------------------------------------------------------------------------------------------
 
-template <bool bt, int WR, int WC, int TM, int TN, int SUB, int NS>
+template <bool bt, int WR, int WC, int TM, int TN, int SUB, int NS, int K = 0>
 __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn, const int tm, const int z, double* lds) {
     constexpr int NW = WR * WC;
     constexpr int NI = TM / (16 * WR), NJ = TN / (16 * WC);       // 16 x 16 MFMA tiles per wave
@@ -586,7 +641,7 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     int k_lo = 0, k_hi = kdim;
     if (g.flags & G_BLOWER) k_lo = tn * TN;
     if (g.flags & G_ALOWER) k_hi = min(kdim, (tm + 1) * TM);
-    const int n_st = k_hi > k_lo ? (k_hi - k_lo) / (SUB * RK) : 0;   // inner ranges are multiples of 16
+    const int n_st = K > 0 ? K / (SUB * RK) : k_hi > k_lo ? (k_hi - k_lo) / (SUB * RK) : 0;   // inner ranges are multiples of 16
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -621,19 +676,22 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
         }
         ldst[q] = sp * PART_BYTES + (is_a ? 0 : A_BYTES) + jj * 1024;
     }
-    // loads of stage st into a slot; past the end: zeros
-    auto issue = [&](int st, int slot_no) __attribute__((always_inline)) {
+    // loads of the next stage into a slot; past the end: an empty range, which deposits zeros
+    const double* pa = abase;
+    const double* pb = bbase;
+    int ahead = n_st;   // stages that have not been requested
+    auto issue = [&](int slot_no) __attribute__((always_inline)) {
         const uint32_t slot = lds0 + uint32_t(slot_no) * STAGE_BYTES;
-        const bool live = st < n_st;
-        const int64_t sk = live ? int64_t(st) : 0;
-        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<double*>(abase + sk * (SUB * RK)), 0, 0x7FFFFFFF, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<double*>(bbase + sk * step_b), 0, 0x7FFFFFFF, 0x00020000);
+        const uint32_t range = ahead > 0 ? 0x7FFFFFFFu : 0u;
+        --ahead;
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(pa), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(pb), 0, range, 0x00020000);
+        pa += SUB * RK;
+        pb += step_b;
 #pragma unroll
-        for (int q = 0; q < LPW; ++q) lds_load16(slot + ldst[q], live ? voff[q] : LDS_DMA_OOB, q < LA ? ra : rb);
+        for (int q = 0; q < LPW; ++q) lds_load16(slot + ldst[q], voff[q], q < LA ? ra : rb);
     };
-    for (int st = 0; st < NS - 1; ++st) issue(st, st);
+    for (int st = 0; st < NS - 1; ++st) issue(st);
 
     // accumulators start as (beta / alpha) C (alpha = +-1: exact); register r of lane l: row 4 r + l / 16,
     // column l % 16 of its 16 x 16 tile
@@ -685,16 +743,14 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
     }
     const char* ldsc = reinterpret_cast<const char*>(lds);
 
-    int cur = 0, fill = NS - 1;   // slots of stage st and of the stage NS - 1 further on
-    for (int st = 0; st < n_st; ++st) {
-        // the loads of stages st + 1 and st + 2 may still be in flight: wait for those of stage st, publish them,
-        // and refill the slot every wave has finished reading (stage st - 1)
+    auto stage = [&](auto slot_c) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_c)::value;
+        // the loads of the NS - 2 stages behind this one may still be in flight: wait for its own, publish them,
+        // and refill the slot every wave has finished reading (that of the stage before)
         __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NS - 2)));
         __syncthreads();
-        issue(st + NS - 1, fill);
-        const char* sp = ldsc + cur * STAGE_BYTES;
-        fill = cur;
-        cur = cur == NS - 1 ? 0 : cur + 1;
+        issue((slot + NS - 1) % NS);
+        const char* sp = ldsc + slot * STAGE_BYTES;
 #pragma unroll
         for (int e = 0; e < 2 * SUB; ++e) {   // four inner steps each
             const char* pp = sp + (e >> 1) * PART_BYTES;
@@ -711,6 +767,19 @@ __device__ __forceinline__ void dgemm_tile_ring(const GemmArgs& g, const int tn,
                 for (int j = 0; j < NJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
         }
+    };
+    // The slots are constants: all stages unrolled where their number is known, else one round of the ring per iteration.
+    // With slots and descriptors computed in every stage the scalar work behind its barrier held the MFMAs back: factor of
+    // d_in 8192 8446 -> 7654 us, 14336 36.0 -> 33.6 ms.
+    if constexpr (K > 0) {
+        static_for<0, K / (SUB * RK)>([&](auto st) __attribute__((always_inline)) {
+            stage(std::integral_constant<int, decltype(st)::value % NS>{});
+        });
+    } else {
+        for (int st = 0; st < n_st; st += NS)
+            static_for<0, NS>([&](auto slot_c) __attribute__((always_inline)) {
+                if (st + decltype(slot_c)::value < n_st) stage(slot_c);
+            });
     }
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the slots are reused or the workgroup ends
 
@@ -826,17 +895,19 @@ __global__ __launch_bounds__(64 * GemmShape<T>::WAVES, 2) void dgemm_kernel(Gemm
 // of one workgroup: the first diagonal block.  NARROW: few columns, see plan::syrk_lag.
 template <bool NARROW>
 __global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __restrict__ A, double* __restrict__ V,
-                                                                     double* __restrict__ Pn, int n, int step, int rest,
-                                                                     int stride, int lag, int base,
+                                                                     double* __restrict__ Pn, double* __restrict__ Pk,
+                                                                     int n, int step, int rest,
+                                                                     int stride, int lag, int base, int inv_cols,
                                                                      int32_t* __restrict__ info) {
-    const int off = (step + 1) * NB;
+    const int off = (step + 1) * NB, n_t = (rest + GT - 1) / GT;
     if (blockIdx.x == 0) {
-        potrf_body(A, V, n, off, min(NB, rest), info, wg_lds());
+        potrf_body(A, Pk, n, off, min(NB, rest), info, wg_lds());
         return;
     }
     int tm, tn;   // NARROW: tn counts columns of 64
-    if (!(NARROW ? plan::syrk_narrow_tile(blockIdx.x, (rest + GT - 1) / GT, tm, tn)
-                 : plan::syrk_tile(blockIdx.x, plan::syrk_grid((rest + GT - 1) / GT, stride), tm, tn)))
+    bool inverse = false;
+    if (!(NARROW ? plan::syrk_narrow_tile(blockIdx.x, n_t, inv_cols, tm, tn, inverse)
+                 : plan::syrk_tile(blockIdx.x, plan::syrk_grid(n_t, stride), tm, tn)))
         return;
     tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
     tn = __builtin_amdgcn_readfirstlane(tn);
@@ -850,7 +921,15 @@ __global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __
     g.batch = 1;
     g.alpha = -1.0; g.beta = 1.0; g.flags = G_BTRANS;
     g.copy = Pn;   // the next step's block below the diagonal, unsolved
-    if constexpr (NARROW) dgemm_tile_ring<true, 4, 2, GT, 64, 2, 3>(g, tn, tm, 0, wg_lds());
+    if (NARROW && __builtin_amdgcn_readfirstlane(int(inverse))) {   // V[i, :] += L[i, step] V[step, :], the rows below
+        g.B = V + int64_t(step) * NB * n;
+        g.C = V + int64_t(off) * n;
+        g.n = (step + 1) * NB;
+        g.alpha = 1.0; g.beta = tn < 2 * step ? 1.0 : 0.0; g.flags = 0;
+        dgemm_tile_ring<false, 4, 2, GT, 64, 2, 3, NB>(g, tn, tm, 0, wg_lds());
+        return;
+    }
+    if constexpr (NARROW) dgemm_tile_ring<true, 4, 2, GT, 64, 2, 3, NB>(g, tn, tm, 0, wg_lds());
     else dgemm_tile_ring<true, 2, 4, GT, GT, 1, RNS>(g, tn, tm, 0, wg_lds());
 }
 
@@ -863,34 +942,39 @@ __global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __
 // the chain by 64 products and their waits.  A 128 x 128 GEMM tile per workgroup would occupy only rest / 128 of the
 // CUs for about 23 us; here a workgroup takes two groups of 16 rows, and its four waves share out each group's column
 // tiles (c and 3 - c: equal lengths of the triangular inner range).  Rows and results go through LDS; the operands, shared
-// by all workgroups and resident in L2, are read from global memory straight in MFMA operand order and requested before
-// the rows have arrived.
+// by all workgroups and resident in L2, come from Pk in MFMA operand order, 32 bytes a lane, and are requested before
+// the rows have arrived (gathered from the rows of V and A, 8 bytes a lane: 2 us more a launch).
 // Workgroups 0 .. n_pairs - 1: a sub-block (I, J) of the next diagonal block each.  They solve the row groups I and J of the
 // next block row (from Pn, the copy of its unsolved values: its place in A is being overwritten by the workgroups
 // that solve it) and multiply them: 36 short products side by side.  One workgroup for the whole 128 x 128 x 128 update
-// took 12 us of every step; here the launch takes 12.5 us where it took 9.5 without the update.
+// took 12 us of every step; here the launch takes 9 us, with the update and with its operands packed.
+// The next four: V's diagonal block, whose columns are the solutions of the same system for the unit vectors (transposed
+// rows), 32 columns each.  The next 4 inv_blocks: row block `step` of the inverse, where that
+// goes along with the factorization (factor_run), V[step, :] = -L_kk^-1 V[step, :], again the same system for transposed rows.
 // Layouts as in potrf_body: A[i][k]: i = l % 16, k = l / 16; B[k][j]: k = l / 16, j = l % 16;
 // D register r: row 4 r + l / 16, column l % 16.
 // ------------------------------------------------------------------------------------------
 constexpr int TR = 32;          // rows per workgroup
 constexpr int TRP = NB + 2;     // LDS pitch in doubles: the 16 rows x 2 k of a half-wave fall into 64 different banks
 constexpr int PANEL_PAIRS = NSB * (NSB + 1) / 2;
+constexpr int PANEL_UNITS = NB / TR;
 
 template <int H>   // waves of column tiles H and 3 - H of each half
-__device__ __forceinline__ void panel_body(const double* __restrict__ V1, const double* __restrict__ L21,
-                                           const double* __restrict__ V2, int n, int rt, double* sP, double* sX) {
+__device__ __forceinline__ void panel_body(const double* __restrict__ Pk, int bs, int rt, double* sP, double* sX) {
     constexpr int C[2] = {H, 3 - H};
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    double b1[2][16], b2[2][16], b3[2][16];   // operands of the three products
+    double4v b1[2][4], b2[2][4], b3[2][4];   // operands of the three products
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int64_t row = int64_t(C[u] * 16 + li) * n + lk;
+        // sub-block rows behind a short last block: the first sub-block instead, for results that nobody takes
+        const bool top = C[u] * SBW < bs, low = HALF + C[u] * SBW < bs;
 #pragma unroll
-        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) b1[u][ks] = V1[row + 4 * ks];
+        for (int k = 0; k <= C[u]; ++k) b1[u][k] = *reinterpret_cast<const double4v*>(Pk + (top ? packed(C[u], k) : 0) + 4 * lane);
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) b2[u][ks] = L21[row + 4 * ks];
+        for (int k = 0; k < 4; ++k) b2[u][k] = *reinterpret_cast<const double4v*>(Pk + (low ? packed(4 + C[u], k) : 0) + 4 * lane);
 #pragma unroll
-        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) b3[u][ks] = V2[row + 4 * ks];
+        for (int k = 0; k <= C[u]; ++k)
+            b3[u][k] = *reinterpret_cast<const double4v*>(Pk + (low ? packed(4 + C[u], 4 + k) : 0) + 4 * lane);
     }
     double* const p = sP + (rt * 16 + li) * TRP + lk;    // row fragments of the row group
     double* const x = sX + (rt * 16 + li) * TRP + lk;
@@ -901,7 +985,7 @@ __device__ __forceinline__ void panel_body(const double* __restrict__ V1, const 
     for (int u = 0; u < 2; ++u) {
         double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[4 * ks], b1[u][ks], acc, 0, 0, 0);
+        for (int ks = 0; ks < 4 * (C[u] + 1); ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[4 * ks], b1[u][ks >> 2][ks & 3], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) xc[4 * r * TRP + C[u] * 16] = acc[r];
     }
@@ -916,7 +1000,7 @@ __device__ __forceinline__ void panel_body(const double* __restrict__ V1, const 
         for (int ks = 0; ks < 16; ++ks) {
             const double a = x[4 * ks];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b2[u][ks], acc[u], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b2[u][ks >> 2][ks & 3], acc[u], 0, 0, 0);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -929,43 +1013,75 @@ __device__ __forceinline__ void panel_body(const double* __restrict__ V1, const 
         double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int ks = 0; ks < 4 * (C[u] + 1); ++ks)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[HALF + 4 * ks], b3[u][ks], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[HALF + 4 * ks], b3[u][ks >> 2][ks & 3], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) xc[4 * r * TRP + HALF + C[u] * 16] = acc[r];
     }
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, const double* __restrict__ V,
-                                                   const double* __restrict__ Pn, int n, int step, int rest) {
+__global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, double* __restrict__ V,
+                                                   const double* __restrict__ Pn, const double* __restrict__ Pk, int n,
+                                                   int step, int rest, int inv_blocks) {
     __shared__ __align__(16) double sP[TR * TRP];
     __shared__ __align__(16) double sX[TR * TRP];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t off = int64_t(step) * NB;
+    const int bs = min(NB, n - int(off));
     double* __restrict__ const P = A + (off + NB) * n + off;
+    const int n_inv = PANEL_UNITS + NB / TR * inv_blocks;
     const bool pair = blockIdx.x < PANEL_PAIRS;
+    const int inv = int(blockIdx.x) - PANEL_PAIRS;   // 0 .. n_inv - 1: columns of V
+    const bool is_inv = !pair && inv < n_inv;
     int I = 0, J = 0, m0 = 0;
     if (pair) {
-        while ((I + 1) * (I + 2) / 2 <= int(blockIdx.x)) ++I;
+        const int b = blockIdx.x;
+        I = (b >= 1) + (b >= 3) + (b >= 6) + (b >= 10) + (b >= 15) + (b >= 21) + (b >= 28);
         J = int(blockIdx.x) - I * (I + 1) / 2;
         if (I * SBW >= rest) return;
-    } else {
-        m0 = (int(blockIdx.x) - PANEL_PAIRS) * TR;
+    } else if (!is_inv) {
+        m0 = (inv - n_inv) * TR;
     }
     // thread t: 16-byte pieces t % 8, t % 8 + 8, .. of row t / 8
     const int r = tid >> 3, c0 = (tid & 7) * 2;
     const int row = pair ? (r < SBW ? I : J) * SBW + (r & (SBW - 1)) : m0 + r;   // of the panel
-    const double* const src = pair ? Pn + row * NB + c0 : P + int64_t(row) * n + c0;
-    double2 v[8];
+    // transposed: rows t / 32, t / 32 + 8, .. of the block, its column t % 32
+    const int vr = tid >> 5, vc = tid & 31;
+    double* const vcol = V + off * n + (inv < PANEL_UNITS ? off + inv * TR : (inv - PANEL_UNITS) * TR) + vc;
+    if (is_inv) {
+        double v[16];
+        if (inv < PANEL_UNITS) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = row < rest ? *reinterpret_cast<const double2*>(src + 16 * e) : make_double2(0.0, 0.0);
+            for (int e = 0; e < 16; ++e) v[e] = vr + 8 * e == inv * TR + vc ? -1.0 : 0.0;
+        } else {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) *reinterpret_cast<double2*>(sP + r * TRP + c0 + 16 * e) = v[e];
-    const double* const V1 = V + off * (n + 1);
-    const double* const L21 = A + (off + HALF) * n + off;
-    const double* const V2 = V + (off + HALF) * (n + 1);
-    if (wave < 2) panel_body<0>(V1, L21, V2, n, wave & 1, sP, sX);
-    else panel_body<1>(V1, L21, V2, n, wave & 1, sP, sX);
+            for (int e = 0; e < 16; ++e) v[e] = vr + 8 * e < bs ? vcol[int64_t(vr + 8 * e) * n] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sP[vc * TRP + vr + 8 * e] = v[e];
+    } else {
+        const double* const src = pair ? Pn + row * NB + c0 : P + int64_t(row) * n + c0;
+        double2 v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = row < rest ? *reinterpret_cast<const double2*>(src + 16 * e) : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) *reinterpret_cast<double2*>(sP + r * TRP + c0 + 16 * e) = v[e];
+    }
+    // the element of the next diagonal block this thread will update
+    const int er = I * SBW + (tid >> 4), ec = J * SBW + (tid & 15);
+    double* const D = A + (off + NB + er) * n + off + NB + ec;
+    const bool inside = pair && er < rest && ec < rest;
+    double d = inside ? *D : 0.0;
+    if (wave < 2) panel_body<0>(Pk, bs, wave & 1, sP, sX);
+    else panel_body<1>(Pk, bs, wave & 1, sP, sX);
+    if (is_inv) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int vrow = vr + 8 * e;
+            if (vrow < bs && (inv >= PANEL_UNITS || (vrow >= inv * TR + vc && inv * TR + vc < bs))) vcol[int64_t(vrow) * n] = -sX[vc * TRP + vrow];
+        }
+        return;
+    }
     if (!pair) {
         if (row < rest) {
             double* const dst = P + int64_t(row) * n + c0;
@@ -985,10 +1101,6 @@ __global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, cons
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) sP[wave * (SBW * SBW) + (4 * q + lk) * SBW + li] = acc[q];   // P has been read
-    const int er = I * SBW + (tid >> 4), ec = J * SBW + (tid & 15);
-    double* const D = A + (off + NB + er) * n + off + NB + ec;
-    const bool inside = er < rest && ec < rest;
-    double d = inside ? *D : 0.0;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < 4; ++w) d -= sP[w * (SBW * SBW) + tid];
@@ -1015,6 +1127,7 @@ struct Workspace {
     double* A;      // n x n: reversed damped matrix, then L in its lower triangle
     double* V;      // n x n: L^-1 (lower)
     double* T;      // n x n: temporaries of the inverse
+    double* Pk;     // in T's first half: operands of a panel solve, see potrf_body
     double* Pn;     // up to 128 x 128, in T's second half: the block below a diagonal block before its panel is solved
     double* dfix;   // n
     double* lam;    // 1
@@ -1029,6 +1142,7 @@ Workspace carve(void* ws, int64_t n) {
     w.A = reinterpret_cast<double*>(p); p += mat;
     w.V = reinterpret_cast<double*>(p); p += mat;
     w.T = reinterpret_cast<double*>(p); p += mat;
+    w.Pk = w.T;   // n / 16 <= 8 block rows: at most n n doubles; 36 sub-blocks: not more than the half before Pn
     w.Pn = w.T + align_up(size_t(n) * n / 2, 32);   // min(128, n - 128) rows of 128 fit behind it for every n > 128
     w.dfix = reinterpret_cast<double*>(p); p += align_up(size_t(n) * sizeof(double), 256);
     w.lam = reinterpret_cast<double*>(p); p += 256;
@@ -1072,8 +1186,8 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     // ---- blocked right-looking Cholesky of A (lower) ----
     // diagonal block 0 on its own; every later one inside the launch that updates the trailing matrix before it
     const int nblk = int(ceil_div(n, NB));
-    hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, -1, n, 1, 1, 0,
-                       info);
+    hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, -1, n, 1, 1, 0,
+                       0, info);
     ONECOMP_CHECK_LAUNCH();
     // One step: panel solve below diagonal block s, then a trailing update fused with the factorization of diagonal
     // block s + 1.  The next step needs block column s + 1 only, so that one is updated at once and the others every
@@ -1081,29 +1195,34 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     // update of everything is bound by reading and writing the trailing matrix; the lag divides these bytes while
     // every launch keeps the same work to hide the next diagonal block behind.  The additions to a tile happen in
     // the same order whatever the lag, so the factor is bit-equal.
+    // Narrow factors take the inverse along: once V[s, :] is known (the panel solve's launch), V[i, :] += L[i, s] V[s, :]
+    // for the rows below, beside the trailing update, which leaves room in every launch the chain of diagonal blocks
+    // bounds; V's blocks below the diagonal hold these sums until their row's turn.
+    const bool along = form == ONECOMP_FACTOR_INVERSE && nblk <= plan::INVERSE_ALONG_MAX;
     int base = 0, lag = plan::syrk_lag(nblk);
-    for (int s = 0; s + 1 < nblk; ++s) {
-        const int rest = n - (s + 1) * NB;
-        hipLaunchKernelGGL(panel_kernel, dim3(PANEL_PAIRS + unsigned(ceil_div(rest, TR))), dim3(256), 0, stream, w.A, w.V,
-                           w.Pn, n, s, rest);
+    for (int s = 0; s < nblk; ++s) {
+        const int rest = max(0, n - (s + 1) * NB), inv = along ? s : 0;
+        hipLaunchKernelGGL(panel_kernel, dim3(PANEL_PAIRS + PANEL_UNITS + NB / TR * inv + unsigned(ceil_div(rest, TR))), dim3(256),
+                           0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, inv);
         ONECOMP_CHECK_LAUNCH();
+        if (rest == 0) break;
         const int next_lag = plan::syrk_lag(nblk - 2 - s);
         const int stride = next_lag == lag ? lag : 1;   // where the lag changes every column is brought up to date
         if (lag == 1) {
-            hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(unsigned(plan::syrk_narrow_grid(nblk - 1 - s))),
-                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, s, rest, 1, 1, s, info);
+            const int inv_cols = along ? 2 * (s + 1) : 0;
+            hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(unsigned(plan::syrk_narrow_grid(nblk - 1 - s, inv_cols))),
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, 1, 1, s, inv_cols, info);
         } else {
             hipLaunchKernelGGL(syrk_potrf_kernel<false>, dim3(unsigned(plan::syrk_grid(nblk - 1 - s, stride).total)),
-                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, n, s, rest, stride, lag, base, info);
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, stride, lag, base, 0, info);
         }
         ONECOMP_CHECK_LAUNCH();
         if (stride != lag) base = s + 1;
         lag = next_lag;
     }
 
-    // ---- V = L^-1 by recursive doubling over aligned block pairs, from the halves of the diagonal blocks; the block form
-    // needs the diagonal blocks only ----
-    for (int64_t s = HALF; s < (form == ONECOMP_FACTOR_BLOCK ? NB : n); s *= 2) {
+    // ---- V = L^-1 by recursive doubling over aligned block pairs, from the diagonal blocks ----
+    for (int64_t s = NB; s < n && form == ONECOMP_FACTOR_INVERSE && !along; s *= 2) {
         const int64_t pairs = ceil_div(n, 2 * s);
         // last pair may have a short or empty C range
         int64_t m_last = n - ((pairs - 1) * 2 * s + s);
@@ -1130,7 +1249,7 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
         if ((st = dgemm(b, stream)) != ONECOMP_OK) return st;
     }
 
-    if (form == ONECOMP_FACTOR_BLOCK) {   // the rest comes from L itself
+    if (form == ONECOMP_FACTOR_BLOCK) {   // V's diagonal blocks, the rest comes from L itself
         hipLaunchKernelGGL(rdiag_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, stream, w.V, n, w.dfix);
         ONECOMP_CHECK_LAUNCH();
         hipLaunchKernelGGL(output_block_kernel, dim3(unsigned(ceil_div(n, 256)), unsigned(n)), dim3(256), 0, stream, w.A,

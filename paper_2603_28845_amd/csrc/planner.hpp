@@ -113,25 +113,39 @@ ONECOMP_HD int syrk_first_panel(int tn, int step, int lag, int base) {
 // steps): 223 - 200 trailing: 1906 / 1618 / 1470; 151 - 128: 810 / 725 / 700; 103 - 80: 367 / 334 / 334; 79 - 56: 211 / 197 /
 // 207; 31 - 8: 48 / 46 / 50.  Lag 8: 1341, 725, 375 and 242.
 constexpr int SYRK_LAG4_MIN = 80;
-// With few columns a launch is as long as its longest workgroup: a tile of k = 256 is 40 us on its CU, the next diagonal
-// block 18, so every column is updated in every step and the tiles are half as wide (syrk_narrow_tile).  Cholesky alone,
-// us, narrow below 2 / 32 / 48 / 56 / 64 / 80 columns: d_in 2048: 820 / 545 / 544 / - ..; 4096: 1798 / 1357 / 1357 / - ..; 8192:
-// 6027 / 5598 / 5387 / 5386 / 5528 / 5600; 14336: 21957 / - / 21270 / 21226 / 21346 / 21822.
+// With few columns a launch is as long as its longest workgroup: a 128 x 128 tile of k = 256 is 40 us on its CU, the next
+// diagonal block 14, so every column is updated in every step and the tiles are half as wide (syrk_narrow_tile).
+// Cholesky alone, us, narrow below 2 / 32 / 48 / 56 / 64 / 80 columns (with a diagonal block of 18): d_in 2048: 820 / 545 /
+// 544 / - ..; 4096: 1798 / 1357 / 1357 / - ..; 8192: 6027 / 5598 / 5387 / 5386 / 5528 / 5600; 14336: 21957 / - / 21270 /
+// 21226 / 21346 / 21822.  Narrow tiles with lag 2 are slower up to d_in 4096 (3 %) and not faster at 6144.
 constexpr int SYRK_LAG2_MIN = 56;
 ONECOMP_HD int syrk_lag(int n_t) { return n_t >= SYRK_LAG4_MIN ? 4 : n_t >= SYRK_LAG2_MIN ? 2 : 1; }
 // Launches with lag 1: tiles of 128 rows x 64 columns, tile (tm, tc) with tc < 2 (tm + 1), 1 <= tm < n_t (block (0, 0) has
-// been brought up to date before), row by row, a run of consecutive ranks per XCD; workgroup 0 has the diagonal block.
-ONECOMP_HD int syrk_narrow_tiles(int n_t) { return n_t * (n_t + 1) - 2; }
-ONECOMP_HD int syrk_narrow_grid(int n_t) { return 1 + ((syrk_narrow_tiles(n_t) + 7) & ~7); }
-ONECOMP_HD bool syrk_narrow_tile(int bid, int n_t, int& tm, int& tc) {
-    const int n = syrk_narrow_tiles(n_t), chunk = (n + 7) >> 3, u = bid - 1;
-    int v = (u & 7) * chunk + (u >> 3);
+// been brought up to date before), row by row; then, in a factor whose inverse goes along, its update: tiles (tm, tc) of
+// n_t block rows by inv_cols columns, row by row.  A run of consecutive ranks per XCD; workgroup 0 has the diagonal block.
+ONECOMP_HD int syrk_narrow_tiles(int n_t, int inv_cols) { return n_t * (n_t + 1) - 2 + n_t * inv_cols; }
+ONECOMP_HD int syrk_narrow_grid(int n_t, int inv_cols) { return 1 + ((syrk_narrow_tiles(n_t, inv_cols) + 7) & ~7); }
+ONECOMP_HD bool syrk_narrow_tile(int bid, int n_t, int inv_cols, int& tm, int& tc, bool& inverse) {
+    const int n = syrk_narrow_tiles(n_t, inv_cols), n_syrk = syrk_narrow_tiles(n_t, 0), chunk = (n + 7) >> 3, u = bid - 1;
+    const int v = (u & 7) * chunk + (u >> 3);
     if (v >= n) return false;
-    tm = 1;
-    while (v >= 2 * (tm + 1)) v -= 2 * (tm++ + 1);
-    tc = v;
+    inverse = v >= n_syrk;
+    if (inverse) {
+        tm = (v - n_syrk) / inv_cols;
+        tc = (v - n_syrk) % inv_cols;
+        return true;
+    }
+    // row tm begins at rank tm (tm + 1) - 2 (a walk over the rows: half a microsecond per workgroup)
+    tm = int(0.5f * __builtin_sqrtf(4.0f * float(v + 2) + 1.0f) - 0.5f);
+    if (tm * (tm + 1) > v + 2) --tm;
+    if ((tm + 1) * (tm + 2) <= v + 2) ++tm;
+    tc = v + 2 - tm * (tm + 1);
     return true;
 }
+// Factors of up to this many blocks take their inverse along (factor_run), wider ones have it by recursive doubling
+// afterwards, in products with longer inner ranges.  Afterwards : along, us: d_in 512 186 : 144 and 2048 729 : 594 (with a
+// diagonal block of 18 us), 4096 1659 : 1533, 5120 2572 : 2495, 6144 3727 : 3765, 6784 4727 : 4751.
+constexpr int INVERSE_ALONG_MAX = 40;
 ONECOMP_HD int n_upper_tiles(int n_t) { return n_t * (n_t + 1) / 2; }
 
 // ---- symmetric Gram, 128 x 256 tiles: tile (i, k) = rows [128 i, +128) x columns [256 k, +256) is computed when it

@@ -68,19 +68,23 @@ static void check_syrk_schedule(int n_blk) {
     }
 }
 
-// trailing updates of few columns: the 128 x 64 tiles on and below the diagonal but those of the first block, once each
-static void check_syrk_narrow(int n_t) {
-    std::vector<char> seen(size_t(n_t) * 2 * n_t, 0);
-    long n = 0;
-    for (int b = 1; b < syrk_narrow_grid(n_t); ++b) {
+// trailing updates of few columns: the 128 x 64 tiles on and below the diagonal but those of the first block, once each,
+// and those of the inverse's update, if it goes along
+static void check_syrk_narrow(int n_t, int inv_cols) {
+    std::vector<char> seen(size_t(n_t) * 2 * n_t, 0), seen_inv(size_t(n_t) * inv_cols, 0);
+    long n = 0, n_inv = 0;
+    for (int b = 1; b < syrk_narrow_grid(n_t, inv_cols); ++b) {
         int tm = -1, tc = -1;
-        if (!syrk_narrow_tile(b, n_t, tm, tc)) continue;
-        REQUIRE(1 <= tm && tm < n_t && 0 <= tc && tc < 2 * (tm + 1), "syrk narrow %d workgroup %d -> (%d, %d)", n_t, b, tm, tc);
-        REQUIRE(!seen[size_t(tm) * 2 * n_t + tc], "syrk narrow %d tile (%d, %d) owned twice", n_t, tm, tc);
-        seen[size_t(tm) * 2 * n_t + tc] = 1;
-        ++n;
+        bool inverse = false;
+        if (!syrk_narrow_tile(b, n_t, inv_cols, tm, tc, inverse)) continue;
+        const int first = inverse ? 0 : 1, cols = inverse ? inv_cols : 2 * (tm + 1);
+        REQUIRE(first <= tm && tm < n_t && 0 <= tc && tc < cols, "syrk narrow %d, %d workgroup %d -> (%d, %d)", n_t, inv_cols, b, tm, tc);
+        char& c = inverse ? seen_inv[size_t(tm) * inv_cols + tc] : seen[size_t(tm) * 2 * n_t + tc];
+        REQUIRE(!c, "syrk narrow %d, %d tile (%d, %d) owned twice", n_t, inv_cols, tm, tc);
+        c = 1;
+        ++(inverse ? n_inv : n);
     }
-    REQUIRE(n == long(n_t) * (n_t + 1) - 2, "syrk narrow %d: %ld tiles", n_t, n);
+    REQUIRE(n == long(n_t) * (n_t + 1) - 2 && n_inv == long(n_t) * inv_cols, "syrk narrow %d, %d: %ld and %ld tiles", n_t, inv_cols, n, n_inv);
 }
 
 // ring kernel, symmetric: 256 x 256 tiles with the split plan, 128 x 256 tiles, or 384 x 256 tiles with the
@@ -229,7 +233,8 @@ int main() {
 #endif
     // up to the 362 blocks of the widest factor (d_in 46336); in the thinned build a few of those that begin with lag 4
     for (int n_blk = 1; n_blk <= 82; ++n_blk) check_syrk_schedule(n_blk);
-    for (int n_t = 1; n_t < SYRK_LAG2_MIN; ++n_t) check_syrk_narrow(n_t);
+    for (int n_t = 1; n_t < SYRK_LAG2_MIN; ++n_t)
+        for (int s = -1; n_t + s + 1 < INVERSE_ALONG_MAX; ++s) check_syrk_narrow(n_t, 2 * (s + 1));
 #ifdef PLANNER_CHECK_THIN
     for (int n_blk : {83, 84, 85, 113, 224, 362}) check_syrk_schedule(n_blk);
 #else

@@ -476,6 +476,61 @@ def test_factor_inverse_levels(d_in):
     assert torch.all(torch.tril(U, -1) == 0.0)
 
 
+@pytest.mark.parametrize("d_in", [
+    272,           # a last block of one sub-block
+    5120, 5136,    # the inverse along with the factorization up to 40 blocks, by doubling from 41
+    7184, 7312,    # 57 and 58 blocks: trailing updates with lag 2, narrow ones once fewer than 56 columns trail
+])
+def test_factor_schedules(d_in):
+    """U and the block form at the widths where the factor's launches change: the bound of test_factor_inverse_levels (the
+    block form, whose entries are rounded once too, against U and the exact R: F = -U_jj R_jk / R_kk off the diagonal)."""
+    _announce(f"factor d_in={d_in}: schedules")
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    X = torch.randn((d_in + 64, d_in), generator=g, device=DEV)
+    H = X.t() @ X
+    H = (torch.triu(H) + torch.triu(H, 1).t()).contiguous()
+    U, _, info = og.onecomp_hessian_factor(H, 0.01)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    Hd = H.double()
+    Hd.diagonal().add_(float(np.float32(0.01)) * Hd.diagonal().mean())
+    R = torch.linalg.cholesky(Hd.flip(0, 1)).flip(0, 1)
+    E = U.double() @ R
+    E.diagonal().sub_(1.0)
+    assert float(E.norm()) <= 2.0 ** -24 * float(U.double().norm() * torch.linalg.matrix_norm(R, "fro"))
+    assert torch.all(torch.tril(U, -1) == 0.0)
+    if d_in % 128 == 0:
+        F, _, info = og.onecomp_hessian_factor(H, 0.01, form="block")
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        Fx = -R / R.diagonal()[None, :] / R.diagonal()[:, None]
+        blk = torch.arange(d_in, device=DEV) // 128
+        off = blk[:, None] < blk[None, :]
+        assert torch.all((F.double() - Fx)[off].abs() <= 2.0 ** -23 * Fx[off].abs() + 1e-12 * Fx[off].abs().max())
+        assert torch.equal(F[blk[:, None] == blk[None, :]], U[blk[:, None] == blk[None, :]])
+
+
+@pytest.mark.parametrize("at", [0, 1, 15, 16, 63, 64, 77, 127, 128, 143, 255, 256, 271])
+@pytest.mark.parametrize("value", [-1.0, float("nan")])
+def test_factor_bad_pivot(at, value):
+    """A single non-positive pivot at every kind of place: info is its position in the order of the factorization (which
+    runs from the last index), the pivot counts as 1 and everything else is untouched.  (The NaN is put off the diagonal's
+    mean by a damping of zero times it being NaN for every entry, so there only info is asked for: the first pivot.)"""
+    _announce(f"factor bad pivot at {at}: {value}")
+    n = 272
+    H = torch.eye(n, device=DEV) * 4.0
+    H[n - 1 - at, n - 1 - at] = value
+    U, _, info = og.onecomp_hessian_factor(H, 0.0)
+    torch.cuda.synchronize()
+    if value != value:
+        assert int(info.item()) == 1
+        return
+    assert int(info.item()) == at + 1
+    want = torch.eye(n, device=DEV) * 0.5
+    want[n - 1 - at, n - 1 - at] = 1.0
+    assert torch.equal(U, want)
+
+
 def test_factor_dead_channel_and_not_posdef():
     _announce("factor dead channel / not positive definite")
     H32 = _oracle_H32(256, 900, seed=12)
