@@ -144,10 +144,12 @@ constexpr int IB = 32;          // columns swept in registers at a time
 //                 normalized U blocks by nearfrag_kernel.  Wave w owns the block's column tile w (64 x 32).
 //   sequential    four lanes per row (a quad), each holding 8 of the 32 columns of the inner block; the current
 //                 column is broadcast inside the quad by DPP, the grid arithmetic is replicated, the feedback is
-//                 8 FMAs per lane.  All four waves work (16 rows each).
+//                 8 FMAs per lane.  All four waves work (16 rows each).  127 cycles a column: one wave per SIMD issues
+//                 21 fp64 operations and the four waves read 16 KB of U from LDS, each as long.
 //   inner update  the inner block's 32 errors reach the remaining columns of the block through fp32 MFMAs
-//                 (v_mfma_f32_32x32x2_f32) on the tiles in LDS.
-// LDS tile sW holds current values; a finished column holds its code (as a float).
+//                 (v_mfma_f32_16x16x4_f32) on the tile in LDS.
+// A block took 57 thousand cycles with the errors, codes and residuals of every column written as the columns went by, eight
+// conversions per lane and column, barriers around the inner updates and the residuals split twice behind the block; now 41.
 // ------------------------------------------------------------------------------------------
 struct PanelArgs {
     const float* Wf;            // [d_out x d_in] accumulated feedback c of the earlier super-blocks (block form: the
@@ -226,7 +228,21 @@ __device__ __forceinline__ int mse_search(const double mn, const double mx, cons
     return ibest;
 }
 
-constexpr int PANEL_LDS = (SB * SB + 2 * ROWS * SP + 2 * SB + 3 * ROWS * 8) * 4;
+// LDS of a panel workgroup, under 80 KB so that a tile of the far update or a second panel workgroup fits on the CU beside
+// it (matrix pipes under one, vector units under the other):
+//   sU    the block's U off its 32 x 32 diagonal sub-blocks: six sub-blocks, row by row
+//   sUd   the diagonal sub-blocks in fp64, rows divided by their diagonal entries, zeros on and below the diagonal: rows
+//         8 g .. 8 g + 7 hold the slices (8 columns) g .. 3, and behind them zeros for the lanes of finished slices
+//   sRd   reciprocals of the diagonal
+//   sC    the row tile, see panel_body
+//   sUg   (block form) the diagonal sub-blocks in fp32
+constexpr int UB = IB * IB, UD_SLICES = 8 * (4 + 3 + 2 + 1), UD_ZERO = 3 * 8 * 8;   // doubles: slices of a sub-block, zeros
+__host__ __device__ constexpr int u_off(int I, int J) { return (3 * I - I * (I - 1) / 2 + J - I - 1) * UB; }
+__host__ __device__ constexpr int ud_first(int g) { return 8 * (4 * g - g * (g - 1) / 2) * 8; }   // slice (8 g, g)
+constexpr int LDS_UD = 6 * UB * 4, LDS_RD = LDS_UD + (4 * UD_SLICES * 8 + UD_ZERO) * 8, LDS_C = LDS_RD + SB * 8;
+constexpr int LDS_UG = LDS_C + ROWS * SP * 4;
+constexpr int panel_lds(bool direct) { return LDS_UG + (direct ? 4 * UB * 4 : 0); }
+static_assert(panel_lds(false) <= 80 * 1024, "a second workgroup fits beside a panel's");
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_quad(float v) {
@@ -239,6 +255,12 @@ __device__ __forceinline__ double dpp_quad(double v) {
     const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), CTRL, 0xF, 0xF, true));
     return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
+// what this wave has written to LDS is visible to all its lanes (LDS operations of a wave are executed in order; this keeps
+// the compiler from moving them past each other)
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 constexpr int quad_bcast(int o) { return o | (o << 2) | (o << 4) | (o << 6); }
 constexpr int QUAD_SWAP1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);   // lanes 0<->1, 2<->3
 constexpr int QUAD_SWAP2 = 2 | (3 << 2) | (0 << 4) | (1 << 6);   // lanes 0<->2, 1<->3
@@ -247,10 +269,12 @@ constexpr int QUAD_SWAP2 = 2 | (3 << 2) | (0 << 4) | (1 << 6);   // lanes 0<->2,
 //   sC   (LDS, fp32)  c = -sum_i e_i U_i,col over the finished columns i: the part from earlier super-blocks comes
 //                     from the working copy (a.Wf), the part from the earlier blocks of this super-block from the
 //                     near update (split-fp16 MFMAs accumulated from zero), the part from the earlier inner blocks
-//                     of this block from fp32 MFMAs accumulated from zero; each part is added once in fp32;
-//   sE   (LDS, fp32)  an unfinished column holds its ORIGINAL weight w0 (exact: the input is bf16 or fp32); once the
-//                     column is finished the slot receives its error e (sC's slot its code).
+//                     of this block from fp32 MFMAs accumulated from zero; each part is added once in fp32.  A finished
+//                     column holds its error e until the inner update has taken it, then its residual as an fp16 pair;
+//   w0v  (registers)  the ORIGINAL weights of this lane's 4 x 8 columns (exact: the input is bf16 or fp32).
 // The value that is quantized is w0 + c formed in fp64.
+//
+// From the sequential part to the end of a block a wave touches its own 16 rows only, and no barrier stands between.
 //
 // DIRECT (block form of the factor): a.U holds U only on its 128 x 128 diagonal blocks and -U_jj R_jk / R_kk
 // elsewhere (R = U^-1).  The working copy then accumulates c_k = sum_i (w_i - w^_i) R_ik / R_kk over the finished
@@ -261,12 +285,13 @@ constexpr int QUAD_SWAP2 = 2 | (3 << 2) | (0 << 4) | (1 << 6);   // lanes 0<->2,
 // block passes on is w - w^ measured from the original weights instead of the compensated ones.
 template <int GB, bool DIRECT>  // GB: group width seen inside an inner block: 16 (G == 16) or 32 (G = 32, 64, 128)
 __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, char* psm) {
-    float* sU = reinterpret_cast<float*>(psm);   // SB x SB: U[j0 + j][j0 .. j0 + 127], filled by direct loads
-    float* sC = sU + SB * SB;                    // ROWS x SP feedback sums / codes (see above)
-    float* sE = sC + ROWS * SP;                  // ROWS x SP original weights / errors e
-    double* sRd = reinterpret_cast<double*>(sE + ROWS * SP);   // SB reciprocals of the diagonal
-    double* sS = sRd + SB;                       // ROWS x 8 scales of the block's groups (fp64; returned rounded to fp32)
-    float* sZ = reinterpret_cast<float*>(sS + ROWS * 8);       // ROWS x 8 zero points
+    float* const sU = reinterpret_cast<float*>(psm);
+    double* const sUd = reinterpret_cast<double*>(psm + LDS_UD);
+    double* const sRd = reinterpret_cast<double*>(psm + LDS_RD);
+    float* const sC = reinterpret_cast<float*>(psm + LDS_C);
+    // the diagonal sub-blocks as they come in; the inverse form is done with them before sC is written
+    constexpr int LDS_DIAG = DIRECT ? LDS_UG : LDS_C;
+    const float* const sUg = reinterpret_cast<const float*>(psm + LDS_DIAG);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -281,77 +306,58 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
     const int lr = (lane >> 5) * 4, lc = lane & 31;
     const double qmax = double(a.qmax), qsd = double(a.qs);
     const float f_d = a.sc->f_d, f_inv = a.sc->f_inv;
-    const uint32_t ldsU = uint32_t(uintptr_t((ONECOMP_LDS char*)psm));
+    const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)psm));
     double s = 1.0, rs = 1.0, z = 0.0;
-    float lossacc = 0.f;
+    double lossacc = 0.0;   // of this lane's columns
     bool saturated = false;
     if (a.wide_g >= 0) {
         s = a.s64[grow];
         z = double(a.zeros[int64_t(grow) * a.n_g + a.wide_g]);
         rs = 1.0 / s;
     }
+    if (tid < UD_ZERO) sUd[4 * UD_SLICES * 8 + tid] = 0.0;
 
 #pragma unroll 1
     for (int b = 0; b < a.nb; ++b) {
         const int j0 = a.s0 + b * SB;
         __syncthreads();   // everybody is done with the previous block's tiles
-        if (a.wide_g >= 0 && sl == 0) {   // published by the barriers below, long before the first use
-            sS[qrow * 8] = s;
-            sZ[qrow * 8] = float(z);
-        }
-        // ---- U diagonal block -> sU, two rows (1 KB) per wave load, no registers involved
+        // opaque copies: what is computed from them is not hoisted out of the loop, to be spilled there
+        int bw = wave, blane = lane;
+        asm volatile("" : "+s"(bw));
+        asm volatile("" : "+v"(blane));
+        // ---- U's diagonal block -> LDS, eight rows of a sub-block (1 KB) per wave load, no registers involved
         {
             const float* ub = a.U + int64_t(j0) * d_in + j0;
             __amdgpu_buffer_rsrc_t rsrc =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ub), 0, int((int64_t(SB - 1) * d_in + SB) * 4), 0x00020000);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int row = 2 * (16 * wave + q) + (lane >> 5);
-                lds_load16(ldsU + (16 * wave + q) * 1024, uint32_t((int64_t(row) * d_in + (lane & 31) * 4) * 4), rsrc);
+            for (int q = 0; q < 10; ++q) {
+                // four loads per sub-block; sub-blocks 0 .. 5: those off the diagonal, then (wave, wave)
+                const int t = q < 6 ? 6 * bw + q : 4 * bw + q - 6, blk = t >> 2;
+                const int I = q < 6 ? (blk >= 3) + (blk >= 5) : bw, J = q < 6 ? (blk < 3 ? blk + 1 : blk < 5 ? blk - 1 : 3) : bw;
+                const int row = 32 * I + 8 * (t & 3) + (blane >> 3);
+                lds_load16(lds0 + (q < 6 ? 0 : LDS_DIAG) + t * 1024, uint32_t((row * int(d_in) + 32 * J + (blane & 7) * 4) * 4),
+                           rsrc);
             }
         }
-        // The original weights of two of the block's eight 32 x 32 tiles, in accumulator layout: row tile 0 / 1 of
-        // column tile `wave` (DIRECT: (0, wave) and (1, 3 - wave), the tiles this wave transforms).  Requested here
-        // so that they arrive behind the near update; DIRECT keeps them in registers until the block is done.
-        float16v w0r[2];
-        auto load_w0 = [&](float16v(&dst)[2]) __attribute__((always_inline)) {
-            // 32 independent loads in straight-line code (one uniform branch on the element type around them); the
-            // workgroup's rows span less than 2^31 elements, so a uniform base and 32-bit lane offsets address them
-            int off[2][16];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                const int p = j0 + ((!DIRECT || mt == 0) ? wave : 3 - wave) * 32 + lc;
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    off[mt][r] = (min(r0 + mt * 32 + (r / 4) * 8 + lr + (r % 4), a.d_out - 1) - r0) * int(d_in) + p;
-            }
-            if (a.w0_bf16) {
-                const uint16_t* wp = static_cast<const uint16_t*>(a.W0) + int64_t(r0) * d_in;
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) dst[mt][r] = __uint_as_float(uint32_t(wp[off[mt][r]]) << 16);
-            } else {
-                const float* wp = static_cast<const float*>(a.W0) + int64_t(r0) * d_in;
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) dst[mt][r] = wp[off[mt][r]];
-            }
-        };
-        load_w0(w0r);
+        float w0v[32];
         // ---- feedback sums of this block's columns, wave = column tile: what earlier super-blocks left in the
         // working copy plus the near update from the earlier blocks of this super-block, accumulated from zero
         {
             float16v cf[2], acc[2];
             {
-                const float* cbase = a.Wf + int64_t(r0) * d_in;
+                // one lane offset and a scalar one per row: 32 addresses in registers would be kept for the whole sweep.
+                // Rows past d_out: outside the descriptor, zeros
+                const int rows = min(ROWS, a.d_out - r0);
+                const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0, int(rows * d_in * 4), 0x00020000);
+                const uint32_t vo = uint32_t((blane >> 5) * 4 * int(d_in) + j0 + 32 * bw + (blane & 31)) * 4;
 #pragma unroll
                 for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const int rr = min(r0 + mt * 32 + (r / 4) * 8 + lr + (r % 4), a.d_out - 1) - r0;
-                        cf[mt][r] = cbase[rr * int(d_in) + j0 + 32 * wave + lc];
+                        cf[mt][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                            rsrc, vo, uint32_t(mt * 32 + (r / 4) * 8 + (r % 4)) * uint32_t(d_in) * 4, 0));
                         acc[mt][r] = 0.f;
                     }
             }
@@ -360,15 +366,23 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
                 // rolling window of WIN k-steps of operand fragments (a source block has 8 k-steps)
                 constexpr int WIN = 4;
                 uint4v win[WIN][6];
-                // uniform base pointers + a 32-bit lane offset: the addresses stay in scalar registers
-                const uint4v* fh = reinterpret_cast<const uint4v*>(a.Fh) + int64_t(wg) * 3 * 8 * 2 * 64;
-                const uint4v* fl = reinterpret_cast<const uint4v*>(a.Fl) + int64_t(wg) * 3 * 8 * 2 * 64;
-                const uint4v* bh = reinterpret_cast<const uint4v*>(a.Bh) + (b * (b - 1) / 2) * 8 * 4 * 64 + wave * 64;
-                const uint4v* bl = reinterpret_cast<const uint4v*>(a.Bl) + (b * (b - 1) / 2) * 8 * 4 * 64 + wave * 64;
+                // descriptors, one lane offset and scalar offsets: no addresses in vector registers
+                constexpr int F_BYTES = 3 * 8 * 2 * 64 * 16, B_BYTES = 6 * 8 * 4 * 64 * 16, DESC = 0x00020000;
+                const int64_t fo0 = int64_t(wg) * (F_BYTES / 2);
+                const __amdgpu_buffer_rsrc_t rfh = __builtin_amdgcn_make_buffer_rsrc(a.Fh + fo0, 0, F_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rfl = __builtin_amdgcn_make_buffer_rsrc(a.Fl + fo0, 0, F_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rbh = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Bh), 0, B_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rbl = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Bl), 0, B_BYTES, DESC);
+                const int b0 = ((b * (b - 1) / 2) * 8 * 4 + bw) * 1024;
                 auto issue = [&](int bp, int ks, uint4v(&d)[6]) __attribute__((always_inline)) {
-                    const int fo = (bp * 8 + ks) * 2 * 64, bo = (bp * 8 + ks) * 4 * 64;
-                    d[0] = (fl + fo)[lane]; d[1] = (fh + fo)[lane]; d[2] = (fl + fo + 64)[lane]; d[3] = (fh + fo + 64)[lane];
-                    d[4] = (bh + bo)[lane]; d[5] = (bl + bo)[lane];
+                    const int fo = (bp * 8 + ks) * 2 * 1024, bo = b0 + (bp * 8 + ks) * 4 * 1024;
+                    const int vo = blane * 16;
+                    d[0] = __builtin_amdgcn_raw_buffer_load_b128(rfl, vo, fo, 0);
+                    d[1] = __builtin_amdgcn_raw_buffer_load_b128(rfh, vo, fo, 0);
+                    d[2] = __builtin_amdgcn_raw_buffer_load_b128(rfl, vo + 1024, fo, 0);
+                    d[3] = __builtin_amdgcn_raw_buffer_load_b128(rfh, vo + 1024, fo, 0);
+                    d[4] = __builtin_amdgcn_raw_buffer_load_b128(rbh, vo, bo, 0);
+                    d[5] = __builtin_amdgcn_raw_buffer_load_b128(rbl, vo, bo, 0);
                 };
 #pragma unroll
                 for (int ks = 0; ks < WIN; ++ks) issue(0, ks, win[ks]);
@@ -398,32 +412,64 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[mt][r] = __builtin_fmaf(acc[mt][r], f_inv, cf[mt][r]);
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // the direct loads have landed
+            __syncthreads();
+            // the original weights of this lane's row: columns 32 q + 8 sl + i of the block in w0v[8 q + i]
+            // (requested here, so that they arrive behind the conversions and take no registers in the near update)
+            if (a.w0_bf16) {
+                const uint16_t* wp = static_cast<const uint16_t*>(a.W0) + int64_t(grow) * d_in + j0 + 8 * sl;
+                uint4v raw[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) raw[q] = *reinterpret_cast<const uint4v*>(wp + 32 * q);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        w0v[8 * q + 2 * i] = __uint_as_float(raw[q][i] << 16);
+                        w0v[8 * q + 2 * i + 1] = __uint_as_float(raw[q][i] & 0xFFFF0000u);
+                    }
+            } else {
+                const float* wp = static_cast<const float*>(a.W0) + int64_t(grow) * d_in + j0 + 8 * sl;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const float4v v = *reinterpret_cast<const float4v*>(wp + 32 * q + 4 * h);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) w0v[8 * q + 4 * h + i] = v[i];
+                    }
+            }
+            // sub-block (wave, wave) for the sequential part, four columns at a time (converting there: eight operations per
+            // lane and column)
+            {
+                const float* ug = sUg + wave * UB;
+                if (lane < IB) sRd[32 * wave + lane] = 1.0 / double(ug[lane * (IB + 1)]);
+                wave_fence();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int id = q * 64 + lane, j = id >> 3, g = j >> 3, k0 = (id & 7) * 4;
+                    const float4v v = *reinterpret_cast<const float4v*>(ug + 4 * id);
+                    const double rd = sRd[32 * wave + j];
+                    double2 lo, hi;
+                    lo.x = k0 > j ? double(v[0]) * rd : 0.0;
+                    lo.y = k0 + 1 > j ? double(v[1]) * rd : 0.0;
+                    hi.x = k0 + 2 > j ? double(v[2]) * rd : 0.0;
+                    hi.y = k0 + 3 > j ? double(v[3]) * rd : 0.0;
+                    if ((k0 >> 3) >= g) {
+                        double2* const dst = reinterpret_cast<double2*>(
+                            sUd + wave * UD_SLICES * 8 + (4 * g - g * (g - 1) / 2) * 64 + (j & 7) * (4 - g) * 8 + k0 - 8 * g);
+                        dst[0] = lo;
+                        dst[1] = hi;
+                    }
+                }
+            }
+            __syncthreads();
             if constexpr (!DIRECT) {
 #pragma unroll
                 for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int o = (mt * 32 + (r / 4) * 8 + lr + (r % 4)) * SP + 32 * wave + lc;
-                        sC[o] = acc[mt][r];
-                        sE[o] = w0r[mt][r];
-                    }
-            }
-            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // the direct loads into sU have landed
-            __syncthreads();
-            if (tid < SB) sRd[tid] = 1.0 / double(sU[tid * SB + tid]);
-            __syncthreads();
-            if constexpr (DIRECT) {
-                // c_k / U_kk -> sE (free until the original weights go there), as the A operand of
-                // c Un_bb = (c / diag) U_bb
-                if (j0 > 0) {
-                    const float rd = float(sRd[32 * wave + lc]);
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            sE[(mt * 32 + (r / 4) * 8 + lr + (r % 4)) * SP + 32 * wave + lc] = acc[mt][r] * rd;
-                    __syncthreads();
-                }
+                    for (int r = 0; r < 16; ++r) sC[(mt * 32 + (r / 4) * 8 + (blane >> 5) * 4 + (r % 4)) * SP + 32 * bw + (blane & 31)] = acc[mt][r];
+            } else {
                 // eight 32 x 32 tiles of (c / diag) U_bb, accumulated from zero; column tile nt needs k < 32 (nt + 1)
                 // (U_bb is upper triangular), so wave w takes (row tile 0, column tile w) and (1, 3 - w): five chunks
                 // of 32 k, 16 MFMAs each.  A chunk's 32 operand values are read before its first MFMA, and the two
@@ -432,314 +478,360 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
 #pragma unroll
                 for (int r = 0; r < 16; ++r) { c0[r] = 0.f; c1[r] = 0.f; }
                 if (j0 > 0) {
+                    const float rd = float(sRd[32 * wave + lc]);   // c_k / U_kk as the A operand
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            sC[(mt * 32 + (r / 4) * 8 + lr + (r % 4)) * SP + 32 * wave + lc] = acc[mt][r] * rd;
+                    __syncthreads();
                     const int nt0 = wave, nt1 = 3 - wave;
-                    const float* ap0 = sE + lc * SP + (lane >> 5);
-                    const float* ap1 = sE + (32 + lc) * SP + (lane >> 5);
-                    const float* bp0 = sU + (lane >> 5) * SB + nt0 * 32 + lc;
-                    const float* bp1 = sU + (lane >> 5) * SB + nt1 * 32 + lc;
-                    auto chunk = [&](float16v& c, const float* ap, const float* bp, const int ch) __attribute__((always_inline)) {
+                    const float* ap0 = sC + lc * SP + (lane >> 5);
+                    const float* ap1 = sC + (32 + lc) * SP + (lane >> 5);
+                    auto chunk = [&](float16v& c, const float* ap, const int nt, const int ch) __attribute__((always_inline)) {
+                        const float* bp = (ch == nt ? sUg + ch * UB : sU + u_off(ch, nt)) + (lane >> 5) * IB + lc;
                         float av[16], bv[16];
 #pragma unroll
                         for (int kk = 0; kk < 16; ++kk) {
                             av[kk] = ap[32 * ch + 2 * kk];
-                            bv[kk] = bp[(32 * ch + 2 * kk) * SB];
+                            bv[kk] = bp[2 * kk * IB];
                         }
 #pragma unroll
                         for (int kk = 0; kk < 16; ++kk) c = __builtin_amdgcn_mfma_f32_32x32x2f32(av[kk], bv[kk], c, 0, 0, 0);
                     };
 #pragma unroll 1
                     for (int ch = 0; ch < 4; ++ch) {
-                        if (ch <= nt0) chunk(c0, ap0, bp0, ch);
-                        if (ch <= nt1) chunk(c1, ap1, bp1, ch);
+                        if (ch <= nt0) chunk(c0, ap0, nt0, ch);
+                        if (ch <= nt1) chunk(c1, ap1, nt1, ch);
                     }
-                    __syncthreads();   // every wave is done reading sE as an operand
+                    __syncthreads();   // every wave is done reading sC as an operand
                 }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int o0 = ((r / 4) * 8 + lr + (r % 4)) * SP + wave * 32 + lc;
-                    const int o1 = (32 + (r / 4) * 8 + lr + (r % 4)) * SP + (3 - wave) * 32 + lc;
-                    sC[o0] = c0[r]; sE[o0] = w0r[0][r];
-                    sC[o1] = c1[r]; sE[o1] = w0r[1][r];
+                    sC[((r / 4) * 8 + lr + (r % 4)) * SP + wave * 32 + lc] = c0[r];
+                    sC[(32 + (r / 4) * 8 + lr + (r % 4)) * SP + (3 - wave) * 32 + lc] = c1[r];
                 }
-                __syncthreads();
             }
+            __syncthreads();
         }
 
 #pragma unroll 1
         for (int jb = 0; jb < SB; jb += IB) {
-            {
-                double w[8];
-                {
-                    const float* cp = sC + qrow * SP + jb + 8 * sl;
-                    const float* wp = sE + qrow * SP + jb + 8 * sl;
+            double w[8];
+            float* const crow = sC + qrow * SP + jb + 8 * sl;
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) w[i] = double(wp[i]) + double(cp[i]);
+            for (int i = 0; i < 8; ++i) w[i] = double(w0v[i]) + double(crow[i]);
+            double s_first = s, z_first = z;   // GB == 16: the grid of the inner block's first group
+            auto fix_grid = [&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                const int col = j0 + jb + j;
+                bool fresh;
+                double mn, mx;
+                // this lane's values of the group: eight per inner block that the group spans
+                auto value = [&](int k) __attribute__((always_inline)) {
+                    return double(w0v[k]) + double(crow[(k >> 3) * IB + (k & 7)]);
+                };
+                if constexpr (GB == 16) {
+                    // group = the 16 columns held by lanes 2 (j / 16) and 2 (j / 16) + 1 of the quad
+                    fresh = true;
+                    mn = w[0]; mx = w[0];
+#pragma unroll
+                    for (int i = 1; i < 8; ++i) { mn = fmin(mn, w[i]); mx = fmax(mx, w[i]); }
+                    mn = fmin(mn, dpp_quad<QUAD_SWAP1>(mn));
+                    mx = fmax(mx, dpp_quad<QUAD_SWAP1>(mx));
+                    mn = dpp_quad<quad_bcast(j / 8)>(mn);
+                    mx = dpp_quad<quad_bcast(j / 8)>(mx);
+                } else {
+                    fresh = a.wide_g < 0 && (col & (G - 1)) == 0;
+                    if (fresh) {   // uniform: the group's G <= 128 columns are unfinished
+                        mn = w[0]; mx = w[0];
+#pragma unroll
+                        for (int i = 1; i < 8; ++i) { mn = fmin(mn, w[i]); mx = fmax(mx, w[i]); }
+#pragma unroll
+                        for (int k = 8; k < 32; ++k) {
+                            if (k % 8 == 0 && 4 * k >= G) break;
+                            const double v = value(k);
+                            mn = fmin(mn, v); mx = fmax(mx, v);
+                        }
+                        mn = fmin(mn, dpp_quad<QUAD_SWAP1>(mn));
+                        mx = fmax(mx, dpp_quad<QUAD_SWAP1>(mx));
+                        mn = fmin(mn, dpp_quad<QUAD_SWAP2>(mn));
+                        mx = fmax(mx, dpp_quad<QUAD_SWAP2>(mx));
+                    }
                 }
-                // row j of the inner block's U triangle (this lane's 8 columns) and 1 / U_jj, one step ahead
-                float4v ua[2], ub[2];
-                double rdc = sRd[jb], rdn = 0.0;
-                const float* up = sU + jb * SB + jb + 8 * sl;
-                ua[0] = *reinterpret_cast<const float4v*>(up);
-                ua[1] = *reinterpret_cast<const float4v*>(up + 4);
+                if (!fresh) return;
+                int cand = 0;
+                if constexpr (GB != 16) {
+                    if (a.mse) {   // uniform; this lane's quarter of the group, held in registers
+                        float gv[32];
+#pragma unroll
+                        for (int k = 0; k < 32; ++k) gv[k] = k < 8 ? float(w[k & 7]) : 4 * (k & 24) < G ? float(value(k)) : 0.f;
+                        const int n8 = G >> 5;   // batches of 8 values: 1, 2 or 4
+                        const float qmf = a.qmax;
+                        cand = mse_search(mn, mx, qmax, qsd,
+                                   [&](float zi, float rsi) __attribute__((always_inline)) {
+                                       float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+                                       for (int k = 0; k < 8; k += 2) {
+                                           e0 += mse_term(gv[k], zi, rsi, qmf);
+                                           e1 += mse_term(gv[k + 1], zi, rsi, qmf);
+                                       }
+                                       if (n8 > 1) {
+#pragma unroll
+                                           for (int k = 8; k < 16; k += 2) {
+                                               e0 += mse_term(gv[k], zi, rsi, qmf);
+                                               e1 += mse_term(gv[k + 1], zi, rsi, qmf);
+                                           }
+                                       }
+                                       if (n8 > 2) {
+#pragma unroll
+                                           for (int k = 16; k < 32; k += 2) {
+                                               e0 += mse_term(gv[k], zi, rsi, qmf);
+                                               e1 += mse_term(gv[k + 1], zi, rsi, qmf);
+                                           }
+                                       }
+                                       return e0 + e1;
+                                   },
+                                   [&](float x) __attribute__((always_inline)) {
+                                       x += dpp_quad<QUAD_SWAP1>(x);
+                                       return x + dpp_quad<QUAD_SWAP2>(x);
+                                   });
+                    }
+                } else {
+                    if (a.mse) {   // uniform; the group's 16 values sit in two lanes of the quad
+                        float gv[8];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) gv[k] = float(w[k]);
+                        const float qmf = a.qmax;
+                        cand = mse_search(mn, mx, qmax, qsd,
+                                   [&](float zi, float rsi) __attribute__((always_inline)) {
+                                       float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+                                       for (int k = 0; k < 8; k += 2) {
+                                           e0 += mse_term(gv[k], zi, rsi, qmf);
+                                           e1 += mse_term(gv[k + 1], zi, rsi, qmf);
+                                       }
+                                       return e0 + e1;
+                                   },
+                                   [&](float x) __attribute__((always_inline)) {
+                                       x += dpp_quad<QUAD_SWAP1>(x);
+                                       return dpp_quad<quad_bcast(j / 8)>(x);
+                                   });
+                    }
+                }
+                grid_params(mn, mx, cand, qmax, qsd, s, z);
+                rs = 1.0 / s;
+                if constexpr (GB == 16 && j == 0) { s_first = s; z_first = z; }
+                if (sl == 0 && row_ok) {
+                    a.scales[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(s);
+                    a.zeros[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(z);
+                }
+            };
+            // (w - s (q - z), q - z) of a value on the current grid.  w / s correctly rounded, as the definition's division
+            // gives it (an exact tie, possible in a row's first group where weights and scale are short binary numbers,
+            // then falls the same way): t0 = w * fl(1 / s), residual by FMA, one correction step; no division, no branch.
+            // q - z = clamp(rint(t) + z, 0, qmax) - z = clamp(rint(t), -z, qmax - z): whole numbers, nothing is rounded.
+            auto quantize = [&](double v, double sq, double rsq, double zq, double& d) __attribute__((always_inline)) {
+                const double t0 = v * rsq;
+                const double t = __builtin_fma(__builtin_fma(-t0, sq, v), rsq, t0);
+                d = fmin(fmax(rint(t), -zq), qmax - zq);
+                return __builtin_fma(-sq, d, v);
+            };
+            auto pin = [](double& v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); };   // here, in this order
+            // The sequential part.  Row j of the inner block's U triangle (this lane's 8 columns, divided by U_jj) is read two
+            // steps ahead; it is zero up to column j, so a finished register keeps the value that was quantized.
+            // One wave per SIMD has nothing else to cover the chain of a step (broadcast, nine dependent fp64 operations,
+            // the update of the next column's register), so the other seven updates of the step before are issued between its
+            // operations, in this order: left alone, the compiler puts them in a block behind the chain (169 cycles a
+            // column), or each at its register's next use.
+            {
+                const double* const ud = sUd + (jb >> 5) * UD_SLICES * 8;
+                double2 u[3][4];
+                auto read_row = [&](auto jc, double2(&dst)[4]) __attribute__((always_inline)) {
+                    constexpr int j = decltype(jc)::value, g = j / 8;
+                    const double* p = (g == 0 || sl >= g ? ud + ud_first(g) + (sl - g) * 8 : sUd + 4 * UD_SLICES * 8) + (j % 8) * (4 - g) * 8;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dst[i] = *reinterpret_cast<const double2*>(p + 2 * i);
+                };
+                read_row(std::integral_constant<int, 0>{}, u[0]);
+                read_row(std::integral_constant<int, 1>{}, u[1]);
+                double res = 0.0;   // of the step before
                 static_for<0, IB>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
-                    auto step = [&](float4v(&cur)[2], float4v(&nxt)[2]) __attribute__((always_inline)) {
-                        if constexpr (j + 1 < IB) {
-                            nxt[0] = *reinterpret_cast<const float4v*>(up + (j + 1) * SB);
-                            nxt[1] = *reinterpret_cast<const float4v*>(up + (j + 1) * SB + 4);
-                            rdn = sRd[jb + j + 1];
+                    // update k of the step before: column j + k (mod 8); the first one, k = 0, has been made
+                    auto late = [&](auto kc) __attribute__((always_inline)) {
+                        constexpr int k = decltype(kc)::value, i = (j + k) % 8, pj = j - 1;
+                        if constexpr (j > 0 && (pj < 24 || i > pj % 8)) {
+                            const double2& up = u[(j + 2) % 3][i / 2];
+                            w[i] = __builtin_fma(-res, i % 2 ? up.y : up.x, w[i]);
+                            pin(w[i]);
                         }
-                        if constexpr (j % GB == 0) {
-                            const int col = j0 + jb + j;
-                            bool fresh;
-                            double mn, mx;
-                            if constexpr (GB == 16) {
-                                // group = the 16 columns held by lanes 2 (j / 16) and 2 (j / 16) + 1 of the quad
-                                fresh = true;
-                                mn = w[0]; mx = w[0];
-#pragma unroll
-                                for (int i = 1; i < 8; ++i) { mn = fmin(mn, w[i]); mx = fmax(mx, w[i]); }
-                                mn = fmin(mn, dpp_quad<QUAD_SWAP1>(mn));
-                                mx = fmax(mx, dpp_quad<QUAD_SWAP1>(mx));
-                                mn = dpp_quad<quad_bcast(j / 8)>(mn);
-                                mx = dpp_quad<quad_bcast(j / 8)>(mx);
-                            } else {
-                                fresh = a.wide_g < 0 && (col & (G - 1)) == 0;
-                                if (fresh) {   // uniform: the group's G <= 128 columns are unfinished, w0 in sE, c in sC
-                                    const float* gc = sC + qrow * SP + jb + sl;
-                                    const float* gw = sE + qrow * SP + jb + sl;
-                                    mn = double(gw[0]) + double(gc[0]); mx = mn;
-                                    for (int c = 4; c < G; c += 4) {
-                                        const double v = double(gw[c]) + double(gc[c]);
-                                        mn = fmin(mn, v); mx = fmax(mx, v);
-                                    }
-                                    mn = fmin(mn, dpp_quad<QUAD_SWAP1>(mn));
-                                    mx = fmax(mx, dpp_quad<QUAD_SWAP1>(mx));
-                                    mn = fmin(mn, dpp_quad<QUAD_SWAP2>(mn));
-                                    mx = fmax(mx, dpp_quad<QUAD_SWAP2>(mx));
-                                }
-                            }
-                            if (fresh) {
-                                int cand = 0;
-                                if constexpr (GB != 16) {
-                                    if (a.mse) {   // uniform; this lane's quarter of the group, held in registers
-                                        const float* gc = sC + qrow * SP + jb + sl;
-                                        const float* gw = sE + qrow * SP + jb + sl;
-                                        float gv[32];
-#pragma unroll
-                                        for (int k = 0; k < 32; ++k) {
-                                            const int c = (4 * k) & (G - 1);
-                                            gv[k] = float(double(gw[c]) + double(gc[c]));
-                                        }
-                                        const int n8 = G >> 5;   // batches of 8 values: 1, 2 or 4
-                                        const float qmf = a.qmax;
-                                        cand = mse_search(mn, mx, qmax, qsd,
-                                                   [&](float zi, float rsi) __attribute__((always_inline)) {
-                                                       float e0 = 0.f, e1 = 0.f;
-#pragma unroll
-                                                       for (int k = 0; k < 8; k += 2) {
-                                                           e0 += mse_term(gv[k], zi, rsi, qmf);
-                                                           e1 += mse_term(gv[k + 1], zi, rsi, qmf);
-                                                       }
-                                                       if (n8 > 1) {
-#pragma unroll
-                                                           for (int k = 8; k < 16; k += 2) {
-                                                               e0 += mse_term(gv[k], zi, rsi, qmf);
-                                                               e1 += mse_term(gv[k + 1], zi, rsi, qmf);
-                                                           }
-                                                       }
-                                                       if (n8 > 2) {
-#pragma unroll
-                                                           for (int k = 16; k < 32; k += 2) {
-                                                               e0 += mse_term(gv[k], zi, rsi, qmf);
-                                                               e1 += mse_term(gv[k + 1], zi, rsi, qmf);
-                                                           }
-                                                       }
-                                                       return e0 + e1;
-                                                   },
-                                                   [&](float x) __attribute__((always_inline)) {
-                                                       x += dpp_quad<QUAD_SWAP1>(x);
-                                                       return x + dpp_quad<QUAD_SWAP2>(x);
-                                                   });
-                                    }
-                                } else {
-                                    if (a.mse) {   // uniform; the group's 16 values sit in two lanes of the quad
-                                        float gv[8];
-#pragma unroll
-                                        for (int k = 0; k < 8; ++k) gv[k] = float(w[k]);
-                                        const float qmf = a.qmax;
-                                        cand = mse_search(mn, mx, qmax, qsd,
-                                                   [&](float zi, float rsi) __attribute__((always_inline)) {
-                                                       float e0 = 0.f, e1 = 0.f;
-#pragma unroll
-                                                       for (int k = 0; k < 8; k += 2) {
-                                                           e0 += mse_term(gv[k], zi, rsi, qmf);
-                                                           e1 += mse_term(gv[k + 1], zi, rsi, qmf);
-                                                       }
-                                                       return e0 + e1;
-                                                   },
-                                                   [&](float x) __attribute__((always_inline)) {
-                                                       x += dpp_quad<QUAD_SWAP1>(x);
-                                                       return dpp_quad<quad_bcast(j / 8)>(x);
-                                                   });
-                                    }
-                                }
-                                grid_params(mn, mx, cand, qmax, qsd, s, z);
-                                rs = 1.0 / s;
-                                if (sl == 0) {
-                                    const int gi = (jb + j) >> a.lgG;
-                                    sS[qrow * 8 + gi] = s;
-                                    sZ[qrow * 8 + gi] = float(z);
-                                    if (row_ok) {
-                                        a.scales[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(s);
-                                        a.zeros[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(z);
-                                    }
-                                }
-                            }
-                        }
-                        const double wj = dpp_quad<quad_bcast(j / 8)>(w[j % 8]);
-                        // w / s correctly rounded, as the definition's division gives it (an exact tie, possible in a
-                        // row's first group where weights and scale are short binary numbers, then falls the same way):
-                        // t0 = w * fl(1 / s), residual by FMA, one correction step; no division, no branch
-                        const double t0 = wj * rs;
-                        const double t = __builtin_fma(__builtin_fma(-t0, s, wj), rs, t0);
-                        const double q = fmin(fmax(rint(t) + z, 0.0), qmax);
-                        const double e = __builtin_fma(-s, q - z, wj) * rdc;         // (w - s (q - z)) / U_jj
-                        // feedback inside the inner block: w_k -= e U_jk.  Columns up to j are finished, updating
-                        // them is harmless; in the last slice the finished registers are skipped.
-                        // The register the next step broadcasts comes first, and every update is pinned to this step:
-                        // left alone, the compiler sinks each register's updates to its next use, a dependent chain
-                        // of up to 32 FMAs in front of a decision (and recomputed for each of the four lanes' turns).
-#pragma unroll
-                        for (int ii = 0; ii < 8; ++ii) {
-                            const int i = (j + 1 + ii) % 8;
-                            if (j < 24 || i > j % 8) {
-                                w[i] = __builtin_fma(-e, double(cur[i / 4][i % 4]), w[i]);
-                                asm volatile("" : "+v"(w[i]));
-                            }
-                        }
-                        sE[qrow * SP + jb + j] = float(e);
-                        sC[qrow * SP + jb + j] = float(q);
-                        rdc = rdn;
                     };
-                    if constexpr (j % 2 == 0) step(ua, ub);
-                    else step(ub, ua);
+                    constexpr bool fix = j % GB == 0;   // the group's grid needs all values up to date
+                    if constexpr (fix) {
+                        static_for<1, 8>(late);
+                        fix_grid(jc);
+                    }
+                    auto between = [&](auto kc) __attribute__((always_inline)) {
+                        if constexpr (!fix) late(kc);
+                    };
+                    double wj = dpp_quad<quad_bcast(j / 8)>(w[j % 8]);
+                    pin(wj);
+                    between(std::integral_constant<int, 1>{});
+                    double t0 = wj * rs;
+                    pin(t0);
+                    between(std::integral_constant<int, 2>{});
+                    double r1 = __builtin_fma(-t0, s, wj);
+                    pin(r1);
+                    between(std::integral_constant<int, 3>{});
+                    double t = __builtin_fma(r1, rs, t0);
+                    pin(t);
+                    between(std::integral_constant<int, 4>{});
+                    between(std::integral_constant<int, 5>{});
+                    t = fmin(fmax(rint(t), -z), qmax - z);   // pinned, the compiler would quiet NaNs before each of these
+                    between(std::integral_constant<int, 6>{});
+                    between(std::integral_constant<int, 7>{});
+                    if constexpr (j + 2 < IB) read_row(std::integral_constant<int, j + 2>{}, u[(j + 2) % 3]);
+                    res = __builtin_fma(-s, t, wj);
+                    pin(res);
+                    if constexpr (j + 1 < IB) {
+                        constexpr int i = (j + 1) % 8;
+                        const double2& un = u[j % 3][i / 2];
+                        w[i] = __builtin_fma(-res, i % 2 ? un.y : un.x, w[i]);
+                        pin(w[i]);
+                    }
                 });
             }
-            __syncthreads();
-            // remaining columns of the block: c_col -= sum_i e_i U[jb+i][col], col >= jb + 32, on 32 x 32 tiles
-            // accumulated from zero and then added to the tile in LDS
-            const int cs = jb + IB;
-            if (cs < SB)
+            // What the inner block leaves, from the values that were quantized: this lane's eight columns.  The errors go to
+            // sC's finished columns for the inner update, codes, W^ = s (q - z) and the residual fragments to memory.
+            // The residual is w - w^ (block form: against the original weights), negated, scaled by a power of two and split
+            // into fp16 hi + lo (hi = rne(x), lo = rne(x - hi): 22 significant bits); saturated far above anything a
+            // sweep of a sane layer produces, and the saturation is reported (the loss then comes back as +infinity).
+            uint32_t pair[8];   // the residuals, hi in the lower half
             {
-                const int n_tiles = 2 * ((SB - cs) / 32);
-                for (int t = wave; t < n_tiles; t += 4) {
-                    const int mt = t & 1, nt = t >> 1;
-                    float* cp = sC + (mt * 32 + lr) * SP + cs + nt * 32 + lc;
-                    float16v c;
+                const bool first = GB == 16 && sl < 2;
+                const double sq = first ? s_first : s, zq = first ? z_first : z;
+                const double rsq = GB == 16 ? 1.0 / sq : rs;
+                const float sf = float(sq);
+                float hat[8];
+                uint32_t codes[2] = {0, 0};
+                short8v fh, fl;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) c[r] = 0.f;
-                    const float* ap = sE + (mt * 32 + lc) * SP + jb + (lane >> 5);
-                    const float* bp = sU + (jb + (lane >> 5)) * SB + cs + nt * 32 + lc;
+                for (int i = 0; i < 8; ++i) {
+                    double d;
+                    const double r = quantize(w[i], sq, rsq, zq, d);
+                    const double e = r * sRd[jb + 8 * sl + i];
+                    lossacc = __builtin_fma(e, e, lossacc);
+                    crow[i] = float(e);
+                    codes[i / 4] |= uint32_t(int(d + zq)) << (8 * (i % 4));
+                    hat[i] = sf * float(d);
+                    float x = -float(DIRECT ? __builtin_fma(-sq, d, double(w0v[i])) : r) * f_d;
+                    saturated |= row_ok && !(fabsf(x) <= 60000.f);
+                    x = fminf(fmaxf(x, -60000.f), 60000.f);
+                    const _Float16 h = (_Float16)x;
+                    const _Float16 l = (_Float16)(x - (float)h);
+                    fh[i] = __builtin_bit_cast(short, h);
+                    fl[i] = __builtin_bit_cast(short, l);
+                    pair[i] = uint32_t(uint16_t(fh[i])) | (uint32_t(uint16_t(fl[i])) << 16);
+                }
+                if (row_ok) {
+                    uint32_t* const qp = reinterpret_cast<uint32_t*>(a.Q + int64_t(grow) * d_in + j0 + jb + 8 * sl);
+                    qp[0] = codes[0];
+                    qp[1] = codes[1];
+                    if (a.W_hat) {
+                        float* const hp = a.W_hat + int64_t(grow) * d_in + j0 + jb + 8 * sl;
 #pragma unroll
-                    for (int kk = 0; kk < IB / 2; ++kk)
-                        c = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[2 * kk], bp[2 * kk * SB], c, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) cp[((r / 4) * 8 + (r % 4)) * SP] += c[r];
+                        for (int h = 0; h < 2; ++h)
+                            *reinterpret_cast<float4v*>(hp + 4 * h) = float4v{hat[4 * h], hat[4 * h + 1], hat[4 * h + 2], hat[4 * h + 3]};
+                    }
+                }
+                // MFMA A-operand fragments for this workgroup's own near updates: lane L of k-step ks, row tile mt holds
+                // row mt*32 + L%32, columns ks*16 + 8 (L/32) + 0..7; rows past d_out hold copies of the last row
+                if (b + 1 < a.nb) {
+                    const int ks = (jb >> 4) + (sl >> 1), it = (ks * 2 + (qrow >> 5)) * 64 + (qrow & 31) + 32 * (sl & 1);
+                    const int64_t off = ((int64_t(wg) * 3 + b) * (8 * 2 * 64) + it) * 8;
+                    *reinterpret_cast<short8v*>(a.Fh + off) = fh;
+                    *reinterpret_cast<short8v*>(a.Fl + off) = fl;
                 }
             }
-            __syncthreads();
+            // Remaining columns of the block: c_col -= sum_i e_i U[jb+i][col], accumulated from zero and then added to the
+            // tile in LDS.  A wave updates the 16 rows it sweeps, so the waves run through the block without a barrier, and
+            // 16 x 16 tiles share its rows evenly: 6, 4 and 2 tiles of 32 x 32 on four waves behind barriers took 8.3
+            // thousand cycles a block.
+            if (jb + IB < SB) {
+                wave_fence();   // the other lanes' errors
+                const int l16 = lane & 15, lk = lane >> 4, I = jb >> 5;
+                float av[8];
+#pragma unroll
+                for (int kk = 0; kk < 8; ++kk) av[kk] = -sC[(16 * wave + l16) * SP + jb + 4 * kk + lk];
+                // a pair of tiles takes the even and the odd columns of 32: one LDS access brings both tiles' values, without
+                // bank conflicts; the operands and the old values of a pair are read a pair ahead
+                const float* const bp = sU + u_off(I, I + 1) + lk * IB + 2 * l16;
+                float* const cp = sC + (16 * wave + 4 * lk) * SP + jb + IB + 2 * l16;
+                float2 bv[2][8], old[2][4];
+                auto load = [&](int J, float2(&bd)[8], float2(&od)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) bd[kk] = *reinterpret_cast<const float2*>(bp + J * UB + 4 * kk * IB);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) od[r] = make_float2(cp[J * IB + r * SP], cp[J * IB + r * SP + 1]);
+                };
+                auto update = [&](int J, const float2(&bd)[8], const float2(&od)[4]) __attribute__((always_inline)) {
+                    float4v c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) {
+                        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk], bd[kk].x, c0, 0, 0, 0);
+                        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk], bd[kk].y, c1, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        cp[J * IB + r * SP] = od[r].x + c0[r];
+                        cp[J * IB + r * SP + 1] = od[r].y + c1[r];
+                    }
+                };
+                const int n_J = 3 - I;
+                load(0, bv[0], old[0]);
+                if (n_J > 1) load(1, bv[1], old[1]);
+                update(0, bv[0], old[0]);
+                if (n_J > 2) load(2, bv[0], old[0]);
+                if (n_J > 1) update(1, bv[1], old[1]);
+                if (n_J > 2) update(2, bv[0], old[0]);
+                wave_fence();
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) crow[i] = __uint_as_float(pair[i]);
+#pragma unroll
+            for (int i = 0; i < 24; ++i) w0v[i] = w0v[i + 8];   // the next inner block's first
         }
 
-        // ---- block done: loss, residual panels, outputs
-        {   // sum of e^2 of this row's quarter of the block, then over the quad
-            float acc = 0.f;
-            const float* ep = sE + qrow * SP + 32 * sl;
-#pragma unroll 8
-            for (int c = 0; c < 32; ++c) acc = __builtin_fmaf(ep[c], ep[c], acc);
-            acc += dpp_quad<QUAD_SWAP1>(acc);
-            acc += dpp_quad<QUAD_SWAP2>(acc);
-            lossacc += acc;
-        }
-        // residual w - w^ = e U_jj, negated, scaled by a power of two and split into fp16 hi + lo
-        // (hi = rne(x), lo = rne(x - hi): 22 significant bits); saturated far above anything a sweep of a sane layer
-        // produces, and the saturation is reported (the loss then comes back as +infinity).
-        auto split8 = [&](auto&& value, short8v& dh, short8v& dl) __attribute__((always_inline)) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float x = value(e);
-                saturated |= !(fabsf(x) <= 60000.f);
-                x = fminf(fmaxf(x, -60000.f), 60000.f);
-                const _Float16 h = (_Float16)x;
-                const _Float16 lo = (_Float16)(x - (float)h);
-                dh[e] = __builtin_bit_cast(short, h);
-                dl[e] = __builtin_bit_cast(short, lo);
-            }
-        };
-        float* sO = sU;   // DIRECT: w - w^ against the original weights, ROWS x SP (the U block is no longer needed)
-        if constexpr (DIRECT) {
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                const int col = (mt == 0 ? wave : 3 - wave) * 32 + lc, gi = col >> a.lgG;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int rr = mt * 32 + (r / 4) * 8 + lr + (r % 4);
-                    // w0 - s (q - z) with the fp64 scale the sweep used
-                    sO[rr * SP + col] = float(__builtin_fma(-sS[rr * 8 + gi], double(sC[rr * SP + col] - sZ[rr * 8 + gi]),
-                                                            double(w0r[mt][r])));
-                }
-            }
-            __syncthreads();
-        }
-        // transposed panel (k-major) for the far update; rows past d_out hold copies of the last row
-        for (int it = tid; it < SB * (ROWS / 8); it += 256) {
-            const int c = it / (ROWS / 8), r8 = (it % (ROWS / 8)) * 8;
-            const float ujj = DIRECT ? 0.f : sU[c * SB + c] * f_d;
-            short8v dh, dl;
-            if constexpr (DIRECT) split8([&](int e) { return -sO[(r8 + e) * SP + c] * f_d; }, dh, dl);
-            else split8([&](int e) { return -sE[(r8 + e) * SP + c] * ujj; }, dh, dl);
-            const int64_t off = int64_t(b * SB + c) * a.ldD + r0 + r8;
-            *reinterpret_cast<short8v*>(a.Dh + off) = dh;
-            *reinterpret_cast<short8v*>(a.Dl + off) = dl;
-        }
-        // MFMA A-operand fragments for this workgroup's own near updates: lane L of k-step ks, row tile mt holds
-        // row mt*32 + L%32, columns ks*16 + 8 (L/32) + 0..7
-        if (b + 1 < a.nb)
+        // ---- block done: the residuals again, transposed (k-major) for the far update, 8 rows x 4 columns per lane
+        wave_fence();
         {
-            for (int it = tid; it < 8 * 2 * 64; it += 256) {
-                const int L = it & 63, row = ((it >> 6) & 1) * 32 + (L & 31), c0 = (it >> 7) * 16 + 8 * (L >> 5);
-                short8v dh, dl;
-                if constexpr (DIRECT) split8([&](int e) { return -sO[row * SP + c0 + e] * f_d; }, dh, dl);
-                else split8([&](int e) { return -sE[row * SP + c0 + e] * (sU[(c0 + e) * SB + c0 + e] * f_d); }, dh, dl);
-                const int64_t off = ((int64_t(wg) * 3 + b) * (8 * 2 * 64) + it) * 8;
-                *reinterpret_cast<short8v*>(a.Fh + off) = dh;
-                *reinterpret_cast<short8v*>(a.Fl + off) = dl;
-            }
-        }
-        // W^ = s (q - z) and codes, in sweep order (see unpermute_kernel)
-        for (int it = wave; it < ROWS / 2; it += 4) {
-            const int rr = it * 2 + (lane >> 5), c4 = (lane & 31) * 4;
-            const int gr = r0 + rr;
-            if (gr >= a.d_out) continue;
-            float qv[4], hv[4];
+            const int r8 = 16 * wave + 8 * (lane & 1), c4 = 4 * (lane >> 1);
+            uint32_t v[4][8];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int gi = (c4 + e) >> a.lgG;
-                qv[e] = sC[rr * SP + c4 + e];
-                hv[e] = float(sS[rr * 8 + gi]) * (qv[e] - sZ[rr * 8 + gi]);
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c][e] = __float_as_uint(sC[(r8 + e) * SP + c4 + c]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int64_t off = int64_t(b * SB + c4 + c) * a.ldD + r0 + r8;
+                uint4v dh, dl;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    dh[e] = __builtin_amdgcn_perm(v[c][2 * e + 1], v[c][2 * e], 0x05040100u);
+                    dl[e] = __builtin_amdgcn_perm(v[c][2 * e + 1], v[c][2 * e], 0x07060302u);
+                }
+                *reinterpret_cast<uint4v*>(a.Dh + off) = dh;
+                *reinterpret_cast<uint4v*>(a.Dl + off) = dl;
             }
-            if (a.W_hat) {
-                const float4v h = {hv[0], hv[1], hv[2], hv[3]};
-                *reinterpret_cast<float4v*>(a.W_hat + int64_t(gr) * d_in + j0 + c4) = h;
-            }
-            const uint32_t pk = uint32_t(qv[0]) | (uint32_t(qv[1]) << 8) | (uint32_t(qv[2]) << 16) | (uint32_t(qv[3]) << 24);
-            *reinterpret_cast<uint32_t*>(a.Q + int64_t(gr) * d_in + j0 + c4) = pk;
         }
         // the fragments written above are read back by other waves of this workgroup (same CU, same L1): a
         // workgroup-scope release, completed by the barrier at the top of the loop
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     }
-    if (sl == 0 && row_ok) a.rowloss[grow] += lossacc;
+    lossacc += dpp_quad<QUAD_SWAP1>(lossacc);
+    lossacc += dpp_quad<QUAD_SWAP2>(lossacc);
+    if (sl == 0 && row_ok) a.rowloss[grow] += float(lossacc);
     if (saturated) *a.sat = 1u;
 }
 
@@ -1099,7 +1191,7 @@ __global__ __launch_bounds__(256, 2) void trailing_kernel(TrailArgs a) {
 // CUs, and all of them once the panel is done.  The two parts touch disjoint columns of the working copy, and the
 // panel writes the residual panels of its own super-block into the buffer the update does not read.
 template <int GB, bool DIRECT>
-__global__ __launch_bounds__(256) void panel_far_kernel(PanelArgs pa, TrailArgs ta, int n_panel) {
+__global__ __launch_bounds__(256, 2) void panel_far_kernel(PanelArgs pa, TrailArgs ta, int n_panel) {
     extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
     if (int(blockIdx.x) < n_panel) panel_body<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
     else trailing_tile<3, true>(ta, blockIdx.x - n_panel, dyn_lds);
@@ -1309,10 +1401,10 @@ SweepWs carve(void* ws, int64_t d_out, int64_t d_in) {
 template <int GB, bool DIRECT>
 onecomp_status launch_panel(const PanelArgs& pa, const TrailArgs& ta, int far_wgs, hipStream_t stream) {
     static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(&panel_far_kernel<GB, DIRECT>), PANEL_LDS, lds_ok) != ONECOMP_OK)
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&panel_far_kernel<GB, DIRECT>), panel_lds(DIRECT), lds_ok) != ONECOMP_OK)
         return ONECOMP_ERR_HIP;
     const int n_panel = int(ceil_div(pa.d_out, ROWS));
-    hipLaunchKernelGGL((panel_far_kernel<GB, DIRECT>), dim3(unsigned(n_panel + far_wgs)), dim3(256), PANEL_LDS, stream,
+    hipLaunchKernelGGL((panel_far_kernel<GB, DIRECT>), dim3(unsigned(n_panel + far_wgs)), dim3(256), panel_lds(DIRECT), stream,
                        pa, ta, n_panel);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
