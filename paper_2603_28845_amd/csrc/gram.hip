@@ -16,7 +16,8 @@
 //     order that walks bands of 4 tile rows column by column.  The 32 workgroups that share an
 //     XCD's L2 at any time then cover a compact 4 x 8 patch of tiles (12 X panels, not 64).  A wide layer is
 //     launched one round of tiles (one per CU) at a time, so that those 32 also stay together along the tokens.
-//   * calls of few tokens and narrow layers: register-staged 128 x 128 tiles (few_tokens_bf16).
+//   * calls of few tokens: 128 x 128 tiles, several per CU (few_tokens_bf16); narrow layers: 64 x 64 tiles whose tokens
+//     sixteen waves share out (split_bf16).
 //   * fp32 path (small layers): v_mfma_f32_32x32x2_f32, products in fp32; 32- or 64-wide tiles whose tokens eight waves
 //     share out, 128-wide tiles for wide layers with few tokens (f32_tile).
 #include "common.hpp"
@@ -305,7 +306,11 @@ __global__ __launch_bounds__(256) void gram_merge_kernel(float* __restrict__ H, 
 
 // -------------------------------------------------------------------------------------------
 // bf16 ring kernel: global -> LDS without passing through registers (buffer_load_dwordx4 ... lds), in steps of
-// 16 tokens through a ring of NBUF LDS slots.  Three shapes:
+// 16 tokens through a ring of NBUF LDS slots.  Four shapes:
+//   RingSmall 128 x 128 tile, 4 waves (2 x 2, 64 x 64 each), three workgroups per CU, which cover each other's first
+//            loads and reading and writing of H: for calls of few tokens (five slots and a budget of 168 registers; four
+//            workgroups of 128 registers spill in the epilogue, two with eight slots leave it uncovered: d_in 4096, 2048
+//            tokens 70 us against 78 and 77).
 //   RingWide 384 x 256 tile, 4 waves (2 x 2, 192 x 128 each = 24 MFMA tiles = 384 accumulator registers per lane),
 //            one wave per SIMD with the whole register file.  The fewest L2 and LDS bytes per flop (17 % less than
 //            256 x 256, 10 fragments for 24 MFMAs per step instead of 6 for 8).  The compiler cannot place 384
@@ -333,6 +338,9 @@ __global__ __launch_bounds__(256) void gram_merge_kernel(float* __restrict__ H, 
 //     time behind the MFMAs.  Half-iteration h: MT NT MFMAs on the fragments of step h (registers); LDS ->
 //     fragments of step h+1; loads of step h+NBUF into the slot step h was read from; wait for step h+2 + barrier.
 // -------------------------------------------------------------------------------------------
+struct RingSmall {
+    static constexpr int TM = 128, TN = 128, WM = 2, WN = 2, NBUF = 5, MIN_WAVES = 3;
+};
 struct RingMid {
     static constexpr int TM = 128, TN = 256, WM = 2, WN = 2, NBUF = 6, MIN_WAVES = 2;
 };
@@ -910,6 +918,175 @@ onecomp_status launch_f32_split(const float* X, int64_t n_tokens, int64_t d_in, 
     return ONECOMP_OK;
 }
 
+// -------------------------------------------------------------------------------------------
+// bf16 kernel for few tiles: a 64 x 64 tile per workgroup, its tokens cut into sixteen runs, one per wave, as in the
+// fp32 kernel above.  Operands come straight from global memory: a lane loads two neighbouring channels of each of eight tokens
+// (a load reads 128 bytes of two tokens) and packs them by channel, so a wave's 64 channels are two operands, the even and
+// the odd channels, four MFMAs per 16 tokens and no LDS.  The ring kernels have such a tile walk through all tokens in
+// one workgroup, 0.15 to 0.3 us per 16 of them: d_in 512, 8192 tokens 156 us against 66 (see split_bf16).
+// With one tile per CU the loads' latency bounds it (sixteen waves with three steps in flight each; eight waves: 79 us at
+// that size).
+// The partial sums meet in LDS: eight waves hand theirs to the other eight, whose sums are added in wave order.
+// -------------------------------------------------------------------------------------------
+constexpr int B16S_WAVES = 16, B16S_TS = 64, B16S_PITCH = B16S_TS + 1, B16S_STEP = 16;
+constexpr size_t B16S_LDS = size_t(B16S_WAVES / 2) * B16S_TS * B16S_PITCH * sizeof(float);
+template <bool DIAG>
+__device__ __forceinline__ void gram_bf16_run(const uint16_t* __restrict__ X, int64_t t_begin, int64_t t_end, int64_t ldx,
+                                              int d_in, int i0, int k0, int lane, float16v (&acc)[2][2]) {
+    const int th = lane >> 5, cl = lane & 31;
+    // byte offsets of this lane's channels in its first token; channels past the last ones read those again (their sums
+    // are not stored)
+    const int oa = int(8 * th * ldx + min(i0 + 2 * cl, d_in - 2)) * 2;
+    const int ob = int(8 * th * ldx + min(k0 + 2 * cl, d_in - 2)) * 2;
+    const int row = int(ldx) * 2;   // bytes from one token to the next
+    struct Batch {
+        uint32_t a[8], b[DIAG ? 1 : 8];
+    };
+    // As in the fp32 kernel: the address of a step is scalar (descriptor base, scalar offset of the token), which is no part
+    // of the bounds check; a step that reaches past the run's last token steps its vector offsets instead, and what lies
+    // behind that token reads as zero.
+    auto load = [&](Batch& f, int64_t t0, auto inside) __attribute__((always_inline)) {
+        const int64_t left = t0 < t_end ? ((t_end - t0 - 1) * ldx + d_in) * 2 : 0;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(X + (left > 0 ? t0 : 0) * ldx), 0, int(min(left, int64_t(0x7FFFFFFF))), 0x00020000);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if constexpr (decltype(inside)::value) {
+                f.a[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, oa, e * row, 0);
+                if constexpr (!DIAG) f.b[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, ob, e * row, 0);
+            } else {
+                f.a[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, oa + e * row, 0, 0);
+                if constexpr (!DIAG) f.b[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, ob + e * row, 0, 0);
+            }
+        }
+    };
+    auto pack = [&](const uint32_t* v, uint32_t sel) __attribute__((always_inline)) {   // eight tokens of one channel
+        uint4v o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], sel);
+        return __builtin_bit_cast(bf16x8, o);
+    };
+    auto multiply = [&](const Batch& f) __attribute__((always_inline)) {
+        constexpr uint32_t SEL[2] = {0x05040100u, 0x07060302u};
+        bf16x8 a[2], b[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            a[m] = pack(f.a, SEL[m]);
+            if constexpr (DIAG) b[m] = a[m];
+            else b[m] = pack(f.b, SEL[m]);
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[n], acc[m][n], 0, 0, 0);
+    };
+    // three steps in flight; the fences keep the compiler from moving the loads down to their use
+    constexpr std::false_type checked{};
+    constexpr std::true_type inside{};
+    Batch f0, f1, f2;
+    load(f0, t_begin, checked);
+    load(f1, t_begin + B16S_STEP, checked);
+    load(f2, t_begin + 2 * B16S_STEP, checked);
+    int64_t t = t_begin;
+    auto step = [&](Batch& f, int64_t t0, auto in) __attribute__((always_inline)) {
+        multiply(f);
+        __builtin_amdgcn_sched_barrier(0);
+        load(f, t0, in);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll 1
+    for (; t + 6 * B16S_STEP <= t_end; t += 3 * B16S_STEP) {   // the steps to load lie inside the run
+        step(f0, t + 3 * B16S_STEP, inside);
+        step(f1, t + 4 * B16S_STEP, inside);
+        step(f2, t + 5 * B16S_STEP, inside);
+    }
+#pragma unroll 1
+    for (; t < t_end; t += 3 * B16S_STEP) {
+        step(f0, t + 3 * B16S_STEP, checked);
+        step(f1, t + 4 * B16S_STEP, checked);
+        step(f2, t + 5 * B16S_STEP, checked);
+    }
+}
+__global__ __launch_bounds__(64 * B16S_WAVES, 4) void gram_bf16_split_kernel(const uint16_t* __restrict__ X, int64_t n_tokens,
+                                                                            int d_in, int64_t ldx, float* __restrict__ H,
+                                                                            int n_t, int n_tiles, int chunk) {
+    extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
+    constexpr int TS = B16S_TS, PITCH = B16S_PITCH, HALF = B16S_WAVES / 2;
+    float* part = reinterpret_cast<float*>(dyn_lds);   // [HALF][TS][PITCH]
+    const int v = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+    if (v >= n_tiles) return;
+    int ti, tk;
+    tile_from_rank(v, n_t, ti, tk);
+    const bool diag = ti == tk;
+    const int i0 = ti * TS, k0 = tk * TS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t run = (n_tokens + B16S_STEP * B16S_WAVES - 1) / (B16S_STEP * B16S_WAVES) * B16S_STEP;
+    const int64_t t0 = min(n_tokens, wave * run), t1 = min(n_tokens, t0 + run);
+    float16v acc[2][2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
+    if (diag) gram_bf16_run<true>(X, t0, t1, ldx, d_in, i0, k0, lane, acc);
+    else gram_bf16_run<false>(X, t0, t1, ldx, d_in, i0, k0, lane, acc);
+    // register r of lane l: row (r/4)*8 + (l/32)*4 + r%4, column l%32 of the tile of one parity of channels each way
+    float* const slot = part + (wave % HALF) * TS * PITCH + 2 * (lane >> 5) * 4 * PITCH + 2 * (lane & 31);
+    auto at = [&](int m, int n, int r) __attribute__((always_inline)) -> float& {
+        return slot[(2 * ((r / 4) * 8 + (r % 4)) + m) * PITCH + n];
+    };
+    if (wave >= HALF) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) at(m, n, r) = acc[m][n][r];
+    }
+    __syncthreads();
+    if (wave < HALF) {   // in place: this wave's positions only
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) at(m, n, r) += acc[m][n][r];
+    }
+    __syncthreads();
+    // H += 2 sum along its rows, then the mirror positions along theirs, from the values kept in the first partial
+    for (int e = tid; e < TS * TS; e += 64 * B16S_WAVES) {
+        const int r = e / TS, c = e % TS, i = i0 + r, k = k0 + c;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < HALF; ++w) sum += part[(w * TS + r) * PITCH + c];
+        if (i >= d_in || k >= d_in || (diag && i > k)) continue;
+        float* p = H + int64_t(i) * d_in + k;
+        const float nv = *p + 2.0f * sum;
+        *p = nv;
+        part[r * PITCH + c] = nv;
+    }
+    __syncthreads();
+    for (int e = tid; e < TS * TS; e += 64 * B16S_WAVES) {
+        const int c = e / TS, r = e % TS, i = i0 + r, k = k0 + c;
+        if (i >= d_in || k >= d_in || (diag && i >= k)) continue;
+        H[int64_t(k) * d_in + i] = part[r * PITCH + c];
+    }
+}
+onecomp_status launch_bf16_split(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H, hipStream_t stream) {
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&gram_bf16_split_kernel), int(B16S_LDS), lds_ok) != ONECOMP_OK)
+        return ONECOMP_ERR_HIP;
+    const int n_t = int(ceil_div(d_in, B16S_TS));
+    const int n_tiles = n_t * (n_t + 1) / 2;
+    const int chunk = int(ceil_div(n_tiles, 8));
+    hipLaunchKernelGGL(gram_bf16_split_kernel, dim3(unsigned(chunk * 8)), dim3(64 * B16S_WAVES), B16S_LDS, stream,
+                       static_cast<const uint16_t*>(X), n_tokens, int(d_in), ldx, H, n_t, n_tiles, chunk);
+    ONECOMP_CHECK_LAUNCH();
+    return ONECOMP_OK;
+}
+
 template <int WT>
 onecomp_status launch_bf16(const void* X, int64_t n_tokens, int64_t d_in, int64_t ldx, float* H,
                            hipStream_t stream) {
@@ -1035,8 +1212,8 @@ onecomp_status launch_bf16_ring(const void* X, const void* Xb, int64_t n_tokens,
 // plus 15 % for its higher L2 traffic per flop; a 384 x 256 tile runs one per CU, is 1.5 times the work and moves 17 %
 // fewer L2 and LDS bytes per flop, which makes a round of them about 10 % shorter than its work (2.7 units).  The
 // 384-row shape needs the workspace for a last round that is not full.
-// ONECOMP_GRAM_SHAPE=big|mid|wide in the environment forces a shape (testing and tuning).
-enum class GramShape { Big, Mid, Wide };
+// ONECOMP_GRAM_SHAPE=big|mid|wide|small in the environment forces a shape (testing and tuning).
+enum class GramShape { Big, Mid, Wide, Small };
 constexpr double WIDE_UNITS = 2.7;
 // The 384-row shape pays for its size when a call has few tokens: its four waves read, add and write 1.2 MB of H per
 // tile, a latency chain of 0.66 ms per call at d_in 14336 against 0.28 ms with 256 x 256 tiles on eight waves (close to
@@ -1050,8 +1227,36 @@ int forced_shape() {
     if (!strcmp(e, "big")) return int(GramShape::Big);
     if (!strcmp(e, "mid")) return int(GramShape::Mid);
     if (!strcmp(e, "wide")) return int(GramShape::Wide);
+    if (!strcmp(e, "small")) return int(GramShape::Small);
     return -1;
 }
+// Layers of few tiles, at most one of 64 x 64 per CU, whose tokens are shared out inside the workgroup.  us of a call, the
+// ring kernels (below d_in 1024 and from 4097 tokens on the register-staged one) : this one:
+//   d_in  512,  128 tokens: 18 : 15;  512: 21 : 17;  4096: 55 : 35;  8192: 156 : 66;  65536: 1206 : 320;  262144: 4792 : 1224
+//   d_in 1024,  128 tokens: 18.5 : 16;  1024: 27 : 26;  4096: 62 : 47;  8192: 97 : 66;  12288: 101 : 80;  16384: 105 : 103;  32768: 123 : 179
+//   d_in 1360,  512 tokens: 24 : 22;  1024: 30 : 33;  2048: 45 : 39;  8192: 103 : 70;  12288: 107 : 90;  16384: 111 : 116 (253 tiles)
+//   d_in 1536,  2048 tokens: 46 : 70 (300 tiles)
+// Under 256 tokens it gains 3 us and is left out.
+bool split_bf16(int64_t n_tokens, int64_t d_in) {
+    if (d_in < 1024) return n_tokens >= 256;
+    return d_in <= 1360 && n_tokens >= 2048 && n_tokens <= 12288;
+}
+// Calls whose time is the start and end of a tile as much as its tokens take 128 x 128 tiles, several per CU.  Per token
+// they are slower, by more the wider the layer (operand bytes).  us of a call, the shape chosen otherwise : RingSmall, and
+// in brackets the register-staged 128 x 128 kernel:
+//   d_in 1024,  256 tokens: 33 : 18.5 (19);  2048: 56 : 35 (42);  4096: 95 : 61 (87);  8192: 96 : 98
+//   d_in 2048,  256 tokens: 41 : 20 (20.5);  2048: 71 : 44 (56);  4096: 93 : 63 (89);  8192: 101 : 101
+//   d_in 4096,  256 tokens: 61 : 40 (43);  1024: 78 : 54 (68);  2048: 97 : 70;  4096: 139 : 114;  8192: 209 : 195
+//   d_in 6144,  512 tokens: 78 : 71;  2048: 127 : 126;  4096: 235 : 201;  8192: 383 : 356
+//   d_in 8192,  512 tokens: 135 : 112;  2048: 248 : 205;  4096: 393 : 351;  8192: 608 : 627
+//   d_in 11008, 512 tokens: 283 : 223;  2048: 406 : 374;  4096: 596 : 625
+//   d_in 14336, 512 tokens: 410 : 334;  1024: 478 : 424;  2048: 645 : 601;  4096: 961 : 1103
+// Without a workspace, which callers give for speed, wide layers keep to the line that onecomp_accumulate_describe has told
+// them of, n_tokens d_in^2 < 3e10 (1788 tokens at d_in 4096), and to the larger tiles beyond it.
+bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
+    return n_tokens <= 4096 && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
+}
+
 GramShape choose_shape(int64_t d_in, int64_t n_tokens, int n_cus, size_t ws_bytes) {
     const int64_t n256 = ceil_div(d_in, 256), n128 = ceil_div(d_in, 128), n384 = ceil_div(d_in, 384);
     const int64_t big = n256 * (n256 + 1) / 2;
@@ -1064,20 +1269,6 @@ GramShape choose_shape(int64_t d_in, int64_t n_tokens, int n_cus, size_t ws_byte
     if (f >= 0) return GramShape(f);
     if (n_tokens >= WIDE_MIN_TOKENS && cost_wide < cost_big && cost_wide < cost_mid) return GramShape::Wide;
     return cost_big <= cost_mid ? GramShape::Big : GramShape::Mid;
-}
-
-// Calls whose time is the start and end of a tile rather than its tokens: the ring kernels fill eight slots first, and
-// their 256-wide tiles (one per CU) leave little in flight while H is read and written; the 128 x 128 kernel has four
-// times the workgroups, several per CU.  It is the slower one per token, by more the wider the layer (operand bytes).
-// us of a call, ring (best shape) : 128 x 128:
-//   d_in 1024,  128 tokens: 33 : 17;  2048: 56 : 43;  4096: 96 : 86;  4900: 99 : 101 (8192: 147 : 157)
-//   d_in 2048,  128 tokens: 41 : 19;  2048: 72 : 57;  4096: 97 : 90;  4900: 102 : 102 (8192: 146 : 158)
-//   d_in 3072,  128 tokens: 51 : 32;  2048: 77 : 67;  3115: 88 : 87 (4096: 102 : 104)
-//   d_in 4096,  128 tokens: 61 : 40;  1024: 79 : 68;  1752: 92 : 92 (2048: 99 : 102)
-//   d_in 6144,  128 tokens: 78 : 56;   512: 91 : 76;   778: 100 : 90 (1024: 97 : 102)
-//   d_in 8192,  128 tokens: 110 : 88;  438: 128 : 113     d_in 14336, 128 tokens: 354 : 307
-bool few_tokens_bf16(int64_t n_tokens, int64_t d_in) {
-    return n_tokens <= 4096 && n_tokens * d_in * d_in < 30000000000;
 }
 
 }  // namespace
@@ -1101,9 +1292,21 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
                                     size_t ws_bytes, hipStream_t stream, GramPlanInfo* info) {
     float* ws = static_cast<float*>(wsv);
     if (info) *info = GramPlanInfo{128, 128, 0};
-    // The direct-to-LDS kernels need 32-bit byte offsets inside a step of tokens; narrow layers and calls of few tokens
-    // take the register-staged 128 x 128 kernel.
-    if (ldx * 64 >= (int64_t(1) << 31) || d_in < 1024 || (few_tokens_bf16(n_tokens, d_in) && forced_shape() < 0)) {
+    // The other kernels need 32-bit byte offsets inside a step of tokens
+    const bool far_rows = ldx * 64 >= (int64_t(1) << 31);
+    if (!far_rows && forced_shape() < 0) {
+        if (split_bf16(n_tokens, d_in)) {
+            if (!info) return launch_bf16_split(X, n_tokens, d_in, ldx, H, stream);
+            *info = GramPlanInfo{B16S_TS, B16S_TS, 1};
+            return ONECOMP_OK;
+        }
+        if (few_tokens_bf16(n_tokens, d_in, ws_bytes > 0)) {
+            if (!info) return launch_bf16_ring<RingSmall, false>(X, X, n_tokens, d_in, ldx, ldx, H, nullptr, 0, stream);
+            info->launches = 1;
+            return ONECOMP_OK;
+        }
+    }
+    if (far_rows || d_in < 1024) {
         if (info) {
             info->launches = 1;
             return ONECOMP_OK;
@@ -1115,6 +1318,8 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
     // describing a call: the workspace is only a size
     float* wsp = info ? reinterpret_cast<float*>(uintptr_t(ws_bytes ? 256 : 0)) : ws;
     switch (choose_shape(d_in, n_tokens, n_cus, wsp ? ws_bytes : 0)) {
+        case GramShape::Small:
+            return launch_bf16_ring<RingSmall, false>(X, X, n_tokens, d_in, ldx, ldx, H, nullptr, 0, stream, info);
         case GramShape::Wide:
             return launch_bf16_ring<RingWide, false>(X, X, n_tokens, d_in, ldx, ldx, H, wsp, ws_bytes, stream, info);
         case GramShape::Big:

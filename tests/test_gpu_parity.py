@@ -157,6 +157,31 @@ def test_gram_ring_of_few_tokens(monkeypatch, shape, d_in, n_tok):
 
 
 @pytest.mark.parametrize("d_in,n_tok,pad,tile", [
+    # 64-wide tiles, sixteen runs of tokens in steps of 16: from 256 tokens on below d_in 1024, from 2048 to 12288 up to 1360
+    (16, 256, 0, 64), (48, 257, 16, 64), (144, 271, 0, 64), (528, 1000, 16, 64), (1008, 4097, 0, 64), (80, 20001, 0, 64),
+    (1024, 2048, 16, 64), (1360, 3001, 0, 64), (1360, 12288, 0, 64),
+    # around them, 128 x 128 tiles of the ring: a ragged edge, fewer tokens than its slots hold
+    (16, 1, 0, 128), (144, 255, 16, 128), (1024, 2047, 0, 128), (1376, 2049, 0, 128), (2064, 4096, 16, 128), (4112, 4096, 0, 128), (9984, 77, 0, 128),
+])
+def test_gram_bf16_few_tokens_or_channels(d_in, n_tok, pad, tile):
+    _announce(f"gram bf16 d_in={d_in} n_tok={n_tok} pad={pad}")
+    ws = torch.empty(256, dtype=torch.uint8, device=DEV)
+    plan = og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, 256)
+    assert (plan["tile_rows"], plan["tile_cols"], plan["launches"]) == (tile, tile, 1)
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    wide = torch.full((n_tok + 1, d_in + pad), float("nan"), device=DEV, dtype=torch.bfloat16)   # what lies around X is not read
+    wide[:n_tok, :d_in] = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    X = wide[:n_tok, :d_in]
+    H = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H, workspace=ws)
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd) + 0.5
+    assert torch.equal(H, H.t())
+    # exact products, n_tok fp32 additions whose rounding errors add up like a random walk (see the fp32 tiles)
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
+@pytest.mark.parametrize("d_in,n_tok,pad,tile", [
     # 32-wide tiles: one ragged tile, a ragged last tile, token counts around the eight runs and their batches of 32
     (16, 1, 0, 32), (48, 7, 0, 32), (80, 255, 4, 32), (512, 257, 0, 32), (1424, 3001, 16, 32), (2672, 257, 0, 32),
     (1360, 2047, 0, 32), (2560, 2049, 0, 32),
