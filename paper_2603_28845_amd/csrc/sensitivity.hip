@@ -7,14 +7,15 @@
 //
 // gfx950: W is read once from HBM.  A team of TS <= 64 lanes of one wave owns a group at a time, 16 bytes per lane and
 // load.  Per-workgroup partial sums are combined in a fixed order: bit-wise reproducible.
-// Once W comes in at full width the kernel is bound by its VALU operations: 24 per weight at 4096 x 4096 bf16 in groups of
-// 64 and 128 (counted by SQ_INSTS_VALU), nine of them the weight's own (unpacking, range, rounding, sum), the rest what a
-// group costs every lane of its team for eight weights: the reduction of the range, two divisions and a reciprocal,
-// addresses.  That rest is kept small: a group of up to two loads per lane stays in registers between the pass for min / max
+// Once W comes in at full width the kernel is bound by its VALU operations: with eight weights of a group per lane 24 per
+// weight at 4096 x 4096 bf16 in groups of 64 and 128 (counted by SQ_INSTS_VALU), nine of them the weight's own (unpacking,
+// range, rounding, sum), the rest what a group costs every lane of its team: the reduction of the range, two divisions and a
+// reciprocal, addresses.  So a lane takes 16 weights of a group where there are as many (sensitivity_run), and that rest is
+// kept small: a group of up to two (fp32: four) loads per lane stays in registers between the pass for min / max
 // and the one that rounds (wider groups read it again, from cache), the lanes of a row of 16 meet through DPP operands,
 // the position in the matrix advances by additions (a 64-bit division per group cost more than the group's arithmetic),
 // and the grid is a multiple of the groups of a row where it can be, so that a team keeps its slice of `a`.
-// 4096 x 4096 bf16, G 64 / 128: 16.2 -> 13.5 us per candidate.
+// 4096 x 4096 bf16, G 64 / 128, us of a call with eight and with 16 weights per lane: 14.0 -> 12.3.
 #include "common.hpp"
 
 namespace onecomp {
@@ -183,20 +184,26 @@ __global__ __launch_bounds__(256) void sens_kernel(SensArgs g) {
     }
 }
 
-__global__ __launch_bounds__(256) void sens_final_kernel(const float* __restrict__ partial, int n, float* __restrict__ err) {
-    __shared__ double part[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) s += double(partial[i]);
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *err = float(0.5 * part[0]);
-}
-
 constexpr int SENS_WGS = 2048;
+// one load latency, then the waves' butterflies and one exchange (a tree over LDS: 1 us more)
+__global__ __launch_bounds__(1024) void sens_final_kernel(const float* __restrict__ partial, int n, float* __restrict__ err) {
+    __shared__ double part[16];
+    const int tid = threadIdx.x;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < SENS_WGS / 1024; ++k)
+        if (tid + 1024 * k < n) s += double(partial[tid + 1024 * k]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = s;
+    __syncthreads();
+    if (tid < 16) {
+        s = part[tid];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 16);
+        if (tid == 0) *err = float(0.5 * s);
+    }
+}
 
 // Scratch of the entry point that takes no workspace: the per-workgroup partial sums, SENS_WGS floats (8 KB), in
 // device memory that belongs to the loaded code object (one copy per GPU, held until the process ends).  In host
@@ -238,6 +245,11 @@ onecomp_status sensitivity_run(const void* W, onecomp_dtype w_dtype, int64_t d_o
     const int vec = w_dtype == ONECOMP_BF16 ? 8 : 4;          // elements per 16-byte lane load
     int ts = 2;
     while (ts < 64 && ts * 2 * vec <= group_size) ts *= 2;    // one pass over the group if it fits 64 lanes
+    // Up to 16 weights per lane, in two or four loads: what a group costs every lane of its team is then shared by twice or
+    // four times as many.  us of a candidate, one load : 16 : 32 weights, 14336 x 4096: bf16, groups of 64 35.2 : 28.3 : 31.9,
+    // of 128 35.8 : 28.6 : 28.4; fp32 (4 : 8 : 16), groups of 64 55.9 : 41.9 : 40.3.
+    const int loads = w_dtype == ONECOMP_BF16 ? 2 : 4;
+    while (ts > 2 && ceil_div(group_size, ts / 2 * vec) <= loads) ts /= 2;
     g.ts = ts;
     g.qs = grid == ONECOMP_GRID_SYMMETRIC ? float((1 << (bits - 1)) - 1) : 0.f;
     g.qmax = grid == ONECOMP_GRID_SYMMETRIC ? 2.f * g.qs : float((1 << bits) - 1);
@@ -252,9 +264,9 @@ onecomp_status sensitivity_run(const void* W, onecomp_dtype w_dtype, int64_t d_o
     const int k = int(ceil_div(group_size, ts * vec));        // loads per lane and group
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(wgs), dim3(256), 0, stream, g); };
     if (w_dtype == ONECOMP_BF16) launch(k == 1 ? sens_kernel<uint16_t, 1> : k == 2 ? sens_kernel<uint16_t, 2> : sens_kernel<uint16_t, 0>);
-    else launch(k == 1 ? sens_kernel<float, 1> : k == 2 ? sens_kernel<float, 2> : sens_kernel<float, 0>);
+    else launch(k <= 2 ? sens_kernel<float, 2> : k <= 4 ? sens_kernel<float, 4> : sens_kernel<float, 0>);
     ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(sens_final_kernel, dim3(1), dim3(256), 0, stream, g.partial, wgs, err);
+    hipLaunchKernelGGL(sens_final_kernel, dim3(1), dim3(1024), 0, stream, g.partial, wgs, err);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
 }
