@@ -136,12 +136,16 @@ __global__ __launch_bounds__(256) void jq_residual_kernel(const void* __restrict
 // k < k_count, zero for k_count <= k < k_pad and for the padding rows up to ldD.  f_d = 2^(13 - exponent of the
 // maximum in sc), so that the largest value lands in [2^12, 2^13); thread 0 of the grid leaves f_d, f_all = f_d f_u
 // and f_inv in sc for the product (f_u, a power of two, is already there) and clears the maximum of `other` (the
-// slot the next producer accumulates into).  64 x 64 tiles through LDS.
+// slot the next producer accumulates into).  Tiles of 32 rows x 64 k through LDS, four elements per load and store:
+// a visit's operand is 4096 x 128 and its launch is latency only, so all of a thread's loads are in flight at once
+// and the call makes 256 workgroups (5.0 us; 9.5 with 64 x 64 tiles, an element per load and store).  vec: k_count,
+// ld_src, src and d allow 16-byte loads.
+constexpr int DS_ROWS = 32;
 __global__ __launch_bounds__(256) void jq_dsplit_kernel(const float* __restrict__ src, int64_t ld_src, int d_out,
                                                         int k_count, int k_pad, const float* __restrict__ d,
                                                         Scalars* sc, Scalars* other, uint16_t* __restrict__ Dh,
-                                                        uint16_t* __restrict__ Dl, int64_t ldD) {
-    __shared__ float tile[64][65];
+                                                        uint16_t* __restrict__ Dl, int64_t ldD, int vec) {
+    __shared__ float tile[DS_ROWS][65];
     const float mx = __uint_as_float(sc->max_w_bits);
     int e = 0;
     if (mx > 0.f) (void)frexpf(mx, &e);
@@ -154,22 +158,50 @@ __global__ __launch_bounds__(256) void jq_dsplit_kernel(const float* __restrict_
         sc->f_inv = 1.0f / (f_d * f_u);
         if (other) other->max_w_bits = 0u;
     }
-    const int k0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int rr = ty; rr < 64; rr += 4) {
-        const int r = r0 + rr, k = k0 + tx;
-        tile[rr][tx] = (r < d_out && k < k_count) ? src[int64_t(r) * ld_src + k] * (d ? d[k] : 1.0f) * f_d : 0.f;
+    const int k0 = blockIdx.x * 64, r0 = blockIdx.y * DS_ROWS;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int k = k0 + 4 * tx;
+    float4v x[DS_ROWS / 16];
+    if (vec) {
+        const bool in = k < k_count;   // k_count % 4 == 0
+        const float4v dk = d && in ? *reinterpret_cast<const float4v*>(d + k) : float4v{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+        for (int i = 0; i < DS_ROWS / 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+            x[i] = in && r < d_out ? *reinterpret_cast<const float4v*>(src + int64_t(r) * ld_src + k) * dk * f_d
+                                   : float4v{0.f, 0.f, 0.f, 0.f};
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < DS_ROWS / 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                x[i][e] = r < d_out && k + e < k_count ? src[int64_t(r) * ld_src + k + e] * (d ? d[k + e] : 1.0f) * f_d : 0.f;
+        }
     }
+#pragma unroll
+    for (int i = 0; i < DS_ROWS / 16; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[ty + 16 * i][4 * tx + e] = x[i][e];
     __syncthreads();
-    for (int kk = ty; kk < 64; kk += 4) {
-        const int k = k0 + kk, r = r0 + tx;
-        if (k >= k_pad || r >= ldD) continue;
-        float x = tile[tx][kk];
-        x = fminf(fmaxf(x, -60000.f), 60000.f);
-        const _Float16 h = (_Float16)x;
-        const _Float16 lo = (_Float16)(x - (float)h);
-        Dh[int64_t(k) * ldD + r] = __builtin_bit_cast(uint16_t, h);
-        Dl[int64_t(k) * ldD + r] = __builtin_bit_cast(uint16_t, lo);
+    // four rows of one k per thread; ldD is a multiple of 4
+    const int r4 = 4 * (threadIdx.x & (DS_ROWS / 4 - 1));
+#pragma unroll
+    for (int kk = threadIdx.x / (DS_ROWS / 4); kk < 64; kk += 256 / (DS_ROWS / 4)) {
+        if (k0 + kk >= k_pad || r0 + r4 >= ldD) continue;
+        short4v h4, l4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float y = tile[r4 + e][kk];
+            y = fminf(fmaxf(y, -60000.f), 60000.f);
+            const _Float16 h = (_Float16)y;
+            const _Float16 lo = (_Float16)(y - (float)h);
+            h4[e] = __builtin_bit_cast(short, h);
+            l4[e] = __builtin_bit_cast(short, lo);
+        }
+        *reinterpret_cast<short4v*>(Dh + int64_t(k0 + kk) * ldD + r0 + r4) = h4;
+        *reinterpret_cast<short4v*>(Dl + int64_t(k0 + kk) * ldD + r0 + r4) = l4;
     }
 }
 
@@ -633,8 +665,9 @@ onecomp_status split_left_operand(const float* src, int64_t ld_src, int64_t d_ou
                                   Scalars* sc, Scalars* other, uint16_t* Dh, uint16_t* Dl, hipStream_t stream) {
     const int64_t ldD = split_update_ld(d_out);
     const int k_pad = (k_count + 31) / 32 * 32;
-    hipLaunchKernelGGL(jq_dsplit_kernel, dim3(unsigned(ceil_div(k_pad, 64)), unsigned(ceil_div(ldD, 64))), dim3(256), 0,
-                       stream, src, ld_src, int(d_out), k_count, k_pad, d, sc, other, Dh, Dl, ldD);
+    const int vec = k_count % 4 == 0 && ld_src % 4 == 0 && (uintptr_t(src) | uintptr_t(d)) % 16 == 0;
+    hipLaunchKernelGGL(jq_dsplit_kernel, dim3(unsigned(ceil_div(k_pad, 64)), unsigned(ceil_div(ldD, DS_ROWS))), dim3(256),
+                       0, stream, src, ld_src, int(d_out), k_count, k_pad, d, sc, other, Dh, Dl, ldD, vec);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
 }
@@ -681,12 +714,8 @@ onecomp_status jointq_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, i
     // left operand rows [row0, row0 + pad32(k_count)) of the D buffers from src[:, 0 .. k_count), columns c_first ..
     auto dsplit = [&](const float* src, int64_t ld_src, int k_count, int c_first, int row0, Scalars* sc,
                       Scalars* other) -> onecomp_status {
-        const int k_pad = pad32(k_count);
-        hipLaunchKernelGGL(jq_dsplit_kernel, dim3(unsigned(ceil_div(k_pad, 64)), unsigned(ceil_div(ldD, 64))), dim3(256), 0,
-                           stream, src, ld_src, int(d_out), k_count, k_pad, w.d + c_first, sc, other,
-                           w.Dh + int64_t(row0) * ldD, w.Dl + int64_t(row0) * ldD, ldD);
-        ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
+        return split_left_operand(src, ld_src, d_out, k_count, w.d + c_first, sc, other, w.Dh + int64_t(row0) * ldD,
+                                  w.Dl + int64_t(row0) * ldD, stream);
     };
     // Gm~[:, c_lo .. c_hi) += (rows row0 .. of D)^T A~[u0 .. u0 + pad32(k_count), c_lo .. c_hi)
     auto update_to = [&](float* C, int row0, int k_count, int u0, int c_lo, int c_hi,
@@ -695,6 +724,12 @@ onecomp_status jointq_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, i
     };
     auto update = [&](int row0, int k_count, int u0, int c_lo, int c_hi, const Scalars* sc) -> onecomp_status {
         return update_to(w.Gm, row0, k_count, u0, c_lo, c_hi, sc);
+    };
+    // the same for the columns on both sides of [h0, h1), in one launch
+    auto update_around = [&](float* C, int k_count, int u0, int c_lo, int h0, int h1, int c_hi,
+                             const Scalars* sc) -> onecomp_status {
+        return split_update_around(C, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, sc, 0, pad32(k_count), u0, c_lo, h0, h1,
+                                   c_hi, stream);
     };
     if ((st = dsplit(w.R, d_in, int(d_in), 0, 0, w.sc, nullptr)) != ONECOMP_OK) return st;
     if ((st = fill_zero(w.Gm, d_out * d_in / 4, stream)) != ONECOMP_OK) return st;
@@ -751,8 +786,8 @@ onecomp_status jointq_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, i
                 // all other columns once per super-block
                 if ((st = dsplit(w.dR, v.ldr, (t1 - t0) * G, t0 * G, 0, sc_far, w.sc + 3 + ((n_sb + 1) & 1))) != ONECOMP_OK)
                     return st;
-                if ((st = update(0, (t1 - t0) * G, t0 * G, 0, t0 * G, sc_far)) != ONECOMP_OK) return st;
-                if ((st = update(0, (t1 - t0) * G, t0 * G, t1 * G, int(d_in), sc_far)) != ONECOMP_OK) return st;
+                if ((st = update_around(w.Gm, (t1 - t0) * G, t0 * G, 0, t0 * G, t1 * G, int(d_in), sc_far)) != ONECOMP_OK)
+                    return st;
             }
     } else {
         // A group spans n_b blocks of 128 columns.  Visit of group g: a = (A_gg + lam I) u for the whole group by one
@@ -792,8 +827,8 @@ onecomp_status jointq_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, i
                         }
                         if ((st = dsplit(w.dR, v.ldr, sb1 - sb0, sb0, 0, sc_far, w.sc + 3 + ((n_sb + 1) & 1))) != ONECOMP_OK)
                             return st;
-                        if ((st = update_to(w.Am, 0, sb1 - sb0, sb0, g0, sb0, sc_far)) != ONECOMP_OK) return st;
-                        if ((st = update_to(w.Am, 0, sb1 - sb0, sb0, sb1, g0 + G, sc_far)) != ONECOMP_OK) return st;
+                        if ((st = update_around(w.Am, sb1 - sb0, sb0, g0, sb0, sb1, g0 + G, sc_far)) != ONECOMP_OK)
+                            return st;
                     }
                     hipLaunchKernelGGL(jq_scan_end_kernel, dim3(unsigned(ceil_div(d_out, 256))), dim3(256), 0, stream,
                                        int(d_out), w.flags);

@@ -965,6 +965,7 @@ struct TrailArgs {
     int d_out, ldD, d_in;
     int ek, K, u0, c0, c1;     // K % 32 == 0, c0 % 8 == 0, c1 % 8 == 0
     int n_mt, n_nt, chunk;
+    int n_nt0, h0, h1;         // not FROM_ZERO: the first n_nt0 column tiles cover [c0, h0), the others [h1, c1)
 };
 
 // FROM_ZERO: the accumulators start at zero and the product is added to the tile of C once, at the end, with one
@@ -976,12 +977,13 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     int mt_, nt_;
     if (!plan::trail_tile(bid, a.chunk, a.n_mt, a.n_nt, mt_, nt_)) return;
     const int m0 = mt_ * TM;
-    const int n0 = a.c0 + nt_ * TN;
+    const bool beyond = !FROM_ZERO && nt_ >= a.n_nt0;
+    const int n0 = beyond ? a.h1 + (nt_ - a.n_nt0) * TN : a.c0 + nt_ * TN;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave >> 1, wc = wave & 1;
-    const int d_out = a.d_out, c1 = a.c1;
+    const int d_out = a.d_out, c1 = FROM_ZERO || beyond ? a.c1 : a.h0;
     const int64_t d_in = a.d_in;
     const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)tl));
 
@@ -1426,7 +1428,13 @@ size_t sweep_workspace_bytes(int64_t d_out, int64_t d_in, int block) {
 onecomp_status split_update(float* C, int64_t d_out, int64_t d_in, const uint16_t* Dh, const uint16_t* Dl, int64_t ldD,
                             const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int ek, int K, int u0, int c0,
                             int c1, hipStream_t stream) {
-    if (c1 <= c0 || K <= 0) return ONECOMP_OK;
+    return split_update_around(C, d_out, d_in, Dh, Dl, ldD, Bh, Bl, sc, ek, K, u0, c0, c1, c1, c1, stream);
+}
+
+onecomp_status split_update_around(float* C, int64_t d_out, int64_t d_in, const uint16_t* Dh, const uint16_t* Dl,
+                                   int64_t ldD, const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int ek, int K,
+                                   int u0, int c0, int h0, int h1, int c1, hipStream_t stream) {
+    if ((h0 <= c0 && c1 <= h1) || K <= 0) return ONECOMP_OK;
     static std::atomic<uint64_t> lds_ok{0};
     if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<false>), int(tg::LDS_BYTES), lds_ok) != ONECOMP_OK)
         return ONECOMP_ERR_HIP;
@@ -1435,7 +1443,9 @@ onecomp_status split_update(float* C, int64_t d_out, int64_t d_in, const uint16_
     t.d_out = int(d_out); t.ldD = int(ldD); t.d_in = int(d_in);
     t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
     t.n_mt = int(ceil_div(d_out, tg::TM));
-    t.n_nt = int(ceil_div(c1 - c0, tg::TN));
+    t.h0 = h0; t.h1 = h1;
+    t.n_nt0 = h0 > c0 ? int(ceil_div(h0 - c0, tg::TN)) : 0;
+    t.n_nt = t.n_nt0 + (c1 > h1 ? int(ceil_div(c1 - h1, tg::TN)) : 0);
     t.chunk = int(ceil_div(int64_t(t.n_mt) * t.n_nt, 8));
     hipLaunchKernelGGL(trailing_kernel<false>, dim3(unsigned(t.chunk * 8)), dim3(256), tg::LDS_BYTES, stream, t);
     ONECOMP_CHECK_LAUNCH();

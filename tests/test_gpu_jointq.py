@@ -155,6 +155,18 @@ def test_jointq_smallest_shapes(bits, G, d_out, d_in, act, lam):
     _run(*r[:6], bits, G, lam=lam, n_pass=2, max_scans=3, perm=perm)
 
 
+@pytest.mark.parametrize("G,d_out,d_in", [
+    (48, 40, 1440),     # three super-blocks of 480 columns: neither side of the middle one is whole 256-column tiles
+    (128, 33, 1152),    # a last super-block of one group: nothing to its right
+])
+def test_jointq_far_columns_on_both_sides(G, d_out, d_in):
+    """The far update of a super-block takes the columns before and behind it in one launch; two passes, so that the
+    columns before it matter."""
+    _announce(f"jointq both sides g{G} {d_out}x{d_in}")
+    r = _start(d_out, d_in, 4, G, seed=600 + G, start="gptq")
+    _run(*r[:6], 4, G, n_pass=2, max_scans=3)
+
+
 def test_jointq_group_with_one_code_left_is_not_emptied():
     """2-bit symmetric grid, groups of 16: one row reaches a group with a single code away from the zero-point.  The
     move that would empty it has c' = 0 and N = 0 in exact arithmetic and rounding noise in fp32; it is no candidate
