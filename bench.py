@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # L2 <-> fabric bytes per call from rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a plain 4 GiB copy), taken with
 # `python bench.py --phase gram|sweep` under rocprofv3 --pmc; see profiles/c3b_hbm_traffic_pmc.md for the commands
 GRAM_TRAFFIC_C3B = 69.3e9     # 68.1 GB fetched + 1.2 GB written per accumulate call (384 x 256 tiles, paced launches)
-SWEEP_TRAFFIC_C3B = 13.6e9
+SWEEP_TRAFFIC_C3B = 13.3e9
 
 
 def sweep_model_bytes_b128(d_out, d_in, B, G, w_bytes):
