@@ -289,6 +289,21 @@ ONECOMP_HD bool trail_tile(int bid, int chunk, int n_mt, int n_nt, int& mt, int&
     return true;
 }
 
+// ---- sweep: the feedback sums of a panel workgroup's `rows` rows, read from the working copy into MFMA accumulators:
+// lane `lane`, register r of row tile mt, column col; byte offsets from the first of the rows.  A buffer load's scalar
+// offset is no part of its bounds check, so only whole workgroups (rows == PANEL_ROWS) may step through the rows with it;
+// in a short one the row is part of the lane's offset, and rows past the end read the last one again.
+constexpr int PANEL_ROWS = 64;
+struct FeedbackOffset {
+    uint32_t lane, scalar;
+};
+template <bool WHOLE>
+ONECOMP_HD FeedbackOffset panel_feedback_offset(int rows, int d_in, int lane, int mt, int r, int col) {
+    const int lane_row = (lane >> 5) * 4, row = mt * 32 + (r / 4) * 8 + (r % 4);
+    if (WHOLE) return {uint32_t(lane_row * d_in + col) * 4, uint32_t(row) * uint32_t(d_in) * 4};
+    return {uint32_t(imin(lane_row + row, rows - 1) * d_in + col) * 4, 0u};
+}
+
 // ---- sweep: width of a super-block.  512 columns; for groups wider than a 128-column block that are not the whole
 // row, the largest of 512 / 384 / 256 / 128 that divides the group, so that a group is a run of whole super-blocks.
 inline int sweep_superblock_width(int group_size, int64_t d_in) {

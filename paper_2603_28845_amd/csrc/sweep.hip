@@ -49,7 +49,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 constexpr int SB = 128;        // lazy-batch block
 constexpr int SBIG = 512;      // super-block: columns beyond it are updated once per 512 columns
-constexpr int ROWS = 64;       // rows per workgroup of the panel kernel
+constexpr int ROWS = plan::PANEL_ROWS;   // rows per workgroup of the panel kernel
 constexpr int SP = SB + 1;     // LDS pitch (floats) of row tiles: lane l reading column c hits bank (l + c) % 32
 
 // ------------------------------------------------------------------------------------------
@@ -346,20 +346,24 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
         {
             float16v cf[2], acc[2];
             {
-                // one lane offset and a scalar one per row: 32 addresses in registers would be kept for the whole sweep.
-                // Rows past d_out: outside the descriptor, zeros
-                const int rows = min(ROWS, a.d_out - r0);
+                // Whole workgroups: one lane offset and a scalar one per row (32 addresses in registers would be kept for
+                // the whole sweep).  In a short one rows past d_out read the last row: see panel_feedback_offset.
+                const int rows = min(ROWS, a.d_out - r0), col = j0 + 32 * bw + (blane & 31);
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                     const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0, int(rows * d_in * 4), 0x00020000);
-                const uint32_t vo = uint32_t((blane >> 5) * 4 * int(d_in) + j0 + 32 * bw + (blane & 31)) * 4;
+                auto load = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
+                    for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        cf[mt][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                            rsrc, vo, uint32_t(mt * 32 + (r / 4) * 8 + (r % 4)) * uint32_t(d_in) * 4, 0));
-                        acc[mt][r] = 0.f;
-                    }
+                        for (int r = 0; r < 16; ++r) {
+                            const plan::FeedbackOffset o =
+                                plan::panel_feedback_offset<decltype(whole)::value>(rows, int(d_in), blane, mt, r, col);
+                            cf[mt][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o.lane, o.scalar, 0));
+                            acc[mt][r] = 0.f;
+                        }
+                };
+                if (rows == ROWS) load(std::true_type{});
+                else load(std::false_type{});
             }
             if (b > 0)
             {

@@ -224,6 +224,23 @@ static void check_trailing(int d_out, int n_cols) {
     REQUIRE(int(seen.size()) == n_mt * n_nt, "trailing %d x %d: %zu of %d tiles", d_out, n_cols, seen.size(), n_mt * n_nt);
 }
 
+// feedback sums of a panel workgroup: every value read lies in the workgroup's own rows, whatever the buffer's bounds check
+// makes of the scalar offset; rows past the last one read it again; only whole workgroups use the scalar offset
+static void check_panel_feedback(int rows, int d_in) {
+    for (int col : {0, 31, d_in - 1})
+        for (int lane = 0; lane < 64; ++lane)
+            for (int mt = 0; mt < 2; ++mt)
+                for (int r = 0; r < 16; ++r) {
+                    const FeedbackOffset o = rows == PANEL_ROWS ? panel_feedback_offset<true>(rows, d_in, lane, mt, r, col)
+                                                                : panel_feedback_offset<false>(rows, d_in, lane, mt, r, col);
+                    const int row = imin(mt * 32 + (r / 4) * 8 + (lane / 32) * 4 + r % 4, rows - 1);
+                    REQUIRE(int64_t(o.lane) + o.scalar == (int64_t(row) * d_in + col) * 4, "panel rows %d d_in %d lane %d register %d of %d",
+                            rows, d_in, lane, r, mt);
+                    REQUIRE(rows == PANEL_ROWS || o.scalar == 0, "panel rows %d: scalar offset %u", rows, o.scalar);
+                    REQUIRE(int64_t(o.lane) + 4 <= int64_t(rows) * d_in * 4, "panel rows %d: lane offset %u", rows, o.lane);
+                }
+}
+
 int main() {
     const int n_cus = 256;
 #ifdef PLANNER_CHECK_THIN
@@ -263,6 +280,8 @@ int main() {
     }
     for (int d_out : {1, 7, 64, 128, 129, 1000, 4096, 8192, 14336, 28672})
         for (int cols = 8; cols <= 28672; cols = cols < 2048 ? cols + 8 : cols + 512) check_trailing(d_out, cols);
+    for (int rows = 1; rows <= PANEL_ROWS; ++rows)
+        for (int d_in : {128, 2048, 65408}) check_panel_feedback(rows, d_in);
     // super-block widths: a wide group is a run of whole super-blocks, each a run of whole 128-column blocks
     for (int G = 16; G <= 32768; G += 16) {
         for (int64_t d_in : {int64_t(G), int64_t(2) * G, int64_t(3) * G}) {
