@@ -18,8 +18,10 @@ HIPCC_FLAGS = [
 ]
 # Per-source extras.  sweep.hip: keep MFMA accumulators in the architectural VGPRs.  With the 512-register budget
 # of a one-wave-per-SIMD kernel the compiler otherwise moves them to AGPRs and then serializes the loads that
-# initialize them (one wait per load), which more than doubles the time of a trailing-update tile.
-EXTRA_FLAGS = {"sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# initialize them (one wait per load), which more than doubles the time of a trailing-update tile.  Loops begin on 32
+# bytes: the scale search's takes 3 to 4 % longer where the code in front of it happens to shift it (421 x 5120 in groups
+# of 32: 4143 us a sweep aligned, 4290 and 4333 at bytes 12 and 20 of 32).
+EXTRA_FLAGS = {"sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-falign-loops=32"]}
 
 
 def _hipcc() -> str:
