@@ -195,7 +195,9 @@ onecomp_status onecomp_hessian_factor_form(const float* H, int64_t d_in, float d
  * across blocks as (w_j - w^_j) * (U_jk / U_jj) with both factors rounded to 22 significant bits: two fp16 halves
  * after an exact power-of-two scaling taken from max |W| and max |U_jk / U_jj|, fp32 accumulation) and added to c
  * once.  A residual above 8 max|W|, which no sweep of a sane layer produces, would saturate on its way into the fp16
- * halves: `loss` then comes back as +infinity.
+ * halves: `loss` then comes back as +infinity.  So it does when W holds a NaN or an infinity: that row is lost from there
+ * on (an infinite weight: from the first column of its group; a NaN does not count for its group's range), the columns in
+ * front of it keep their codes.
  *
  *   W          [d_out x d_in] row-major (dense, stride d_in), dtype w_dtype, ORIGINAL column order. Read only.
  *   U          [d_in x d_in] fp32, as written by onecomp_hessian_factor. Read only.

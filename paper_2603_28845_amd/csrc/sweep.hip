@@ -643,13 +643,13 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
             };
             auto pin = [](double& v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); };   // here, in this order
             // The sequential part.  Row j of the inner block's U triangle (this lane's 8 columns, divided by U_jj) is read two
-            // steps ahead; it is zero up to column j, so a finished register keeps the value that was quantized.
+            // steps ahead; it is zero up to column j, so a finished register keeps the value that was quantized (but see below).
             // One wave per SIMD has nothing else to cover the chain of a step (broadcast, nine dependent fp64 operations,
             // the update of the next column's register), so the other seven updates of the step before are issued between its
             // operations, in this order: left alone, the compiler puts them in a block behind the chain (169 cycles a
             // column), or each at its register's next use.
+            const double* const ud = sUd + (jb >> 5) * UD_SLICES * 8;
             {
-                const double* const ud = sUd + (jb >> 5) * UD_SLICES * 8;
                 double2 u[3][4];
                 auto read_row = [&](auto jc, double2(&dst)[4]) __attribute__((always_inline)) {
                     constexpr int j = decltype(jc)::value, g = j / 8;
@@ -716,38 +716,80 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
                 const bool first = GB == 16 && sl < 2;
                 const double sq = first ? s_first : s, zq = first ? z_first : z;
                 const double rsq = GB == 16 ? 1.0 / sq : rs;
-                const float sf = float(sq);
-                float hat[8];
-                uint32_t codes[2] = {0, 0};
-                short8v fh, fl;
+                float err[8];
+                uint32_t codes[2];
+                double loss;
+                bool big;
+                auto settle = [&]() __attribute__((always_inline)) {
+                    codes[0] = codes[1] = 0;
+                    loss = lossacc;
+                    big = false;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    double d;
-                    const double r = quantize(w[i], sq, rsq, zq, d);
-                    const double e = r * sRd[jb + 8 * sl + i];
-                    lossacc = __builtin_fma(e, e, lossacc);
-                    crow[i] = float(e);
-                    codes[i / 4] |= uint32_t(int(d + zq)) << (8 * (i % 4));
-                    hat[i] = sf * float(d);
-                    float x = -float(DIRECT ? __builtin_fma(-sq, d, double(w0v[i])) : r) * f_d;
-                    saturated |= row_ok && !(fabsf(x) <= 60000.f);
-                    x = fminf(fmaxf(x, -60000.f), 60000.f);
-                    const _Float16 h = (_Float16)x;
-                    const _Float16 l = (_Float16)(x - (float)h);
-                    fh[i] = __builtin_bit_cast(short, h);
-                    fl[i] = __builtin_bit_cast(short, l);
-                    pair[i] = uint32_t(uint16_t(fh[i])) | (uint32_t(uint16_t(fl[i])) << 16);
+                    for (int i = 0; i < 8; ++i) {
+                        double d;
+                        const double r = quantize(w[i], sq, rsq, zq, d);
+                        const double e = r * sRd[jb + 8 * sl + i];
+                        loss = __builtin_fma(e, e, loss);
+                        err[i] = float(e);
+                        codes[i / 4] |= uint32_t(int(d + zq)) << (8 * (i % 4));
+                        float x = -float(DIRECT ? __builtin_fma(-sq, d, double(w0v[i])) : r) * f_d;
+                        big |= !(fabsf(x) <= 60000.f);
+                        x = fminf(fmaxf(x, -60000.f), 60000.f);
+                        const _Float16 h = (_Float16)x;
+                        const _Float16 l = (_Float16)(x - (float)h);
+                        pair[i] = uint32_t(__builtin_bit_cast(uint16_t, h)) | (uint32_t(__builtin_bit_cast(uint16_t, l)) << 16);
+                    }
+                };
+                settle();
+                // A residual that is not finite (an infinite weight or a NaN) times U's zero has also reached the columns in
+                // front of it, whose codes are decided: the wave then takes its rows through the inner block again, column by
+                // column from where they began, and spares finished columns.
+                if (__builtin_expect(__any(!(loss < __builtin_inf())), 0)) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) w[i] = double(w0v[i]) + double(crow[i]);
+#pragma unroll 1
+                    for (int j = 0; j < IB; ++j) {   // w turns: column j is in w[0] of slice g
+                        const int g = j >> 3, jr = j & 7;
+                        const double sg = GB == 16 && g < 2 ? s_first : s, zg = GB == 16 && g < 2 ? z_first : z;
+                        const double rsg = GB == 16 ? 1.0 / sg : rs;
+                        double d;
+                        const double r = quantize(__shfl(w[0], (lane & ~3) + g, 64), sg, rsg, zg, d);
+                        const double* const p = ud + ud_first(g) + (sl - g) * 8 + jr * (4 - g) * 8;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            if (sl > g || (sl == g && i > 0 && jr + i < 8)) w[i] = __builtin_fma(-r, p[(jr + i) & 7], w[i]);
+                        const double w0 = w[0];
+#pragma unroll
+                        for (int i = 0; i < 7; ++i) w[i] = w[i + 1];
+                        w[7] = w0;
+                    }
+                    settle();
                 }
+                lossacc = loss;
+                saturated |= row_ok && big;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) crow[i] = err[i];
                 if (row_ok) {
                     uint32_t* const qp = reinterpret_cast<uint32_t*>(a.Q + int64_t(grow) * d_in + j0 + jb + 8 * sl);
                     qp[0] = codes[0];
                     qp[1] = codes[1];
                     if (a.W_hat) {
                         float* const hp = a.W_hat + int64_t(grow) * d_in + j0 + jb + 8 * sl;
+                        const float sf = float(sq), zf = float(zq);
 #pragma unroll
-                        for (int h = 0; h < 2; ++h)
-                            *reinterpret_cast<float4v*>(hp + 4 * h) = float4v{hat[4 * h], hat[4 * h + 1], hat[4 * h + 2], hat[4 * h + 3]};
+                        for (int h = 0; h < 2; ++h) {
+                            float4v hat;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) hat[e] = sf * (float((codes[h] >> (8 * e)) & 255u) - zf);
+                            *reinterpret_cast<float4v*>(hp + 4 * h) = hat;
+                        }
                     }
+                }
+                short8v fh, fl;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    fh[i] = short(uint16_t(pair[i]));
+                    fl[i] = short(uint16_t(pair[i] >> 16));
                 }
                 // MFMA A-operand fragments for this workgroup's own near updates: lane L of k-step ks, row tile mt holds
                 // row mt*32 + L%32, columns ks*16 + 8 (L/32) + 0..7; rows past d_out hold copies of the last row

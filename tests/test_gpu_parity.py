@@ -806,6 +806,35 @@ def test_sweep_degenerate_and_one_signed_groups():
 
 
 # ------------------------------------------------------------------------------ end to end ---
+@pytest.mark.parametrize("value,at,lost,G,form,dtype", [
+    # a NaN is no part of its group's range: the columns in front of it stay
+    (float("nan"), 52, 52, 16, "inverse", torch.float32), (float("nan"), 33, 33, 16, "block", torch.bfloat16),
+    (float("nan"), 95, 95, 32, "inverse", torch.bfloat16), (float("nan"), 170, 170, 64, "block", torch.float32),
+    (float("nan"), 287, 287, 128, "inverse", torch.float32), (float("nan"), 383, 383, 384, "block", torch.float32),
+    # an infinite weight takes its group with it
+    (float("inf"), 52, 48, 16, "inverse", torch.float32), (float("-inf"), 63, 48, 16, "block", torch.bfloat16),
+    (float("inf"), 40, 32, 32, "inverse", torch.bfloat16),
+])
+def test_sweep_columns_before_a_weight_that_is_not_finite(value, at, lost, G, form, dtype):
+    """What a row holds in front of a NaN or an infinite weight, in the same 32 columns too, is what it holds with an
+    ordinary weight in that place; other rows are not touched by a NaN.  The loss says that something is lost."""
+    _announce(f"sweep {value} at {at} g{G} {form} {dtype}")
+    d_out, d_in, rows = 70, 384, [3, 37, 69]
+    W, U32, F32, _ = _layer_block(d_out, d_in, 1000, 77, dtype)
+    F = F32 if form == "block" else U32
+    W[rows, at] = 0.0
+    ref = og.onecomp_quantize_layer(W, F, 4, G, form=form)
+    W[rows, at] = value
+    out = og.onecomp_quantize_layer(W, F, 4, G, form=form)
+    torch.cuda.synchronize()
+    n_g = (lost + G - 1) // G   # groups whose grid is fixed before
+    for r in range(d_out):
+        cols, groups = (lost, n_g) if r in rows else (d_in, d_in // G) if value != value else (0, 0)
+        for k, n in (("Q_codes", cols), ("W_hat", cols), ("scales", groups), ("zeros", groups)):
+            assert torch.equal(out[k][r, :n], ref[k][r, :n]), (k, r)
+    assert float(out["loss"].item()) == float("inf")
+
+
 def test_end_to_end_c1():
     cfg = synth.CONFIGS["c1"]
     _announce("end to end c1: accumulate -> factor -> quantize, all on the GPU, against the oracle end to end")
