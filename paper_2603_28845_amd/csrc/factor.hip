@@ -278,7 +278,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ int packed(int I, int J) { return (I * (I + 1) / 2 + J) * (SBW * SBW); }
 
 // The leaf of potrf_body again, on the sub-block D in LDS, where a pivot was not positive: every such pivot is replaced by 1
-// and the first one of the factorization left in *info.  Returns D_i, and Z = Lh^-1 in x.
+// and the first one of the factorization left in *info.  Returns D_i, and Z = Lh^-1 in x.  Columns are scaled by the refined
+// reciprocal as there, not divided: an infinite pivot leaves NaN, and so a pivot that is reported, by either.
 __device__ __forceinline__ double leaf_with_bad_pivots(double* D, int i, int lk, double (&x)[4], int32_t* info, int row0) {
     double my_d = 1.0;
     int bad_at = -1;
@@ -292,7 +293,8 @@ __device__ __forceinline__ double leaf_with_bad_pivots(double* D, int i, int lk,
             p = 1.0;
         }
         if (i == j) my_d = p;
-        const double nm = i > j ? -(D[i * SBP + j] / p) : 0.0;
+        const double y = __builtin_amdgcn_rcp(p), t = -(D[i * SBP + j] * y);
+        const double nm = i > j ? __builtin_fma(t, __builtin_fma(-p, y, 1.0), t) : 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int c = 4 * k + lk;

@@ -556,6 +556,18 @@ def test_factor_bad_pivot(at, value):
     assert torch.equal(U, want)
 
 
+@pytest.mark.parametrize("d_in", [16, 272])
+def test_factor_infinite_diagonal(d_in):
+    """One infinite entry makes the damping and with it every diagonal entry infinite: nothing can be factored.  The column
+    behind the first pivot is 0 times the reciprocal of infinity as the refinement has it, NaN, and so is the next pivot."""
+    _announce(f"factor infinite diagonal d_in={d_in}")
+    H = torch.eye(d_in, device=DEV)
+    H[3, 3] = float("inf")
+    _, _, info = og.onecomp_hessian_factor(H, 0.01)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 2
+
+
 def test_factor_dead_channel_and_not_posdef():
     _announce("factor dead channel / not positive definite")
     H32 = _oracle_H32(256, 900, seed=12)
