@@ -16,7 +16,7 @@
 //     order that walks bands of 4 tile rows column by column.  The 32 workgroups that share an
 //     XCD's L2 at any time then cover a compact 4 x 8 patch of tiles (12 X panels, not 64).  A wide layer is
 //     launched one round of tiles (one per CU) at a time, so that those 32 also stay together along the tokens.
-//   * calls of few tokens: 128 x 128 tiles, several per CU (few_tokens_bf16); narrow layers: 64 x 64 tiles whose tokens
+//   * calls of few tokens: 128 x 128 tiles, several per CU (few_tokens_bf16, staged_bf16); narrow layers: 64 x 64 tiles whose tokens
 //     sixteen waves share out (split_bf16).
 //   * fp32 path (small layers): v_mfma_f32_32x32x2_f32, products in fp32; 32- or 64-wide tiles whose tokens eight waves
 //     share out, 128-wide tiles for wide layers with few tokens (f32_tile).
@@ -1257,6 +1257,13 @@ bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
     return n_tokens <= 4096 && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
 }
 
+// ... and the smallest of them the register-staged kernel, which has no ring to fill.  us of a call, staged : RingSmall:
+//   d_in   64,  16 tokens: 11.8 : 12.1;  64: 12.6 : 12.6;  128: 13.4 : 13.3
+//   d_in 1024,  16 tokens: 15.3 : 15.6;  64: 15.8 : 16.0;  128: 16.7 : 16.5;  200: 17.9 : 17.4
+//   d_in 4096,   1 token:  36.6 : 38.2;  64: 38.5 : 38.6;  128: 40.9 : 39.3;  200: 43.8 : 40.5
+//   d_in 8192,  64 tokens: 80.7 : 82.3
+bool staged_bf16(int64_t n_tokens, int64_t d_in) { return n_tokens <= 64 && few_tokens_bf16(n_tokens, d_in, false); }
+
 GramShape choose_shape(int64_t d_in, int64_t n_tokens, int n_cus, size_t ws_bytes) {
     const int64_t n256 = ceil_div(d_in, 256), n128 = ceil_div(d_in, 128), n384 = ceil_div(d_in, 384);
     const int64_t big = n256 * (n256 + 1) / 2;
@@ -1292,7 +1299,8 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
                                     size_t ws_bytes, hipStream_t stream, GramPlanInfo* info) {
     float* ws = static_cast<float*>(wsv);
     if (info) *info = GramPlanInfo{128, 128, 0};
-    // The other kernels need 32-bit byte offsets inside a step of tokens
+    // The register-staged kernel takes the smallest calls, rows too far apart for the 32-bit byte offsets that the others
+    // have inside a step of tokens, and narrow layers when a shape of wide ones is forced
     const bool far_rows = ldx * 64 >= (int64_t(1) << 31);
     if (!far_rows && forced_shape() < 0) {
         if (split_bf16(n_tokens, d_in)) {
@@ -1300,13 +1308,13 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
             *info = GramPlanInfo{B16S_TS, B16S_TS, 1};
             return ONECOMP_OK;
         }
-        if (few_tokens_bf16(n_tokens, d_in, ws_bytes > 0)) {
+        if (!staged_bf16(n_tokens, d_in) && few_tokens_bf16(n_tokens, d_in, ws_bytes > 0)) {
             if (!info) return launch_bf16_ring<RingSmall, false>(X, X, n_tokens, d_in, ldx, ldx, H, nullptr, 0, stream);
             info->launches = 1;
             return ONECOMP_OK;
         }
     }
-    if (far_rows || d_in < 1024) {
+    if (far_rows || d_in < 1024 || (forced_shape() < 0 && staged_bf16(n_tokens, d_in))) {
         if (info) {
             info->launches = 1;
             return ONECOMP_OK;

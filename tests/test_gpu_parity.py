@@ -215,6 +215,8 @@ def test_gram_f32_tiles(d_in, n_tok, pad, tile):
 @pytest.mark.parametrize("d_in,n_tok,pad,tile", [
     (1024, 1, 0, 128), (1040, 33, 16, 128), (2064, 4096, 0, 128), (2048, 4097, 0, 256), (4096, 1788, 0, 128), (4096, 1789, 0, 256),
     (8208, 65, 8, 128),
+    # up to 64 tokens the register-staged kernel, then the ring
+    (16, 64, 0, 128), (16, 65, 0, 128), (1008, 64, 16, 128), (1008, 65, 16, 128), (4112, 64, 0, 128),
 ])
 def test_gram_bf16_few_tokens(monkeypatch, d_in, n_tok, pad, tile):
     monkeypatch.delenv("ONECOMP_GRAM_SHAPE", raising=False)
