@@ -1253,8 +1253,12 @@ bool split_bf16(int64_t n_tokens, int64_t d_in) {
 //   d_in 14336, 512 tokens: 410 : 334;  1024: 478 : 424;  2048: 645 : 601;  4096: 961 : 1103
 // Without a workspace, which callers give for speed, wide layers keep to the line that onecomp_accumulate_describe has told
 // them of, n_tokens d_in^2 < 3e10 (1788 tokens at d_in 4096), and to the larger tiles beyond it.
+// Where 256 x 256 tiles come to four fifths of the CUs or more in one round (d_in 4865 to 5632 on 256) these are as fast from
+// 3584 tokens on: d_in 5120, 2048 tokens: 110 : 100;  3584: 142 : 142;  4096: 153 : 157;  5632, 4096: 166 : 170 (4864: 146 : 128;  5888: 228 : 190).
 bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
-    return n_tokens <= 4096 && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
+    const int64_t n256 = ceil_div(d_in, 256), big = n256 * (n256 + 1) / 2, n_cus = device_cus();
+    const int64_t most = 5 * big >= 4 * n_cus && big <= n_cus ? 3584 : 4096;
+    return n_tokens <= most && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
 }
 
 // ... and the smallest of them the register-staged kernel, which has no ring to fill.  us of a call, staged : RingSmall:

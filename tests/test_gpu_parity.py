@@ -235,6 +235,26 @@ def test_gram_bf16_few_tokens(monkeypatch, d_in, n_tok, pad, tile):
     assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
 
 
+@pytest.mark.parametrize("d_in,n_tok,tile", [
+    (4864, 4096, 128), (4880, 3584, 128), (4880, 3585, 256), (5632, 3584, 128), (5632, 4096, 256), (5648, 4096, 128),
+])
+def test_gram_bf16_few_tokens_where_larger_tiles_fill_the_chip(d_in, n_tok, tile):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("widths for 256 compute units")
+    ws = torch.empty(og.onecomp_accumulate_workspace_bytes(torch.bfloat16, d_in) or 256, dtype=torch.uint8, device=DEV)
+    plan = og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, ws.numel())
+    assert (plan["tile_rows"], plan["tile_cols"]) == (tile, tile)
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    X = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    H = torch.zeros((d_in, d_in), device=DEV)
+    og.onecomp_hessian_accumulate(X, H, workspace=ws)
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd)
+    assert torch.equal(H, H.t())
+    # see test_gram_bf16_few_tokens
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
 def test_gram_big_tiles_bf16():
     # d_in large enough for the direct-to-LDS tile kernels, several stages and a ragged token tail
     _announce("gram d_in=8192 n_tok=1055 bf16 (direct-to-LDS tiles)")
