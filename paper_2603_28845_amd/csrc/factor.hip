@@ -244,18 +244,13 @@ __device__ inline double rsqrt_refined(double p) {
 
 // DPP row_newbcast:J (lane J of every 16-lane row) is the one DPP form of 64-bit instructions; hipcc's builtin offers it
 // for 32 bits only, which costs two moves per broadcast instead of none.  A DPP operand must not have been written by
-// the two instructions before: the compiler does not look into these statements, so they keep that distance themselves
-// (s_nop 1) where the operand is fresh, and are volatile, that is, stay in order.  Where it is not, they rely on
+// the two instructions before: the compiler does not look into these statements, so the broadcast keeps that distance
+// itself (s_nop 1), and they are volatile, that is, stay in order.  The update relies on its operand being older and on
 // the compiler placing no copy of it right in front, which tests/test_factor_isa.py checks in the generated code.
-// c += (lane J of b) * m.  FRESH: b may come from the instruction before.
-template <int J, bool FRESH>
+// c += (lane J of b) * m; b does not come from the two instructions before
+template <int J>
 __device__ __forceinline__ void fma_bcast16(double& c, double b, double m) {
-    if constexpr (FRESH)
-        asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-                     : "+v"(c) : "v"(b), "v"(m), "n"(J));
-    else
-        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-                     : "+v"(c) : "v"(b), "v"(m), "n"(J));
+    asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(c) : "v"(b), "v"(m), "n"(J));
 }
 // value of lane J of every 16-lane row, in all lanes of the row
 template <int J>
@@ -438,7 +433,7 @@ __device__ __forceinline__ void potrf_body(const double* __restrict__ A, double*
             constexpr int j = decltype(jc)::value;
             if constexpr (j + 1 < SBW) {
                 const double nm = __builtin_fma(t, e, t);
-                fma_bcast16<j + 1, false>(r[j + 1], r[j], nm);   // r[j] was last written before p was broadcast
+                fma_bcast16<j + 1>(r[j + 1], r[j], nm);   // r[j] was last written before p was broadcast
                 const double pj = p;
                 p = bcast16<j + 1>(r[j + 1]);
                 y = __builtin_amdgcn_rcp(p);
@@ -450,11 +445,11 @@ __device__ __forceinline__ void potrf_body(const double* __restrict__ A, double*
                 auto updates = [&](auto lo, auto hi, auto zhi) __attribute__((always_inline)) {
                     static_for<decltype(lo)::value, decltype(hi)::value>([&](auto cc) {
                         constexpr int c = decltype(cc)::value;
-                        fma_bcast16<c, false>(r[c], r[j], nm);
+                        fma_bcast16<c>(r[c], r[j], nm);
                     });
                     static_for<0, decltype(zhi)::value>([&](auto kc) {
                         constexpr int k = decltype(kc)::value;
-                        fma_bcast16<j, false>(x[k], x[k], nlh);   // x[k] was last written a pivot ago
+                        fma_bcast16<j>(x[k], x[k], nlh);   // x[k] was last written a pivot ago
                     });
                     __builtin_amdgcn_sched_barrier(0);
                 };
@@ -610,9 +605,10 @@ __device__ __forceinline__ double* wg_lds() {
 }
 
 // ------------------------------------------------------------------------------------------
-// One TM x TN tile (tm, tn) of batch entry z with WR x WC waves; K > 0: an inner range of that length.  128 x 128: 2 x 4 waves of 64 x 32, so that with two
-// workgroups per CU four waves share a SIMD and cover each other's waits.  64 x 64 (2 x 2 waves of 32 x 32) and 128 x 64
-// (4 x 2 of 32 x 32): for launches whose 128-wide tiles would leave CUs idle.
+// One TM x TN tile (tm, tn) of batch entry z with WR x WC waves; K > 0: an inner range of that length.
+// 128 x 128: 2 x 4 waves of 64 x 32, so that with two workgroups per CU four waves share a SIMD and cover each other's
+// waits.  64 x 64 (2 x 2 waves of 32 x 32) and 128 x 64 (4 x 2 of 32 x 32): for launches whose 128-wide tiles would
+// leave CUs idle.
 // The operands are streamed global -> LDS directly (buffer_load ... lds) through a ring of NS slots
 // of SUB parts of RK inner steps each, NS - 1 stages ahead of the MFMAs: no staging registers, no LDS stores, no
 // multiplication by alpha on the way (alpha = +-1 is folded into the accumulators: they start as (beta / alpha) C and the

@@ -49,9 +49,10 @@ ONECOMP_HD void tile_from_rank_band(int v, int n_t, int& ti, int& tk) {
 ONECOMP_HD void tile_from_rank(int v, int n_t, int& ti, int& tk) { tile_from_rank_band<GRAM_BAND>(v, n_t, ti, tk); }
 // ---- factor: the tiles of a trailing update.  The trailing matrix has n_t block columns; a launch updates column 0 (its
 // first tile is the next diagonal block) and the columns 1, 1 + stride, 1 + 2 stride, ...: tiles (tm, tn), tn <= tm < n_t.
-// Workgroup 0 owns tile (0, 0) (and factors it: it has been brought up to date before the launch), the next ones the strided columns, dealt to the XCDs in runs of consecutive ranks (bands
-// of SYRK_BAND of these columns walked row by row: two workgroups per CU, 64 tiles of an XCD in flight, an 8 x 8 patch
-// of them shares 16 operand panels), the last ones the rest of column 0.
+// Workgroup 0 owns tile (0, 0) (and factors it: it has been brought up to date before the launch), the next ones the
+// strided columns, dealt to the XCDs in runs of consecutive ranks (bands of SYRK_BAND of these columns walked row by row:
+// two workgroups per CU, 64 tiles of an XCD in flight, an 8 x 8 patch of them shares 16 operand panels), the last ones the
+// rest of column 0.
 constexpr int SYRK_BAND = 8;
 struct SyrkGrid {
     int n_t, stride, n_c, n_s, chunk, total;   // strided columns and their tiles, ranks per XCD, workgroups
