@@ -39,27 +39,45 @@ static void check_simple_upper(int d_in, int ts) {
 }
 
 // trailing updates of the blocked Cholesky of n_blk blocks: every launch's tiles are owned once and workgroup 0 owns the
-// diagonal tile; over the steps every tile receives the panels 0 .. (its column - 1) once each and in order, and a column
-// is complete when its diagonal block and its panel solve need it
+// diagonal tile, which the panel solve before it has updated; over the steps, lagged launches and the narrow ones behind
+// them, every tile receives the panels 0 .. (its column - 1) once each and in order, and a column is complete when its
+// diagonal block and its panel solve need it
 static void check_syrk_schedule(int n_blk) {
     std::vector<std::vector<int>> done(n_blk);   // done[i][j]: panels that tile (i, j) has received
     for (int i = 0; i < n_blk; ++i) done[i].assign(i + 1, 0);
     int base = 0, lag = syrk_lag(n_blk);
     for (int s = 0; s + 1 < n_blk; ++s) {
         const int next_lag = syrk_lag(n_blk - 2 - s), stride = next_lag == lag ? lag : 1, n_t = n_blk - 1 - s;
-        const SyrkGrid q = syrk_grid(n_t, stride);
-        std::vector<char> seen(size_t(n_t) * n_t, 0);
-        for (int b = 0; b < q.total; ++b) {
-            int tm = -1, tn = -1;
-            if (!syrk_tile(b, q, tm, tn)) continue;
-            REQUIRE(0 <= tn && tn <= tm && tm < n_t, "syrk %d step %d workgroup %d -> (%d, %d)", n_blk, s, b, tm, tn);
-            REQUIRE(b != 0 || (tm == 0 && tn == 0), "syrk %d step %d: workgroup 0 owns (%d, %d)", n_blk, s, tm, tn);
-            REQUIRE(!seen[size_t(tm) * n_t + tn], "syrk %d step %d tile (%d, %d) owned twice", n_blk, s, tm, tn);
-            seen[size_t(tm) * n_t + tn] = 1;
-            const int k0 = tn == 0 ? s : syrk_first_panel(tn, s, lag, base);
+        auto update = [&](int tm, int tn, int k0) {
             int& d = done[s + 1 + tm][s + 1 + tn];
             REQUIRE(d == k0 && k0 <= s, "syrk %d step %d tile (%d, %d): has %d panels, next %d", n_blk, s, tm, tn, d, k0);
             d = s + 1;
+        };
+        if (lag == 1) {
+            update(0, 0, s);   // the panel solve's launch
+            std::vector<char> halves(size_t(n_t) * n_t, 0);
+            for (int b = 1; b < syrk_narrow_grid(n_t, 0); ++b) {
+                int tm = -1, tc = -1;
+                bool inverse = false;
+                if (!syrk_narrow_tile(b, n_t, 0, tm, tc, inverse)) continue;
+                REQUIRE(!inverse && 0 <= tc && tc / 2 <= tm && tm < n_t, "syrk %d step %d workgroup %d -> (%d, %d)", n_blk, s, b, tm, tc);
+                char& h = halves[size_t(tm) * n_t + tc / 2];
+                REQUIRE(!(h & (1 << (tc & 1))), "syrk %d step %d half tile (%d, %d) owned twice", n_blk, s, tm, tc);
+                h |= char(1 << (tc & 1));
+                if (h == 3) update(tm, tc / 2, s);
+            }
+        } else {
+            const SyrkGrid q = syrk_grid(n_t, stride);
+            std::vector<char> seen(size_t(n_t) * n_t, 0);
+            for (int b = 0; b < q.total; ++b) {
+                int tm = -1, tn = -1;
+                if (!syrk_tile(b, q, tm, tn)) continue;
+                REQUIRE(0 <= tn && tn <= tm && tm < n_t, "syrk %d step %d workgroup %d -> (%d, %d)", n_blk, s, b, tm, tn);
+                REQUIRE(b != 0 || (tm == 0 && tn == 0), "syrk %d step %d: workgroup 0 owns (%d, %d)", n_blk, s, tm, tn);
+                REQUIRE(!seen[size_t(tm) * n_t + tn], "syrk %d step %d tile (%d, %d) owned twice", n_blk, s, tm, tn);
+                seen[size_t(tm) * n_t + tn] = 1;
+                update(tm, tn, tn == 0 ? s : syrk_first_panel(tn, s, lag, base));
+            }
         }
         for (int i = s + 1; i < n_blk; ++i)
             REQUIRE(done[i][s + 1] == s + 1, "syrk %d step %d: tile (%d, %d) incomplete", n_blk, s, i, s + 1);

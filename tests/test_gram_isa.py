@@ -4,8 +4,8 @@ and look at the ISA (CPU only).
 The 384 x 256 kernel pins its accumulator tiles through inline-assembly MFMAs, which the compiler's hazard handling
 cannot see: the loop is only correct while the compiler neither spills nor copies an accumulator inside it.
 
-The fp32 kernel whose waves share out the tokens takes what lies behind a run's last token as zero, from the bounds check
-of its buffer loads.  An instruction's scalar offset is no part of that check, so only batches that lie inside the run may
+The fp32 and bf16 kernels whose waves share out the tokens take what lies behind a run's last token as zero, from the
+bounds check of their buffer loads.  An instruction's scalar offset is no part of that check, so only batches that lie inside the run may
 use one."""
 import os
 import re
@@ -74,4 +74,21 @@ def test_f32_runs_check_every_offset_past_the_run(isa, mt, steps):
         assert all(o == "0" for o in first) and all(o == "0" for o in past)
         assert sum(o != "0" for o in inside) == 2 * (steps - 1) * per_step
         pos += 5 * n
+    assert pos == len(loads)
+
+
+def test_bf16_runs_check_every_offset_past_the_run(isa):
+    body = re.search(r"^_ZN\S*gram_bf16_split_kernel\S*:[^\n]*\n(.*?)^\.Lfunc_end", isa, re.S | re.M).group(1)
+    loads = [m.group(1) for m in re.finditer(r"buffer_load_dword v\d+, v\d+, s\[\d+:\d+\], (\S+) offen", body)]
+    assert "buffer_load_dwordx" not in body and len(re.findall("buffer_load", body)) == len(loads)
+    # per kind of tile (one operand on the diagonal, else two), eight tokens per operand: three batches first, three inside
+    # the run, three that may reach past its end
+    assert len(loads) == 9 * 8 * (1 + 2)
+    sizes = (8, 16) if next(i for i, o in enumerate(loads) if o != "0") < 3 * 16 else (16, 8)
+    pos = 0
+    for n in sizes:
+        first, inside, past = loads[pos:pos + 3 * n], loads[pos + 3 * n:pos + 6 * n], loads[pos + 6 * n:pos + 9 * n]
+        assert all(o == "0" for o in first) and all(o == "0" for o in past)
+        assert sum(o != "0" for o in inside) == 3 * (n - n // 8)   # a batch's first token has offset 0
+        pos += 9 * n
     assert pos == len(loads)

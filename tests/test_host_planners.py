@@ -1,8 +1,9 @@
 """The launches' work maps (which tile and which piece of the token axis a workgroup owns, how a Gram call is cut
-into pieces, the sweep's super-block widths, far-update tiles and the rows a panel workgroup reads) are plain integer logic in csrc/planner.hpp, shared
-by kernels and launchers.  tests/planner_check.cpp enumerates them on the host for every supported width (d_in in
-steps of 16 up to 32768, 256 compute units, token counts and workspace sizes around the plan's thresholds) and
-requires that every tile, and every piece of a split tile, is owned exactly once and lies inside the matrix."""
+into pieces, the sweep's super-block widths, far-update tiles and the rows a panel workgroup reads) are plain integer
+logic in csrc/planner.hpp, shared by kernels and launchers.  tests/planner_check.cpp enumerates them on the host for
+every supported width (d_in in steps of 16 up to 32768, 256 compute units, token counts and workspace sizes around the
+plan's thresholds) and requires that every tile, and every piece of a split tile, is owned exactly once and lies inside
+the matrix."""
 import os
 import shutil
 import subprocess
