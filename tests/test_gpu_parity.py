@@ -369,6 +369,30 @@ def test_gram_tile_shapes(monkeypatch, shape, d_in, n_tok, with_ws):
     assert rel_fro(H2.cpu().numpy().astype(np.float64), ref2) <= 1e-5
 
 
+@pytest.mark.parametrize("shape,d_in,n_tok,pad", [
+    # 128 x 128 tiles of the ring with many tokens: ragged edges, odd numbers of steps
+    ("small", 1040, 9001, 16), ("small", 2304, 4999, 0), ("small", 4112, 12345, 8),
+    # narrow layers: the register-staged kernel, whatever the shape
+    ("mid", 16, 4097, 0), ("small", 528, 9001, 16), ("wide", 1008, 333, 8),
+])
+def test_gram_forced_small_tiles(monkeypatch, shape, d_in, n_tok, pad):
+    monkeypatch.setenv("ONECOMP_GRAM_SHAPE", shape)
+    _announce(f"gram {shape} d_in={d_in} n_tok={n_tok} pad={pad}")
+    plan = og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, 0)
+    assert (plan["tile_rows"], plan["tile_cols"]) == (128, 128)
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    wide = torch.full((n_tok + 1, d_in + pad), float("nan"), device=DEV, dtype=torch.bfloat16)
+    wide[:n_tok, :d_in] = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    X = wide[:n_tok, :d_in]
+    H = torch.full((d_in, d_in), 0.5, device=DEV)
+    og.onecomp_hessian_accumulate(X, H)
+    Xd = X.double()
+    ref = 2.0 * (Xd.t() @ Xd) + 0.5
+    assert torch.equal(H, H.t())
+    # see test_gram_bf16_few_tokens
+    assert float((H.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
 def test_gram_schedule_of_the_benchmark_layer(monkeypatch):
     """What the library reports for the call bench.py times: with the workspace the 384 x 256 shape in four whole rounds
     plus one launch of pieces, without it 256 x 256 tiles in six rounds plus the split last round."""
@@ -558,24 +582,71 @@ def test_factor_schedules(d_in):
 
 
 @pytest.mark.parametrize("at", [0, 1, 15, 16, 63, 64, 77, 127, 128, 143, 255, 256, 271])
-@pytest.mark.parametrize("value", [-1.0, float("nan")])
-def test_factor_bad_pivot(at, value):
+def test_factor_bad_pivot(at):
     """A single non-positive pivot at every kind of place: info is its position in the order of the factorization (which
-    runs from the last index), the pivot counts as 1 and everything else is untouched.  (The NaN is put off the diagonal's
-    mean by a damping of zero times it being NaN for every entry, so there only info is asked for: the first pivot.)"""
-    _announce(f"factor bad pivot at {at}: {value}")
+    runs from the last index), the pivot counts as 1 and everything else is untouched."""
+    _announce(f"factor bad pivot at {at}")
     n = 272
     H = torch.eye(n, device=DEV) * 4.0
-    H[n - 1 - at, n - 1 - at] = value
+    H[n - 1 - at, n - 1 - at] = -1.0
     U, _, info = og.onecomp_hessian_factor(H, 0.0)
     torch.cuda.synchronize()
-    if value != value:
-        assert int(info.item()) == 1
-        return
     assert int(info.item()) == at + 1
     want = torch.eye(n, device=DEV) * 0.5
     want[n - 1 - at, n - 1 - at] = 1.0
     assert torch.equal(U, want)
+
+
+def test_factor_nan_diagonal():
+    """A NaN makes the damping and with it every diagonal entry NaN: the first pivot is reported."""
+    _announce("factor NaN on the diagonal")
+    H = torch.eye(272, device=DEV) * 4.0
+    H[100, 100] = float("nan")
+    _, _, info = og.onecomp_hessian_factor(H, 0.0)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 1
+
+
+def _factor_with_bad_pivots(H, lower):
+    """U and info of a dense matrix in 64 bits on the CPU, every pivot that is not positive replaced by 1 (its column is not
+    scaled).  lower: positions in the order of the factorization whose diagonal entry is lowered by twice the pivot that is
+    met there; returns the matrix that this gives, too."""
+    n = len(H)
+    S = H[::-1, ::-1].astype(np.float64)
+    A, L, info = S.copy(), np.zeros((n, n)), 0
+    for j in range(n):
+        if j in lower:
+            d = float(np.float32(A[j, j] - 2.0 * S[j, j]))
+            S[j, j] += d - A[j, j]
+            A[j, j] = d
+        assert abs(S[j, j]) > 0.1          # no pivot near zero: its sign does not hang on rounding
+        p = S[j, j]
+        if p <= 0.0:
+            info, p = info or j + 1, 1.0
+        L[j, j] = p ** 0.5
+        L[j + 1:, j] = S[j + 1:, j] / L[j, j]
+        S[j + 1:, j + 1:] -= np.outer(L[j + 1:, j], L[j + 1:, j])
+    U = np.linalg.inv(L)[::-1, ::-1]
+    return A[::-1, ::-1].astype(np.float32), np.triu(U), info
+
+
+@pytest.mark.parametrize("lower", [
+    (0,), (5, 9), (14, 15), (16,), (63, 64), (77, 200), (127, 128), (255, 256), (261,), (271,),
+])
+def test_factor_bad_pivots_in_a_dense_matrix(lower):
+    """Pivots that are not positive inside a leaf, at its ends, in either half of a block, in later blocks and in the short
+    last one, with everything around them coupled."""
+    _announce(f"factor dense, bad pivots at {lower}")
+    n = 272
+    g = np.random.default_rng(sum(lower) + 1)
+    B = g.standard_normal((n, n))
+    H, ref, want = _factor_with_bad_pivots((4.0 * np.eye(n) + 0.05 * (B + B.T)).astype(np.float32), lower)
+    U, _, info = og.onecomp_hessian_factor(torch.from_numpy(H.copy()).to(DEV), 0.0)
+    torch.cuda.synchronize()
+    assert int(info.item()) == want == min(lower) + 1
+    U = to_f64(U)
+    # rounded once to fp32; 64-bit rounding errors of a few hundred steps, far below that
+    assert np.all(np.abs(U - ref) <= 2.0 ** -24 * np.abs(ref) * 1.01 + 1e-11 * np.abs(ref).max())
 
 
 @pytest.mark.parametrize("d_in", [16, 272])

@@ -63,10 +63,11 @@ def test_crossgram_shapes(d_in, n_tok):
     assert rel_fro(Gxx.cpu().numpy().astype(np.float64), H.cpu().numpy().astype(np.float64)) <= 1e-6
 
 
-@pytest.mark.parametrize("shape", ["wide", "big", "mid"])
+@pytest.mark.parametrize("shape", ["wide", "big", "mid", "small"])
 @pytest.mark.parametrize("d_in,n_tok", [(1040, 515), (2304, 1000), (4096, 300)])
 def test_crossgram_tile_shapes(monkeypatch, shape, d_in, n_tok):
-    """Each tile shape of the cross-Gram kernel (384 x 256, 256 x 256, 128 x 256) on the same inputs."""
+    """Each tile shape of the cross-Gram kernel (384 x 256, 256 x 256, 128 x 256, which it also takes for 128 x 128) on the
+    same inputs."""
     _announce(f"cross-Gram tile shape {shape}: d_in={d_in} n_tok={n_tok}")
     monkeypatch.setenv("ONECOMP_GRAM_SHAPE", shape)
     _, X, Xh = _pair(d_in, n_tok, seed=60 + d_in % 7)
