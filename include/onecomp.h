@@ -115,10 +115,12 @@ onecomp_status onecomp_hessian_accumulate(const void* X, onecomp_dtype x_dtype,
  * a workspace the call may also take 384 x 256 tiles (fewer cache and LDS bytes per flop; their last round always
  * needs the workspace): d_in 14336, 262144 tokens: 46-49 -> 43-46 ms.  Without a workspace only the mirror positions
  * of H can hold a second partial sum, which covers a short last round of wide matrices.  The tile shape is chosen by
- * estimated cost; ONECOMP_GRAM_SHAPE=wide|big|mid|small in the environment forces 384 x 256, 256 x 256, 128 x 256 or 128 x 128 tiles
- * for d_in >= 1024 (testing and tuning; onecomp_accumulate_describe reports the choice).
- * bf16 calls of few tokens for the width (at most 4096, n_tokens d_in^2 < 4e11 with a workspace and 3e10
- * without) take 128 x 128 tiles unless a shape is forced; narrow layers (d_in below 1024 with 256 or more tokens, up to 1360 with 2048 to 12288) 64 x 64 tiles.
+ * estimated cost; ONECOMP_GRAM_SHAPE=wide|big|mid|small in the environment forces 384 x 256, 256 x 256, 128 x 256 or
+ * 128 x 128 tiles for d_in >= 1024 (testing and tuning; onecomp_accumulate_describe reports the choice; the cross-Gram
+ * takes 128 x 256 tiles for the last two).
+ * bf16 calls of few tokens for the width (at most 4096, at most 3584 where 256 x 256 tiles fill the chip, and
+ * n_tokens d_in^2 < 4e11 with a workspace, 3e10 without) take 128 x 128 tiles unless a shape is forced; narrow layers
+ * (d_in below 1024 with 256 or more tokens, up to 1360 with 2048 to 12288) 64 x 64 tiles.
  * A call of fewer than 49152 tokens is one launch, a longer one a launch per round of tiles (one tile per compute unit);
  * ONECOMP_GRAM_ROUND_LAUNCHES=0|1 forces either (tuning).  None of these choices changes what the call computes.
  *   workspace        device scratch or NULL, 256-byte aligned; any size is accepted, the kernel uses what fits

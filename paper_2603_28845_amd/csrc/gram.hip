@@ -16,8 +16,8 @@
 //     order that walks bands of 4 tile rows column by column.  The 32 workgroups that share an
 //     XCD's L2 at any time then cover a compact 4 x 8 patch of tiles (12 X panels, not 64).  A wide layer is
 //     launched one round of tiles (one per CU) at a time, so that those 32 also stay together along the tokens.
-//   * calls of few tokens: 128 x 128 tiles, several per CU (few_tokens_bf16, staged_bf16); narrow layers: 64 x 64 tiles whose tokens
-//     sixteen waves share out (split_bf16).
+//   * calls of few tokens: 128 x 128 tiles, several per CU (few_tokens_bf16, staged_bf16); narrow layers: 64 x 64 tiles
+//     whose tokens sixteen waves share out (split_bf16).
 //   * fp32 path (small layers): v_mfma_f32_32x32x2_f32, products in fp32; 32- or 64-wide tiles whose tokens eight waves
 //     share out, 128-wide tiles for wide layers with few tokens (f32_tile).
 #include "common.hpp"
@@ -1230,13 +1230,16 @@ int forced_shape() {
     if (!strcmp(e, "small")) return int(GramShape::Small);
     return -1;
 }
-// Layers of few tiles, at most one of 64 x 64 per CU, whose tokens are shared out inside the workgroup.  us of a call, the
-// ring kernels (below d_in 1024 and from 4097 tokens on the register-staged one) : this one:
+// Layers of few tiles, at most one of 64 x 64 per CU (of 256), whose tokens are shared out inside the workgroup.  us of a
+// call, the ring kernels (below d_in 1024 and from 4097 tokens on the register-staged one) : this one:
 //   d_in  512,  128 tokens: 18 : 15;  512: 21 : 17;  4096: 55 : 35;  8192: 156 : 66;  65536: 1206 : 320;  262144: 4792 : 1224
-//   d_in 1024,  128 tokens: 18.5 : 16;  1024: 27 : 26;  4096: 62 : 47;  8192: 97 : 66;  12288: 101 : 80;  16384: 105 : 103;  32768: 123 : 179
-//   d_in 1360,  512 tokens: 24 : 22;  1024: 30 : 33;  2048: 45 : 39;  8192: 103 : 70;  12288: 107 : 90;  16384: 111 : 116 (253 tiles)
+//   d_in 1024,  128 tokens: 18.5 : 16;  1024: 27 : 26;  4096: 62 : 47;  8192: 97 : 66;  12288: 101 : 80;  16384: 105 : 103;
+//               32768: 123 : 179
+//   d_in 1360,  512 tokens: 24 : 22;  1024: 30 : 33;  2048: 45 : 39;  8192: 103 : 70;  12288: 107 : 90;
+//               16384: 111 : 116 (253 tiles)
 //   d_in 1536,  2048 tokens: 46 : 70 (300 tiles)
-// Under 256 tokens it gains 3 us and is left out.
+// 1360 is the widest layer measured, not where the gain ends: up to 1408 there are as many tiles.  Under 256 tokens it
+// gains 3 us; such calls are left to the 128 x 128 kernels.
 bool split_bf16(int64_t n_tokens, int64_t d_in) {
     if (d_in < 1024) return n_tokens >= 256;
     return d_in <= 1360 && n_tokens >= 2048 && n_tokens <= 12288;
@@ -1251,10 +1254,12 @@ bool split_bf16(int64_t n_tokens, int64_t d_in) {
 //   d_in 8192,  512 tokens: 135 : 112;  2048: 248 : 205;  4096: 393 : 351;  8192: 608 : 627
 //   d_in 11008, 512 tokens: 283 : 223;  2048: 406 : 374;  4096: 596 : 625
 //   d_in 14336, 512 tokens: 410 : 334;  1024: 478 : 424;  2048: 645 : 601;  4096: 961 : 1103
-// Without a workspace, which callers give for speed, wide layers keep to the line that onecomp_accumulate_describe has told
-// them of, n_tokens d_in^2 < 3e10 (1788 tokens at d_in 4096), and to the larger tiles beyond it.
-// Where 256 x 256 tiles come to four fifths of the CUs or more in one round (d_in 4865 to 5632 on 256) these are as fast from
-// 3584 tokens on: d_in 5120, 2048 tokens: 110 : 100;  3584: 142 : 142;  4096: 153 : 157;  5632, 4096: 166 : 170 (4864: 146 : 128;  5888: 228 : 190).
+// Without a workspace the line is n_tokens d_in^2 < 3e10 (1788 tokens at d_in 4096), as it was for the register-staged
+// kernel and as tests pin it for onecomp_accumulate_describe; this kernel needs no workspace and would be the faster one
+// beyond it as well: d_in 4096, 2048 tokens: 100 : 77;  8192, 1024: 186 : 144;  14336, 512: 410 : 336 (6144, 4096: 195 : 195).
+// Where 256 x 256 tiles come to four fifths of the CUs or more in one round (d_in 4865 to 5632 on 256) these are as fast
+// from 3584 tokens on: d_in 5120, 2048 tokens: 110 : 100;  3584: 142 : 142;  4096: 153 : 157;  5632, 4096: 166 : 170
+// (4864, 4096: 146 : 128;  5888, 4096: 228 : 190).
 bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
     const int64_t n256 = ceil_div(d_in, 256), big = n256 * (n256 + 1) / 2, n_cus = device_cus();
     const int64_t most = 5 * big >= 4 * n_cus && big <= n_cus ? 3584 : 4096;

@@ -228,8 +228,9 @@ __device__ __forceinline__ int mse_search(const double mn, const double mx, cons
     return ibest;
 }
 
-// LDS of a panel workgroup, under 80 KB so that a tile of the far update or a second panel workgroup fits on the CU beside
-// it (matrix pipes under one, vector units under the other):
+// LDS of a panel workgroup.  Inverse form: 79 KB, so that a tile of the far update or a second panel workgroup fits on the CU
+// beside it (matrix pipes under one, vector units under the other).  Block form: 95 KB, so a workgroup, of far tiles too,
+// has its CU to itself.
 //   sU    the block's U off its 32 x 32 diagonal sub-blocks: six sub-blocks, row by row
 //   sUd   the diagonal sub-blocks in fp64, rows divided by their diagonal entries, zeros on and below the diagonal: rows
 //         8 g .. 8 g + 7 hold the slices (8 columns) g .. 3, and behind them zeros for the lanes of finished slices
@@ -243,6 +244,7 @@ constexpr int LDS_UD = 6 * UB * 4, LDS_RD = LDS_UD + (4 * UD_SLICES * 8 + UD_ZER
 constexpr int LDS_UG = LDS_C + ROWS * SP * 4;
 constexpr int panel_lds(bool direct) { return LDS_UG + (direct ? 4 * UB * 4 : 0); }
 static_assert(panel_lds(false) <= 80 * 1024, "a second workgroup fits beside a panel's");
+static_assert(panel_lds(true) <= 160 * 1024, "a CU's LDS");
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_quad(float v) {
