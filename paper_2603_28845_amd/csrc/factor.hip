@@ -16,9 +16,12 @@
 //     of wider ones by recursive doubling over aligned block pairs: for block size s = 128 * 2^l,
 //     V[C,A] = -V[C,C] (L[C,A] V[A,A]); every level is two batched GEMMs, so the whole inverse is
 //     ~2 log2(n/128) large launches instead of n/128 skinny ones.
+//   * wide factors (factor_slabs): left-looking over slabs of columns, whose updates, and the inverse's long products, are
+//     taken from 8-bit residues on the integer matrix cores (residue.hip) with no more rounding than in fp64.
 //   * ordering by rank counting (stable, deterministic), no floating-point atomics anywhere.
 #include "common.hpp"
 #include "planner.hpp"
+#include "residue.hpp"
 #include <type_traits>
 
 namespace onecomp {
@@ -890,13 +893,14 @@ __global__ __launch_bounds__(64 * GemmShape<T>::WAVES, 2) void dgemm_kernel(Gemm
 // has brought it up to date) while the other workgroups update the columns that are due.  Takes the
 // single-workgroup factorization off the critical path of every step whose update is longer.
 // A: the whole matrix; the trailing matrix begins at block row and column step + 1 and has `rest` rows.  Step -1, a launch
-// of one workgroup: the first diagonal block.  NARROW: few columns, see plan::syrk_lag.
+// of one workgroup: the first diagonal block.  NARROW: few columns, see plan::syrk_lag; slab_cols > 0: the first slab_cols
+// block columns only.
 template <bool NARROW>
 __global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __restrict__ A, double* __restrict__ V,
                                                                      double* __restrict__ Pn, double* __restrict__ Pk,
                                                                      int n, int step, int rest,
                                                                      int stride, int lag, int base, int inv_cols,
-                                                                     int32_t* __restrict__ info) {
+                                                                     int slab_cols, int32_t* __restrict__ info) {
     const int off = (step + 1) * NB, n_t = (rest + GT - 1) / GT;
     if (blockIdx.x == 0) {
         potrf_body(A, Pk, n, off, min(NB, rest), info, wg_lds());
@@ -904,8 +908,9 @@ __global__ __launch_bounds__(POTRF_THREADS, 4) void syrk_potrf_kernel(double* __
     }
     int tm, tn;   // NARROW: tn counts columns of 64
     bool inverse = false;
-    if (!(NARROW ? plan::syrk_narrow_tile(blockIdx.x, n_t, inv_cols, tm, tn, inverse)
-                 : plan::syrk_tile(blockIdx.x, plan::syrk_grid(n_t, stride), tm, tn)))
+    if (!(!NARROW         ? plan::syrk_tile(blockIdx.x, plan::syrk_grid(n_t, stride), tm, tn)
+          : slab_cols > 0 ? plan::syrk_slab_tile(blockIdx.x, n_t, slab_cols, tm, tn)
+                          : plan::syrk_narrow_tile(blockIdx.x, n_t, inv_cols, tm, tn, inverse)))
         return;
     tm = __builtin_amdgcn_readfirstlane(tm);   // the divisions leave them in vector registers
     tn = __builtin_amdgcn_readfirstlane(tn);
@@ -1018,9 +1023,11 @@ __device__ __forceinline__ void panel_body(const double* __restrict__ Pk, int bs
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, double* __restrict__ V,
-                                                   const double* __restrict__ Pn, const double* __restrict__ Pk, int n,
-                                                   int step, int rest, int inv_blocks) {
+// n_pairs: PANEL_PAIRS, or 0 where the next diagonal block is brought up to date otherwise.  Vd: V's diagonal block, rows
+// of ldd; V and inv_blocks > 0 only with ldd == n.
+__global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, double* __restrict__ V, double* __restrict__ Vd,
+                                                   int ldd, const double* __restrict__ Pn, const double* __restrict__ Pk,
+                                                   int n, int step, int rest, int n_pairs, int inv_blocks) {
     __shared__ __align__(16) double sP[TR * TRP];
     __shared__ __align__(16) double sX[TR * TRP];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1028,8 +1035,8 @@ __global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, doub
     const int bs = min(NB, n - int(off));
     double* __restrict__ const P = A + (off + NB) * n + off;
     const int n_inv = PANEL_UNITS + NB / TR * inv_blocks;
-    const bool pair = blockIdx.x < PANEL_PAIRS;
-    const int inv = int(blockIdx.x) - PANEL_PAIRS;   // 0 .. n_inv - 1: columns of V
+    const bool pair = int(blockIdx.x) < n_pairs;
+    const int inv = int(blockIdx.x) - n_pairs;   // 0 .. n_inv - 1: columns of V
     const bool is_inv = !pair && inv < n_inv;
     int I = 0, J = 0, m0 = 0;
     if (pair) {
@@ -1045,7 +1052,7 @@ __global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, doub
     const int row = pair ? (r < SBW ? I : J) * SBW + (r & (SBW - 1)) : m0 + r;   // of the panel
     // transposed: rows t / 32, t / 32 + 8, .. of the block, its column t % 32
     const int vr = tid >> 5, vc = tid & 31;
-    double* const vcol = V + off * n + (inv < PANEL_UNITS ? off + inv * TR : (inv - PANEL_UNITS) * TR) + vc;
+    double* const vcol = (inv < PANEL_UNITS ? Vd + inv * TR : V + off * n + (inv - PANEL_UNITS) * TR) + vc;
     if (is_inv) {
         double v[16];
         if (inv < PANEL_UNITS) {
@@ -1053,7 +1060,7 @@ __global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, doub
             for (int e = 0; e < 16; ++e) v[e] = vr + 8 * e == inv * TR + vc ? -1.0 : 0.0;
         } else {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = vr + 8 * e < bs ? vcol[int64_t(vr + 8 * e) * n] : 0.0;
+            for (int e = 0; e < 16; ++e) v[e] = vr + 8 * e < bs ? vcol[int64_t(vr + 8 * e) * ldd] : 0.0;
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) sP[vc * TRP + vr + 8 * e] = v[e];
@@ -1076,7 +1083,7 @@ __global__ __launch_bounds__(256) void panel_kernel(double* __restrict__ A, doub
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int vrow = vr + 8 * e;
-            if (vrow < bs && (inv >= PANEL_UNITS || (vrow >= inv * TR + vc && inv * TR + vc < bs))) vcol[int64_t(vrow) * n] = -sX[vc * TRP + vrow];
+            if (vrow < bs && (inv >= PANEL_UNITS || (vrow >= inv * TR + vc && inv * TR + vc < bs))) vcol[int64_t(vrow) * ldd] = -sX[vc * TRP + vrow];
         }
         return;
     }
@@ -1149,6 +1156,80 @@ Workspace carve(void* ws, int64_t n) {
     return w;
 }
 
+// V's diagonal blocks from where factor_slabs keeps them, zeros above their diagonals
+__global__ __launch_bounds__(256) void place_diagonal_kernel(const double* __restrict__ Vd, int n, double* __restrict__ V) {
+    const int b = blockIdx.x, c = threadIdx.x & (NB - 1);
+    for (int r = threadIdx.x / NB; r < NB; r += 256 / NB) {
+        const int row = b * NB + r, col = b * NB + c;
+        if (row < n && col < n) V[int64_t(row) * n + col] = c <= r ? Vd[(int64_t(b) * NB + r) * NB + c] : 0.0;
+    }
+}
+
+// ---- left-looking Cholesky of wide matrices -----------------------------------------------------------------------------
+// A slab of block columns is brought up to date by everything left of it in one product of 8-bit residues, then factored
+// block by block as the narrow matrices are, the trailing updates ending at the slab's edge, and its own residues are
+// taken.  Left-looking, so that every entry is put together from residues once, over the longest inner range there is.
+// Whole factor, right-looking in fp64 : by residues, us, inverse and block form: d_in 5120 2603 : 2859, 1656 : 1793; 6528 4340 :
+// 4433, 2787 : 2769; 6656 4549 : 4524, 2917 : 2792; 7168 5407 : 5163, 3521 : 3168; 8192 7708 : 6431, 4949 : 3901; 14336 33.9 :
+// 22.4 ms, 19.9 : 12.0; 28672 233 : 129, 130 : 66.9.  Wider than RESIDUE_MAX the sums' bounds have not been worked out.
+constexpr int RESIDUE_MIN = 6656, RESIDUE_MAX = residue::MAX_K;
+bool by_residues(int n) { return n >= RESIDUE_MIN && n <= RESIDUE_MAX; }
+// Columns of a slab: longer inner ranges and whole patches of tiles against the updates inside the slab.  512 : 768 : 1024, us,
+// inverse form: d_in 7168 5068 : 5041 : -; 8192 6592 : 6491 : 6428; 14336 23.0 ms : - : 22.3; 28672 129.3 : - : 127.8.
+int slab_width(int n) { return n >= 8192 ? 1024 : 512; }
+// The inverse's products of block pairs of at least this size go by residues.  From 2048 on: d_in 8192 6592 -> 6769 us, 28672
+// 127.8 -> 128.9 ms.  Blocks of 4096 with a last one of so many rows below, whole factor by residues : in fp64, us: 2432 4542 :
+// 4433, 2560 4623 : 4524, 2816 4883 : 5006, 3072 5163 : 5309, 3584 5957 : 6200.
+constexpr int64_t RESIDUE_INVERSE_MIN = 4096, RESIDUE_INVERSE_MIN_ROWS = 2816;
+
+onecomp_status factor_slabs(const Workspace& w, int n, char* product, int32_t* info, hipStream_t stream) {
+    const int slab_cols = slab_width(n), slab = slab_cols / NB, nblk = int(ceil_div(n, NB));
+    // residues of L, V's diagonal blocks, operands of the panel solve and the block below the diagonal: in place of V and T
+    char* p = reinterpret_cast<char*>(w.V);
+    const residue::Operand R(p, n, n);
+    p += align_up(residue::operand_bytes(n, n), 256);
+    double* const Vd = reinterpret_cast<double*>(p);
+    p += size_t(nblk) * NB * NB * sizeof(double);
+    double* const Pk = reinterpret_cast<double*>(p);
+    p += size_t(PANEL_PAIRS) * SBW * SBW * sizeof(double);
+    double* const Pn1 = reinterpret_cast<double*>(p);
+    p += size_t(NB) * NB * sizeof(double);
+    if (p > reinterpret_cast<char*>(w.dfix) || residue::product_bytes(n, slab_cols) > size_t(n) * n * sizeof(float)) return ONECOMP_ERR_UNSUPPORTED;
+    int32_t* const shift = reinterpret_cast<int32_t*>(w.keys);
+    double* const left = w.dfix;
+    onecomp_status st = residue::row_bounds(w.A, n, shift, left, stream);
+    if (st != ONECOMP_OK) return st;
+    for (int s0 = 0; s0 < nblk; s0 += slab) {
+        const int s1 = min(s0 + slab, nblk), c0 = s0 * NB, width = min(slab_cols, n - c0);
+        double* const Pn = s0 > 0 ? Pn1 : w.Pn;   // the first one has been written beside the matrix
+        if (s0 > 0) {
+            st = residue::update_columns(w.A, n, c0, width, shift, R, Pn, product, stream);
+            if (st != ONECOMP_OK) return st;
+        }
+        hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, Pn, Pk, n, s0 - 1, n - c0, 1,
+                           1, 0, 0, 0, info);
+        ONECOMP_CHECK_LAUNCH();
+        for (int s = s0; s < s1; ++s) {
+            const int rest = max(0, n - (s + 1) * NB), pairs = s + 1 < s1 ? PANEL_PAIRS : 0;
+            hipLaunchKernelGGL(panel_kernel, dim3(pairs + PANEL_UNITS + unsigned(ceil_div(rest, TR))), dim3(256), 0, stream, w.A, w.V,
+                               Vd + int64_t(s) * NB * NB, NB, Pn, Pk, n, s, rest, pairs, 0);
+            ONECOMP_CHECK_LAUNCH();
+            if (s + 1 == s1) break;
+            const int cols = s1 - 1 - s;   // block columns of the slab behind this one
+            hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(unsigned(plan::syrk_slab_grid(nblk - 1 - s, cols))),
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, Pn, Pk, n, s, rest, 1, 1, s, 0, cols, info);
+            ONECOMP_CHECK_LAUNCH();
+        }
+        if (s1 < nblk) {
+            st = residue::convert_columns(w.A, n, s1 * NB, c0, width, shift, left, R, stream);
+            if (st != ONECOMP_OK) return st;
+        }
+    }
+    hipLaunchKernelGGL(place_diagonal_kernel, dim3(unsigned(nblk)), dim3(256), 0, stream, Vd, n, w.V);
+    ONECOMP_CHECK_LAUNCH();
+    return ONECOMP_OK;
+}
+
 }  // namespace
 
 size_t factor_workspace_bytes(int64_t n) {
@@ -1181,12 +1262,17 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     }
     ONECOMP_CHECK_LAUNCH();
 
+    const int nblk = int(ceil_div(n, NB));
+    const bool wide = by_residues(n);
+    if (wide && (st = factor_slabs(w, n, reinterpret_cast<char*>(U), info, stream)) != ONECOMP_OK) return st;
+
     // ---- blocked right-looking Cholesky of A (lower) ----
     // diagonal block 0 on its own; every later one inside the launch that updates the trailing matrix before it
-    const int nblk = int(ceil_div(n, NB));
-    hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, -1, n, 1, 1, 0,
-                       0, info);
-    ONECOMP_CHECK_LAUNCH();
+    if (!wide) {
+        hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(1), dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, -1, n, 1, 1,
+                           0, 0, 0, info);
+        ONECOMP_CHECK_LAUNCH();
+    }
     // One step: panel solve below diagonal block s, then a trailing update fused with the factorization of diagonal
     // block s + 1.  The next step needs block column s + 1 only, so that one is updated at once and the others every
     // `lag` steps, by all panels solved since, in turn: a launch updates every lag-th column with k = 128 lag.  A rank-128
@@ -1196,12 +1282,12 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     // Narrow factors take the inverse along: once V[s, :] is known (the panel solve's launch), V[i, :] += L[i, s] V[s, :]
     // for the rows below, beside the trailing update, which leaves room in every launch the chain of diagonal blocks
     // bounds; V's blocks below the diagonal hold these sums until their row's turn.
-    const bool along = form == ONECOMP_FACTOR_INVERSE && nblk <= plan::INVERSE_ALONG_MAX;
+    const bool along = !wide && form == ONECOMP_FACTOR_INVERSE && nblk <= plan::INVERSE_ALONG_MAX;
     int base = 0, lag = plan::syrk_lag(nblk);
-    for (int s = 0; s < nblk; ++s) {
+    for (int s = 0; s < nblk && !wide; ++s) {
         const int rest = max(0, n - (s + 1) * NB), inv = along ? s : 0;
         hipLaunchKernelGGL(panel_kernel, dim3(PANEL_PAIRS + PANEL_UNITS + NB / TR * inv + unsigned(ceil_div(rest, TR))), dim3(256),
-                           0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, inv);
+                           0, stream, w.A, w.V, w.V + int64_t(s) * NB * (n + 1), n, w.Pn, w.Pk, n, s, rest, PANEL_PAIRS, inv);
         ONECOMP_CHECK_LAUNCH();
         if (rest == 0) break;
         const int next_lag = plan::syrk_lag(nblk - 2 - s);
@@ -1209,10 +1295,10 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
         if (lag == 1) {
             const int inv_cols = along ? 2 * (s + 1) : 0;
             hipLaunchKernelGGL(syrk_potrf_kernel<true>, dim3(unsigned(plan::syrk_narrow_grid(nblk - 1 - s, inv_cols))),
-                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, 1, 1, s, inv_cols, info);
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, 1, 1, s, inv_cols, 0, info);
         } else {
             hipLaunchKernelGGL(syrk_potrf_kernel<false>, dim3(unsigned(plan::syrk_grid(nblk - 1 - s, stride).total)),
-                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, stride, lag, base, 0, info);
+                               dim3(POTRF_THREADS), 0, stream, w.A, w.V, w.Pn, w.Pk, n, s, rest, stride, lag, base, 0, 0, info);
         }
         ONECOMP_CHECK_LAUNCH();
         if (stride != lag) base = s + 1;
@@ -1220,6 +1306,7 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     }
 
     // ---- V = L^-1 by recursive doubling over aligned block pairs, from the diagonal blocks ----
+    const size_t mat = align_up(size_t(n) * n * sizeof(double), 256);
     for (int64_t s = NB; s < n && form == ONECOMP_FACTOR_INVERSE && !along; s *= 2) {
         const int64_t pairs = ceil_div(n, 2 * s);
         // last pair may have a short or empty C range
@@ -1229,20 +1316,43 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
         if (batch <= 0) continue;
         if (m_last > s) m_last = s;
         const int64_t stride = 2 * s * (int64_t(n) + 1);
+        // Row c of L carries channel c's scale and column c of V its inverse: the first product's terms are free of them, the
+        // second one's operands are balanced.
+        int32_t* const inner = reinterpret_cast<int32_t*>(w.dfix);
+        int64_t first = 0;   // pairs that go by residues
+        if (wide && s >= RESIDUE_INVERSE_MIN) {
+            first = m_last >= RESIDUE_INVERSE_MIN_ROWS ? batch : batch - 1;
+            if (first > 0 && (st = residue::inner_exponents(w.V, n, inner, stream)) != ONECOMP_OK) return st;
+        }
+        for (int64_t p = 0; p < first; ++p) {
+            const int64_t o = 2 * s * p, m = p == batch - 1 ? m_last : s;
+            double* const ca = w.V + (o + s) * n + o;
+            // V[C,A] = L[C,A] V[A,A], then V[C,A] = -V[C,C] V[C,A]; U is free until the factor is written
+            st = residue::triangular_product(w.A + (o + s) * n + o, n, w.V + o * (int64_t(n) + 1), n, ca, n, int(m), int(s), int(s), true,
+                                             1.0, w.T, mat, U, size_t(n) * n * sizeof(float), nullptr,
+                                             reinterpret_cast<int32_t*>(w.keys), w.perm, stream);
+            if (st != ONECOMP_OK) return st;
+            st = residue::triangular_product(w.V + (o + s) * (int64_t(n) + 1), n, ca, n, ca, n, int(m), int(s), int(m), false, -1.0, w.T,
+                                             mat, U, size_t(n) * n * sizeof(float), inner + o + s,
+                                             reinterpret_cast<int32_t*>(w.keys), w.perm, stream);
+            if (st != ONECOMP_OK) return st;
+        }
+        if (first == batch) continue;
+        const int64_t skip = first * stride;
         // T[C,A] = L[C,A] * V[A,A]        (V[A,A] lower triangular)
         GemmArgs a{};
-        a.A = w.A + s * n; a.lda = n; a.sa = stride;
-        a.B = w.V; a.ldb = n; a.sb = stride;
-        a.C = w.T + s * n; a.ldc = n; a.sc = stride;
-        a.m = int(s); a.m_last = int(m_last); a.n = int(s); a.k = int(s); a.k_last = int(s); a.batch = int(batch);
+        a.A = w.A + s * n + skip; a.lda = n; a.sa = stride;
+        a.B = w.V + skip; a.ldb = n; a.sb = stride;
+        a.C = w.T + s * n + skip; a.ldc = n; a.sc = stride;
+        a.m = int(s); a.m_last = int(m_last); a.n = int(s); a.k = int(s); a.k_last = int(s); a.batch = int(batch - first);
         a.alpha = 1.0; a.beta = 0.0; a.flags = G_BLOWER;
         if ((st = dgemm(a, stream)) != ONECOMP_OK) return st;
         // V[C,A] = -V[C,C] * T[C,A]       (V[C,C] lower triangular)
         GemmArgs b{};
-        b.A = w.V + s * (int64_t(n) + 1); b.lda = n; b.sa = stride;
-        b.B = w.T + s * n; b.ldb = n; b.sb = stride;
-        b.C = w.V + s * n; b.ldc = n; b.sc = stride;
-        b.m = int(s); b.m_last = int(m_last); b.n = int(s); b.k = int(s); b.k_last = int(m_last); b.batch = int(batch);
+        b.A = w.V + s * (int64_t(n) + 1) + skip; b.lda = n; b.sa = stride;
+        b.B = w.T + s * n + skip; b.ldb = n; b.sb = stride;
+        b.C = w.V + s * n + skip; b.ldc = n; b.sc = stride;
+        b.m = int(s); b.m_last = int(m_last); b.n = int(s); b.k = int(s); b.k_last = int(m_last); b.batch = int(batch - first);
         b.alpha = -1.0; b.beta = 0.0; b.flags = G_ALOWER;
         if ((st = dgemm(b, stream)) != ONECOMP_OK) return st;
     }

@@ -143,6 +143,28 @@ ONECOMP_HD bool syrk_narrow_tile(int bid, int n_t, int inv_cols, int& tm, int& t
     tc = v + 2 - tm * (tm + 1);
     return true;
 }
+// Launches inside a slab of a left-looking factorization (factor_run), which has `cols` >= 1 block columns left: the tiles
+// above of the first 2 cols columns only.
+ONECOMP_HD int syrk_slab_tiles(int n_t, int cols) {
+    const int c = imin(cols, n_t);
+    return c * (c + 1) - 2 + 2 * c * (n_t - c);
+}
+ONECOMP_HD int syrk_slab_grid(int n_t, int cols) { return 1 + ((syrk_slab_tiles(n_t, cols) + 7) & ~7); }
+ONECOMP_HD bool syrk_slab_tile(int bid, int n_t, int cols, int& tm, int& tc) {
+    const int c = imin(cols, n_t), n = syrk_slab_tiles(n_t, cols), chunk = (n + 7) >> 3, u = bid - 1;
+    const int v = (u & 7) * chunk + (u >> 3) + 2;   // the two tiles of row 0 are not there
+    if (v >= n + 2) return false;
+    const int head = c * (c + 1);   // rows 0 .. c - 1
+    if (v >= head) {
+        tm = c + (v - head) / (2 * c);
+        tc = (v - head) % (2 * c);
+        return true;
+    }
+    tm = 0;
+    while ((tm + 1) * (tm + 2) <= v) ++tm;
+    tc = v - tm * (tm + 1);
+    return true;
+}
 // Factors of up to this many blocks take their inverse along (factor_run), wider ones have it by recursive doubling
 // afterwards, in products with longer inner ranges.  Afterwards : along, us: d_in 512 186 : 144 and 2048 729 : 594 (with a
 // diagonal block of 18 us), 4096 1659 : 1533, 5120 2572 : 2495, 6144 3727 : 3765, 6784 4727 : 4751.

@@ -259,6 +259,20 @@ static void check_panel_feedback(int rows, int d_in) {
                 }
 }
 
+// launches inside a slab: of the tiles of the narrow launches those of the first `cols` block columns, once each
+static void check_syrk_slab(int n_t, int cols) {
+    std::set<std::pair<int, int>> seen;
+    for (int b = 1; b < syrk_slab_grid(n_t, cols); ++b) {
+        int tm = -1, tc = -1;
+        if (!syrk_slab_tile(b, n_t, cols, tm, tc)) continue;
+        REQUIRE(1 <= tm && tm < n_t && 0 <= tc && tc / 2 <= tm && tc < 2 * cols, "syrk slab %d, %d workgroup %d -> (%d, %d)", n_t, cols, b, tm, tc);
+        REQUIRE(seen.insert({tm, tc}).second, "syrk slab %d, %d tile (%d, %d) owned twice", n_t, cols, tm, tc);
+    }
+    long want = 0;
+    for (int tm = 1; tm < n_t; ++tm) want += 2 * imin(tm + 1, cols);
+    REQUIRE(long(seen.size()) == want, "syrk slab %d, %d: %zu of %ld tiles", n_t, cols, seen.size(), want);
+}
+
 int main() {
     const int n_cus = 256;
 #ifdef PLANNER_CHECK_THIN
@@ -275,6 +289,8 @@ int main() {
 #else
     for (int n_blk = 83; n_blk <= 362; n_blk += n_blk < 130 || n_blk > 300 ? 1 : 7) check_syrk_schedule(n_blk);
 #endif
+    for (int n_t : {1, 2, 3, 4, 5, 7, 8, 9, 49, 50, 111, 223, 255})
+        for (int cols = 1; cols <= 7; ++cols) check_syrk_slab(n_t, cols);
     for (int d_in = 16; d_in <= 32768; d_in += step) {
         if (d_in <= 4096 || d_in % 256 == 0) {            // every width up to 4096, then every multiple of 256 (set-based checks)
             check_simple_upper(d_in, 128);

@@ -581,6 +581,78 @@ def test_factor_schedules(d_in):
         assert torch.equal(F[blk[:, None] == blk[None, :]], U[blk[:, None] == blk[None, :]])
 
 
+@pytest.mark.parametrize("d_in,tokens", [
+    (6656, 3000),     # the first width of the products by residues; H of less than half rank
+    (6672, 7000),     # a last slab of 16 columns behind whole tiles
+    (6928, 7000),     # the inverse's products by residues too, the second operand of 2832 rows
+    (8208, 9000),     # slabs of 1024, a last one of 16
+    (10368, 10500),   # a last slab of 128 columns
+])
+def test_factor_by_residues(d_in, tokens):
+    """The wide factor in both forms, channels of scales from 2^-20 to 2^20: the bound of test_factor_inverse_levels, and entries
+    that are not the exact ones rounded to fp32 as rare as 64-bit arithmetic leaves them.  (An entry is, where its error and
+    that of torch's own, each of some 2^-53 sqrt(d_in) times the condition number of the scaled matrix, 2^7 here, meet a
+    rounding boundary: 2^-53 2^6.5 2^7 2^24 = 2^-15.5 of the entries at most; 14 bits would make it all of them.)"""
+    _announce(f"factor by residues d_in={d_in}")
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    scale = torch.exp2(torch.randint(-20, 21, (d_in,), generator=g, device=DEV).float())
+    X = torch.randn((tokens, d_in), generator=g, device=DEV)
+    H = X.t() @ X
+    H = (torch.triu(H) + torch.triu(H, 1).t())
+    H.diagonal().add_(0.1 * tokens)
+    H = (H * scale[:, None] * scale[None, :]).contiguous()
+    R = torch.linalg.cholesky(H.double().flip(0, 1)).flip(0, 1).contiguous()
+    for form in ("inverse", "block")[:2 if d_in % 128 == 0 else 1]:
+        U, _, info = og.onecomp_hessian_factor(H, 0.0, form=form)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        if form == "inverse":
+            n = -(-d_in // 128) * 128   # (the library's solver takes no ragged width of this size)
+            P = torch.eye(n, dtype=torch.float64, device=DEV)
+            P[:d_in, :d_in] = R
+            ref = torch.linalg.solve_triangular(P, torch.eye(n, dtype=torch.float64, device=DEV), upper=True)[:d_in, :d_in]
+            assert torch.all(torch.tril(U, -1) == 0.0)
+            blocks = U.clone()
+            # scaling channels by powers of two rounds nothing differently
+            plain, _, _ = og.onecomp_hessian_factor((H / scale[:, None] / scale[None, :]).contiguous(), 0.0)
+            assert torch.equal(U * scale[None, :], plain)
+        else:
+            ref = -R / R.diagonal()[None, :] / R.diagonal()[:, None]
+            blk = torch.arange(d_in, device=DEV) // 128
+            same = blk[:, None] == blk[None, :]
+            assert torch.equal(U[same], blocks[same])
+            ref = torch.where(same, U.double(), ref)
+        N = torch.triu(ref) * scale.double()[None, :]   # columns are scaled by the channels' inverses, in both forms
+        E = U.double() * scale.double()[None, :] - N
+        assert float(E.norm()) <= 2.0 ** -24 * float(N.norm())
+        wrong = int((torch.triu(U) != torch.triu(ref).float()).sum())
+        _announce(f"   {form}: {wrong} of {d_in * (d_in + 1) // 2} entries not the rounded 64-bit ones")
+        assert wrong <= 2.0 ** -15.5 * d_in * (d_in + 1) / 2
+
+
+@pytest.mark.parametrize("entries,want", [
+    ([(20, 20, -1.0)], 21),                                     # first slab
+    ([(3000, 3000, -1.0)], 3001),                               # later slab: no scale fits its row
+    ([(3000, 3000, float("nan"))], 1),                          # damping and with it every diagonal entry
+    ([(5000, 100, 10.0)], 5001),                                # a row longer than its diagonal entry, in the first slab
+    ([(5000, 100, 1e30), (4000, 3500, 10.0)], 4001),            # .. and a failing row before it
+    ([(6655, 700, float("inf"))], 6656), ([(5000, 100, float("nan"))], 5001),
+    ([(700, 600, 10.0), (6000, 6000, -1.0)], 701),              # inside a slab
+])
+def test_factor_by_residues_bad_pivots(entries, want):
+    """The first pivot that is not positive is reported wherever it is, also where a row's entries exceed the bound that its
+    diagonal entry puts on them (positions in the order of the factorization)."""
+    _announce(f"factor by residues, bad pivots {entries}")
+    n = 6656
+    for form in ("inverse", "block"):
+        H = torch.eye(n, device=DEV) * 4.0
+        for i, j, v in entries:
+            H[n - 1 - i, n - 1 - j] = H[n - 1 - j, n - 1 - i] = v
+        _, _, info = og.onecomp_hessian_factor(H, 0.0, form=form)
+        torch.cuda.synchronize()
+        assert int(info.item()) == want
+
+
 @pytest.mark.parametrize("at", [0, 1, 15, 16, 63, 64, 77, 127, 128, 143, 255, 256, 271])
 def test_factor_bad_pivot(at):
     """A single non-positive pivot at every kind of place: info is its position in the order of the factorization (which
