@@ -364,6 +364,14 @@ struct Ring {
     static_assert(MT + NT <= MT * NT && LPW <= MT * NT, "fragment reads and loads are placed one behind each MFMA");
     static_assert((A_ROWB / 16) % 16 == 0 && (B_ROWB / 16) % 16 == 0, "the chunk swizzle stays inside groups of 16 chunks");
 };
+// Whether a wave's part of the tile at (i0, k0) lies below the diagonal: 5.6 % of the waves of the 384 x 256 shape at d_in
+// 4096, 1.7 % at 14336, whose MFMAs and LDS reads cost the others clock.  Calls of 262144 tokens with them : without, us: d_in 4096
+// 4010 : 3955; 14336 44410 : 44230; 32768 tokens at 4096 655 : 637.
+template <typename C>
+__device__ __forceinline__ bool below_diagonal(int i0, int k0, int wave) {
+    using R = Ring<C>;
+    return i0 + wave / C::WN * 32 * R::MT >= k0 + (wave % C::WN + 1) * 32 * R::NT;
+}
 // CROSS = false: H += 2 X^T X, tiles on or above the diagonal, mirrored.  CROSS = true: H += 2 X^T Xb for two
 // different matrices (A panels from X, B panels from Xb), every tile, no mirror.
 // PACED: every wave sleeps 64 cycles at the start of each step.  In a launch of many thousand steps the workgroups of
@@ -498,6 +506,24 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
             for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
     __syncthreads();
+    if constexpr (!CROSS && C::TM >= 256) {
+        if (below_diagonal<C>(i0, k0, wave)) {   // nothing to compute: this wave's loads and barriers only
+            __syncthreads();
+            int s0 = 0;
+#pragma unroll 1
+            for (int64_t st = 0; st < n_st2; ++st) {
+                if constexpr (PACED) __builtin_amdgcn_s_sleep(1);
+                const Desc d = make_desc(st + NBUF);
+#pragma unroll
+                for (int q = 0; q < LPW; ++q) gload(d, lds0 + s0 * STAGEB, q);
+                __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NBUF - 2)));
+                __syncthreads();
+                s0 = (s0 == NBUF - 1) ? 0 : s0 + 1;
+            }
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+            return;
+        }
+    }
     Frags Fc, FH;
 #pragma unroll
     for (int r = 0; r < MT + NT; ++r) rd(Fc, r, 0);
@@ -616,6 +642,8 @@ __global__ __launch_bounds__(64) void gram_reduce_kernel(const float* __restrict
     const int lane = threadIdx.x;
     const int wave = sub / (RC::RS * RC::NS), part = (sub / RC::NS) % RC::RS, nh = sub % RC::NS;
     const int wr = wave / C::WN, wc = wave % C::WN;
+    // below the diagonal: nothing to store, and maybe nothing in the slots
+    if (i0 + wr * (32 * MT) + part * (32 * MTS) >= k0 + wc * (32 * NT) + (nh + 1) * (32 * NTS)) return;
     float16v acc[MTS][NTS];
 #pragma unroll
     for (int m = 0; m < MTS; ++m)
