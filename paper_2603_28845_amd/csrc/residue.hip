@@ -81,21 +81,31 @@ __device__ __forceinline__ int32_t shift_of(double s) {
     return (d & 1) ? (d - 1) / 2 : f <= BOUND_MANT ? d / 2 : d / 2 - 1;
 }
 
-// 16 entries of one row -> 16 bytes per modulus at dst, dst + plane, ...
-// N = rint(x 2^s) = n2 2^36 + n1 2^18 + n0 with |n0|, |n1| <= 2^17 and |n2| < 2^19, so n2 c2 + n1 c1 + n0 stays below 2^26 and
-// its quotient by m, from fp32, is off by 2 / m at most.  1.5 2^23 + q holds q in its low bits; the offset 2^22 m it brings
-// into the product leaves the low byte alone.
-__device__ __forceinline__ void convert_piece(const double (&x)[16], int s, char* __restrict__ dst, int64_t plane) {
+// a c + b, 24-bit factors: two of these are what the compiler makes two products and a sum of three of
+__device__ __forceinline__ int mad24(int a, int c, int b) {
+    int r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(c), "v"(b));
+    return r;
+}
+__device__ __forceinline__ int low_word(double x) { return int(uint32_t(__builtin_bit_cast(uint64_t, x))); }
+
+// 16 entries of one row, scaled by 2^s -> 16 bytes per modulus at dst, dst + plane, ...
+// N = rint(x) = n2 2^36 + n1 2^18 + n0 with |n0|, |n1| <= 2^17 and |n2| < 2^19, each rounded by adding 1.5 2^52, whose sum holds
+// it in its low word; so n2 c2 + n1 c1 + n0 stays below 2^26 and its quotient by m, from fp32, is off by 2 / m at most.
+// 1.5 2^23 + q holds q in its low bits; the offset 2^22 m it brings into the product leaves the low byte alone.
+// Conversions of fp64 to integers and back instead, and the compiler's choice of products: 120 vector instructions an entry,
+// 30 of them fp64 at a quarter of the rate; now 100.
+__device__ __forceinline__ void convert_piece(const double (&x)[16], char* __restrict__ dst, int64_t plane) {
+    constexpr double MAGIC = 0x1.8p52;
     int n0[16], n1[16], n2[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        const double y = __builtin_rint(__builtin_ldexp(x[e], s));
-        const double h = __builtin_rint(y * 0x1p-36);
-        const double l = __builtin_fma(-h, 0x1p36, y);
-        const double g = __builtin_rint(l * 0x1p-18);
-        n2[e] = int(h);
-        n1[e] = int(g);
-        n0[e] = int(__builtin_fma(-g, 0x1p18, l));
+        const double h = __builtin_fma(x[e], 0x1p-36, MAGIC);
+        const double l = __builtin_fma(-(h - MAGIC), 0x1p36, x[e]);
+        const double g = __builtin_fma(l, 0x1p-18, MAGIC);
+        n2[e] = low_word(h);
+        n1[e] = low_word(g);
+        n0[e] = low_word(__builtin_fma(-(g - MAGIC), 0x1p18, l) + MAGIC);
     }
 #pragma unroll
     for (int i = 0; i < MODULI; ++i) {
@@ -105,12 +115,12 @@ __device__ __forceinline__ void convert_piece(const double (&x)[16], int s, char
             uint32_t b[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int v = __mul24(n2[4 * q + e], TAB.c2[i]) + __mul24(n1[4 * q + e], TAB.c1[i]) + n0[4 * q + e];
                 if (MOD[i] == 256) {
-                    b[e] = uint32_t(v);
+                    b[e] = uint32_t(n0[4 * q + e]);   // 2^18 and 2^36 are zero mod 256
                 } else {
+                    const int v = mad24(n2[4 * q + e], TAB.c2[i], mad24(n1[4 * q + e], TAB.c1[i], n0[4 * q + e]));
                     const float t = __builtin_fmaf(float(v), TAB.inv[i], 12582912.0f);
-                    b[e] = uint32_t(v - __mul24(int(__float_as_uint(t)), MOD[i]));
+                    b[e] = uint32_t(mad24(int(__float_as_uint(t)), -MOD[i], v));
                 }
             }
             // the low bytes of the four
@@ -120,6 +130,8 @@ __device__ __forceinline__ void convert_piece(const double (&x)[16], int s, char
         *reinterpret_cast<uint4v*>(dst + i * plane) = w;
     }
 }
+// 2^e for the exponents that scales have
+__device__ __forceinline__ double power(int e) { return __builtin_ldexp(1.0, e); }
 // where entries [k, k + 16) of row `row` go inside a plane
 __device__ __forceinline__ int64_t piece_offset(int row, int k, int64_t block) {
     return int64_t(row >> 5) * block + (k >> 5) * 1024 + ((k >> 4) & 1) * 512 + (row & 31) * 16;
@@ -141,7 +153,7 @@ constexpr int CV_COLS = 128, CV_PITCH = CV_COLS + 2;
 __device__ __forceinline__ void stage_rows(const double* __restrict__ src, int64_t ld, int rows_ok, int cols_ok, double* tile,
                                            const int32_t* __restrict__ inner = nullptr) {
     const int r = threadIdx.x >> 6, c = (threadIdx.x & 63) * 2;
-    const int32_t e0 = inner && c < cols_ok ? inner[c] : 0, e1 = inner && c < cols_ok ? inner[c + 1] : 0;
+    const double p0 = power(inner && c < cols_ok ? inner[c] : 0), p1 = power(inner && c < cols_ok ? inner[c + 1] : 0);
     double2 v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -150,7 +162,7 @@ __device__ __forceinline__ void stage_rows(const double* __restrict__ src, int64
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        if (inner) v[q] = make_double2(__builtin_ldexp(v[q].x, e0), __builtin_ldexp(v[q].y, e1));
+        if (inner) v[q] = make_double2(v[q].x * p0, v[q].y * p1);
         *reinterpret_cast<double2*>(tile + (r + 4 * q) * CV_PITCH + c) = v[q];
     }
 }
@@ -201,16 +213,16 @@ __global__ __launch_bounds__(256) void convert_columns_kernel(const double* __re
         left[row] = rest;
         shift[row] = sh;
     }
+    const double scale = power(sh == NO_SHIFT ? 0 : sh);
     for (int c = 0; c < width; c += CV_COLS) {
         __syncthreads();
         stage_rows(src + c, n, n - row0, width - c, tile);
         __syncthreads();
         take_piece(tile, x);
-        if (sh == NO_SHIFT)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = 0.0;
+        for (int e = 0; e < 16; ++e) x[e] = sh == NO_SHIFT ? 0.0 : x[e] * scale;
         const int k = c0 + c + seg * 16;
-        if (c + seg * 16 < width) convert_piece(x, sh == NO_SHIFT ? 0 : sh, R.data + piece_offset(row, k, R.block), R.plane);
+        if (c + seg * 16 < width) convert_piece(x, R.data + piece_offset(row, k, R.block), R.plane);
     }
 }
 
@@ -225,6 +237,7 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const double* __restr
     const int row0 = blockIdx.x * 32, row = row0 + (threadIdx.x & 31), seg = threadIdx.x >> 5;
     const int k_end = min(min(int(R.block >> 5), int(blockIdx.y + 1) * CV_CHUNK), lower ? (row0 / TILE + 1) * TILE : INT32_MAX);
     const int32_t sh = row < rows ? shift[row] : NO_SHIFT;
+    const double scale = power(sh == NO_SHIFT ? 0 : sh);
     double x[16];
     for (int k0 = blockIdx.y * CV_CHUNK; k0 < k_end; k0 += CV_COLS) {
         __syncthreads();
@@ -234,18 +247,27 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const double* __restr
         const int k = k0 + seg * 16;
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            if (sh == NO_SHIFT || (lower && k + e > row)) x[e] = 0.0;
-        if (k < k_end) convert_piece(x, sh == NO_SHIFT ? 0 : sh, R.data + piece_offset(row, k, R.block), R.plane);
+            x[e] = sh == NO_SHIFT || (lower && k + e > row) ? 0.0 : x[e] * scale;
+        if (k < k_end) convert_piece(x, R.data + piece_offset(row, k, R.block), R.plane);
     }
 }
-// Columns [c0, c0 + cols) of a matrix of k_len rows, as rows of R.  lower: the matrix is lower triangular.
+// Columns [c0, c0 + cols) of a matrix of k_len rows and n columns, as rows of R; partial: column_norm_kernel's.  lower: the
+// matrix is lower triangular.
 __global__ __launch_bounds__(256) void convert_transposed_kernel(const double* __restrict__ src, int64_t ld, int c0, int cols,
                                                                 int k_len, int lower, const int32_t* __restrict__ inner,
-                                                                const int32_t* __restrict__ shift, Operand R) {
+                                                                const double* __restrict__ partial, int n,
+                                                                int32_t* __restrict__ shift, Operand R) {
     const int r = blockIdx.x * 32 + (threadIdx.x & 31), seg = threadIdx.x >> 5, col = c0 + r;
     const int k_end = min(int(R.block >> 5), int(blockIdx.y + 1) * CV_CHUNK);
     const int k_begin = lower ? (c0 + int(blockIdx.x) * 32) / TILE * TILE : 0;
-    const int32_t sh = r < cols ? shift[col] : NO_SHIFT;
+    int32_t sh = NO_SHIFT;
+    if (r < cols) {
+        double norm = 0.0;
+        for (int y = 0; y * CV_CHUNK < k_len; ++y) norm += partial[int64_t(y) * n + col];
+        sh = shift_of(norm);
+        if (blockIdx.y == 0 && seg == 0) shift[col] = sh;
+    }
+    const int s = sh == NO_SHIFT ? 0 : sh;
     for (int k = blockIdx.y * CV_CHUNK + seg * 16; k < k_end; k += 128) {
         if (k < k_begin) continue;
         double x[16];
@@ -254,10 +276,9 @@ __global__ __launch_bounds__(256) void convert_transposed_kernel(const double* _
             x[e] = 0.0;
             if (sh != NO_SHIFT && k + e < k_len && !(lower && k + e < col)) x[e] = src[int64_t(k + e) * ld + col];
         }
-        if (inner)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = __builtin_ldexp(x[e], k + e < k_len ? -inner[k + e] : 0);
-        convert_piece(x, sh == NO_SHIFT ? 0 : sh, R.data + piece_offset(r, k, R.block), R.plane);
+        for (int e = 0; e < 16; ++e) x[e] = x[e] * (inner && k + e < k_len ? power(s - inner[k + e]) : power(s));
+        convert_piece(x, R.data + piece_offset(r, k, R.block), R.plane);
     }
 }
 
@@ -268,35 +289,32 @@ __global__ __launch_bounds__(256) void row_shift_kernel(const double* __restrict
     if (row >= rows) return;
     const int end = lower ? min(k_len, row + 1) : k_len;
     double s = 0.0;
+#pragma unroll 8
     for (int k = lane; k < end; k += 64) {
-        const double v = __builtin_ldexp(src[int64_t(row) * ld + k], inner ? inner[k] : 0);
+        const double v = src[int64_t(row) * ld + k] * (inner ? power(inner[k]) : 1.0);
         s = __builtin_fma(v, v, s);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) shift[row] = shift_of(s);
 }
-// scales of columns [c0, c0 + cols), 32 of them per workgroup
-__global__ __launch_bounds__(1024) void column_shift_kernel(const double* __restrict__ src, int64_t ld, int c0, int cols, int k_len,
-                                                           int lower, const int32_t* __restrict__ inner,
-                                                           int32_t* __restrict__ shift) {
-    __shared__ double part[32][33];
-    const int l = threadIdx.x & 31, seg = threadIdx.x >> 5, col = c0 + blockIdx.x * 32 + l;
-    const bool ok = blockIdx.x * 32 + l < cols;
+// partial[y][col]: squares of column `col` in rows [512 y, 512 y + 512); lower as above
+__global__ __launch_bounds__(256) void column_norm_kernel(const double* __restrict__ src, int64_t ld, int cols, int k_len, int lower,
+                                                         const int32_t* __restrict__ inner, double* __restrict__ partial) {
+    __shared__ double part[4][64];
+    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6, col = blockIdx.x * 64 + l;
+    const int k1 = min(k_len, int(blockIdx.y + 1) * CV_CHUNK);
     double s = 0.0;
-    if (ok) {
-#pragma unroll 4
-        for (int k = (lower ? (c0 + int(blockIdx.x) * 32) : 0) + seg; k < k_len; k += 32) {
-            const double v = lower && k < col ? 0.0 : __builtin_ldexp(src[int64_t(k) * ld + col], inner ? -inner[k] : 0);
+    if (col < cols) {
+#pragma unroll 8
+        for (int k = max(int(blockIdx.y) * CV_CHUNK, lower ? int(blockIdx.x) * 64 : 0) + seg; k < k1; k += 4) {
+            const double v = lower && k < col ? 0.0 : src[int64_t(k) * ld + col] * (inner ? power(-inner[k]) : 1.0);
             s = __builtin_fma(v, v, s);
         }
     }
     part[seg][l] = s;
     __syncthreads();
-    if (seg != 0 || !ok) return;
-    s = 0.0;
-    for (int q = 0; q < 32; ++q) s += part[q][l];
-    shift[col] = shift_of(s);
+    if (seg == 0 && col < cols) partial[int64_t(blockIdx.y) * cols + col] = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
 }
 
 __global__ __launch_bounds__(256) void inner_exponents_kernel(const double* __restrict__ V, int n, int32_t* __restrict__ inner) {
@@ -307,6 +325,10 @@ __global__ __launch_bounds__(256) void inner_exponents_kernel(const double* __re
     if (d > 0.0 && d < __builtin_inf()) __builtin_frexp(d, &e);
     inner[i] = -e;
 }
+
+// Columns of B taken at a time: few enough that their residues and those of the product stay in the 256 MB cache behind the
+// L2s for the most part, enough tiles to fill the chip.
+constexpr int64_t PIECE_COLS = 2048;
 
 // ---- the products -----------------------------------------------------------------------------------------------------
 // out = A B^T mod m for every modulus m, A and B by their residues: 256 x 256 tile per workgroup, eight waves of 128 x 64, two
@@ -537,29 +559,32 @@ onecomp_status update_columns(double* A, int n, int c0, int width, const int32_t
 onecomp_status triangular_product(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int m, int n,
                                   int k, bool lower_b, double alpha, void* operands, size_t operand_len, void* product_mem,
                                   size_t product_len, const int32_t* inner, int32_t* shift_a, int32_t* shift_b, hipStream_t stream) {
-    const Operand RA(operands, m, k);
-    const size_t len_a = align_up(operand_bytes(m, k), 256);
-    // the columns are taken in pieces that leave room for their residues and those of the product
-    int64_t piece = ceil_div(n, TILE) * TILE;
-    while (piece > TILE && (len_a + operand_bytes(piece, k) > operand_len || product_bytes(m, piece) > product_len || piece > 2048))
-        piece -= TILE;
-    if (len_a + operand_bytes(piece, k) > operand_len || product_bytes(m, piece) > product_len || k > MAX_K) return ONECOMP_ERR_UNSUPPORTED;
+    // scratch: the columns' partial norms, the residues of A, those of as many columns of B as there is room for
     const unsigned chunks = unsigned(ceil_div(pad_k(k), CV_CHUNK));
+    double* const partial = static_cast<double*>(operands);
+    const size_t len_p = align_up(size_t(chunks) * n * sizeof(double), 256), len_a = align_up(operand_bytes(m, k), 256);
+    int64_t piece = n < PIECE_COLS ? pad_rows(n) : PIECE_COLS;
+    auto fits = [&]() {
+        return len_p + len_a + operand_bytes(piece, k) <= operand_len && product_bytes(m, piece) <= product_len;
+    };
+    while (piece > TILE && !fits()) piece -= TILE;
+    if (!fits() || k > MAX_K) return ONECOMP_ERR_UNSUPPORTED;
+    const Operand RA(static_cast<char*>(operands) + len_p, m, k);
     hipLaunchKernelGGL(row_shift_kernel, dim3(unsigned(ceil_div(m, 4))), dim3(256), 0, stream, A, lda, m, k, int(!lower_b), inner,
                        shift_a);
     ONECOMP_CHECK_LAUNCH();
     hipLaunchKernelGGL(convert_rows_kernel, dim3(unsigned(ceil_div(m, 32)), chunks), dim3(256), 0, stream, A, lda, m, k,
                        int(!lower_b), inner, shift_a, RA);
     ONECOMP_CHECK_LAUNCH();
+    hipLaunchKernelGGL(column_norm_kernel, dim3(unsigned(ceil_div(n, 64)), unsigned(ceil_div(k, CV_CHUNK))), dim3(256), 0, stream, B, ldb,
+                       n, k, int(lower_b), inner, partial);
+    ONECOMP_CHECK_LAUNCH();
     char* const out = static_cast<char*>(product_mem);
     for (int64_t c0 = 0; c0 < n; c0 += piece) {
         const int cols = int(n - c0 < piece ? n - c0 : piece);
-        const Operand RB(static_cast<char*>(operands) + len_a, cols, k);
-        hipLaunchKernelGGL(column_shift_kernel, dim3(unsigned(ceil_div(cols, 32))), dim3(1024), 0, stream, B, ldb, int(c0), cols, k,
-                           int(lower_b), inner, shift_b);
-        ONECOMP_CHECK_LAUNCH();
+        const Operand RB(static_cast<char*>(operands) + len_p + len_a, cols, k);
         hipLaunchKernelGGL(convert_transposed_kernel, dim3(unsigned(ceil_div(cols, 32)), chunks), dim3(256), 0, stream, B, ldb,
-                           int(c0), cols, k, int(lower_b), inner, shift_b, RB);
+                           int(c0), cols, k, int(lower_b), inner, partial, n, shift_b, RB);
         ONECOMP_CHECK_LAUNCH();
         onecomp_status st = product(RA, RB, m, cols, k, lower_b ? LOWER_B : LOWER_A, int(c0 / K_STEP), out, stream);
         if (st != ONECOMP_OK) return st;
