@@ -996,14 +996,22 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ U,
 // Tiles are ranked so that each XCD (blockIdx % 8) owns a contiguous run, m fastest inside bands of 8 row tiles:
 // the workgroups resident on one XCD share their Dt and Un panels through its L2.
 // ------------------------------------------------------------------------------------------
-namespace tg {
-constexpr int TM = 128, TN = 256, KT = 16;
-constexpr int A_ROWB = TM * 2, B_ROWB = TN * 2;                     // bytes per panel row
-constexpr int A_PANELB = KT * A_ROWB, B_PANELB = KT * B_ROWB;       // 4 KB, 8 KB
-constexpr int OFF_AH = 0, OFF_AL = A_PANELB, OFF_BH = 2 * A_PANELB, OFF_BL = 2 * A_PANELB + B_PANELB;
-constexpr int STAGEB = 2 * A_PANELB + 2 * B_PANELB;                 // 24 KB
-constexpr size_t LDS_BYTES = size_t(3) * STAGEB;                    // 72 KB with 3 slots: two workgroups per CU
-}  // namespace tg
+// The same with a 64 x 128 tile (32 x 64 per wave, 12 KB a step, six slots) for launches of few tiles, see launch_trailing.  An entry's products are added in the same order.  Rows of 64 left-operand entries are 128 bytes, eight
+// chunks: their position is c ^ ((r & 2) << 1).
+template <int MT_, int NT_, int NBUF_>   // 32 x 32 tiles of a wave, slots of the LDS ring
+struct TrailShape {
+    static constexpr int MT = MT_, NT = NT_, NBUF = NBUF_, TM = 64 * MT, TN = 64 * NT, KT = 16;
+    static constexpr int A_ROWB = TM * 2, B_ROWB = TN * 2;                     // bytes per panel row
+    static constexpr int A_PANELB = KT * A_ROWB, B_PANELB = KT * B_ROWB;       // 4 KB, 8 KB
+    static constexpr int OFF_AH = 0, OFF_AL = A_PANELB, OFF_BH = 2 * A_PANELB, OFF_BL = 2 * A_PANELB + B_PANELB;
+    static constexpr int STAGEB = 2 * A_PANELB + 2 * B_PANELB;                 // 24 KB
+    static constexpr size_t LDS_BYTES = size_t(NBUF) * STAGEB;                 // 72 KB: two workgroups per CU
+    static constexpr int LPW = STAGEB / 4096;                                  // loads per wave and step
+    static constexpr int A_LPW = MT;                                           // .. of the left operand
+    static_assert(MT <= 2 && NT % 2 == 0 && A_LPW + NT == LPW, "a wave loads MT and NT KB");
+};
+using TrailBig = TrailShape<2, 4, 3>;
+using TrailSmall = TrailShape<1, 2, 6>;
 
 struct TrailArgs {
     float* Wf;
@@ -1019,9 +1027,11 @@ struct TrailArgs {
 // FROM_ZERO: the accumulators start at zero and the product is added to the tile of C once, at the end, with one
 // fp32 rounding (the sweep: every rounding inside the MFMA chain then happens at the size of the increment, not of
 // the sum it joins).  Otherwise the tile of C is loaded, scaled, into the accumulators before the loop.
-template <int NBUF, bool FROM_ZERO>   // NBUF: slots of the LDS ring
+template <typename S, bool FROM_ZERO>
 __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid, char* tl) {
-    using namespace tg;
+    constexpr int MT = S::MT, NT = S::NT, NBUF = S::NBUF, TM = S::TM, TN = S::TN, KT = S::KT, LPW = S::LPW;
+    constexpr int A_ROWB = S::A_ROWB, B_ROWB = S::B_ROWB, A_PANELB = S::A_PANELB, B_PANELB = S::B_PANELB, STAGEB = S::STAGEB;
+    constexpr int OFF_AH = S::OFF_AH, OFF_AL = S::OFF_AL, OFF_BH = S::OFF_BH, OFF_BL = S::OFF_BL;
     int mt_, nt_;
     if (!plan::trail_tile(bid, a.chunk, a.n_mt, a.n_nt, mt_, nt_)) return;
     const int m0 = mt_ * TM;
@@ -1035,43 +1045,58 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     const int64_t d_in = a.d_in;
     const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)tl));
 
-    // this wave's six 1 KB loads per k-step: Dt panels rows 4 wave .. 4 wave + 3 (one load each), Un panels the
-    // same rows (two loads of two rows each)
-    uint32_t voff_a, voff_b[2];
+    // this wave's 1 KB loads per k-step.  128 x 256: rows 4 wave .. 4 wave + 3 of both Dt panels (one load each), the same
+    // rows of the Un panels (two loads of two rows each); 64 x 128: eight rows of one Dt panel (waves 0, 1: hi, 2, 3: lo),
+    // four rows of each Un panel
+    uint32_t voff_a, voff_b[NT / 2];
     {
-        const int row = 4 * wave + (lane >> 4);
-        const int c = (lane & 15) ^ ((row & 3) << 2);
+        constexpr int CPR = A_ROWB / 16;   // chunks per row
+        const int row = (MT == 2 ? 4 * wave : 8 * (wave & 1)) + lane / CPR;
+        const int c = (lane % CPR) ^ (MT == 2 ? (row & 3) << 2 : (row & 2) << 1);
         voff_a = (m0 + c * 8 < a.ldD) ? uint32_t((row * a.ldD + m0 + c * 8) * 2) : LDS_DMA_OOB;
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int row = 4 * wave + 2 * q + (lane >> 5);
-        const int c = (lane & 31) ^ ((row & 3) << 2);
+    for (int q = 0; q < NT / 2; ++q) {
+        constexpr int CPR = B_ROWB / 16;
+        const int row = 4 * wave + (NT == 4 ? 2 * q : 0) + lane / CPR;
+        const int c = (lane % CPR) ^ ((row & 3) << 2);
         voff_b[q] = (n0 + c * 8 < c1) ? uint32_t((int64_t(row) * d_in + n0 + c * 8) * 2) : LDS_DMA_OOB;
     }
     const int n_kb = a.K / KT;
     struct Desc {
         __amdgpu_buffer_rsrc_t ah, al, bh, bl;
     };
-    auto make_desc = [&](int kb, bool live) __attribute__((always_inline)) {
+    // descriptors of the next k-step, empty ones behind the last.  The bases advance by additions: formed by products in
+    // every step, they held back a 64 x 128 tile (14.2 against 13.9 us, 512 columns at d_out 4096).
+    const uint16_t *pah = a.Dh + int64_t(a.ek) * a.ldD, *pal = a.Dl + int64_t(a.ek) * a.ldD;
+    const uint16_t *pbh = a.Uh + int64_t(a.u0) * d_in, *pbl = a.Ul + int64_t(a.u0) * d_in;
+    const int step_a = KT * a.ldD, step_b = KT * a.d_in;
+    int ahead = n_kb;
+    auto next_desc = [&]() __attribute__((always_inline)) {
         Desc d;
-        if (!live) kb = 0;
-        const int64_t ea = (int64_t(a.ek) + kb * KT) * a.ldD, eb = (int64_t(a.u0) + kb * KT) * d_in;
-        const int ra = live ? KT * a.ldD * 2 : 0, rb = live ? int(KT * d_in * 2) : 0;
-        d.ah = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Dh + ea), 0, ra, 0x00020000);
-        d.al = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Dl + ea), 0, ra, 0x00020000);
-        d.bh = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Uh + eb), 0, rb, 0x00020000);
-        d.bl = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Ul + eb), 0, rb, 0x00020000);
+        const int ra = ahead > 0 ? step_a * 2 : 0, rb = ahead > 0 ? step_b * 2 : 0;
+        --ahead;
+        d.ah = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(pah), 0, ra, 0x00020000);
+        d.al = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(pal), 0, ra, 0x00020000);
+        d.bh = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(pbh), 0, rb, 0x00020000);
+        d.bl = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(pbl), 0, rb, 0x00020000);
+        pah += step_a;
+        pal += step_a;
+        pbh += step_b;
+        pbl += step_b;
         return d;
     };
-    // load number i (0..5) of a k-step into the slot at LDS byte address dst
+    // load number i of a k-step into the slot at LDS byte address dst
     auto gload1 = [&](const Desc& d, uint32_t dst, int i) __attribute__((always_inline)) {
-        if (i == 0) lds_load16(dst + OFF_AH + wave * 1024, voff_a, d.ah);
-        else if (i == 1) lds_load16(dst + OFF_AL + wave * 1024, voff_a, d.al);
-        else if (i == 2) lds_load16(dst + OFF_BH + wave * 2048, voff_b[0], d.bh);
-        else if (i == 3) lds_load16(dst + OFF_BH + wave * 2048 + 1024, voff_b[1], d.bh);
-        else if (i == 4) lds_load16(dst + OFF_BL + wave * 2048, voff_b[0], d.bl);
-        else lds_load16(dst + OFF_BL + wave * 2048 + 1024, voff_b[1], d.bl);
+        if (i < S::A_LPW) {
+            if (MT == 2) lds_load16(dst + (i == 0 ? OFF_AH : OFF_AL) + wave * 1024, voff_a, i == 0 ? d.ah : d.al);
+            else if (wave < 2) lds_load16(dst + OFF_AH + wave * 1024, voff_a, d.ah);
+            else lds_load16(dst + OFF_AL + (wave - 2) * 1024, voff_a, d.al);
+        } else {
+            const int q = (i - S::A_LPW) % (NT / 2);
+            const bool hi = i - S::A_LPW < NT / 2;
+            lds_load16(dst + (hi ? OFF_BH : OFF_BL) + (wave * (NT / 2) + q) * 1024, voff_b[q], hi ? d.bh : d.bl);
+        }
     };
 
     // transpose-read addressing: within 16 lanes, lane 4 k + c reads 8 bytes of panel row k at byte 8 c of a
@@ -1079,53 +1104,55 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     const int i16 = lane & 15, g16 = (lane >> 4) & 1, kb8 = lane >> 5;
     const int kq = i16 >> 2;
     const int lo = (2 * g16 + ((i16 & 3) >> 1)) * 16 + (i16 & 1) * 8;
-    int fa[2], fb[4];
+    int fa[MT], fb[NT];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) fa[m] = OFF_AH + (kb8 * 8 + kq) * A_ROWB + (((wr * 2 + m) ^ kq) << 6) + lo;
+    for (int m = 0; m < MT; ++m)
+        fa[m] = OFF_AH + (kb8 * 8 + kq) * A_ROWB + (((wr * MT + m) ^ (MT == 2 ? kq : kq >> 1)) << 6) + lo;
 #pragma unroll
-    for (int n = 0; n < 4; ++n) fb[n] = OFF_BH + (kb8 * 8 + kq) * B_ROWB + wc * 256 + ((n ^ kq) << 6) + lo;
+    for (int n = 0; n < NT; ++n) fb[n] = OFF_BH + (kb8 * 8 + kq) * B_ROWB + (((wc * NT + n) ^ kq) << 6) + lo;
 
     struct Frags {
-        half8v ah[2], al[2], bh[4], bl[4];
+        half8v ah[MT], al[MT], bh[NT], bl[NT];
     };
     auto rd2 = [&](const char* p, int rowb) __attribute__((always_inline)) {
         short4v x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ONECOMP_LDS short4v*)(p));
         short4v x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ONECOMP_LDS short4v*)(p + 4 * rowb));
         return __builtin_bit_cast(half8v, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    // fragment r (0..11) of the slot at tl + sb, in the order the MFMAs use them
+    constexpr int N_FRAGS = 2 * (MT + NT), N_MMA = 3 * MT * NT;
+    // fragment r of the slot at tl + sb, in the order the MFMAs use them
     auto rd = [&](Frags& f, int r, int sb) __attribute__((always_inline)) {
         const char* s = tl + sb;
         if (r == 0) f.al[0] = rd2(s + fa[0] + A_PANELB, A_ROWB);
-        else if (r <= 4) f.bh[r - 1] = rd2(s + fb[r - 1], B_ROWB);
-        else if (r == 5) f.ah[0] = rd2(s + fa[0], A_ROWB);
-        else if (r <= 9) f.bl[r - 6] = rd2(s + fb[r - 6] + B_PANELB, B_ROWB);
-        else if (r == 10) f.al[1] = rd2(s + fa[1] + A_PANELB, A_ROWB);
-        else f.ah[1] = rd2(s + fa[1], A_ROWB);
+        else if (r <= NT) f.bh[r - 1] = rd2(s + fb[r - 1], B_ROWB);
+        else if (r == NT + 1) f.ah[0] = rd2(s + fa[0], A_ROWB);
+        else if (r <= 2 * NT + 1) f.bl[r - NT - 2] = rd2(s + fb[r - NT - 2] + B_PANELB, B_ROWB);
+        else if (r == 2 * NT + 2) f.al[MT - 1] = rd2(s + fa[MT - 1] + A_PANELB, A_ROWB);
+        else f.ah[MT - 1] = rd2(s + fa[MT - 1], A_ROWB);
     };
 
-    // prologue: k-steps 0 .. 2 in flight, then the W tile (scaled by the exact power of two f_d f_u) straight into
+    // prologue: the ring's k-steps in flight, then the W tile (scaled by the exact power of two f_d f_u) straight into
     // the accumulators; register r of lane l is row (r/4)*8 + (l/32)*4 + r%4, column l%32 of a 32 x 32 tile
     for (int kb = 0; kb < NBUF; ++kb)
         if (kb < n_kb) {
-            const Desc d = make_desc(kb, true);
+            const Desc d = next_desc();
 #pragma unroll
-            for (int i = 0; i < 6; ++i) gload1(d, lds0 + kb * STAGEB, i);
+            for (int i = 0; i < LPW; ++i) gload1(d, lds0 + kb * STAGEB, i);
         }
     const float f_all = a.sc->f_all, f_inv = a.sc->f_inv;
-    float16v acc[2][4];
+    float16v acc[MT][NT];
     const int lr = (lane >> 5) * 4, lc = lane & 31;
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int n = 0; n < 4; ++n)
+        for (int n = 0; n < NT; ++n)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 if constexpr (FROM_ZERO) {
                     acc[m][n][r] = 0.f;
                 } else {
-                    const int rr = min(m0 + wr * 64 + m * 32 + (r / 4) * 8 + lr + (r % 4), d_out - 1);
-                    const int cc = min(n0 + wc * 128 + n * 32 + lc, c1 - 1);
+                    const int rr = min(m0 + wr * (32 * MT) + m * 32 + (r / 4) * 8 + lr + (r % 4), d_out - 1);
+                    const int cc = min(n0 + wc * (32 * NT) + n * 32 + lc, c1 - 1);
                     acc[m][n][r] = a.Wf[int64_t(rr) * d_in + cc] * f_all;
                 }
             }
@@ -1133,15 +1160,14 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     __syncthreads();
     Frags Fc, FH;
 #pragma unroll
-    for (int r = 0; r < 12; ++r) rd(Fc, r, 0);
+    for (int r = 0; r < N_FRAGS; ++r) rd(Fc, r, 0);
     __syncthreads();   // slot 0 is overwritten by the loads of the first half-iteration
 
-    // the 24 MFMAs of one k-step: per row tile m the products lo*hi, hi*lo, hi*hi against the four column tiles,
-    // consecutive MFMAs on different accumulators; `between(i)` is placed behind MFMA i
+    // the MFMAs of one k-step: per row tile m the products lo*hi, hi*lo, hi*hi against the column tiles, consecutive MFMAs on different accumulators; `between(i)` is placed behind MFMA i
     auto mma = [&](const Frags& f, auto&& between) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 24; ++i) {
-            const int m = i / 12, p = (i % 12) / 4, n = i % 4;
+        for (int i = 0; i < N_MMA; ++i) {
+            const int m = i / (3 * NT), p = i % (3 * NT) / NT, n = i % NT;
             if (p == 0) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.al[m], f.bh[n], acc[m][n], 0, 0, 0);
             else if (p == 1) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.ah[m], f.bl[n], acc[m][n], 0, 0, 0);
             else acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.ah[m], f.bh[n], acc[m][n], 0, 0, 0);
@@ -1150,6 +1176,18 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         }
     };
 
+    // what goes behind MFMA i of a k-step: a fragment of the next one or a load
+    auto beside = [&](Frags& f, int i, int sb, const Desc& d, uint32_t dst) __attribute__((always_inline)) {
+        if constexpr (N_MMA >= 2 * N_FRAGS) {
+            if ((i & 1) == 0) rd(f, i / 2, sb);
+            else if (i / 2 < LPW) gload1(d, dst, i / 2);
+        } else {
+            rd(f, i, sb);
+            if (i < LPW) gload1(d, dst, i);
+        }
+    };
+    static_assert(N_MMA >= N_FRAGS && N_FRAGS >= LPW, "every fragment and every load has its place");
+
     int s0 = 0;   // slot of k-step kb
 #pragma unroll 1
     for (int kb = 0; kb < n_kb; kb += 2) {
@@ -1157,25 +1195,23 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         // Loads and fragment reads past the last k-step are not branched around: the loads get an empty
         // descriptor (they deposit zeros into a slot nobody reads again), the reads fetch stale data nobody uses.
         {   // k-step kb from Fc; fragments of kb+1 -> FH; loads of kb+NBUF -> slot s0
-            const Desc d = make_desc(kb + NBUF, kb + NBUF < n_kb);
+            const Desc d = next_desc();
             const uint32_t dst = lds0 + s0 * STAGEB;
             const int sb = s1 * STAGEB;
             mma(Fc, [&](int i) __attribute__((always_inline)) {
-                if ((i & 1) == 0) rd(FH, i / 2, sb);
-                else if (i < 12) gload1(d, dst, i / 2);
+                beside(FH, i, sb, d, dst);
             });
-            __builtin_amdgcn_s_waitcnt(wait_vmcnt(6 * (NBUF - 2)));   // k-step kb+2 has landed
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NBUF - 2)));   // k-step kb+2 has landed
             __syncthreads();
         }
         {   // k-step kb+1 from FH; fragments of kb+2 -> Fc; loads of kb+1+NBUF -> slot s1
-            const Desc d = make_desc(kb + 1 + NBUF, kb + 1 + NBUF < n_kb);
+            const Desc d = next_desc();
             const uint32_t dst = lds0 + s1 * STAGEB;
             const int sb = s2 * STAGEB;
             mma(FH, [&](int i) __attribute__((always_inline)) {
-                if ((i & 1) == 0) rd(Fc, i / 2, sb);
-                else if (i < 12) gload1(d, dst, i / 2);
+                beside(Fc, i, sb, d, dst);
             });
-            __builtin_amdgcn_s_waitcnt(wait_vmcnt(6 * (NBUF - 2)));   // k-step kb+3 has landed
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NBUF - 2)));   // k-step kb+3 has landed
             __syncthreads();
         }
         s0 = s2;
@@ -1183,13 +1219,13 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the workgroup ends
     // uniform branch: interior tiles store without per-element masks
     if ((m0 + TM <= d_out) && (n0 + TN <= c1)) {
-        float* wp = a.Wf + int64_t(m0 + wr * 64 + lr) * d_in + n0 + wc * 128 + lc;
+        float* wp = a.Wf + int64_t(m0 + wr * (32 * MT) + lr) * d_in + n0 + wc * (32 * NT) + lc;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
+        for (int m = 0; m < MT; ++m) {
             if constexpr (FROM_ZERO) {
                 // the tile's current values: 32 independent loads at a time (the operand registers are free now)
 #pragma unroll
-                for (int n2 = 0; n2 < 4; n2 += 2) {
+                for (int n2 = 0; n2 < NT; n2 += 2) {
                     float16v old[2];
 #pragma unroll
                     for (int n = 0; n < 2; ++n)
@@ -1205,7 +1241,7 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
                 }
             } else {
 #pragma unroll
-                for (int n = 0; n < 4; ++n)
+                for (int n = 0; n < NT; ++n)
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         wp[int64_t(m * 32 + (r / 4) * 8 + (r % 4)) * d_in + n * 32] = acc[m][n][r] * f_inv;
@@ -1218,8 +1254,8 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
             for (int n = 0; n < 4; ++n)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int rr = m0 + wr * 64 + m * 32 + (r / 4) * 8 + lr + (r % 4);
-                    const int cc = n0 + wc * 128 + n * 32 + lc;
+                    const int rr = m0 + wr * (32 * MT) + m * 32 + (r / 4) * 8 + lr + (r % 4);
+                    const int cc = n0 + wc * (32 * NT) + n * 32 + lc;
                     if (rr < d_out && cc < c1) {
                         float* q = a.Wf + int64_t(rr) * d_in + cc;
                         if constexpr (FROM_ZERO) *q = __builtin_fmaf(acc[m][n][r], f_inv, *q);
@@ -1229,10 +1265,10 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     }
 }
 
-template <bool FROM_ZERO>
+template <typename S, bool FROM_ZERO>
 __global__ __launch_bounds__(256, 2) void trailing_kernel(TrailArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
-    trailing_tile<3, FROM_ZERO>(a, blockIdx.x, dyn_lds);
+    trailing_tile<S, FROM_ZERO>(a, blockIdx.x, dyn_lds);
 }
 
 // One launch = the panel sweep of a super-block next to the far update of the previous super-block on the
@@ -1244,7 +1280,7 @@ template <int GB, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void panel_far_kernel(PanelArgs pa, TrailArgs ta, int n_panel) {
     extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
     if (int(blockIdx.x) < n_panel) panel_body<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
-    else trailing_tile<3, true>(ta, blockIdx.x - n_panel, dyn_lds);
+    else trailing_tile<TrailBig, true>(ta, blockIdx.x - n_panel, dyn_lds);
 }
 
 // Scale and zero-point of one wide group (columns g0 .. g0 + G - 1 of every row, G a multiple of 128) from its current
@@ -1448,6 +1484,39 @@ SweepWs carve(void* ws, int64_t d_out, int64_t d_in) {
     return w;
 }
 
+// fills in t's work map; returns the number of workgroups
+template <typename S, bool FROM_ZERO>
+int trail_grid(TrailArgs& t) {
+    t.n_mt = int(ceil_div(t.d_out, S::TM));
+    if (FROM_ZERO) {
+        t.n_nt = int(ceil_div(t.c1 - t.c0, S::TN));
+    } else {
+        t.n_nt0 = t.h0 > t.c0 ? int(ceil_div(t.h0 - t.c0, S::TN)) : 0;
+        t.n_nt = t.n_nt0 + (t.c1 > t.h1 ? int(ceil_div(t.c1 - t.h1, S::TN)) : 0);
+    }
+    t.chunk = int(ceil_div(int64_t(t.n_mt) * t.n_nt, 8));
+    return t.chunk * 8;
+}
+template <typename S, bool FROM_ZERO>
+onecomp_status launch_trailing_shape(TrailArgs t, hipStream_t stream) {
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<S, FROM_ZERO>), int(S::LDS_BYTES), lds_ok) != ONECOMP_OK)
+        return ONECOMP_ERR_HIP;
+    const int wgs = trail_grid<S, FROM_ZERO>(t);
+    hipLaunchKernelGGL((trailing_kernel<S, FROM_ZERO>), dim3(unsigned(wgs)), dim3(256), S::LDS_BYTES, stream, t);
+    ONECOMP_CHECK_LAUNCH();
+    return ONECOMP_OK;
+}
+// The 128 x 256 tiles move half the operand bytes per flop, but a launch of few of them is as long as one tile on a CU of its
+// own.  us of a launch, 128 x 256 : 64 x 128 tiles, d_out 4096 (64 of the former), 512 columns: K 512 22.6 : 13.9, K 128 13 :
+// 7.5; d_out 8192 (128 tiles), 512 columns, K 512 32.0 : 26.6.  Whole sweep, 4096 columns, d_out 10240 (160 tiles) 1193 : 1193,
+// 14336 (224) 1441 : 1457.
+template <bool FROM_ZERO>
+onecomp_status launch_trailing(TrailArgs t, hipStream_t stream) {
+    return 2 * trail_grid<TrailBig, FROM_ZERO>(t) <= device_cus() ? launch_trailing_shape<TrailSmall, FROM_ZERO>(t, stream)
+                                                                  : launch_trailing_shape<TrailBig, FROM_ZERO>(t, stream);
+}
+
 template <int GB, bool DIRECT>
 onecomp_status launch_panel(const PanelArgs& pa, const TrailArgs& ta, int far_wgs, hipStream_t stream) {
     static std::atomic<uint64_t> lds_ok{0};
@@ -1483,21 +1552,12 @@ onecomp_status split_update_around(float* C, int64_t d_out, int64_t d_in, const 
                                    int64_t ldD, const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int ek, int K,
                                    int u0, int c0, int h0, int h1, int c1, hipStream_t stream) {
     if ((h0 <= c0 && c1 <= h1) || K <= 0) return ONECOMP_OK;
-    static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<false>), int(tg::LDS_BYTES), lds_ok) != ONECOMP_OK)
-        return ONECOMP_ERR_HIP;
     TrailArgs t;
     t.Wf = C; t.Dh = Dh; t.Dl = Dl; t.Uh = Bh; t.Ul = Bl; t.sc = sc;
     t.d_out = int(d_out); t.ldD = int(ldD); t.d_in = int(d_in);
     t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
-    t.n_mt = int(ceil_div(d_out, tg::TM));
     t.h0 = h0; t.h1 = h1;
-    t.n_nt0 = h0 > c0 ? int(ceil_div(h0 - c0, tg::TN)) : 0;
-    t.n_nt = t.n_nt0 + (c1 > h1 ? int(ceil_div(c1 - h1, tg::TN)) : 0);
-    t.chunk = int(ceil_div(int64_t(t.n_mt) * t.n_nt, 8));
-    hipLaunchKernelGGL(trailing_kernel<false>, dim3(unsigned(t.chunk * 8)), dim3(256), tg::LDS_BYTES, stream, t);
-    ONECOMP_CHECK_LAUNCH();
-    return ONECOMP_OK;
+    return launch_trailing<false>(t, stream);
 }
 
 int64_t split_update_ld(int64_t d_out) { return ld_d(d_out); }
@@ -1536,14 +1596,11 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
                        int(d_in), w.sc, w.Uh, w.Ul);
     ONECOMP_CHECK_LAUNCH();
 
-    static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<true>), int(tg::LDS_BYTES), lds_ok) != ONECOMP_OK)
-        return ONECOMP_ERR_HIP;
     TrailArgs t;
     t.Wf = w.Wf; t.Dh = w.Dh; t.Dl = w.Dl; t.Uh = w.Uh; t.Ul = w.Ul; t.sc = w.sc;
     t.ek = 0; t.K = 0; t.u0 = 0; t.c0 = 0; t.c1 = 0; t.n_nt = 0; t.chunk = 0;
     t.d_out = int(d_out); t.ldD = int(ld_d(d_out)); t.d_in = int(d_in);
-    t.n_mt = int(ceil_div(d_out, tg::TM));
+    t.n_nt0 = 0; t.h0 = 0; t.h1 = 0;
     // fills t for Wf[:, c0 .. c1) += residual columns ek .. ek+K of buffer `buf` times rows u0 .. u0+K of Un;
     // returns the number of workgroups (0: nothing to do)
     const size_t d_buf = size_t(SBIG) * ld_d(d_out);
@@ -1551,16 +1608,10 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
         if (c1 <= c0) return 0;
         t.Dh = w.Dh + buf * d_buf; t.Dl = w.Dl + buf * d_buf;
         t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
-        t.n_nt = int(ceil_div(c1 - c0, tg::TN));
-        t.chunk = int(ceil_div(int64_t(t.n_mt) * t.n_nt, 8));
-        return t.chunk * 8;
+        return trail_grid<TrailBig, true>(t);
     };
     auto trailing = [&](int buf, int ek, int K, int u0, int c0, int c1) -> onecomp_status {
-        const int wgs = set_trailing(buf, ek, K, u0, c0, c1);
-        if (wgs == 0) return ONECOMP_OK;
-        hipLaunchKernelGGL(trailing_kernel<true>, dim3(unsigned(wgs)), dim3(256), tg::LDS_BYTES, stream, t);
-        ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
+        return set_trailing(buf, ek, K, u0, c0, c1) == 0 ? ONECOMP_OK : launch_trailing<true>(t, stream);
     };
 
     onecomp_status st;

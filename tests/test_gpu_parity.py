@@ -1220,6 +1220,27 @@ def test_factor_order_of_nan_diagonal():
     assert torch.equal(perm.long(), torch.argsort(keys, descending=True, stable=True))
 
 
+@pytest.mark.parametrize("d_in,group,form,dtype", [
+    (1152, 128, "inverse", torch.bfloat16),   # super-blocks of 512, 512 and 128 columns
+    (1280, 1280, "block", torch.float32),     # one group per row, a last super-block of 256
+])
+def test_sweep_tile_shapes_agree(d_in, group, form, dtype):
+    """Rows are independent, so the first ones of a layer whose updates take 128 x 256 tiles are those of a short layer, whose
+    updates take 64 x 128 ones: the same products in the same order.  (The largest weight, which sets a scale, is in row 0.)"""
+    _announce(f"tile shapes of the updates, d_in={d_in} {form}")
+    cfg = synth.scaled(synth.CONFIGS["c2"], d_out=16500, d_in=d_in, n_tokens=16, seed=71, dtype=dtype)
+    W = synth.make_weight(cfg, DEV)
+    W[0, 0] = 2.0 * W.abs().max()
+    H = torch.from_numpy(_oracle_H32(d_in, 512, seed=72)).to(DEV)
+    F, _, info = og.onecomp_hessian_factor(H, 0.1, form=form)
+    assert int(info.item()) == 0
+    whole = og.onecomp_quantize_layer(W, F, 4, group, form=form)
+    for rows in (1, 64, 93, 200):
+        part = og.onecomp_quantize_layer(W[:rows].contiguous(), F, 4, group, form=form)
+        for k in ("Q_codes", "scales", "zeros", "W_hat"):
+            assert torch.equal(part[k], whole[k][:rows]), (rows, k)
+
+
 @pytest.mark.parametrize("bits,G,d_out,d_in,dtype,grid", [
     (4, 4224, 5, 4224, torch.float32, "symmetric_mse"),     # one group per row, two chunks of values in LDS
     (3, 640, 37, 1280, torch.bfloat16, "minmax_mse"),       # groups of five blocks, the second one on compensated values
