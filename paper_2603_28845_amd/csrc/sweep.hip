@@ -883,6 +883,440 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
     if (saturated) *a.sat = 1u;
 }
 
+// ------------------------------------------------------------------------------------------
+// The panel with 16 rows per workgroup and 16 lanes per row, two of an inner block's 32 columns each, for layers whose
+// workgroups of 64 rows would leave most CUs idle.  The steps of a row, and what reaches an entry of it in which order, are
+// panel_body's, so the results are bit-equal; what a wave does besides the chain of steps (codes, errors, residuals, grids,
+// feedback sums) is a quarter: a block of 128 columns takes 13 us instead of 20.
+//   near update   one 32-row tile whose rows 16 .. 31 repeat rows 0 .. 15 (its results are not taken)
+//   sequential    the current column reaches the row's lanes as one DPP move (row_newbcast) of 64 bits
+//   inner update  all 16 rows in one tile, the waves take 32 columns each, between two barriers
+// LDS: sU, sRd, sC as there; sUd the diagonal sub-blocks in fp64, zeros up to the diagonal, rows 0 .. 15 whole, of rows 16 ..
+// 31 the last 16 columns, and zeros for the lanes of the other ones.  The diagonal sub-blocks come in where sC will be (inverse
+// form), or behind it (block form).  Two workgroups fit on a CU in either.
+// No scale search (its sums would be added in another order): groups whose search runs in the panel take panel_body.
+// ------------------------------------------------------------------------------------------
+constexpr int ROWS16 = 16, F16_BYTES = 3 * 8 * 2 * ROWS16 * 8 * 2;   // .. of residual fragments, hi or lo, per workgroup
+constexpr int UD16 = 16 * IB + 16 * 16, UD16_ZERO = 16 * 16;   // doubles of a diagonal sub-block, and of the zeros behind the four
+constexpr int L16_RD = LDS_UD + (4 * UD16 + UD16_ZERO) * 8, L16_C = L16_RD + SB * 8, L16_C_BYTES = ROWS16 * SP * 4;
+constexpr int panel16_lds(bool direct) { return L16_C + (direct ? L16_C_BYTES + 4 * UB * 4 : 4 * UB * 4); }
+static_assert(L16_C_BYTES <= 4 * UB * 4 && L16_C_BYTES % 16 == 0, "the diagonal sub-blocks as they come in cover sC");
+static_assert(panel16_lds(true) <= 80 * 1024, "a second workgroup fits beside a panel's");
+
+// value of lane J of every 16 lanes, in all of them.  A DPP operand must not come from the two instructions before, which the
+// compiler does not see into the statement: it keeps that distance itself.
+template <int J>
+__device__ __forceinline__ double row_bcast(double v) {
+    double o;
+    asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(o) : "v"(v), "n"(J));
+    return o;
+}
+constexpr int ROW_ROR = 0x120, ROW_HALF_MIRROR = 0x141;   // DPP: rotation in 16 lanes (+ distance), mirror in 8
+
+template <int GB, bool DIRECT>
+__device__ __forceinline__ void panel_body16(const PanelArgs& a, const int wg, char* psm) {
+    float* const sU = reinterpret_cast<float*>(psm);
+    double* const sUd = reinterpret_cast<double*>(psm + LDS_UD);
+    double* const sRd = reinterpret_cast<double*>(psm + L16_RD);
+    float* const sC = reinterpret_cast<float*>(psm + L16_C);
+    constexpr int LDS_DIAG = DIRECT ? L16_C + L16_C_BYTES : L16_C;
+    const float* const sUg = reinterpret_cast<const float*>(psm + LDS_DIAG);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r0 = wg * ROWS16;
+    const int64_t d_in = a.d_in;
+    const int G = 1 << a.lgG;
+    const int srow = tid >> 4, sl = tid & 15;   // sequential part: row, slice of two columns
+    const int grow = min(r0 + srow, a.d_out - 1);
+    const bool row_ok = (r0 + srow) < a.d_out;
+    const int lr = (lane >> 5) * 4, lc = lane & 31;   // 32 x 32 accumulators: register r = row (r/4)*8 + lr + r%4, column lc
+    const double qmax = double(a.qmax), qsd = double(a.qs);
+    const float f_d = a.sc->f_d, f_inv = a.sc->f_inv;
+    const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)psm));
+    uint16_t* const Fh = a.Fh + int64_t(wg) * (F16_BYTES / 2);
+    uint16_t* const Fl = a.Fl + int64_t(wg) * (F16_BYTES / 2);
+    double s = 1.0, rs = 1.0, z = 0.0;
+    double lossacc = 0.0;   // of this lane's columns
+    bool saturated = false;
+    if (a.wide_g >= 0) {
+        s = a.s64[grow];
+        z = double(a.zeros[int64_t(grow) * a.n_g + a.wide_g]);
+        rs = 1.0 / s;
+    }
+    static_assert(UD16_ZERO == 256, "a zero per thread");
+    sUd[4 * UD16 + tid] = 0.0;
+
+#pragma unroll 1
+    for (int b = 0; b < a.nb; ++b) {
+        const int j0 = a.s0 + b * SB;
+        __syncthreads();   // everybody is done with the previous block's tiles
+        {   // U's diagonal block -> LDS as in panel_body
+            const float* ub = a.U + int64_t(j0) * d_in + j0;
+            const __amdgpu_buffer_rsrc_t rsrc =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ub), 0, int((int64_t(SB - 1) * d_in + SB) * 4), 0x00020000);
+#pragma unroll
+            for (int q = 0; q < 10; ++q) {
+                const int t = q < 6 ? 6 * wave + q : 4 * wave + q - 6, blk = t >> 2;
+                const int I = q < 6 ? (blk >= 3) + (blk >= 5) : wave, J = q < 6 ? (blk < 3 ? blk + 1 : blk < 5 ? blk - 1 : 3) : wave;
+                const int row = 32 * I + 8 * (t & 3) + (lane >> 3);
+                lds_load16(lds0 + (q < 6 ? 0 : LDS_DIAG) + t * 1024, uint32_t((row * int(d_in) + 32 * J + (lane & 7) * 4) * 4), rsrc);
+            }
+        }
+        float w0v[8];   // original weights: columns 32 q + 2 sl + i of the block in w0v[2 q + i]
+        {
+            float cf[8];
+            float16v acc;
+            const int rows = min(ROWS16, a.d_out - r0), col = j0 + 32 * wave + lc;
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0,
+                                                                                  int(rows * d_in * 4), 0x00020000);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {   // rows past d_out read the last one
+                const plan::FeedbackOffset o = plan::panel_feedback_offset<false>(rows, int(d_in), lane, 0, r, col);
+                cf[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o.lane, o.scalar, 0));
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            if (a.w0_bf16) {
+                const uint16_t* wp = static_cast<const uint16_t*>(a.W0) + int64_t(grow) * d_in + j0 + 2 * sl;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w0v[2 * q] = __uint_as_float(*reinterpret_cast<const uint32_t*>(wp + 32 * q));
+            } else {
+                const float* wp = static_cast<const float*>(a.W0) + int64_t(grow) * d_in + j0 + 2 * sl;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float2 v = *reinterpret_cast<const float2*>(wp + 32 * q);
+                    w0v[2 * q] = v.x;
+                    w0v[2 * q + 1] = v.y;
+                }
+            }
+            if (b > 0) {
+                constexpr int WIN = 4, B_BYTES = 6 * 8 * 4 * 64 * 16, DESC = 0x00020000;
+                uint4v win[WIN][4];
+                const __amdgpu_buffer_rsrc_t rfh = __builtin_amdgcn_make_buffer_rsrc(Fh, 0, F16_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rfl = __builtin_amdgcn_make_buffer_rsrc(Fl, 0, F16_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rbh = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Bh), 0, B_BYTES, DESC);
+                const __amdgpu_buffer_rsrc_t rbl = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.Bl), 0, B_BYTES, DESC);
+                const int b0 = ((b * (b - 1) / 2) * 8 * 4 + wave) * 1024;
+                const int va = (lane >> 5) * 256 + (lane & 15) * 16, vb = lane * 16;
+                auto issue = [&](int bp, int ks, uint4v(&d)[4]) __attribute__((always_inline)) {
+                    const int fo = (bp * 8 + ks) * 512, bo = b0 + (bp * 8 + ks) * 4 * 1024;
+                    d[0] = __builtin_amdgcn_raw_buffer_load_b128(rfl, va, fo, 0);
+                    d[1] = __builtin_amdgcn_raw_buffer_load_b128(rfh, va, fo, 0);
+                    d[2] = __builtin_amdgcn_raw_buffer_load_b128(rbh, vb, bo, 0);
+                    d[3] = __builtin_amdgcn_raw_buffer_load_b128(rbl, vb, bo, 0);
+                };
+#pragma unroll
+                for (int ks = 0; ks < WIN; ++ks) issue(0, ks, win[ks]);
+#pragma unroll 1
+                for (int bp = 0; bp < b; ++bp) {
+                    const bool more = bp + 1 < b;
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks) {
+                        uint4v(&cur)[4] = win[ks % WIN];
+                        const half8v al = __builtin_bit_cast(half8v, cur[0]), ah = __builtin_bit_cast(half8v, cur[1]);
+                        const half8v bh = __builtin_bit_cast(half8v, cur[2]), bl = __builtin_bit_cast(half8v, cur[3]);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc, 0, 0, 0);
+                        if (ks + WIN < 8) issue(bp, ks + WIN, cur);
+                        else if (more) issue(bp + 1, ks + WIN - 8, cur);
+                    }
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) cf[r] = __builtin_fmaf(acc[r], f_inv, cf[r]);
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // the direct loads have landed
+            __syncthreads();
+            {   // sub-block (wave, wave) for the sequential part
+                const float* ug = sUg + wave * UB;
+                if (lane < IB) sRd[32 * wave + lane] = 1.0 / double(ug[lane * (IB + 1)]);
+                wave_fence();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int id = q * 64 + lane, j = id >> 3, k0 = (id & 7) * 4;
+                    const float4v v = *reinterpret_cast<const float4v*>(ug + 4 * id);
+                    const double rd = sRd[32 * wave + j];
+                    double2 lo, hi;
+                    lo.x = k0 > j ? double(v[0]) * rd : 0.0;
+                    lo.y = k0 + 1 > j ? double(v[1]) * rd : 0.0;
+                    hi.x = k0 + 2 > j ? double(v[2]) * rd : 0.0;
+                    hi.y = k0 + 3 > j ? double(v[3]) * rd : 0.0;
+                    if (j < 16 || k0 >= 16) {
+                        double2* const dst = reinterpret_cast<double2*>(sUd + wave * UD16 + (j < 16 ? j * IB + k0 : 16 * j + 256 + k0 - 16));
+                        dst[0] = lo;
+                        dst[1] = hi;
+                    }
+                }
+            }
+            if (a.w0_bf16)
+#pragma unroll
+                for (int q = 3; q >= 0; --q) {
+                    const uint32_t v = __float_as_uint(w0v[2 * q]);
+                    w0v[2 * q] = __uint_as_float(v << 16);
+                    w0v[2 * q + 1] = __uint_as_float(v & 0xFFFF0000u);
+                }
+            __syncthreads();
+            auto to_lds = [&](auto&& v) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) sC[((r / 4) * 8 + lr + (r % 4)) * SP + 32 * wave + lc] = v(r);
+            };
+            if constexpr (!DIRECT) {
+                to_lds([&](int r) __attribute__((always_inline)) { return cf[r]; });
+            } else {
+                // (c / diag) U_bb as in panel_body, a column tile per wave
+                float16v c0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) c0[r] = 0.f;
+                if (j0 > 0) {
+                    const float rd = float(sRd[32 * wave + lc]);
+                    to_lds([&](int r) __attribute__((always_inline)) { return cf[r] * rd; });
+                    __syncthreads();
+                    const float* ap = sC + (lc & 15) * SP + (lane >> 5);
+#pragma unroll 1
+                    for (int ch = 0; ch <= wave; ++ch) {
+                        const float* bp = (ch == wave ? sUg + ch * UB : sU + u_off(ch, wave)) + (lane >> 5) * IB + lc;
+                        float av[16], bv[16];
+#pragma unroll
+                        for (int kk = 0; kk < 16; ++kk) {
+                            av[kk] = ap[32 * ch + 2 * kk];
+                            bv[kk] = bp[2 * kk * IB];
+                        }
+#pragma unroll
+                        for (int kk = 0; kk < 16; ++kk) c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[kk], bv[kk], c0, 0, 0, 0);
+                    }
+                    __syncthreads();   // every wave is done reading sC as an operand
+                }
+                to_lds([&](int r) __attribute__((always_inline)) { return c0[r]; });
+            }
+            __syncthreads();
+        }
+
+#pragma unroll 1
+        for (int jb = 0; jb < SB; jb += IB) {
+            float* const crow = sC + srow * SP + jb + 2 * sl;
+            double w[2] = {double(w0v[0]) + double(crow[0]), double(w0v[1]) + double(crow[1])};
+            double s_first = s, z_first = z;   // GB == 16: the grid of the inner block's first group
+            auto fix_grid = [&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                const int col = j0 + jb + j;
+                double mn, mx;
+                if constexpr (GB == 16) {   // the 16 columns of lanes 8 (j / 16) .. + 7
+                    mn = fmin(w[0], w[1]);
+                    mx = fmax(w[0], w[1]);
+                    mn = fmin(mn, dpp_quad<QUAD_SWAP1>(mn));
+                    mx = fmax(mx, dpp_quad<QUAD_SWAP1>(mx));
+                    mn = fmin(mn, dpp_quad<QUAD_SWAP2>(mn));
+                    mx = fmax(mx, dpp_quad<QUAD_SWAP2>(mx));
+                    mn = fmin(mn, dpp_quad<ROW_HALF_MIRROR>(mn));
+                    mx = fmax(mx, dpp_quad<ROW_HALF_MIRROR>(mx));
+                    mn = row_bcast<j / 2>(mn);
+                    mx = row_bcast<j / 2>(mx);
+                } else {
+                    if (a.wide_g >= 0 || (col & (G - 1)) != 0) return;   // uniform: the group's G <= 128 columns are unfinished
+                    mn = fmin(w[0], w[1]);
+                    mx = fmax(w[0], w[1]);
+#pragma unroll
+                    for (int k = 2; k < 8; ++k) {   // two values per inner block that the group spans
+                        if (k % 2 == 0 && 16 * k >= G) break;
+                        const double v = double(w0v[k]) + double(crow[(k >> 1) * IB + (k & 1)]);
+                        mn = fmin(mn, v);
+                        mx = fmax(mx, v);
+                    }
+                    mn = fmin(mn, dpp_quad<ROW_ROR + 8>(mn));
+                    mx = fmax(mx, dpp_quad<ROW_ROR + 8>(mx));
+                    mn = fmin(mn, dpp_quad<ROW_ROR + 4>(mn));
+                    mx = fmax(mx, dpp_quad<ROW_ROR + 4>(mx));
+                    mn = fmin(mn, dpp_quad<ROW_ROR + 2>(mn));
+                    mx = fmax(mx, dpp_quad<ROW_ROR + 2>(mx));
+                    mn = fmin(mn, dpp_quad<ROW_ROR + 1>(mn));
+                    mx = fmax(mx, dpp_quad<ROW_ROR + 1>(mx));
+                }
+                grid_params(mn, mx, 0, qmax, qsd, s, z);
+                rs = 1.0 / s;
+                if constexpr (GB == 16 && j == 0) { s_first = s; z_first = z; }
+                if (sl == 0 && row_ok) {
+                    a.scales[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(s);
+                    a.zeros[int64_t(grow) * a.n_g + (col >> a.lgG)] = float(z);
+                }
+            };
+            // (w - s (q - z), q - z) of a value on the current grid, see panel_body
+            auto quantize = [&](double v, double sq, double rsq, double zq, double& d) __attribute__((always_inline)) {
+                const double t0 = v * rsq;
+                const double t = __builtin_fma(__builtin_fma(-t0, sq, v), rsq, t0);
+                d = fmin(fmax(rint(t), -zq), qmax - zq);
+                return __builtin_fma(-sq, d, v);
+            };
+            auto pin = [](double& v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); };   // here, in this order
+            // this lane's columns of U's rows 0 .. 15 and 16 .. 31, zero up to the diagonal
+            const double* const ud = sUd + (jb >> 5) * UD16 + 2 * sl;
+            const double* const ud_hi = sUd + (sl >= 8 ? (jb >> 5) * UD16 + 16 * IB + 2 * (sl - 8) : 4 * UD16 + 2 * sl);
+            auto u_row = [&](int j) __attribute__((always_inline)) { return j < 16 ? ud + j * IB : ud_hi + (j - 16) * 16; };
+            {
+                double2 u[3];
+                u[0] = *reinterpret_cast<const double2*>(u_row(0));
+                u[1] = *reinterpret_cast<const double2*>(u_row(1));
+                double res = 0.0;   // of the step before
+                static_for<0, IB>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    auto late = [&]() __attribute__((always_inline)) {   // the other column's update of the step before
+                        if constexpr (j > 0) {
+                            const double2& up = u[(j + 2) % 3];
+                            w[(j + 1) % 2] = __builtin_fma(-res, (j + 1) % 2 ? up.y : up.x, w[(j + 1) % 2]);
+                            pin(w[(j + 1) % 2]);
+                        }
+                    };
+                    constexpr bool fix = j % GB == 0;   // the group's grid needs all values up to date
+                    if constexpr (fix) {
+                        late();
+                        fix_grid(jc);
+                    }
+                    double wj = row_bcast<j / 2>(w[j % 2]);
+                    if constexpr (!fix) late();
+                    double t0 = wj * rs;
+                    pin(t0);
+                    if constexpr (j + 2 < IB) u[(j + 2) % 3] = *reinterpret_cast<const double2*>(u_row(j + 2));
+                    double r1 = __builtin_fma(-t0, s, wj);
+                    pin(r1);
+                    double t = __builtin_fma(r1, rs, t0);
+                    pin(t);
+                    t = fmin(fmax(rint(t), -z), qmax - z);   // pinned, the compiler would quiet NaNs before each of these
+                    res = __builtin_fma(-s, t, wj);
+                    pin(res);
+                    if constexpr (j + 1 < IB) {
+                        const double2& un = u[j % 3];
+                        w[(j + 1) % 2] = __builtin_fma(-res, (j + 1) % 2 ? un.y : un.x, w[(j + 1) % 2]);
+                        pin(w[(j + 1) % 2]);
+                    }
+                });
+            }
+            uint32_t pair[2];   // the residuals, hi in the lower half
+            {
+                const bool first = GB == 16 && sl < 8;
+                const double sq = first ? s_first : s, zq = first ? z_first : z;
+                const double rsq = GB == 16 ? 1.0 / sq : rs;
+                float err[2];
+                uint32_t codes;
+                double loss;
+                bool big;
+                auto settle = [&]() __attribute__((always_inline)) {
+                    codes = 0;
+                    loss = lossacc;
+                    big = false;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        double d;
+                        const double r = quantize(w[i], sq, rsq, zq, d);
+                        const double e = r * sRd[jb + 2 * sl + i];
+                        loss = __builtin_fma(e, e, loss);
+                        err[i] = float(e);
+                        codes |= uint32_t(int(d + zq)) << (8 * i);
+                        float x = -float(DIRECT ? __builtin_fma(-sq, d, double(w0v[i])) : r) * f_d;
+                        big |= !(fabsf(x) <= 60000.f);
+                        x = fminf(fmaxf(x, -60000.f), 60000.f);
+                        const _Float16 h = (_Float16)x;
+                        const _Float16 l = (_Float16)(x - (float)h);
+                        pair[i] = uint32_t(__builtin_bit_cast(uint16_t, h)) | (uint32_t(__builtin_bit_cast(uint16_t, l)) << 16);
+                    }
+                };
+                settle();
+                if (__builtin_expect(__any(!(loss < __builtin_inf())), 0)) {   // see panel_body
+                    w[0] = double(w0v[0]) + double(crow[0]);
+                    w[1] = double(w0v[1]) + double(crow[1]);
+#pragma unroll 1
+                    for (int j = 0; j < IB; ++j) {
+                        const double sg = GB == 16 && j < 16 ? s_first : s, zg = GB == 16 && j < 16 ? z_first : z;
+                        const double rsg = GB == 16 ? 1.0 / sg : rs;
+                        double d;
+                        const double r = quantize(__shfl((j & 1) ? w[1] : w[0], (lane & ~15) + (j >> 1), 64), sg, rsg, zg, d);
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            if (2 * sl + i > j) w[i] = __builtin_fma(-r, u_row(j)[i], w[i]);
+                    }
+                    settle();
+                }
+                lossacc = loss;
+                saturated |= row_ok && big;
+                crow[0] = err[0];
+                crow[1] = err[1];
+                if (row_ok) {
+                    *reinterpret_cast<uint16_t*>(a.Q + int64_t(grow) * d_in + j0 + jb + 2 * sl) = uint16_t(codes);
+                    if (a.W_hat) {
+                        const float sf = float(sq), zf = float(zq);
+                        *reinterpret_cast<float2*>(a.W_hat + int64_t(grow) * d_in + j0 + jb + 2 * sl) =
+                            make_float2(sf * (float(codes & 255u) - zf), sf * (float(codes >> 8) - zf));
+                    }
+                }
+                // A-operand fragments for the near updates: k-step, half of its columns, row, column of the half
+                if (b + 1 < a.nb) {
+                    const int off = ((b * 8 + (jb >> 4) + (sl >> 3)) * 2 + ((sl >> 2) & 1)) * (ROWS16 * 8) + srow * 8 + 2 * (sl & 3);
+                    *reinterpret_cast<uint32_t*>(Fh + off) = __builtin_amdgcn_perm(pair[1], pair[0], 0x05040100u);
+                    *reinterpret_cast<uint32_t*>(Fl + off) = __builtin_amdgcn_perm(pair[1], pair[0], 0x07060302u);
+                }
+            }
+            // Remaining columns of the block, see panel_body: 32 columns per wave
+            if (jb + IB < SB) {
+                __syncthreads();   // the other waves' errors
+                const int I = jb >> 5;
+                if (wave < 3 - I) {
+                    const int l16 = lane & 15, lk = lane >> 4;
+                    const float* const bp = sU + u_off(I, I + 1 + wave) + lk * IB + 2 * l16;
+                    float* const cp = sC + 4 * lk * SP + jb + IB * (1 + wave) + 2 * l16;
+                    float av[8];
+                    float2 bv[8], old[4];
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) {
+                        av[kk] = -sC[l16 * SP + jb + 4 * kk + lk];
+                        bv[kk] = *reinterpret_cast<const float2*>(bp + 4 * kk * IB);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) old[r] = make_float2(cp[r * SP], cp[r * SP + 1]);
+                    float4v c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) {
+                        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk], bv[kk].x, c0, 0, 0, 0);
+                        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk], bv[kk].y, c1, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        cp[r * SP] = old[r].x + c0[r];
+                        cp[r * SP + 1] = old[r].y + c1[r];
+                    }
+                }
+                __syncthreads();
+            }
+            crow[0] = __uint_as_float(pair[0]);
+            crow[1] = __uint_as_float(pair[1]);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) w0v[i] = w0v[i + 2];   // the next inner block's first
+        }
+
+        // ---- block done: the residuals transposed (k-major) for the far update, 8 rows of a column per lane
+        __syncthreads();
+        {
+            const int r8 = 8 * (tid & 1), c = tid >> 1;
+            uint32_t v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __float_as_uint(sC[(r8 + e) * SP + c]);
+            const int64_t off = int64_t(b * SB + c) * a.ldD + r0 + r8;
+            uint4v dh, dl;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dh[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x05040100u);
+                dl[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x07060302u);
+            }
+            *reinterpret_cast<uint4v*>(a.Dh + off) = dh;
+            *reinterpret_cast<uint4v*>(a.Dl + off) = dl;
+        }
+        // the fragments written above are read back by other waves of this workgroup: see panel_body
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o *= 2) lossacc += __shfl_xor(lossacc, o, 16);
+    if (sl == 0 && row_ok) a.rowloss[grow] += float(lossacc);
+    if (saturated) *a.sat = 1u;
+}
+
 // Fragments of the normalized U blocks the panel kernel's near updates multiply with: for super-block S (sbw
 // columns wide, gridDim.x = its number of block pairs), block pair p = b (b - 1) / 2 + b' (b' < b), k-step ks,
 // column tile nt, lane L:
@@ -1276,10 +1710,13 @@ __global__ __launch_bounds__(256, 2) void trailing_kernel(TrailArgs a) {
 // its workgroups are the first of the grid, so they are resident from the start; the update's tiles fill the other
 // CUs, and all of them once the panel is done.  The two parts touch disjoint columns of the working copy, and the
 // panel writes the residual panels of its own super-block into the buffer the update does not read.
-template <int GB, bool DIRECT>
+template <int GB, bool DIRECT, int ROWS_WG>
 __global__ __launch_bounds__(256, 2) void panel_far_kernel(PanelArgs pa, TrailArgs ta, int n_panel) {
     extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
-    if (int(blockIdx.x) < n_panel) panel_body<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
+    if (int(blockIdx.x) < n_panel) {
+        if constexpr (ROWS_WG == ROWS) panel_body<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
+        else panel_body16<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
+    }
     else trailing_tile<TrailBig, true>(ta, blockIdx.x - n_panel, dyn_lds);
 }
 
@@ -1517,16 +1954,32 @@ onecomp_status launch_trailing(TrailArgs t, hipStream_t stream) {
                                                                   : launch_trailing_shape<TrailBig, FROM_ZERO>(t, stream);
 }
 
-template <int GB, bool DIRECT>
-onecomp_status launch_panel(const PanelArgs& pa, const TrailArgs& ta, int far_wgs, hipStream_t stream) {
+template <int GB, bool DIRECT, int ROWS_WG>
+onecomp_status launch_panel_rows(const PanelArgs& pa, const TrailArgs& ta, int far_wgs, hipStream_t stream) {
     static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(&panel_far_kernel<GB, DIRECT>), panel_lds(DIRECT), lds_ok) != ONECOMP_OK)
+    // (both bodies share the launch with tiles of the far update)
+    constexpr int own = ROWS_WG == ROWS ? panel_lds(DIRECT) : panel16_lds(DIRECT);
+    constexpr int lds = own > int(TrailBig::LDS_BYTES) ? own : int(TrailBig::LDS_BYTES);
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&panel_far_kernel<GB, DIRECT, ROWS_WG>), lds, lds_ok) != ONECOMP_OK)
         return ONECOMP_ERR_HIP;
-    const int n_panel = int(ceil_div(pa.d_out, ROWS));
-    hipLaunchKernelGGL((panel_far_kernel<GB, DIRECT>), dim3(unsigned(n_panel + far_wgs)), dim3(256), panel_lds(DIRECT), stream,
-                       pa, ta, n_panel);
+    const int n_panel = int(ceil_div(pa.d_out, ROWS_WG));
+    hipLaunchKernelGGL((panel_far_kernel<GB, DIRECT, ROWS_WG>), dim3(unsigned(n_panel + far_wgs)), dim3(256), lds, stream, pa, ta,
+                       n_panel);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
+}
+// 16 rows per workgroup where they all fit on the CUs at once, two on each, and the launch's far tiles add little behind them:
+// more rows per workgroup are less work in all, and a launch of many tiles is as long as its work.  us of a whole sweep, 64 : 16
+// rows, 4096 columns, group 128: d_out 256 (512 columns) 99 : 74, 1024 732 : 523, 4096 825 : 677, 5120 879 : 779, 7168 986 : 945,
+// 8192 1068 : 1051 (up to 256 far tiles; all launches 1106), 9600 1154 : 1209 (panels three deep), 14336 1373 : 1719.  4096 x
+// 14336, inverse form, 64 rows 4335; 16 rows up to 256, 512, 768, 1024 and any number of far tiles 4180, 4086, 4074, 4132, 4338.
+template <int GB, bool DIRECT>
+onecomp_status launch_panel(const PanelArgs& pa, const TrailArgs& ta, int far_wgs, hipStream_t stream) {
+    const int64_t n16 = ceil_div(pa.d_out, ROWS16), cus = device_cus();
+    const bool searched = pa.mse && pa.wide_g < 0;
+    return !searched && n16 <= 2 * cus && 2 * n16 + far_wgs <= 5 * cus
+               ? launch_panel_rows<GB, DIRECT, ROWS16>(pa, ta, far_wgs, stream)
+               : launch_panel_rows<GB, DIRECT, ROWS>(pa, ta, far_wgs, stream);
 }
 
 }  // namespace

@@ -1241,6 +1241,39 @@ def test_sweep_tile_shapes_agree(d_in, group, form, dtype):
             assert torch.equal(part[k], whole[k][:rows]), (rows, k)
 
 
+@pytest.mark.parametrize("d_in,group,form,dtype,grid,n_rows", [
+    (768, 16, "inverse", torch.bfloat16, "minmax", 8200),     # super-blocks of 512 and 256 columns, workgroups of 64 : 16 rows
+    (640, 32, "block", torch.float32, "symmetric", 8200),
+    (1152, 64, "inverse", torch.float32, "minmax", 8200),
+    (640, 128, "block", torch.bfloat16, "symmetric", 8200),
+    (896, 896, "inverse", torch.float32, "minmax_mse", 8200),
+    (4224, 128, "block", torch.bfloat16, "minmax", 8100),     # far updates: workgroups of 64 rows first, of 16 in the last super-blocks
+])
+def test_sweep_panels_agree(d_in, group, form, dtype, grid, n_rows):
+    """Rows are independent and the panel with 16 rows per workgroup takes a row's steps in the same order as the one with
+    64, so the first rows of a layer that takes the latter are those of a short layer, which takes the former, also beside
+    rows that hold a NaN and in front of it.  (The largest weight, which sets a scale, is in row 0.)"""
+    _announce(f"sweep panels, d_in={d_in} g{group} {form} {grid}")
+    cfg = synth.scaled(synth.CONFIGS["c2"], d_out=n_rows, d_in=d_in, n_tokens=16, seed=81, dtype=dtype)
+    W = synth.make_weight(cfg, DEV)
+    W[0, 0] = 2.0 * W.abs().max()
+    at = d_in - 181
+    W[[3, 37], at] = float("nan")
+    H = torch.from_numpy(_oracle_H32(d_in, 512, seed=82)).to(DEV)
+    F, _, info = og.onecomp_hessian_factor(H, 0.1, form=form)
+    assert int(info.item()) == 0
+    whole = og.onecomp_quantize_layer(W, F, 4, group, form=form, grid=grid)
+    for rows in (1, 16, 17, 47, 64, 203):
+        part = og.onecomp_quantize_layer(W[:rows].contiguous(), F, 4, group, form=form, grid=grid)
+        for k in ("Q_codes", "scales", "zeros", "W_hat"):
+            for r0, r1 in ((0, 3), (4, 37), (38, 203)):
+                assert torch.equal(part[k][r0:r1], whole[k][r0:min(r1, rows)]), (rows, k)
+            n = at // group if k in ("scales", "zeros") else at if at >= group else 0
+            for r in (3, 37):
+                if r < rows:
+                    assert torch.equal(part[k][r, :n], whole[k][r, :n]), (rows, k, r)
+
+
 @pytest.mark.parametrize("bits,G,d_out,d_in,dtype,grid", [
     (4, 4224, 5, 4224, torch.float32, "symmetric_mse"),     # one group per row, two chunks of values in LDS
     (3, 640, 37, 1280, torch.bfloat16, "minmax_mse"),       # groups of five blocks, the second one on compensated values
