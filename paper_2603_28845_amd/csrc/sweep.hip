@@ -1683,9 +1683,9 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         }
     } else {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int n = 0; n < 4; ++n)
+            for (int n = 0; n < NT; ++n)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int rr = m0 + wr * (32 * MT) + m * 32 + (r / 4) * 8 + lr + (r % 4);
