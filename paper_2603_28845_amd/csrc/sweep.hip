@@ -66,69 +66,80 @@ __device__ inline float to_f32<uint16_t>(uint16_t v) { return __uint_as_float(ui
 // a residual was saturated
 __device__ __host__ inline uint32_t* sat_flag(Scalars* sc) { return reinterpret_cast<uint32_t*>(sc) + 16; }
 
-__global__ void init_scalars_kernel(Scalars* sc) {
-    sc->max_w_bits = 0u;
-    sc->max_u_bits = 0u;
-    *sat_flag(sc) = 0u;
-}
-
-__device__ inline void block_max_to(uint32_t* dst, float v) {
-    // Atomics on one address are serialized in L2 (~10 ns each), so a launch issues few of them: wave maximum by
-    // butterfly shuffles, workgroup maximum through LDS, one atomic per workgroup of up to 4 waves.
-    __shared__ float wave_max[4];
+// maximum over the workgroup's four waves, in every thread
+__device__ __forceinline__ float block_max(float v, float* part) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int i = 1; i < nw; ++i) v = fmaxf(v, wave_max[i]);
-        atomicMax(dst, __float_as_uint(v));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+}
+
+// Before a sweep, in one launch: rows of U (workgroups 0 .. n_u - 1) and of W (the others).  A workgroup leaves the maximum of
+// its rows in max_u or max_w, which operands_kernel reduces: no scalar has to be cleared before.  Both parts are bound by memory and
+// narrow layers by the launches: with clearing, the two maxima, the scalars, the operands and the panel's fragments in
+// launches of their own and the sums cleared, whole calls, us: 256 x 512 193, 1999 x 2048 798, 14336 x 4096 2937; now 174, 761, 2782.
+constexpr int PREP_WGS = 1024;   // at most, of either part
+__device__ __forceinline__ float row_ratio_max(const float* __restrict__ U, int n, int first, int step, float* part) {
+    // max_k |U_jk / U_jj| = max_k |U_jk| / |U_jj| exactly: rounding a quotient is monotone in the numerator
+    float mm = 0.f;
+    for (int j = first; j < n; j += step) {
+        const float* row = U + int64_t(j) * n;
+        float m = 0.f;
+        for (int k4 = ((j + 1) & ~3) + 4 * threadIdx.x; k4 < n; k4 += 1024) {
+            const float4v v = *reinterpret_cast<const float4v*>(row + k4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (k4 + e > j) m = fmaxf(m, fabsf(v[e]));
+        }
+        m = m / fabsf(row[j]);
+        if (!(m < 3.0e38f)) m = 3.0e38f;   // NaN / inf from a failed factorization: keep the scalars finite
+        mm = fmaxf(mm, m);
     }
+    return block_max(mm, part);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void load_kernel(const T* __restrict__ W, int64_t d_out, int64_t d_in,
-                                                  const int32_t* __restrict__ perm, float* __restrict__ Wf,
-                                                  float* __restrict__ rowloss, Scalars* __restrict__ sc,
-                                                  float* __restrict__ W0p) {
-    // The working copy Wf starts as zeros: it holds only the accumulated feedback; the weights themselves are read
-    // from W or, under a column order, from the gathered copy W0p written here.  Also max |W|.
+__global__ __launch_bounds__(256) void prepare_kernel(const float* __restrict__ U, int n, int n_u, float* __restrict__ max_u,
+                                                     const T* __restrict__ W, int64_t d_out, const int32_t* __restrict__ perm,
+                                                     float* __restrict__ rowloss, float* __restrict__ max_w,
+                                                     float* __restrict__ W0p) {
+    __shared__ float part[4];
+    if (int(blockIdx.x) < n_u) {
+        const float m = row_ratio_max(U, n, blockIdx.x, n_u, part);
+        if (threadIdx.x == 0) max_u[blockIdx.x] = m;
+        return;
+    }
+    // max |W|, and under a column order the gathered copy W0p from which the sweep reads the weights
+    const int64_t d_in = n, wg = blockIdx.x - n_u, n_w = gridDim.x - n_u;
     float m = 0.f;
-    for (int64_t r = blockIdx.x; r < d_out; r += gridDim.x) {   // a workgroup per row, rows strided over the grid
-    if (threadIdx.x == 0) rowloss[r] = 0.f;
-    if (perm) {
-        for (int p = threadIdx.x; p < d_in; p += 256) {
-            const float v = to_f32<T>(W[r * d_in + perm[p]]);
-            Wf[r * d_in + p] = 0.f;
-            if (W0p) W0p[r * d_in + p] = v;
-            m = fmaxf(m, fabsf(v));
-        }
-    } else {   // rows are 16-byte aligned: d_in is a multiple of 128
-        constexpr int V = 16 / sizeof(T);
-        for (int p = threadIdx.x * V; p < d_in; p += 256 * V) {
-            const uint4v raw = *reinterpret_cast<const uint4v*>(W + r * d_in + p);
-            float v[V];
-            if constexpr (sizeof(T) == 2) {
+    for (int64_t r = wg; r < d_out; r += n_w) {
+        if (threadIdx.x == 0) rowloss[r] = 0.f;
+        if (perm) {
+            for (int p = threadIdx.x; p < d_in; p += 256) {
+                const float v = to_f32<T>(W[r * d_in + perm[p]]);
+                W0p[r * d_in + p] = v;
+                m = fmaxf(m, fabsf(v));
+            }
+        } else {   // rows are 16-byte aligned: d_in is a multiple of 128
+            constexpr int V = 16 / sizeof(T);
+            for (int p = threadIdx.x * V; p < d_in; p += 256 * V) {
+                const uint4v raw = *reinterpret_cast<const uint4v*>(W + r * d_in + p);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    v[2 * e] = __uint_as_float(raw[e] << 16);
-                    v[2 * e + 1] = __uint_as_float(raw[e] & 0xFFFF0000u);
+                    if constexpr (sizeof(T) == 2) {
+                        m = fmaxf(m, fabsf(__uint_as_float(raw[e] << 16)));
+                        m = fmaxf(m, fabsf(__uint_as_float(raw[e] & 0xFFFF0000u)));
+                    } else {
+                        m = fmaxf(m, fabsf(__uint_as_float(raw[e])));
+                    }
                 }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(raw[e]);
             }
-#pragma unroll
-            for (int e = 0; e < V; e += 4) {
-                *reinterpret_cast<float4v*>(Wf + r * d_in + p + e) = float4v{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int e = 0; e < V; ++e) m = fmaxf(m, fabsf(v[e]));
         }
     }
-    }
-    block_max_to(&sc->max_w_bits, m);
+    m = block_max(m, part);
+    if (threadIdx.x == 0) max_w[wg] = m;
 }
 
 constexpr int IB = 32;          // columns swept in registers at a time
@@ -153,7 +164,7 @@ constexpr int IB = 32;          // columns swept in registers at a time
 // ------------------------------------------------------------------------------------------
 struct PanelArgs {
     const float* Wf;            // [d_out x d_in] accumulated feedback c of the earlier super-blocks (block form: the
-                                // sums c_k = sum_i (w_i - w^_i) R_ik / R_kk)
+                                // sums c_k = sum_i (w_i - w^_i) R_ik / R_kk); of the first one (s0 == 0) not read
     const void* W0;             // the layer's weights in sweep order (the caller's matrix, or the gathered fp32 copy
                                 // under a column order)
     int w0_bf16;
@@ -352,7 +363,7 @@ __device__ __forceinline__ void panel_body(const PanelArgs& a, const int wg, cha
                 // the whole sweep).  In a short one rows past d_out read the last row: see panel_feedback_offset.
                 const int rows = min(ROWS, a.d_out - r0), col = j0 + 32 * bw + (blane & 31);
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0, int(rows * d_in * 4), 0x00020000);
+                    const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0, a.s0 > 0 ? int(rows * d_in * 4) : 0, 0x00020000);
                 auto load = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
                     for (int mt = 0; mt < 2; ++mt)
@@ -969,7 +980,7 @@ __device__ __forceinline__ void panel_body16(const PanelArgs& a, const int wg, c
             float16v acc;
             const int rows = min(ROWS16, a.d_out - r0), col = j0 + 32 * wave + lc;
             const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.Wf + int64_t(r0) * d_in), 0,
-                                                                                  int(rows * d_in * 4), 0x00020000);
+                                                                                  a.s0 > 0 ? int(rows * d_in * 4) : 0, 0x00020000);
 #pragma unroll
             for (int r = 0; r < 8; ++r) {   // rows past d_out read the last one
                 const plan::FeedbackOffset o = plan::panel_feedback_offset<false>(rows, int(d_in), lane, 0, r, col);
@@ -1317,96 +1328,105 @@ __device__ __forceinline__ void panel_body16(const PanelArgs& a, const int wg, c
     if (saturated) *a.sat = 1u;
 }
 
-// Fragments of the normalized U blocks the panel kernel's near updates multiply with: for super-block S (sbw
-// columns wide, gridDim.x = its number of block pairs), block pair p = b (b - 1) / 2 + b' (b' < b), k-step ks,
-// column tile nt, lane L:
-//   Un[sbw S + 128 b' + 16 ks + 8 (L/32) + e][sbw S + 128 b + 32 nt + L%32] * f_u,  e = 0 .. 7,  fp16 hi and lo.
-__global__ __launch_bounds__(256) void nearfrag_kernel(const float* __restrict__ U, int n, const Scalars* __restrict__ sc,
-                                                      uint16_t* __restrict__ Bh, uint16_t* __restrict__ Bl, int sbw) {
-    const int S = blockIdx.y, p = blockIdx.x;
-    const int b = (p >= 3) ? 3 : (p >= 1 ? 2 : 1), bp = p - b * (b - 1) / 2;
-    const int k00 = S * sbw + bp * SB, n00 = S * sbw + b * SB;
-    if (n00 >= n) return;
-    const float f_u = sc->f_u;
-    for (int it = threadIdx.x; it < 8 * 4 * 64; it += 256) {
-        const int L = it & 63, nt = (it >> 6) & 3, ks = it >> 8;
-        const int col = n00 + nt * 32 + (L & 31), k0 = k00 + ks * 16 + 8 * (L >> 5);
-        short8v h8, l8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float dj = U[int64_t(k0 + e) * n + k0 + e];
-            float x = U[int64_t(k0 + e) * n + col] / dj * f_u;
-            x = fminf(fmaxf(x, -60000.f), 60000.f);
-            const _Float16 h = (_Float16)x;
-            const _Float16 lo = (_Float16)(x - (float)h);
-            h8[e] = __builtin_bit_cast(short, h);
-            l8[e] = __builtin_bit_cast(short, lo);
-        }
-        const int64_t off = ((int64_t(S) * gridDim.x + p) * (8 * 4 * 64) + it) * 8;
-        *reinterpret_cast<short8v*>(Bh + off) = h8;
-        *reinterpret_cast<short8v*>(Bl + off) = l8;
-    }
-}
-
 // ------------------------------------------------------------------------------------------
-// Operands of the trailing GEMMs (once per layer).  The feedback e_j U_jk is computed as
+// Operands of the trailing GEMMs and of the panel's near updates (once per layer).  The feedback e_j U_jk is computed as
 // (w_j - w^_j) * (U_jk / U_jj): the residual is bounded by the weights and the normalized row by the
 // regression coefficients between input channels, so both fit fp16 after a power-of-two scaling taken
 // from their maxima, whereas e and U themselves span the scale of 1 / sqrt(H_jj).
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void umax_kernel(const float* __restrict__ U, int n, Scalars* __restrict__ sc) {
-    // max_k |U_jk / U_jj| = max_k |U_jk| / |U_jj| exactly: rounding a quotient is monotone in the numerator
-    float mm = 0.f;
-    for (int j = blockIdx.x; j < n; j += gridDim.x) {   // a workgroup per row, rows strided over the grid
-        const float* row = U + int64_t(j) * n;
-        float m = 0.f;
-        for (int k4 = ((j + 1) & ~3) + 4 * threadIdx.x; k4 < n; k4 += 1024) {
-            const float4v v = *reinterpret_cast<const float4v*>(row + k4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (k4 + e > j) m = fmaxf(m, fabsf(v[e]));
-        }
-        m = m / fabsf(row[j]);
-        if (!(m < 3.0e38f)) m = 3.0e38f;   // NaN / inf from a failed factorization: keep the scalars finite
-        mm = fmaxf(mm, m);
-    }
-    block_max_to(&sc->max_u_bits, mm);
-}
-
-__global__ void scale_kernel(Scalars* sc) {
+__device__ __forceinline__ Scalars make_scales(float mw, float mu) {
     // largest magnitudes land at 2^13 (residuals, x8 headroom before saturation) and 2^14 (rows of U)
-    const float mw = __uint_as_float(sc->max_w_bits), mu = __uint_as_float(sc->max_u_bits);
     int ew = 0, eu = 0;
     if (mw > 0.f) (void)frexpf(mw, &ew);   // mw = m * 2^ew, 0.5 <= m < 1
     if (mu > 0.f) (void)frexpf(mu, &eu);
     const int sd = max(-60, min(60, 13 - ew)), su = max(-60, min(60, 14 - eu));
-    sc->f_d = ldexpf(1.f, sd);
-    sc->f_u = ldexpf(1.f, su);
-    sc->f_all = ldexpf(1.f, sd + su);
-    sc->f_inv = ldexpf(1.f, -(sd + su));
+    Scalars s;
+    s.max_w_bits = __float_as_uint(mw);
+    s.max_u_bits = __float_as_uint(mu);
+    s.f_d = ldexpf(1.f, sd);
+    s.f_u = ldexpf(1.f, su);
+    s.f_all = ldexpf(1.f, sd + su);
+    s.f_inv = ldexpf(1.f, -(sd + su));
+    return s;
+}
+// u / dj * f_u as fp16 hi + lo
+__device__ __forceinline__ void split_ratio(float u, float dj, float f_u, short& hi, short& lo) {
+    float x = u / dj * f_u;
+    x = fminf(fmaxf(x, -60000.f), 60000.f);
+    const _Float16 h = (_Float16)x;
+    hi = __builtin_bit_cast(short, h);
+    lo = __builtin_bit_cast(short, (_Float16)(x - (float)h));
 }
 
-__global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ U, int n,
-                                                   const Scalars* __restrict__ sc, uint16_t* __restrict__ Uh,
-                                                   uint16_t* __restrict__ Ul) {
-    const int j = blockIdx.y;
-    const int k4 = (blockIdx.x * 256 + threadIdx.x) * 4;
-    // the trailing updates read row j only beyond its 128-column block; the rest of Uh / Ul stays unwritten
-    if (k4 >= n || k4 < (j / SB + 1) * SB) return;
-    const float4v v = *reinterpret_cast<const float4v*>(U + int64_t(j) * n + k4);
-    const float dj = U[int64_t(j) * n + j], f_u = sc->f_u;
-    short4v h4, l4;
+// Every workgroup forms the scales from the maxima that prepare_kernel left (8 KB out of L2; a launch for it: 4.7 us), the first
+// one leaves them in sc and clears the saturation flag.
+// Workgroups 0 .. n_near - 1, NEAR_PARTS per block pair, the fragments of the normalized U blocks that the panel kernel's near
+// updates multiply with: for super-block S (sbw columns wide, n_pairs block pairs), block pair p = b (b - 1) / 2 + b' (b' < b),
+// k-step ks, column tile nt, lane L:
+//   Un[sbw S + 128 b' + 16 ks + 8 (L/32) + e][sbw S + 128 b + 32 nt + L%32] * f_u,  e = 0 .. 7,  fp16 hi and lo.
+// The others, rows of the trailing updates' operand, which is read beyond row j's 128-column block only; the rest of Uh / Ul
+// stays unwritten.
+constexpr int NEAR_PARTS = 4;
+__global__ __launch_bounds__(256) void operands_kernel(const float* __restrict__ U, int n, const float* __restrict__ max_u, int n_u,
+                                                      const float* __restrict__ max_w, int n_w, Scalars* __restrict__ sc,
+                                                      uint16_t* __restrict__ Bh, uint16_t* __restrict__ Bl, int sbw, int n_pairs,
+                                                      int n_near, uint16_t* __restrict__ Uh, uint16_t* __restrict__ Ul) {
+    __shared__ float part[4];
+    float mu = 0.f, mw = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float x = v[e] / dj * f_u;
-        x = fminf(fmaxf(x, -60000.f), 60000.f);
-        const _Float16 h = (_Float16)x;
-        const _Float16 lo = (_Float16)(x - (float)h);
-        h4[e] = __builtin_bit_cast(short, h);
-        l4[e] = __builtin_bit_cast(short, lo);
+    for (int q = 0; q < PREP_WGS / 256; ++q) {
+        const int i = threadIdx.x + 256 * q;
+        if (i < n_u) mu = fmaxf(mu, max_u[i]);
+        if (i < n_w) mw = fmaxf(mw, max_w[i]);
     }
-    *reinterpret_cast<short4v*>(Uh + int64_t(j) * n + k4) = h4;
-    *reinterpret_cast<short4v*>(Ul + int64_t(j) * n + k4) = l4;
+    mu = block_max(mu, part);
+    mw = block_max(mw, part);
+    const Scalars s = make_scales(mw, mu);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *sc = s;
+        *sat_flag(sc) = 0u;
+    }
+    const float f_u = s.f_u;
+    if (int(blockIdx.x) < n_near) {
+        const int pair = blockIdx.x / NEAR_PARTS, S = pair / n_pairs, p = pair % n_pairs;
+        const int b = (p >= 3) ? 3 : (p >= 1 ? 2 : 1), bp = p - b * (b - 1) / 2;
+        const int k00 = S * sbw + bp * SB, n00 = S * sbw + b * SB;
+        if (n00 >= n) return;
+        constexpr int each = 8 * 4 * 64 / NEAR_PARTS;
+        for (int it = blockIdx.x % NEAR_PARTS * each + threadIdx.x, i = 0; i < each / 256; ++i, it += 256) {
+            const int L = it & 63, nt = (it >> 6) & 3, ks = it >> 8;
+            const int col = n00 + nt * 32 + (L & 31), k0 = k00 + ks * 16 + 8 * (L >> 5);
+            short8v h8, l8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                short h, l;
+                split_ratio(U[int64_t(k0 + e) * n + col], U[int64_t(k0 + e) * n + k0 + e], f_u, h, l);
+                h8[e] = h;
+                l8[e] = l;
+            }
+            const int64_t off = (int64_t(pair) * (8 * 4 * 64) + it) * 8;
+            *reinterpret_cast<short8v*>(Bh + off) = h8;
+            *reinterpret_cast<short8v*>(Bl + off) = l8;
+        }
+        return;
+    }
+    for (int j = blockIdx.x - n_near; j < n; j += gridDim.x - n_near) {
+        const int64_t row = int64_t(j) * n;
+        const float dj = U[row + j];
+        for (int k4 = (j / SB + 1) * SB + 4 * threadIdx.x; k4 < n; k4 += 1024) {
+            const float4v v = *reinterpret_cast<const float4v*>(U + row + k4);
+            short4v h4, l4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                short h, l;
+                split_ratio(v[e], dj, f_u, h, l);
+                h4[e] = h;
+                l4[e] = l;
+            }
+            *reinterpret_cast<short4v*>(Uh + row + k4) = h4;
+            *reinterpret_cast<short4v*>(Ul + row + k4) = l4;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1456,6 +1476,7 @@ struct TrailArgs {
     int ek, K, u0, c0, c1;     // K % 32 == 0, c0 % 8 == 0, c1 % 8 == 0
     int n_mt, n_nt, chunk;
     int n_nt0, h0, h1;         // not FROM_ZERO: the first n_nt0 column tiles cover [c0, h0), the others [h1, c1)
+    int first;                 // FROM_ZERO: nothing has been added to these columns, they are written without being read
 };
 
 // FROM_ZERO: the accumulators start at zero and the product is added to the tile of C once, at the end, with one
@@ -1660,12 +1681,14 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
                 // the tile's current values: 32 independent loads at a time (the operand registers are free now)
 #pragma unroll
                 for (int n2 = 0; n2 < NT; n2 += 2) {
-                    float16v old[2];
+                    float16v old[2] = {};
+                    if (!a.first) {
 #pragma unroll
-                    for (int n = 0; n < 2; ++n)
+                        for (int n = 0; n < 2; ++n)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            old[n][r] = wp[int64_t(m * 32 + (r / 4) * 8 + (r % 4)) * d_in + (n2 + n) * 32];
+                            for (int r = 0; r < 16; ++r)
+                                old[n][r] = wp[int64_t(m * 32 + (r / 4) * 8 + (r % 4)) * d_in + (n2 + n) * 32];
+                    }
 #pragma unroll
                     for (int n = 0; n < 2; ++n)
 #pragma unroll
@@ -1692,7 +1715,7 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
                     const int cc = n0 + wc * (32 * NT) + n * 32 + lc;
                     if (rr < d_out && cc < c1) {
                         float* q = a.Wf + int64_t(rr) * d_in + cc;
-                        if constexpr (FROM_ZERO) *q = __builtin_fmaf(acc[m][n][r], f_inv, *q);
+                        if constexpr (FROM_ZERO) *q = __builtin_fmaf(acc[m][n][r], f_inv, a.first ? 0.f : *q);
                         else *q = acc[m][n][r] * f_inv;
                     }
                 }
@@ -2009,7 +2032,7 @@ onecomp_status split_update_around(float* C, int64_t d_out, int64_t d_in, const 
     t.Wf = C; t.Dh = Dh; t.Dl = Dl; t.Uh = Bh; t.Ul = Bl; t.sc = sc;
     t.d_out = int(d_out); t.ldD = int(ldD); t.d_in = int(d_in);
     t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
-    t.h0 = h0; t.h1 = h1;
+    t.h0 = h0; t.h1 = h1; t.first = 0;
     return launch_trailing<false>(t, stream);
 }
 
@@ -2030,30 +2053,25 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
     const int sb_pairs = (sbw / SB) * (sbw / SB - 1) / 2;   // block pairs (b' < b) inside a super-block
     if (direct && group_size > SB && group_size != d_in) return ONECOMP_ERR_UNSUPPORTED;
     SweepWs w = carve(workspace, d_out, d_in);
-    hipLaunchKernelGGL(init_scalars_kernel, dim3(1), dim3(1), 0, stream, w.sc);
+    const int n_u = int(d_in < PREP_WGS ? d_in : PREP_WGS), n_w = int(d_out < PREP_WGS ? d_out : PREP_WGS);
+    float *const max_u = reinterpret_cast<float*>(w.Dh), *const max_w = max_u + PREP_WGS;   // the panels write Dh later
+    auto prepare = [&](auto* W_) {
+        hipLaunchKernelGGL((prepare_kernel<std::remove_const_t<std::remove_pointer_t<decltype(W_)>>>), dim3(unsigned(n_u + n_w)), dim3(256), 0, stream, U, int(d_in), n_u, max_u, W_, d_out, perm,
+                           w.rowloss, max_w, w.W0p);
+    };
+    if (w_dtype == ONECOMP_BF16) prepare(static_cast<const uint16_t*>(W));
+    else prepare(static_cast<const float*>(W));
     ONECOMP_CHECK_LAUNCH();
-    dim3 lgrid{unsigned(d_out < 1024 ? d_out : 1024)};
-    if (w_dtype == ONECOMP_BF16)
-        hipLaunchKernelGGL(load_kernel<uint16_t>, lgrid, dim3(256), 0, stream, static_cast<const uint16_t*>(W), d_out,
-                           d_in, perm, w.Wf, w.rowloss, w.sc, perm ? w.W0p : nullptr);
-    else
-        hipLaunchKernelGGL(load_kernel<float>, lgrid, dim3(256), 0, stream, static_cast<const float*>(W), d_out, d_in,
-                           perm, w.Wf, w.rowloss, w.sc, perm ? w.W0p : nullptr);
-    ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(umax_kernel, dim3(unsigned(d_in < 1024 ? d_in : 1024)), dim3(256), 0, stream, U,
-                       int(d_in), w.sc);
-    ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(scale_kernel, dim3(1), dim3(1), 0, stream, w.sc);
-    ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(split_kernel, dim3(unsigned(ceil_div(d_in, 1024)), unsigned(d_in)), dim3(256), 0, stream, U,
-                       int(d_in), w.sc, w.Uh, w.Ul);
+    const int n_near = NEAR_PARTS * sb_pairs * int(ceil_div(d_in, sbw));
+    hipLaunchKernelGGL(operands_kernel, dim3(unsigned(n_near + (d_in < 2048 ? d_in : 2048))), dim3(256), 0, stream, U, int(d_in), max_u,
+                       n_u, max_w, n_w, w.sc, w.Bh, w.Bl, sbw, sb_pairs, n_near, w.Uh, w.Ul);
     ONECOMP_CHECK_LAUNCH();
 
     TrailArgs t;
     t.Wf = w.Wf; t.Dh = w.Dh; t.Dl = w.Dl; t.Uh = w.Uh; t.Ul = w.Ul; t.sc = w.sc;
     t.ek = 0; t.K = 0; t.u0 = 0; t.c0 = 0; t.c1 = 0; t.n_nt = 0; t.chunk = 0;
     t.d_out = int(d_out); t.ldD = int(ld_d(d_out)); t.d_in = int(d_in);
-    t.n_nt0 = 0; t.h0 = 0; t.h1 = 0;
+    t.n_nt0 = 0; t.h0 = 0; t.h1 = 0; t.first = 0;
     // fills t for Wf[:, c0 .. c1) += residual columns ek .. ek+K of buffer `buf` times rows u0 .. u0+K of Un;
     // returns the number of workgroups (0: nothing to do)
     const size_t d_buf = size_t(SBIG) * ld_d(d_out);
@@ -2061,6 +2079,7 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
         if (c1 <= c0) return 0;
         t.Dh = w.Dh + buf * d_buf; t.Dl = w.Dl + buf * d_buf;
         t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
+        t.first = u0 == 0;   // the first super-block's feedback is the first there is
         return trail_grid<TrailBig, true>(t);
     };
     auto trailing = [&](int buf, int ek, int K, int u0, int c0, int c1) -> onecomp_status {
@@ -2073,11 +2092,6 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
         // blocks is applied inside the panel kernel).  The columns beyond a super-block receive its feedback once,
         // with K = its width: first those of the next super-block, then, in the same launch as the next panel,
         // the rest.
-        if (sb_pairs > 0) {
-            hipLaunchKernelGGL(nearfrag_kernel, dim3(unsigned(sb_pairs), unsigned(ceil_div(d_in, sbw))), dim3(256), 0,
-                               stream, U, int(d_in), w.sc, w.Bh, w.Bl, sbw);
-            ONECOMP_CHECK_LAUNCH();
-        }
         PanelArgs pa;
         pa.Wf = w.Wf; pa.U = U;
         // where the panel finds the original weights in sweep order: under a column order, the gathered fp32 copy

@@ -10,6 +10,8 @@ Bars (from the benchmark spec):
                oracle's U for the same fp32 H (bound: fp32 rounding 6e-8 per entry plus fp64
                factorization error ~ cond * 1e-16)
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -1239,6 +1241,31 @@ def test_sweep_tile_shapes_agree(d_in, group, form, dtype):
         part = og.onecomp_quantize_layer(W[:rows].contiguous(), F, 4, group, form=form)
         for k in ("Q_codes", "scales", "zeros", "W_hat"):
             assert torch.equal(part[k], whole[k][:rows]), (rows, k)
+
+
+@pytest.mark.parametrize("d_out,d_in,group,form,order", [
+    (1, 128, 128, "inverse", False),        # one block: no operand at all
+    (17, 640, 64, "block", False),          # a second super-block of one block
+    (70, 1152, 1152, "inverse", False),     # one group per row
+    (130, 1536, 256, "inverse", True),      # groups of two blocks, super-blocks of 256; gathered weights
+    (1030, 1664, 128, "inverse", False),    # more rows of either matrix than workgroups look for their maximum
+])
+def test_sweep_scratch_is_not_read(d_out, d_in, group, form, order):
+    """The sums of feedback begin in the first super-block's update: nothing that the scratch memory holds (NaNs as fp16, fp32 and
+    fp64, or zeros) reaches a result."""
+    _announce(f"sweep's scratch, {d_out} x {d_in} g{group} {form}")
+    cfg = synth.scaled(synth.CONFIGS["c2"], d_out=d_out, d_in=d_in, n_tokens=16, seed=91)
+    W = synth.make_weight(cfg, DEV)
+    H = torch.from_numpy(_oracle_H32(d_in, 512, seed=92)).to(DEV)
+    F, perm, info = og.onecomp_hessian_factor(H, 0.1, form=form, act_order=order)
+    assert int(info.item()) == 0
+    ws = torch.zeros(og.onecomp_quantize_workspace_bytes(d_out, d_in), dtype=torch.uint8, device=DEV)
+    clean = og.onecomp_quantize_layer(W, F, 4, group, perm=perm, form=form, workspace=ws)
+    ws.fill_(255)
+    dirty = og.onecomp_quantize_layer(W, F, 4, group, perm=perm, form=form, workspace=ws)
+    for k in ("Q_codes", "scales", "zeros", "W_hat", "loss"):
+        assert torch.equal(clean[k], dirty[k]), k
+    assert math.isfinite(float(dirty["loss"].item()))
 
 
 @pytest.mark.parametrize("d_in,group,form,dtype,grid,n_rows", [
