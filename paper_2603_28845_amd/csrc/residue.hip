@@ -331,11 +331,14 @@ __global__ __launch_bounds__(256) void inner_exponents_kernel(const double* __re
 constexpr int64_t PIECE_COLS = 2048;
 
 // ---- the products -----------------------------------------------------------------------------------------------------
-// out = A B^T mod m for every modulus m, A and B by their residues: 256 x 256 tile per workgroup, eight waves of 128 x 64, two
-// per SIMD; both operands are in operand order, so a load is 1 KB of memory -> 1 KB of LDS and a fragment is one
-// conflict-free 16-byte read.  Steps of 64 through a ring of four slots of 32 KB; the operands of a step's first half are
-// read before the barrier that publishes the next step's, so that no MFMA waits behind it.  MFMA and LDS reads share the power of
-// the chip as in the bf16 Gram (2.3 of 3.6 POP/s), so the tile is the largest that two waves per SIMD hold.
+// out = A B^T mod m for every modulus m, A and B by their residues: 256 x 256 tile per workgroup, four waves of 128 x 128, one
+// per SIMD (256 accumulators in AGPRs); both operands are in operand order, so a load is 1 KB of memory -> 1 KB of LDS and a
+// fragment is one conflict-free 16-byte read.  Steps of 64 through a ring of four slots of 32 KB; the operands of a step's first
+// half are read before the barrier that publishes the next step's, and reads and loads stand one by one behind MFMAs, so that
+// with a single wave per SIMD no MFMA waits for them.  The chip's power is the bound (MFMAs busy 73 % of the cycles at 1.49 GHz with
+// eight waves of 128 x 64), so what counts is bytes out of LDS per product: these waves read two thirds of what those did.
+// A factor's products, us, eight waves : four: d_in 28672 91.7 : 87.4 ms (inner ranges of 8192 2171 : 2010, 2048 963 : 950, 1024
+// 494 : 508), 14336 in block form 5785 : 5643.
 // Accumulators start at 2^22 m; |sum| <= 2^14 MAX_K = 2^29 < 2^22 m, so they stay positive and below 2^31.
 // Workgroup -> tile: patches of 32 tiles, each with one modulus, go round the XCDs (workgroup b runs on XCD b % 8), so that
 // the 32 tiles an XCD works on share their operands in its L2; with a triangular operand the longest patches come first.
@@ -349,10 +352,10 @@ struct ProductArgs {
 };
 constexpr int STAGE_BYTES = 2 * TILE * K_STEP, SLOTS = 4;
 
-__global__ __launch_bounds__(512, 2) void product_kernel(ProductArgs g) {
+__global__ __launch_bounds__(256, 1) void product_kernel(ProductArgs g) {
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 2, wc = wave & 3;
+    const int wr = wave >> 1, wc = wave & 1;
     const int patch_rows = 32 / g.patch_cols;
     const int unit = int(blockIdx.x >> 8) * 8 + int(blockIdx.x & 7), w = (blockIdx.x >> 3) & 31;
     const int patch = unit / MODULI, mod = unit % MODULI;
@@ -368,64 +371,85 @@ __global__ __launch_bounds__(512, 2) void product_kernel(ProductArgs g) {
     const int n_st = end - begin;
 
     const uint32_t lds0 = uint32_t(uintptr_t((ONECOMP_LDS char*)lds)), lane16 = lane * 16;
-    const char* pa = g.A + mod * g.a_plane + (tm * 8 + wave) * g.a_block + int64_t(begin) * 2048;
-    const char* pb = g.B + mod * g.b_plane + (tn * 8 + wave) * g.b_block + int64_t(begin) * 2048;
+    // a wave requests two row blocks of either operand, 2 KB each per step
+    const char* pa = g.A + mod * g.a_plane + (tm * 8 + wave * 2) * g.a_block + int64_t(begin) * 2048;
+    const char* pb = g.B + mod * g.b_plane + (tn * 8 + wave * 2) * g.b_block + int64_t(begin) * 2048;
     int ahead = n_st;   // steps not requested yet; past the end: an empty range, which deposits zeros
-    auto issue = [&](int slot) __attribute__((always_inline)) {
+    struct Desc {
+        __amdgpu_buffer_rsrc_t a[2], b[2];
+        uint32_t lds;
+    };
+    auto next_desc = [&](int slot) __attribute__((always_inline)) {
         const uint32_t range = ahead > 0 ? 0x7FFFFFFFu : 0u;
         --ahead;
-        const uint32_t l = __builtin_amdgcn_readfirstlane(lds0 + slot * STAGE_BYTES + wave * 2048);
-        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa), 0, range, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pb), 0, range, 0x00020000);
-        lds_load16(l, lane16, ra);
-        lds_load16(l + 1024, lane16 + 1024, ra);
-        lds_load16(l + STAGE_BYTES / 2, lane16, rb);
-        lds_load16(l + STAGE_BYTES / 2 + 1024, lane16 + 1024, rb);
+        Desc d;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            d.a[q] = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa + q * g.a_block), 0, range, 0x00020000);
+            d.b[q] = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pb + q * g.b_block), 0, range, 0x00020000);
+        }
+        d.lds = lds0 + slot * STAGE_BYTES + wave * 4096;
         pa += 2048;
         pb += 2048;
+        return d;
+    };
+    auto load = [&](const Desc& d, int i) __attribute__((always_inline)) {   // number i of a step's eight
+        const int q = i >> 2, half = i & 1;
+        if (i & 2) lds_load16(d.lds + STAGE_BYTES / 2 + q * 2048 + half * 1024, lane16 + half * 1024, d.b[q]);
+        else lds_load16(d.lds + q * 2048 + half * 1024, lane16 + half * 1024, d.a[q]);
+    };
+    auto issue = [&](int slot) __attribute__((always_inline)) {
+        const Desc d = next_desc(slot);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) load(d, i);
     };
     for (int st = 0; st < SLOTS - 1; ++st) issue(st);
     const int m = d_tab.m[mod];
-    int16v acc[4][2];
+    int16v acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = m << 22;
-    int4v a0[4], b0[2], a1[4], b1[2];
+    struct Frags {
+        int4v a[4], b[4];
+    };
+    Frags F0, F1;
     const char* const fa = lds + wr * 4 * 2048 + lane16;
-    const char* const fb = lds + STAGE_BYTES / 2 + wc * 2 * 2048 + lane16;
-    auto read = [&](int4v (&a)[4], int4v (&b)[2], int off) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const int4v*>(fa + off + i * 2048);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const int4v*>(fb + off + j * 2048);
+    const char* const fb = lds + STAGE_BYTES / 2 + wc * 4 * 2048 + lane16;
+    auto read = [&](Frags& f, int r, int off) __attribute__((always_inline)) {   // fragment r of eight, as the products take them
+        if (r & 1) f.b[r >> 1] = *reinterpret_cast<const int4v*>(fb + off + (r >> 1) * 2048);
+        else f.a[r >> 1] = *reinterpret_cast<const int4v*>(fa + off + (r >> 1) * 2048);
     };
-    auto multiply = [&](const int4v (&a)[4], const int4v (&b)[2]) __attribute__((always_inline)) {
+    // sixteen MFMAs; `between(i)` goes behind number i
+    auto multiply = [&](const Frags& f, auto&& between) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int j = i & 1 ? 1 - u : u;   // one operand stays from one MFMA to the next
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int n = 0; n < 16; ++n) {
+            const int i = n >> 2, j = i & 1 ? 3 - (n & 3) : n & 3;   // one operand stays from one MFMA to the next
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+            between(n);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
-    __builtin_amdgcn_s_waitcnt(wait_vmcnt(4 * (SLOTS - 2)));
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(8 * (SLOTS - 2)));
     __syncthreads();
     issue(SLOTS - 1);
-    read(a0, b0, 0);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) read(F0, r, 0);
     auto stage = [&](auto slot_c) __attribute__((always_inline)) {
         constexpr int slot = decltype(slot_c)::value, next = (slot + 1) % SLOTS;
-        read(a1, b1, slot * STAGE_BYTES + 1024);
-        multiply(a0, b0);
+        multiply(F0, [&](int n) __attribute__((always_inline)) {
+            if (n < 8) read(F1, n, slot * STAGE_BYTES + 1024);
+        });
         // the next step has landed; every wave has read this one
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(4 * (SLOTS - 2)));
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(8 * (SLOTS - 2)));
         __syncthreads();
-        issue(slot);
-        read(a0, b0, next * STAGE_BYTES);
-        multiply(a1, b1);
+        const Desc d = next_desc(slot);
+        multiply(F1, [&](int n) __attribute__((always_inline)) {
+            if (n & 1) load(d, n >> 1);
+            else read(F0, n >> 1, next * STAGE_BYTES);
+        });
     };
     int st = 0;
 #pragma unroll 1
@@ -446,11 +470,11 @@ __global__ __launch_bounds__(512, 2) void product_kernel(ProductArgs g) {
     const float inv = d_tab.inv[mod];
     const int l32 = lane & 31, lh = lane >> 5;
     uint32_t* const o = reinterpret_cast<uint32_t*>(g.out + mod * g.out_plane) + int64_t(tm * (TILE / 4) + wr * 32 + lh) * g.out_cols +
-                        tn * TILE + wc * 64 + l32;
+                        tn * TILE + wc * 128 + l32;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 uint32_t r[4];
@@ -513,7 +537,7 @@ onecomp_status product(const Operand& A, const Operand& B, int m, int n, int k, 
     g.stages = int(pad_k(k) / K_STEP); g.shape = shape; g.out_cols = int(pad_rows(n)); g.k0 = k0;
     g.patch_cols = g.n_t >= 8 ? 8 : g.n_t >= 4 ? 4 : g.n_t >= 2 ? 2 : 1;
     const int64_t units = ceil_div(g.m_t, 32 / g.patch_cols) * ceil_div(g.n_t, g.patch_cols) * MODULI;
-    hipLaunchKernelGGL(product_kernel, dim3(unsigned(ceil_div(units, 8) * 256)), dim3(512), SLOTS * STAGE_BYTES, stream, g);
+    hipLaunchKernelGGL(product_kernel, dim3(unsigned(ceil_div(units, 8) * 256)), dim3(256), SLOTS * STAGE_BYTES, stream, g);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
 }
