@@ -440,25 +440,28 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
     struct Desc {
         __amdgpu_buffer_rsrc_t a, b;   // A panels, B panels (the same matrix unless CROSS)
     };
-    // descriptor of step st: base = its first token row, range = what is left of the matrix (none past the last
-    // step).  The 64-bit products may be computed on the vector ALU: the wave-uniform results are brought back to
-    // scalar registers, where a descriptor has to live.
-    auto make_rsrc = [&](const uint16_t* base, int64_t ld, int64_t st) __attribute__((always_inline)) {
-        const int64_t t0 = st * KT;
-        const int64_t left = (n_tokens - t0) * ld * 2;
-        const bool live = left > 0;
-        const int range = __builtin_amdgcn_readfirstlane(!live ? 0 : (left > 0x7FFFFFFF ? 0x7FFFFFFF : int(left)));
-        const int64_t boff = (live ? t0 : 0) * ld * 2;
-        const uint32_t blo = __builtin_amdgcn_readfirstlane(uint32_t(boff));
-        const uint32_t bhi = __builtin_amdgcn_readfirstlane(uint32_t(uint64_t(boff) >> 32));
-        return __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(reinterpret_cast<const char*>(base) + int64_t((uint64_t(bhi) << 32) | blo)), 0, range,
-            0x00020000);
+    // Descriptor of the next step: base = its first token row, range = what is left of the matrix (none past the last
+    // step).  Bases and ranges advance by additions: formed by 64-bit products in every step they held back the shapes with few
+    // MFMAs a step (us of a call, products : additions, the second including the shorter start below: d_in 4096, 2048 tokens
+    // 68.4 : 65.0; 4096 tokens 107.7 : 101.0; 8192, 2048 190 : 183; 4096 x 262144 4010 : 3960, with 384 x 256 tiles).
+    struct Rows {
+        const char* p;
+        int64_t left, step;   // bytes
+        __device__ __forceinline__ Rows(const uint16_t* base, int64_t tokens, int64_t ld)
+            : p(reinterpret_cast<const char*>(base)), left(tokens > 0 ? tokens * ld * 2 : 0), step(KT * ld * 2) {}
+        __device__ __forceinline__ __amdgpu_buffer_rsrc_t next() {
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char*>(p), 0, left > 0x7FFFFFFF ? 0x7FFFFFFF : left > 0 ? int(left) : 0, 0x00020000);
+            p += step;
+            left -= step;
+            return r;
+        }
     };
-    auto make_desc = [&](int64_t st) __attribute__((always_inline)) {
+    Rows rows_a(X, n_tokens, ldx), rows_b(Xb, n_tokens, ldxb);
+    auto next_desc = [&]() __attribute__((always_inline)) {
         Desc d;
-        d.a = make_rsrc(X, ldx, st);
-        if constexpr (CROSS) d.b = make_rsrc(Xb, ldxb, st);
+        d.a = rows_a.next();
+        if constexpr (CROSS) d.b = rows_b.next();
         else d.b = d.a;
         return d;
     };
@@ -493,7 +496,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
     };
 
     for (int st = 0; st < NBUF; ++st) {
-        const Desc d = make_desc(st);
+        const Desc d = next_desc();
 #pragma unroll
         for (int q = 0; q < LPW; ++q) gload(d, lds0 + st * STAGEB, q);
     }
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
         for (int n = 0; n < NT; ++n)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
-    __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NBUF - 2)));   // the first two steps have landed
     __syncthreads();
     if constexpr (!CROSS && C::TM >= 256) {
         if (below_diagonal<C>(i0, k0, wave)) {   // nothing to compute: this wave's loads and barriers only
@@ -513,7 +516,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
 #pragma unroll 1
             for (int64_t st = 0; st < n_st2; ++st) {
                 if constexpr (PACED) __builtin_amdgcn_s_sleep(1);
-                const Desc d = make_desc(st + NBUF);
+                const Desc d = next_desc();
 #pragma unroll
                 for (int q = 0; q < LPW; ++q) gload(d, lds0 + s0 * STAGEB, q);
                 __builtin_amdgcn_s_waitcnt(wait_vmcnt(LPW * (NBUF - 2)));
@@ -577,7 +580,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
         // past it fetch stale data nobody uses
         {
             if constexpr (PACED) __builtin_amdgcn_s_sleep(1);
-            const Desc d = make_desc(st + NBUF);
+            const Desc d = next_desc();
             const uint32_t dst = lds0 + s0 * STAGEB;
             const int sb = s1 * STAGEB;
             mma(Fc, [&](int i) __attribute__((always_inline)) {
@@ -589,7 +592,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
         }
         {
             if constexpr (PACED) __builtin_amdgcn_s_sleep(1);
-            const Desc d = make_desc(st + 1 + NBUF);
+            const Desc d = next_desc();
             const uint32_t dst = lds0 + s1 * STAGEB;
             const int sb = s2 * STAGEB;
             mma(FH, [&](int i) __attribute__((always_inline)) {
