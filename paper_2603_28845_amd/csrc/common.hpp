@@ -92,6 +92,12 @@ onecomp_status split_update(float* C, int64_t d_out, int64_t d_in, const uint16_
 onecomp_status split_update_around(float* C, int64_t d_out, int64_t d_in, const uint16_t* Dh, const uint16_t* Dl,
                                    int64_t ldD, const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int ek, int K,
                                    int u0, int c0, int h0, int h1, int c1, hipStream_t stream);
+// C = f_inv D^T B over k = 0 .. K-1, all d_in columns (C is not read); max |C| joins *max_bits (bits of a non-negative float; nullptr:
+// not wanted).  TRI_LOWER: B[k][n] is zero for k < n, TRI_UPPER: for k > n; a tile's inner range leaves these out.
+enum Triangle : int { TRI_NONE = 0, TRI_LOWER = 1, TRI_UPPER = 2 };
+onecomp_status split_product(float* C, int64_t d_out, int64_t d_in, const uint16_t* Dh, const uint16_t* Dl, int64_t ldD,
+                             const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int K, Triangle tri, uint32_t* max_bits,
+                             hipStream_t stream);
 int64_t split_update_ld(int64_t d_out);
 // Left operand of split_update from a row-major fp32 matrix: rows [0, k_count rounded up to 32) of Dh / Dl receive
 // (src[:, k] d[k] f_d)^T as fp16 hi + lo (d == nullptr: 1; zero behind k_count), with f_d the power of two that puts

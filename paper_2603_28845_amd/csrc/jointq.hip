@@ -732,8 +732,8 @@ onecomp_status jointq_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, i
                                    c_hi, stream);
     };
     if ((st = dsplit(w.R, d_in, int(d_in), 0, 0, w.sc, nullptr)) != ONECOMP_OK) return st;
-    if ((st = fill_zero(w.Gm, d_out * d_in / 4, stream)) != ONECOMP_OK) return st;
-    if ((st = update(0, int(d_in), 0, 0, int(d_in), w.sc)) != ONECOMP_OK) return st;
+    if ((st = split_product(w.Gm, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, w.sc, pad32(int(d_in)), TRI_NONE, nullptr, stream)) != ONECOMP_OK)
+        return st;
     hipLaunchKernelGGL(jq_objective_kernel, rgrid, dim3(256), 0, stream, W, bf16, int(d_out), int(d_in), Q, scales, zeros,
                        G, n_g, perm, w.Gm, w.d, w.rowf, static_cast<float*>(nullptr));
     ONECOMP_CHECK_LAUNCH();

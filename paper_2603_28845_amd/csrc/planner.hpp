@@ -312,6 +312,17 @@ ONECOMP_HD bool trail_tile(int bid, int chunk, int n_mt, int n_nt, int& mt, int&
     return true;
 }
 
+// Products with a triangular right operand: workgroup bid -> tile (mt, nt), the columns with the longest inner ranges first
+// (lower: the left ones), so that the short ones fill up the last round; behind the first `fold` tiles the shortest first.
+ONECOMP_HD bool triangular_tile(int bid, int n_mt, int n_nt, bool lower, int fold, int& mt, int& nt) {
+    const int total = n_mt * n_nt;
+    if (bid >= total) return false;
+    const int v = bid < fold ? bid : fold + total - 1 - bid, rank = v / n_mt;
+    mt = v % n_mt;
+    nt = lower ? rank : n_nt - 1 - rank;
+    return true;
+}
+
 // ---- sweep: the feedback sums of a panel workgroup's `rows` rows, read from the working copy into MFMA accumulators:
 // lane `lane`, register r of row tile mt, column col; byte offsets from the first of the rows.  A buffer load's scalar
 // offset is no part of its bounds check, so only whole workgroups (rows == PANEL_ROWS) may step through the rows with it;

@@ -76,17 +76,6 @@ __global__ __launch_bounds__(256) void wp_kernel(const T* __restrict__ W, int64_
     block_max_bits(&sc->max_w_bits, mx, &s_max);
 }
 
-// max |M| of a row-major matrix into sc->max_w_bits
-__global__ __launch_bounds__(256) void qep_max_kernel(const float* __restrict__ M, int64_t n4, Scalars* sc) {
-    __shared__ uint32_t s_max;
-    float mx = 0.f;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n4; i += int64_t(gridDim.x) * 256) {
-        const float4v v = reinterpret_cast<const float4v*>(M)[i];
-        mx = fmaxf(fmaxf(fmaxf(mx, fabsf(v[0])), fmaxf(fabsf(v[1]), fabsf(v[2]))), fabsf(v[3]));
-    }
-    block_max_bits(&sc->max_w_bits, mx, &s_max);
-}
-
 // Right operand of a split product, B[k][n] (n contiguous, n_rows rows of which those behind n - 1 are zero), from a
 // square fp32 matrix S:  TRANS: B[k][n] = S[n][k] rs[k] cs[n],  else B[k][n] = S[k][n] rs[k] cs[n]  (rs / cs == nullptr:
 // 1);  upper: entries of S below its diagonal count as zero.  WRITE = false collects max |B| into sc->max_u_bits;
@@ -225,7 +214,6 @@ onecomp_status qep_target_run(const void* W, onecomp_dtype w_dtype, int64_t d_ou
     ONECOMP_CHECK_LAUNCH();
 
     const dim3 bgrid(unsigned(ceil_div(n, 64)), unsigned(ceil_div(n + 32, 64)));
-    const dim3 fgrid{2048};
     // right operand of product i from S (products 0 and 1: transposed; product 2: as stored; the maximum that sets
     // its scale comes from cp_kernel, from a pass of its own, from product 1), then the left operand from `left` (its
     // maximum is in sc[i])
@@ -250,39 +238,19 @@ onecomp_status qep_target_run(const void* W, onecomp_dtype w_dtype, int64_t d_ou
         ONECOMP_CHECK_LAUNCH();
         return split_left_operand(left, d_in, d_out, n, dl, sc, nullptr, w.Dh, w.Dl, stream);
     };
-    auto matmax = [&](const float* M, Scalars* sc) -> onecomp_status {
-        hipLaunchKernelGGL(qep_max_kernel, fgrid, dim3(256), 0, stream, M, d_out * d_in / 4, sc);
-        ONECOMP_CHECK_LAUNCH();
-        return ONECOMP_OK;
+    auto product = [&](int i, float* M, Triangle tri) -> onecomp_status {   // product i, the maximum for the next one's left operand
+        return split_product(M, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, w.sc + i, kp, tri, i < 2 ? &w.sc[i + 1].max_w_bits : nullptr,
+                             stream);
     };
-    auto zero = [&](float* M) -> onecomp_status { return fill_zero(M, d_out * d_in / 4, stream); };
     // M1 = (Wp D) C~^T:  B[k][n] = Cp[n][k] / (d_n d_k)
     if ((st = operands(0, w.Cp, 0, w.rd, w.rd, w.Wp, w.d)) != ONECOMP_OK) return st;
-    if ((st = zero(w.M1)) != ONECOMP_OK) return st;
-    if ((st = split_update(w.M1, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, w.sc, 0, kp, 0, 0, n, stream)) != ONECOMP_OK)
-        return st;
+    if ((st = product(0, w.M1, TRI_NONE)) != ONECOMP_OK) return st;
     // M2 = M1 U~^T:  B[k][n] = U[n][k] d_k, zero for k < n
-    if ((st = matmax(w.M1, w.sc + 1)) != ONECOMP_OK) return st;
     if ((st = operands(1, U, 1, w.d, nullptr, w.M1, nullptr)) != ONECOMP_OK) return st;
-    if ((st = zero(w.M2)) != ONECOMP_OK) return st;
-    constexpr int CH = 1024;
-    for (int c0 = 0; c0 < n; c0 += CH) {
-        const int c1 = c0 + CH < n ? c0 + CH : n;
-        const int k0 = c0 / 32 * 32;
-        if ((st = split_update(w.M2, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, w.sc + 1, k0, kp - k0, k0, c0, c1,
-                               stream)) != ONECOMP_OK)
-            return st;
-    }
+    if ((st = product(1, w.M2, TRI_LOWER)) != ONECOMP_OK) return st;
     // M3 = M2 U~ (into M1's place):  B[k][n] = U[k][n] d_n, zero for k > n
-    if ((st = matmax(w.M2, w.sc + 2)) != ONECOMP_OK) return st;
     if ((st = operands(2, U, 1, nullptr, w.d, w.M2, nullptr)) != ONECOMP_OK) return st;
-    if ((st = zero(w.M1)) != ONECOMP_OK) return st;
-    for (int c0 = 0; c0 < n; c0 += CH) {
-        const int c1 = c0 + CH < n ? c0 + CH : n;
-        if ((st = split_update(w.M1, d_out, d_in, w.Dh, w.Dl, ldD, w.Bh, w.Bl, w.sc + 2, 0, int(pad32(c1)), 0, c0, c1,
-                               stream)) != ONECOMP_OK)
-            return st;
-    }
+    if ((st = product(2, w.M1, TRI_UPPER)) != ONECOMP_OK) return st;
     hipLaunchKernelGGL(qep_final_kernel, wgrid, dim3(256), 0, stream, w.Wp, w.M1, w.rd, perm, d_in, alpha, W_star);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;

@@ -1475,20 +1475,28 @@ struct TrailArgs {
     int d_out, ldD, d_in;
     int ek, K, u0, c0, c1;     // K % 32 == 0, c0 % 8 == 0, c1 % 8 == 0
     int n_mt, n_nt, chunk;
-    int n_nt0, h0, h1;         // not FROM_ZERO: the first n_nt0 column tiles cover [c0, h0), the others [h1, c1)
-    int first;                 // FROM_ZERO: nothing has been added to these columns, they are written without being read
+    int n_nt0, h0, h1;         // not INCREMENT: the first n_nt0 column tiles cover [c0, h0), the others [h1, c1)
+    int first;                 // INCREMENT: nothing has been added to these columns, they are written without being read
+    int tri, fold;             // PRODUCT: Triangle (h0 == c1, c0 == 0) and triangular_tile's argument
+    uint32_t* max_bits;        // PRODUCT: max |C| joins this (nullptr: not wanted)
 };
 
-// FROM_ZERO: the accumulators start at zero and the product is added to the tile of C once, at the end, with one
+// INCREMENT: the accumulators start at zero and the product is added to the tile of C once, at the end, with one
 // fp32 rounding (the sweep: every rounding inside the MFMA chain then happens at the size of the increment, not of
-// the sum it joins).  Otherwise the tile of C is loaded, scaled, into the accumulators before the loop.
-template <typename S, bool FROM_ZERO>
+// the sum it joins).  SUM: the tile of C is loaded, scaled, into the accumulators before the loop.  PRODUCT: C is written without
+// being read, see split_product.
+enum TrailMode : int { SUM, INCREMENT, PRODUCT };
+template <typename S, TrailMode MODE>
 __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid, char* tl) {
+    constexpr bool FROM_ZERO = MODE == INCREMENT;
     constexpr int MT = S::MT, NT = S::NT, NBUF = S::NBUF, TM = S::TM, TN = S::TN, KT = S::KT, LPW = S::LPW;
     constexpr int A_ROWB = S::A_ROWB, B_ROWB = S::B_ROWB, A_PANELB = S::A_PANELB, B_PANELB = S::B_PANELB, STAGEB = S::STAGEB;
     constexpr int OFF_AH = S::OFF_AH, OFF_AL = S::OFF_AL, OFF_BH = S::OFF_BH, OFF_BL = S::OFF_BL;
     int mt_, nt_;
-    if (!plan::trail_tile(bid, a.chunk, a.n_mt, a.n_nt, mt_, nt_)) return;
+    const bool triangle = MODE == PRODUCT && a.tri != TRI_NONE;
+    if (!(triangle ? plan::triangular_tile(bid, a.n_mt, a.n_nt, a.tri == TRI_LOWER, a.fold, mt_, nt_)
+                   : plan::trail_tile(bid, a.chunk, a.n_mt, a.n_nt, mt_, nt_)))
+        return;
     const int m0 = mt_ * TM;
     const bool beyond = !FROM_ZERO && nt_ >= a.n_nt0;
     const int n0 = beyond ? a.h1 + (nt_ - a.n_nt0) * TN : a.c0 + nt_ * TN;
@@ -1517,14 +1525,15 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         const int c = (lane % CPR) ^ ((row & 3) << 2);
         voff_b[q] = (n0 + c * 8 < c1) ? uint32_t((int64_t(row) * d_in + n0 + c * 8) * 2) : LDS_DMA_OOB;
     }
-    const int n_kb = a.K / KT;
+    const int k_lo = triangle && a.tri == TRI_LOWER ? n0 : 0, k_hi = triangle && a.tri == TRI_UPPER ? min(a.K, n0 + TN) : a.K;
+    const int n_kb = (k_hi - k_lo) / KT;
     struct Desc {
         __amdgpu_buffer_rsrc_t ah, al, bh, bl;
     };
     // descriptors of the next k-step, empty ones behind the last.  The bases advance by additions: formed by products in
     // every step, they held back a 64 x 128 tile (14.2 against 13.9 us, 512 columns at d_out 4096).
-    const uint16_t *pah = a.Dh + int64_t(a.ek) * a.ldD, *pal = a.Dl + int64_t(a.ek) * a.ldD;
-    const uint16_t *pbh = a.Uh + int64_t(a.u0) * d_in, *pbl = a.Ul + int64_t(a.u0) * d_in;
+    const uint16_t *pah = a.Dh + int64_t(a.ek + k_lo) * a.ldD, *pal = a.Dl + int64_t(a.ek + k_lo) * a.ldD;
+    const uint16_t *pbh = a.Uh + int64_t(a.u0 + k_lo) * d_in, *pbl = a.Ul + int64_t(a.u0 + k_lo) * d_in;
     const int step_a = KT * a.ldD, step_b = KT * a.d_in;
     int ahead = n_kb;
     auto next_desc = [&]() __attribute__((always_inline)) {
@@ -1603,7 +1612,7 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         for (int n = 0; n < NT; ++n)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                if constexpr (FROM_ZERO) {
+                if constexpr (MODE != SUM) {
                     acc[m][n][r] = 0.f;
                 } else {
                     const int rr = min(m0 + wr * (32 * MT) + m * 32 + (r / 4) * 8 + lr + (r % 4), d_out - 1);
@@ -1672,6 +1681,21 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
         s0 = s2;
     }
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the workgroup ends
+    if (MODE == PRODUCT && a.max_bits) {
+        float mx = 0.f;
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool in = m0 + wr * (32 * MT) + m * 32 + (r / 4) * 8 + lr + (r % 4) < d_out && n0 + wc * (32 * NT) + n * 32 + lc < c1;
+                    mx = fmaxf(mx, in ? fabsf(acc[m][n][r] * f_inv) : 0.f);
+                }
+        mx = wave_max(mx);
+        if (lane == 0 && __float_as_uint(mx) > __hip_atomic_load(a.max_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(a.max_bits, __float_as_uint(mx));
+    }
     // uniform branch: interior tiles store without per-element masks
     if ((m0 + TM <= d_out) && (n0 + TN <= c1)) {
         float* wp = a.Wf + int64_t(m0 + wr * (32 * MT) + lr) * d_in + n0 + wc * (32 * NT) + lc;
@@ -1722,10 +1746,10 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     }
 }
 
-template <typename S, bool FROM_ZERO>
+template <typename S, TrailMode MODE>
 __global__ __launch_bounds__(256, 2) void trailing_kernel(TrailArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
-    trailing_tile<S, FROM_ZERO>(a, blockIdx.x, dyn_lds);
+    trailing_tile<S, MODE>(a, blockIdx.x, dyn_lds);
 }
 
 // One launch = the panel sweep of a super-block next to the far update of the previous super-block on the
@@ -1740,7 +1764,7 @@ __global__ __launch_bounds__(256, 2) void panel_far_kernel(PanelArgs pa, TrailAr
         if constexpr (ROWS_WG == ROWS) panel_body<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
         else panel_body16<GB, DIRECT>(pa, blockIdx.x, dyn_lds);
     }
-    else trailing_tile<TrailBig, true>(ta, blockIdx.x - n_panel, dyn_lds);
+    else trailing_tile<TrailBig, INCREMENT>(ta, blockIdx.x - n_panel, dyn_lds);
 }
 
 // Scale and zero-point of one wide group (columns g0 .. g0 + G - 1 of every row, G a multiple of 128) from its current
@@ -1945,10 +1969,10 @@ SweepWs carve(void* ws, int64_t d_out, int64_t d_in) {
 }
 
 // fills in t's work map; returns the number of workgroups
-template <typename S, bool FROM_ZERO>
+template <typename S, TrailMode MODE>
 int trail_grid(TrailArgs& t) {
     t.n_mt = int(ceil_div(t.d_out, S::TM));
-    if (FROM_ZERO) {
+    if (MODE == INCREMENT) {
         t.n_nt = int(ceil_div(t.c1 - t.c0, S::TN));
     } else {
         t.n_nt0 = t.h0 > t.c0 ? int(ceil_div(t.h0 - t.c0, S::TN)) : 0;
@@ -1957,13 +1981,18 @@ int trail_grid(TrailArgs& t) {
     t.chunk = int(ceil_div(int64_t(t.n_mt) * t.n_nt, 8));
     return t.chunk * 8;
 }
-template <typename S, bool FROM_ZERO>
+template <typename S, TrailMode MODE>
 onecomp_status launch_trailing_shape(TrailArgs t, hipStream_t stream) {
     static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<S, FROM_ZERO>), int(S::LDS_BYTES), lds_ok) != ONECOMP_OK)
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&trailing_kernel<S, MODE>), int(S::LDS_BYTES), lds_ok) != ONECOMP_OK)
         return ONECOMP_ERR_HIP;
-    const int wgs = trail_grid<S, FROM_ZERO>(t);
-    hipLaunchKernelGGL((trailing_kernel<S, FROM_ZERO>), dim3(unsigned(wgs)), dim3(256), S::LDS_BYTES, stream, t);
+    const int wgs = trail_grid<S, MODE>(t);
+    // Triangular products whose tiles are all resident at once, two on a CU: the shortest join the longest (4096 x 4096, us of the
+    // corrected target, 512 tiles, longest first all the way : folded 1072 : 1023; with more tiles 4096 x 8192 3417 : 3437, 14336 x
+    // 4096 2982 : 3019).
+    const int total = t.n_mt * t.n_nt, cus = device_cus();
+    t.fold = total > cus && total <= 2 * cus ? cus : total;
+    hipLaunchKernelGGL((trailing_kernel<S, MODE>), dim3(unsigned(wgs)), dim3(256), S::LDS_BYTES, stream, t);
     ONECOMP_CHECK_LAUNCH();
     return ONECOMP_OK;
 }
@@ -1971,10 +2000,10 @@ onecomp_status launch_trailing_shape(TrailArgs t, hipStream_t stream) {
 // own.  us of a launch, 128 x 256 : 64 x 128 tiles, d_out 4096 (64 of the former), 512 columns: K 512 22.6 : 13.9, K 128 13 :
 // 7.5; d_out 8192 (128 tiles), 512 columns, K 512 32.0 : 26.6.  Whole sweep, 4096 columns, d_out 10240 (160 tiles) 1193 : 1193,
 // 14336 (224) 1441 : 1457.
-template <bool FROM_ZERO>
+template <TrailMode MODE>
 onecomp_status launch_trailing(TrailArgs t, hipStream_t stream) {
-    return 2 * trail_grid<TrailBig, FROM_ZERO>(t) <= device_cus() ? launch_trailing_shape<TrailSmall, FROM_ZERO>(t, stream)
-                                                                  : launch_trailing_shape<TrailBig, FROM_ZERO>(t, stream);
+    return 2 * trail_grid<TrailBig, MODE>(t) <= device_cus() ? launch_trailing_shape<TrailSmall, MODE>(t, stream)
+                                                             : launch_trailing_shape<TrailBig, MODE>(t, stream);
 }
 
 template <int GB, bool DIRECT, int ROWS_WG>
@@ -2032,8 +2061,23 @@ onecomp_status split_update_around(float* C, int64_t d_out, int64_t d_in, const 
     t.Wf = C; t.Dh = Dh; t.Dl = Dl; t.Uh = Bh; t.Ul = Bl; t.sc = sc;
     t.d_out = int(d_out); t.ldD = int(ldD); t.d_in = int(d_in);
     t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
-    t.h0 = h0; t.h1 = h1; t.first = 0;
-    return launch_trailing<false>(t, stream);
+    t.h0 = h0; t.h1 = h1; t.first = 0; t.tri = TRI_NONE; t.max_bits = nullptr;
+    return launch_trailing<SUM>(t, stream);
+}
+
+onecomp_status split_product(float* C, int64_t d_out, int64_t d_in, const uint16_t* Dh, const uint16_t* Dl, int64_t ldD,
+                             const uint16_t* Bh, const uint16_t* Bl, const Scalars* sc, int K, Triangle tri, uint32_t* max_bits,
+                             hipStream_t stream) {
+    TrailArgs t;
+    t.Wf = C; t.Dh = Dh; t.Dl = Dl; t.Uh = Bh; t.Ul = Bl; t.sc = sc;
+    t.d_out = int(d_out); t.ldD = int(ldD); t.d_in = int(d_in);
+    t.ek = 0; t.K = K; t.u0 = 0; t.c0 = 0; t.c1 = int(d_in);
+    t.h0 = t.h1 = t.c1; t.first = 1; t.tri = tri; t.fold = 0; t.max_bits = max_bits;
+    // Tiles of different lengths even out better the smaller they are: up to one 128 x 256 tile per CU 64 x 128 ones are the faster.
+    // us of the corrected target, 128 x 256 : 64 x 128 tiles (number of the former): 2048 x 2048 (128) 298 : 253, 1500 x 4096 (192)
+    // 569 : 520, 2048 x 4096 (256) 650 : 635, 2500 x 4096 (320) 790 : 792, 3072 x 4096 (384) 824 : 855, 14336 x 4096 2982 : 3334.
+    if (tri != TRI_NONE && trail_grid<TrailBig, PRODUCT>(t) <= device_cus()) return launch_trailing_shape<TrailSmall, PRODUCT>(t, stream);
+    return launch_trailing<PRODUCT>(t, stream);
 }
 
 int64_t split_update_ld(int64_t d_out) { return ld_d(d_out); }
@@ -2071,7 +2115,7 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
     t.Wf = w.Wf; t.Dh = w.Dh; t.Dl = w.Dl; t.Uh = w.Uh; t.Ul = w.Ul; t.sc = w.sc;
     t.ek = 0; t.K = 0; t.u0 = 0; t.c0 = 0; t.c1 = 0; t.n_nt = 0; t.chunk = 0;
     t.d_out = int(d_out); t.ldD = int(ld_d(d_out)); t.d_in = int(d_in);
-    t.n_nt0 = 0; t.h0 = 0; t.h1 = 0; t.first = 0;
+    t.n_nt0 = 0; t.h0 = 0; t.h1 = 0; t.first = 0; t.tri = TRI_NONE; t.fold = 0; t.max_bits = nullptr;
     // fills t for Wf[:, c0 .. c1) += residual columns ek .. ek+K of buffer `buf` times rows u0 .. u0+K of Un;
     // returns the number of workgroups (0: nothing to do)
     const size_t d_buf = size_t(SBIG) * ld_d(d_out);
@@ -2080,10 +2124,10 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
         t.Dh = w.Dh + buf * d_buf; t.Dl = w.Dl + buf * d_buf;
         t.ek = ek; t.K = K; t.u0 = u0; t.c0 = c0; t.c1 = c1;
         t.first = u0 == 0;   // the first super-block's feedback is the first there is
-        return trail_grid<TrailBig, true>(t);
+        return trail_grid<TrailBig, INCREMENT>(t);
     };
     auto trailing = [&](int buf, int ek, int K, int u0, int c0, int c1) -> onecomp_status {
-        return set_trailing(buf, ek, K, u0, c0, c1) == 0 ? ONECOMP_OK : launch_trailing<true>(t, stream);
+        return set_trailing(buf, ek, K, u0, c0, c1) == 0 ? ONECOMP_OK : launch_trailing<INCREMENT>(t, stream);
     };
 
     onecomp_status st;

@@ -273,6 +273,23 @@ static void check_syrk_slab(int n_t, int cols) {
     REQUIRE(long(seen.size()) == want, "syrk slab %d, %d: %zu of %ld tiles", n_t, cols, seen.size(), want);
 }
 
+// tiles of a product with a triangular operand: each once, in front of the fold from the longest to the shortest
+static void check_triangular(int n_mt, int n_nt, bool lower, int fold) {
+    std::set<std::pair<int, int>> seen;
+    int last = 0;
+    for (int b = 0; b < n_mt * n_nt + 9; ++b) {
+        int mt = -1, nt = -1;
+        const bool live = triangular_tile(b, n_mt, n_nt, lower, fold, mt, nt);
+        REQUIRE(live == (b < n_mt * n_nt), "triangular %d x %d workgroup %d", n_mt, n_nt, b);
+        if (!live) continue;
+        REQUIRE(0 <= mt && mt < n_mt && 0 <= nt && nt < n_nt, "triangular %d x %d workgroup %d -> (%d, %d)", n_mt, n_nt, b, mt, nt);
+        REQUIRE(seen.insert({mt, nt}).second, "triangular %d x %d tile (%d, %d) owned twice", n_mt, n_nt, mt, nt);
+        const int rank = lower ? nt : n_nt - 1 - nt;
+        REQUIRE(b == 0 || b == fold || (b < fold ? rank >= last : rank <= last), "triangular %d x %d order at %d", n_mt, n_nt, b);
+        last = rank;
+    }
+}
+
 int main() {
     const int n_cus = 256;
 #ifdef PLANNER_CHECK_THIN
@@ -291,6 +308,10 @@ int main() {
 #endif
     for (int n_t : {1, 2, 3, 4, 5, 7, 8, 9, 49, 50, 111, 223, 255})
         for (int cols = 1; cols <= 7; ++cols) check_syrk_slab(n_t, cols);
+    for (int n_mt : {1, 2, 7, 32, 33})
+        for (int n_nt : {1, 3, 8, 16, 31})
+            for (int lower = 0; lower < 2; ++lower)
+                for (int fold : {1, 9, 256, 2000}) check_triangular(n_mt, n_nt, lower, fold < n_mt * n_nt ? fold : n_mt * n_nt);
     for (int d_in = 16; d_in <= 32768; d_in += step) {
         if (d_in <= 4096 || d_in % 256 == 0) {            // every width up to 4096, then every multiple of 256 (set-based checks)
             check_simple_upper(d_in, 128);

@@ -129,6 +129,30 @@ def test_qep_target(d_out, d_in, n_tok, dtype, act, alpha):
     assert torch.equal(W0, W.to(torch.float32))
 
 
+@pytest.mark.parametrize("d_out,d_in", [
+    (8600, 1040),   # 340 tiles of 128 x 256, folded; the last column of tiles 16 wide
+    (4200, 4112),   # 561 of them, longest first all the way
+])
+def test_qep_tiles_agree(d_out, d_in):
+    """Rows share the operands' scales only, which row 0 sets here, so the first rows of a layer whose products take 128 x 256 tiles are
+    those of a short layer, whose products take 64 x 128 ones: the same products in the same order.  Against 64 bits as above."""
+    _announce(f"QEP tiles {d_out} x {d_in}")
+    cfg, X, Xh = _pair(d_in, 600, seed=77)
+    H = torch.zeros((d_in, d_in), dtype=torch.float32, device=DEV)
+    og.onecomp_hessian_accumulate(Xh, H)
+    G = _gpu_cross(Xh, X)
+    U, _, info = og.onecomp_hessian_factor(H, 0.05)
+    assert int(info.item()) == 0
+    W = synth.make_weight(synth.scaled(cfg, d_out=d_out), DEV).float()
+    W[0] *= 8.0
+    whole = og.onecomp_qep_target(W, G, H, U, 0.7)
+    for rows in (1, 70, 300):
+        part = og.onecomp_qep_target(W[:rows].contiguous(), G, H, U, 0.7)
+        assert torch.equal(part, whole[:rows]), rows
+    D = 0.7 * (((W[:300].double() @ (G.double() - H.double()).t()) @ U.double().t()) @ U.double())
+    assert float((whole[:300].double() - W[:300].double() - D).norm()) <= 1e-4 * float(D.norm())
+
+
 def test_qep_full_size_sampled():
     """The error-propagation calls at the 4096 x 14336 layer, in the launch configuration bench.py --qep times
     (bf16, natural order, alpha = 1, accumulate workspace, 384 x 256 cross-Gram tiles): sampled blocks of G against
