@@ -32,62 +32,72 @@ constexpr int NB = 128;  // block size of the factorization (= GEMM tile side)
 // ------------------------------------------------------------------------------------------
 // small preparation kernels
 // ------------------------------------------------------------------------------------------
-// diag -> keys (original diagonal), dfix (dead channels -> 1), lambda = damp * mean(dfix).  One workgroup.
+// diag -> keys (original diagonal), dfix (dead channels -> 1), lambda = damp * mean(dfix); natural: the identity into perm_out.  One
+// workgroup: every entry is a line and a page of its own, so a thread has eight of them on the way.
 __global__ __launch_bounds__(1024) void prep_diag_kernel(const float* __restrict__ H, int n, double damp,
                                                         float* __restrict__ keys, double* __restrict__ dfix,
-                                                        double* __restrict__ lam, int32_t* __restrict__ info) {
+                                                        double* __restrict__ lam, int32_t* __restrict__ info,
+                                                        int natural, int32_t* __restrict__ perm_out) {
     __shared__ double part[1024];
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 1024) {
-        float h = H[int64_t(i) * n + i];
-        keys[i] = h == h ? h : -__builtin_inff();   // a NaN goes last: every position of the order is taken once
-        double d = (h == 0.0f) ? 1.0 : double(h);
-        dfix[i] = d;
-        s += d;  // fixed order per thread
+    for (int i0 = threadIdx.x; i0 < n; i0 += 8 * 1024) {
+        float h[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) h[q] = i0 + 1024 * q < n ? H[int64_t(i0 + 1024 * q) * (n + 1)] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = i0 + 1024 * q;
+            if (i >= n) break;
+            keys[i] = h[q] == h[q] ? h[q] : -__builtin_inff();   // a NaN goes last: every position of the order is taken once
+            const double d = (h[q] == 0.0f) ? 1.0 : double(h[q]);
+            dfix[i] = d;
+            s += d;  // fixed order per thread
+            if (natural && perm_out) perm_out[i] = i;
+        }
     }
     part[threadIdx.x] = s;
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    for (int w = 512; w >= 64; w >>= 1) {
         if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        *lam = damp * (part[0] / double(n));
-        *info = 0;
+    if (threadIdx.x < 64) {
+        s = part[threadIdx.x];
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
+        if (threadIdx.x == 0) {
+            *lam = damp * (s / double(n));
+            *info = 0;
+        }
     }
 }
 
-// perm: act_order ? stable descending order of keys : identity.  rank by counting: n^2 comparisons, two operations each.
+// perm: stable descending order of keys.  rank by counting: n^2 comparisons, two operations each.
 // A lane owns a key and the 16 waves of a workgroup share out the keys it is compared with, which arrive as scalar
 // loads; a thread per key that walked through all of them left the chip to 56 workgroups at d_in 14336 and waited for
 // one load after the other: 805 -> 26 us.
 constexpr int ORDER_KEYS = 64, ORDER_WAVES = 16;
-__global__ __launch_bounds__(64 * ORDER_WAVES) void order_kernel(const float* __restrict__ keys, int n, int act_order,
+__global__ __launch_bounds__(64 * ORDER_WAVES) void order_kernel(const float* __restrict__ keys, int n,
                                                                 int32_t* __restrict__ perm,
                                                                 int32_t* __restrict__ perm_out) {
     __shared__ int part[ORDER_WAVES][ORDER_KEYS];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i0 = blockIdx.x * ORDER_KEYS, i = i0 + lane;
-    if (act_order) {
-        const float ki = keys[min(i, n - 1)];
-        const int each = (n + ORDER_WAVES - 1) / ORDER_WAVES;
-        const int k0 = min(wave * each, n), k1 = min(k0 + each, n);
-        const int b0 = max(k0, min(k1, i0)), b1 = max(k0, min(k1, i0 + ORDER_KEYS));   // this workgroup's own keys
-        int rank = 0;
+    const float ki = keys[min(i, n - 1)];
+    const int each = (n + ORDER_WAVES - 1) / ORDER_WAVES;
+    const int k0 = min(wave * each, n), k1 = min(k0 + each, n);
+    const int b0 = max(k0, min(k1, i0)), b1 = max(k0, min(k1, i0 + ORDER_KEYS));   // this workgroup's own keys
+    int rank = 0;
 #pragma unroll 16
-        for (int k = k0; k < b0; ++k) rank += keys[k] >= ki;
-        for (int k = b0; k < b1; ++k) rank += (keys[k] > ki) || (keys[k] == ki && k < i);
+    for (int k = k0; k < b0; ++k) rank += keys[k] >= ki;
+    for (int k = b0; k < b1; ++k) rank += (keys[k] > ki) || (keys[k] == ki && k < i);
 #pragma unroll 16
-        for (int k = b1; k < k1; ++k) rank += keys[k] > ki;
-        part[wave][lane] = rank;
-        __syncthreads();
-    }
+    for (int k = b1; k < k1; ++k) rank += keys[k] > ki;
+    part[wave][lane] = rank;
+    __syncthreads();
     if (wave != 0 || i >= n) return;
-    int pos = i;
-    if (act_order) {
-        pos = 0;
-        for (int w = 0; w < ORDER_WAVES; ++w) pos += part[w][lane];
-    }
+    int pos = 0;
+    for (int w = 0; w < ORDER_WAVES; ++w) pos += part[w][lane];
     perm[pos] = i;
     if (perm_out) perm_out[pos] = i;
 }
@@ -1243,13 +1253,13 @@ onecomp_status factor_run(const float* H, int64_t d_in, float damp, int act_orde
     Workspace w = carve(workspace, n);
     onecomp_status st;
 
-    hipLaunchKernelGGL(prep_diag_kernel, dim3(1), dim3(1024), 0, stream, H, n, double(damp), w.keys, w.dfix, w.lam,
-                       info);
-    ONECOMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(order_kernel, dim3(unsigned(ceil_div(n, ORDER_KEYS))), dim3(64 * ORDER_WAVES), 0, stream, w.keys, n,
-                       act_order, w.perm, perm_out);
+    hipLaunchKernelGGL(prep_diag_kernel, dim3(1), dim3(1024), 0, stream, H, n, double(damp), w.keys, w.dfix, w.lam, info,
+                       int(!act_order), perm_out);
     ONECOMP_CHECK_LAUNCH();
     if (act_order) {   // w.T is free until the triangular inverse
+        hipLaunchKernelGGL(order_kernel, dim3(unsigned(ceil_div(n, ORDER_KEYS))), dim3(64 * ORDER_WAVES), 0, stream, w.keys, n, w.perm,
+                           perm_out);
+        ONECOMP_CHECK_LAUNCH();
         float* S = reinterpret_cast<float*>(w.T);
         const unsigned tiles = unsigned(ceil_div(n, 64));
         hipLaunchKernelGGL(mirror_kernel, dim3(tiles, tiles), dim3(256), 0, stream, H, n, S);
