@@ -621,14 +621,13 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
 }
 
 // Sum of the n_piece partial sums of each split tile (fixed order), then the usual epilogue: H += 2 sum, mirrored.
-// One single-wave workgroup per part of a tile: the share of one wave of the main kernel, cut into RS parts along its
-// rows and NS along its columns when that share is more than 128 registers per lane.
+// One single-wave workgroup per 32 x 32 tile: many short ones, so that the reads of some go beside the epilogues of others.  us of a
+// call, a wave's whole share or a quarter of it per workgroup : one tile: d_in 1536, 16384 tokens 113 : 74; 2048, 8192 99 : 70;
+// 4096, 8192 217 : 181; 4096, 32768 626 : 582; 4096, 131072 1907 : 1880; 8192, 32768 2008 : 1968 (14336, 32768 the same).
 template <typename C>
 struct ReduceCfg {
-    static constexpr int RS = (Ring<C>::MT * Ring<C>::NT > 8) ? 2 : 1;
-    static constexpr int NS = RS;
+    static constexpr int RS = Ring<C>::MT, NS = Ring<C>::NT;
     static constexpr int PARTS = Ring<C>::WAVES * RS * NS;   // workgroups per tile
-    static_assert(Ring<C>::MT % RS == 0 && Ring<C>::NT % NS == 0, "whole 32 x 32 tiles per part");
 };
 template <typename C>
 __global__ __launch_bounds__(64) void gram_reduce_kernel(const float* __restrict__ ws, float* __restrict__ H, int d_in,
@@ -654,6 +653,7 @@ __global__ __launch_bounds__(64) void gram_reduce_kernel(const float* __restrict
         for (int n = 0; n < NTS; ++n)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
+#pragma unroll 4
     for (int p = 0; p < n_piece; ++p) {
         const float* slot = ws + (int64_t(m_split) * n_piece + p) * (C::TM * C::TN) + wave * (MT * NT * 16 * 64) + lane;
 #pragma unroll

@@ -187,7 +187,7 @@ size_t qep_workspace_bytes(int64_t d_out, int64_t d_in) {
 //     Wp Cp^T U^T U = (Wp D) C~^T U~^T U~ D^-1,
 // each right operand (C~^T, U~^T, U~) scaled by a power of two from its own maximum, each left operand (Wp D, then
 // the two intermediate products) likewise; D^-1 goes into the last step together with alpha and the column order.
-// U is upper triangular: the second product needs k >= n, the third k <= n, taken in column chunks of 1024.
+// U is upper triangular: the second product needs k >= n, the third k <= n.
 onecomp_status qep_target_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, int64_t d_in, const float* G,
                               const float* H, const float* U, const int32_t* perm, float alpha, float* W_star,
                               void* workspace, hipStream_t stream) {

@@ -152,7 +152,7 @@ constexpr int IB = 32;          // columns swept in registers at a time
 //                 the super-block: W_b += D_b' Un[b', b] as split-fp16 MFMAs (see the trailing kernel) whose
 //                 operands are loaded from global memory already in MFMA fragment order, 16 bytes per lane:
 //                 the residual fragments were written by this workgroup after block b', the fragments of the
-//                 normalized U blocks by nearfrag_kernel.  Wave w owns the block's column tile w (64 x 32).
+//                 normalized U blocks by operands_kernel.  Wave w owns the block's column tile w (64 x 32).
 //   sequential    four lanes per row (a quad), each holding 8 of the 32 columns of the inner block; the current
 //                 column is broadcast inside the quad by DPP, the grid arithmetic is replicated, the feedback is
 //                 8 FMAs per lane.  All four waves work (16 rows each).  127 cycles a column: one wave per SIMD issues
@@ -1432,7 +1432,7 @@ __global__ __launch_bounds__(256) void operands_kernel(const float* __restrict__
 // ------------------------------------------------------------------------------------------
 // trailing update:  Wf[:, c0 .. c1) += f_inv * D[:, ek .. ek+K) * Un[u0 .. u0+K, c0 .. c1)
 // with D = -(w - w^) f_d (stored transposed, Dt[k][row], by the panel kernel) and Un = U_jk / U_jj f_u
-// (split_kernel).
+// (operands_kernel).
 //
 // fp32 accuracy from fp16 MFMAs: both operands are split x = hi + lo (fp16 each, |lo| <= 2^-11 |hi|) and
 // three products are accumulated in fp32, hi*hi + hi*lo + lo*hi; the dropped lo*lo term and the rounding
