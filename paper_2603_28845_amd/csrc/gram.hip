@@ -1297,6 +1297,18 @@ bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
     return n_tokens <= most && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
 }
 
+// Before both: layers of few 256 x 256 tiles cut these into pieces, with the workspace (plan_split: up to two thirds of the CUs, 512
+// tokens and more each).  us of a call, the kernel chosen otherwise : pieces:
+//   d_in 1024, 1024 tokens: 24.6 : 26.2;  2048: 33.2 : 28.7;  4096: 45 : 32;  8192: 64 : 41;  12288: 78 : 47 (16384: 62 : 53)
+//   d_in 1408, 1024 tokens: 25.2 : 29.2;  2048: 41 : 32.5;  4096: 61 : 37;  6144: 58 : 43;  8192: 60 : 47
+//   d_in 2048, 1024 tokens: 30.4 : 32.2;  2048: 41.6 : 35.6;  4096: 61 : 46;  6144: 64 : 54 (with 252 pieces 73)
+//   d_in 3072, 1024 tokens: 42 : 41;  2048: 56 : 52;  3072: 68 : 60;  4096: 81 : 68
+bool short_pieces_bf16(int64_t n_tokens, int64_t d_in, size_t ws_bytes) {
+    const int64_t n256 = ceil_div(d_in, 256), big = n256 * (n256 + 1) / 2, n_cus = device_cus();
+    return d_in >= 1024 && n_tokens >= 1536 && 3 * big <= n_cus && n_cus > 0 &&
+           plan_split(big, n256, d_in, n_tokens, int(n_cus), int64_t(ws_bytes / GRAM_SLOT_BYTES)).use_ws;
+}
+
 // ... and the smallest of them the register-staged kernel, which has no ring to fill.  us of a call, staged : RingSmall:
 //   d_in   64,  16 tokens: 11.8 : 12.1;  64: 12.6 : 12.6;  128: 13.4 : 13.3
 //   d_in 1024,  16 tokens: 15.3 : 15.6;  64: 15.8 : 16.0;  128: 16.7 : 16.5;  200: 17.9 : 17.4
@@ -1342,7 +1354,7 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
     // The register-staged kernel takes the smallest calls, rows too far apart for the 32-bit byte offsets that the others
     // have inside a step of tokens, and narrow layers when a shape of wide ones is forced
     const bool far_rows = ldx * 64 >= (int64_t(1) << 31);
-    if (!far_rows && forced_shape() < 0) {
+    if (!far_rows && forced_shape() < 0 && !short_pieces_bf16(n_tokens, d_in, ws_bytes)) {
         if (split_bf16(n_tokens, d_in)) {
             if (!info) return launch_bf16_split(X, n_tokens, d_in, ldx, H, stream);
             *info = GramPlanInfo{B16S_TS, B16S_TS, 1};

@@ -284,9 +284,12 @@ inline SplitPlan plan_split(int64_t n_tiles, int64_t n_ct, int64_t d_in, int64_t
     }
     const int max_pc = mirror_ok ? 16 : 8;   // the larger slots of the other shapes: fewer of them
     for (int pc = 2; pc <= max_pc; ++pc) {
-        if (n_tokens / pc < 2048) break;
+        // Pieces of 512 tokens and more where all pieces together leave a third of the CUs idle (short_pieces_bf16): what is written and
+        // read back grows with their number, and beyond some 150 of 256 KB faster than it.
+        const bool long_pieces = n_tokens / pc >= 2048;
+        if (!long_pieces && !(mirror_ok && n_tokens / pc >= 512 && 3 * n_tiles * pc <= 2 * n_cus)) break;
         const double piece_cost = 1.0 / pc + 0.005;
-        if (r > 0 && n_tiles > n_cus && r * pc <= ws_slots) {   // the leftover tiles, from the end of the rank order
+        if (long_pieces && r > 0 && n_tiles > n_cus && r * pc <= ws_slots) {   // the leftover tiles, from the end of the rank order
             const double rounds = double(n_tiles / n_cus) + double(cdiv(r * pc, n_cus)) * piece_cost;
             if (rounds < best.rounds) best = SplitPlan{int(n_tiles - r), int(r), pc, true, rounds};
         }

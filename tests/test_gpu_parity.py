@@ -323,6 +323,33 @@ def test_gram_with_workspace(d_in, n_tok, ws_frac):
     assert rel_fro(H2.cpu().numpy().astype(np.float64), 2.0 * Hn.astype(np.float64)) <= 5e-6
 
 
+@pytest.mark.parametrize("d_in,n_tok,tile", [
+    (1024, 1535, 128), (1024, 1536, 256),   # three pieces of 512 tokens
+    (1040, 2055, 256),                      # ragged last tiles, four pieces, the last one 3 tokens longer than a step
+    (2048, 2111, 256), (3072, 1537, 256), (3088, 2100, 128),   # the widest; one block wider
+])
+def test_gram_bf16_short_pieces(d_in, n_tok, tile):
+    """Short calls whose 256 x 256 tiles are cut into pieces of 512 tokens and more, onto what H holds, whatever the workspace holds."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("widths for 256 compute units")
+    _announce(f"gram in short pieces, d_in={d_in} n_tok={n_tok}")
+    ws = torch.empty(og.onecomp_accumulate_workspace_bytes(torch.bfloat16, d_in), dtype=torch.uint8, device=DEV)
+    ws.fill_(0xFF)
+    plan = og.onecomp_accumulate_describe(torch.bfloat16, n_tok, d_in, ws.numel())
+    assert plan["tile_rows"] == tile and plan["tile_cols"] == tile
+    g = torch.Generator(device=DEV).manual_seed(d_in + n_tok)
+    X = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    H = torch.eye(d_in, device=DEV)
+    og.onecomp_hessian_accumulate(X, H, workspace=ws)
+    assert torch.equal(H, H.T)
+    Xd = X.double()
+    ref = 2.0 * (Xd.T @ Xd)
+    E = H.double() - ref
+    E.diagonal().sub_(1.0)
+    # products of bf16 are exact; rounding errors of n_tok fp32 additions add up like a random walk (see the fp32 tiles)
+    assert float(E.norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
+
+
 @pytest.mark.parametrize("shape", ["wide", "big", "mid"])
 @pytest.mark.parametrize("d_in,n_tok,with_ws", [
     (1040, 333, False),     # one ragged tile row and column
