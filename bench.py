@@ -26,8 +26,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # L2 <-> fabric bytes per call from rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a plain 4 GiB copy), taken with
 # `python bench.py --phase gram|sweep` under rocprofv3 --pmc; see profiles/c3b_hbm_traffic_pmc.md for the commands
-GRAM_TRAFFIC_C3B = 69.3e9     # 68.1 GB fetched + 1.2 GB written per accumulate call (384 x 256 tiles, paced launches)
-SWEEP_TRAFFIC_C3B = 13.3e9
+GRAM_TRAFFIC_C3B = 76.6e9     # 75.4 GB fetched + 1.2 GB written per accumulate call (384 x 256 tiles, paced launches)
+SWEEP_TRAFFIC_C3B = 12.7e9
 
 
 def sweep_model_bytes_b128(d_out, d_in, B, G, w_bytes):
@@ -45,24 +45,24 @@ def sweep_model_bytes_b128(d_out, d_in, B, G, w_bytes):
 
 def sweep_model_bytes(d_out, d_in, G, w_bytes, SBW=512):
     """HBM bytes of the schedule onecomp_quantize_layer runs for G <= 128 (super-blocks of SBW = 512 columns):
-      preparation   W in, fp32 working copy out; the strict upper block triangle of U read twice (maximum, then
+      preparation   W in; the strict upper block triangle of U read twice (maximum, then
                     split) and written once as two fp16 halves
-      per super-block  its columns of the working copy (the fp32 feedback sums) and of W in, codes / W^ / scales /
+      per super-block  its columns of the working copy (the fp32 feedback sums; not of the first) and of W in, codes / W^ / scales /
                     zeros out, its residuals out as two fp16 halves (transposed panel), the 128 x 128 diagonal blocks
                     of U in
-      far update    the columns beyond the super-block read and written once (8 B / element), the residual panel
+      far update    the columns beyond the super-block read (not by the first) and written once, the residual panel
                     and the super-block's rows of the split U read once
     Operands that the panel kernel writes and reads back itself (residual fragments) and re-reads of the same
     panel by different workgroups are counted once or not at all: they are served by L2."""
-    total = d_out * d_in * (w_bytes + 4)
+    total = d_out * d_in * w_bytes
     upper = d_in * (d_in - 128) // 2
     total += upper * (4 + 4 + 4)
     for s0 in range(0, d_in, SBW):
         s1 = min(d_in, s0 + SBW)
         wdt = s1 - s0
-        total += d_out * wdt * (4 + w_bytes + 1 + 4) + 8 * d_out * wdt // G + d_out * wdt * 4 + (wdt // 128) * 128 * 128 * 4
+        total += d_out * wdt * ((4 if s0 else 0) + w_bytes + 1 + 4) + 8 * d_out * wdt // G + d_out * wdt * 4 + (wdt // 128) * 128 * 128 * 4
         rest = d_in - s1
-        total += 8 * d_out * rest + 4 * d_out * wdt + 4 * wdt * rest
+        total += (8 if s0 else 4) * d_out * rest + 4 * d_out * wdt + 4 * wdt * rest
     return total
 
 
