@@ -1320,13 +1320,13 @@ GramShape choose_shape(int64_t d_in, int64_t n_tokens, int n_cus, size_t ws_byte
     const int64_t n256 = ceil_div(d_in, 256), n128 = ceil_div(d_in, 128), n384 = ceil_div(d_in, 384);
     const int64_t big = n256 * (n256 + 1) / 2;
     const int64_t mid = plan::n_tiles128(int(n128), int(n256)), wide = plan::n_tiles_wide(int(n384), int(n256));
-    const SplitPlan sp_big = plan_split(big, n256, d_in, n_tokens, n_cus, int64_t(ws_bytes / GRAM_SLOT_BYTES));
-    const SplitPlan sp_wide = plan_split(wide, n256, d_in, n_tokens, n_cus, int64_t(ws_bytes / GRAM_WIDE_SLOT_BYTES), false);
-    const double cost_big = 2.0 * sp_big.rounds, cost_wide = WIDE_UNITS * sp_wide.rounds;
+    const double cost_big = 2.0 * plan_split(big, n256, d_in, n_tokens, n_cus, int64_t(ws_bytes / GRAM_SLOT_BYTES)).rounds;
     const double cost_mid = 1.15 * double(ceil_div(mid, n_cus));
+    const double cost_wide =
+        WIDE_UNITS * plan_split(wide, n256, d_in, n_tokens, n_cus, int64_t(ws_bytes / GRAM_WIDE_SLOT_BYTES), false).rounds;
     const int f = forced_shape();
     if (f >= 0) return GramShape(f);
-    if (n_tokens >= WIDE_MIN_TOKENS && WIDE_UNITS * sp_wide.cost < 2.0 * sp_big.cost && cost_wide < cost_mid) return GramShape::Wide;
+    if (n_tokens >= WIDE_MIN_TOKENS && cost_wide < cost_big && cost_wide < cost_mid) return GramShape::Wide;
     return cost_big <= cost_mid ? GramShape::Big : GramShape::Mid;
 }
 

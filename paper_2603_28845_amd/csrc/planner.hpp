@@ -266,8 +266,7 @@ ONECOMP_HD void piece_tokens(int64_t n_tokens, int n_piece, int piece, int kt, i
 struct SplitPlan {
     int split0 = 0, n_split = 0, n_piece = 1;
     bool use_ws = false;
-    double rounds = 0.0;   // over the CUs, in tiles of all tokens
-    double cost = 0.0;     // with what the pieces write and read back
+    double rounds = 0.0;
 };
 // mirror_ok: the tiles are 256 x 256, so the workspace-free form exists (other tile shapes split only with a workspace,
 // whose slots are then partial sums of that shape).
@@ -283,15 +282,6 @@ inline SplitPlan plan_split(int64_t n_tiles, int64_t n_ct, int64_t d_in, int64_t
         best.n_piece = 2;
         best.rounds = double(n_tiles / n_cus) + 0.5 * 1.06;
     }
-    best.cost = best.rounds;
-    // Calls of 12288 to 98304 tokens: what a round of pieces writes and reads back, in tiles of all tokens (0.024 us a token; the larger
-    // tiles 1.35 times that): 64 MB a round of 256, some 35 us; and one round of pieces leaves CUs free, more of them for few tiles,
-    // since it runs a third longer on all of them.  us of a call, without : with both: d_in 1408, 24576 tokens 120 : 88; 2048, 16384 131 : 94,
-    // 32768 228 : 156, 65536 427 : 288; 3072, 32768 395 : 294; 3584, 16384 294 : 214; 4096, 16384 334 : 299, 32768 566 : 534; 5120, 16384
-    // 522 : 409.  Shorter calls lose by it (3072, 8192 106 : 116), longer ones have not been measured.
-    const bool counted = n_tokens >= 12288 && n_tokens <= 98304;
-    const double traffic = counted ? (mirror_ok ? 5.8 : 6.4) * n_cus / double(n_tokens) : 0.0;
-    const bool few = 6 * n_tiles <= n_cus && 16 * n_tiles > n_cus;   // (15 tiles of d_in 1280 in 16 pieces: as fast on 240 CUs, 79 : 81 us)
     const int max_pc = mirror_ok ? 16 : 8;   // the larger slots of the other shapes: fewer of them
     for (int pc = 2; pc <= max_pc; ++pc) {
         // Pieces of 512 tokens and more where all pieces together leave a third of the CUs idle (short_pieces_bf16): what is written and
@@ -301,14 +291,11 @@ inline SplitPlan plan_split(int64_t n_tiles, int64_t n_ct, int64_t d_in, int64_t
         const double piece_cost = 1.0 / pc + 0.005;
         if (long_pieces && r > 0 && n_tiles > n_cus && r * pc <= ws_slots) {   // the leftover tiles, from the end of the rank order
             const double rounds = double(n_tiles / n_cus) + double(cdiv(r * pc, n_cus)) * piece_cost;
-            if (rounds < best.cost) best = SplitPlan{int(n_tiles - r), int(r), pc, true, rounds, rounds};
+            if (rounds < best.rounds) best = SplitPlan{int(n_tiles - r), int(r), pc, true, rounds};
         }
-        // every tile
-        const bool too_full = counted && mirror_ok && n_tiles * pc <= n_cus && 16 * n_tiles * pc > (few ? 14 : 15) * n_cus;
-        if (n_tiles < 2 * n_cus && n_tiles * pc <= ws_slots && !too_full) {
-            const int64_t n_rounds = cdiv(n_tiles * pc, n_cus);
-            const double rounds = double(n_rounds) * piece_cost, cost = rounds + double(n_rounds) * traffic;
-            if (cost < best.cost) best = SplitPlan{0, int(n_tiles), pc, true, rounds, cost};
+        if (n_tiles < 2 * n_cus && n_tiles * pc <= ws_slots) {   // every tile
+            const double rounds = double(cdiv(n_tiles * pc, n_cus)) * piece_cost;
+            if (rounds < best.rounds) best = SplitPlan{0, int(n_tiles), pc, true, rounds};
         }
     }
     return best;

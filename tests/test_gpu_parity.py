@@ -350,6 +350,33 @@ def test_gram_bf16_short_pieces(d_in, n_tok, tile):
     assert float(E.norm() / ref.norm()) <= 2.0 ** -24 * (6.0 * n_tok ** 0.5 + 2.0)
 
 
+@pytest.mark.parametrize("d_in,n_tok,pieces", [(3072, 32768, 13), (3584, 24576, 12), (5120, 12288, 6), (6144, 24576, 6)])
+def test_gram_bf16_pieces_round_little(d_in, n_tok, pieces):
+    """A chain of fp32 additions is as long as a piece of the tokens, so the error against 64 bits is that of as many pieces as fill
+    the compute units best.  Sums of k independent products of unit variance are sqrt(k) in size; the matrix instruction rounds them
+    every 8 tokens, each time by u sqrt(k) at most in the root mean square, u = 2^-24 / sqrt(3), and so do the additions of the pieces:
+    over n tokens in p pieces n u sqrt(1 / (16 p) + p / (2 n)).  (The mantissas' spread makes it some 0.7 of that.)"""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("widths for 256 compute units")
+    _announce(f"gram, rounding of {pieces} pieces, d_in={d_in} n_tok={n_tok}")
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    X = torch.randn((n_tok, d_in), generator=g, device=DEV).bfloat16()
+    ws = torch.empty(og.onecomp_accumulate_workspace_bytes(torch.bfloat16, d_in), dtype=torch.uint8, device=DEV)
+    H = torch.zeros((d_in, d_in), device=DEV)
+    og.onecomp_hessian_accumulate(X, H, workspace=ws)
+    rows = torch.arange(7, d_in, 16, device=DEV)
+    ref = torch.zeros((rows.numel(), d_in), dtype=torch.float64, device=DEV)
+    for t in range(0, n_tok, 4096):
+        x = X[t:t + 4096].double()
+        ref += 2.0 * (x[:, rows].t().contiguous() @ x)
+    E = H[rows].double() - ref
+    E[torch.arange(rows.numel(), device=DEV), rows] = 0.0
+    rms = float(E.square().mean().sqrt()) / (2.0 * n_tok)
+    bound = 2.0 ** -24 / 3.0 ** 0.5 * (1.0 / (16.0 * pieces) + pieces / (2.0 * n_tok)) ** 0.5
+    _announce(f"   {rms / bound:.3f} of the bound")
+    assert rms <= bound
+
+
 @pytest.mark.parametrize("shape", ["wide", "big", "mid"])
 @pytest.mark.parametrize("d_in,n_tok,with_ws", [
     (1040, 333, False),     # one ragged tile row and column
