@@ -398,7 +398,7 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
     // bid: rank of this workgroup in the whole schedule; a launch covers a run of ranks starting at bid0
     const int bid = int(blockIdx.x) + bid0;
     plan::RingWork rw;
-    if (!plan::ring_work(bid, chunk, n_tiles, split0, n_split, rw)) return;
+    if (!plan::ring_work(bid, chunk, n_tiles, split0, n_split, n_piece, rw)) return;
     const int v = rw.v, piece = rw.piece, m_split = rw.m_split;
     if (piece >= 0) {   // this workgroup's share of the tokens: whole steps of KT
         int64_t t_begin, count;

@@ -221,14 +221,17 @@ ONECOMP_HD void cross_tile_from_rank(int v, int n_rt, int n_ct, int& ti, int& tk
 // Workgroups 0 .. 8 chunk - 1 take whole tiles: the ranks outside [split0, split0 + n_split), `chunk` of them per
 // XCD (hardware deals consecutive workgroups round-robin to the 8 XCDs, so workgroup b takes position
 // (b % 8) * chunk + b / 8: each XCD owns a contiguous run of the order).  The workgroups after them take the n_split
-// tiles of that range in n_piece pieces of the token axis each; on an XCD the pieces run tile after tile for one
-// range of tokens, then for the next.  Returns false for a workgroup with nothing to do.
+// tiles of that range in n_piece pieces of the token axis each, an eighth of all pieces per XCD; on an XCD the pieces run tile
+// after tile for one range of tokens, then for the next.  Returns false for a workgroup with nothing to do.
+// (With an eighth of the tiles and all their pieces instead, 36 tiles in 7 pieces are 35 workgroups on seven XCDs of 32 CUs and 7 on
+// the last: a second round.  us of a call, so : pieces dealt: d_in 1024, 8192 tokens 41.5 : 34.8; 1408, 32768 148 : 98; 2048, 32768
+// 236 : 153; 3072, 32768 411 : 376; 3584, 16384 307 : 264; 8192, 98304 5960 : 5540.)
 struct RingWork {
     int v;         // tile rank in the order of the tile map
     int piece;     // -1: the whole token axis; else the piece number
     int m_split;   // index of the tile among the split ones
 };
-ONECOMP_HD bool ring_work(int bid, int chunk, int n_tiles, int split0, int n_split, RingWork& w) {
+ONECOMP_HD bool ring_work(int bid, int chunk, int n_tiles, int split0, int n_split, int n_piece, RingWork& w) {
     w.piece = -1;
     w.m_split = 0;
     if (bid < 8 * chunk) {
@@ -237,15 +240,24 @@ ONECOMP_HD bool ring_work(int bid, int chunk, int n_tiles, int split0, int n_spl
         if (w.v >= split0) w.v += n_split;
         return true;
     }
-    const int b = bid - 8 * chunk, per_xcd = (n_split + 7) >> 3, j = b >> 3;
-    w.m_split = (b & 7) * per_xcd + j % per_xcd;
-    if (w.m_split >= n_split) return false;
+    // an XCD's run of (tile, piece): the first tile from piece s0 on, the last one up to piece l1; taken piece by piece
+    const int b = bid - 8 * chunk, total = n_split * n_piece, per_xcd = (total + 7) >> 3, j = b >> 3;
+    const int first = (b & 7) * per_xcd, end = imin(first + per_xcd, total);
+    if (first + j >= end) return false;
+    const int t0 = first / n_piece, t1 = (end - 1) / n_piece, s0 = first - t0 * n_piece, l1 = end - t1 * n_piece;
+    int p = 0, before = 0;   // pieces of the run with numbers below p
+    for (;; ++p) {
+        const int here = t1 - t0 + 1 - (p < s0) - (p >= l1);
+        if (j < before + here) break;
+        before += here;
+    }
+    w.piece = p;
+    w.m_split = t0 + (p < s0) + j - before;
     w.v = split0 + w.m_split;
-    w.piece = j / per_xcd;
     return true;
 }
 // total workgroups of the schedule
-ONECOMP_HD int ring_total_blocks(int chunk, int n_split, int n_piece) { return chunk * 8 + 8 * n_piece * int(cdiv(n_split, 8)); }
+ONECOMP_HD int ring_total_blocks(int chunk, int n_split, int n_piece) { return chunk * 8 + 8 * int(cdiv(n_split * n_piece, 8)); }
 // tokens [t_begin, t_begin + count) of a piece: whole steps of kt tokens; count <= 0: nothing left for this piece
 ONECOMP_HD void piece_tokens(int64_t n_tokens, int n_piece, int piece, int kt, int64_t& t_begin, int64_t& count) {
     const int64_t n_st_all = (n_tokens + kt - 1) / kt;

@@ -165,9 +165,10 @@ static void check_ring(int d_in, int64_t n_tokens, int n_cus, int64_t ws_slots, 
     const int total = ring_total_blocks(chunk, sp.n_split, sp.n_piece);
     std::vector<int> whole(n_tiles, 0);
     std::vector<std::vector<int>> pieces(n_tiles);
+    int on_xcd[8] = {};   // pieces per XCD: an eighth each, so that whole rounds of the chip are whole rounds of its XCDs
     for (int bid = 0; bid < total; ++bid) {
         RingWork w;
-        if (!ring_work(bid, chunk, n_tiles, sp.split0, sp.n_split, w)) continue;
+        if (!ring_work(bid, chunk, n_tiles, sp.split0, sp.n_split, sp.n_piece, w)) continue;
         REQUIRE(w.v >= 0 && w.v < n_tiles, "d_in %d block %d -> rank %d of %d", d_in, bid, w.v, n_tiles);
         int ti, tk;
         tile_of(shape, w.v, n_rt, n_ct, ti, tk);
@@ -182,6 +183,7 @@ static void check_ring(int d_in, int64_t n_tokens, int n_cus, int64_t ws_slots, 
                     "d_in %d piece of a tile outside the split range", d_in);
             REQUIRE(w.piece < sp.n_piece, "d_in %d piece %d of %d", d_in, w.piece, sp.n_piece);
             pieces[w.v].push_back(w.piece);
+            REQUIRE(++on_xcd[bid % 8] <= cdiv(int64_t(sp.n_split) * sp.n_piece, 8), "d_in %d: more than an eighth of the pieces on an XCD", d_in);
         }
     }
     for (int v = 0; v < n_tiles; ++v) {
@@ -220,7 +222,7 @@ static void check_cross(int d_in, Shape shape) {
     std::set<std::pair<int, int>> seen;
     for (int bid = 0; bid < ring_total_blocks(chunk, 0, 1); ++bid) {
         RingWork w;
-        if (!ring_work(bid, chunk, n_tiles, 0, 0, w)) continue;
+        if (!ring_work(bid, chunk, n_tiles, 0, 0, 1, w)) continue;
         int ti, tk;
         cross_tile_from_rank(w.v, n_rt, n_ct, ti, tk);
         REQUIRE(ti >= 0 && ti < n_rt && tk >= 0 && tk < n_ct, "cross d_in %d rank %d -> (%d, %d)", d_in, w.v, ti, tk);
