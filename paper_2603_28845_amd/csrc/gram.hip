@@ -1297,12 +1297,13 @@ bool few_tokens_bf16(int64_t n_tokens, int64_t d_in, bool workspace) {
     return n_tokens <= most && n_tokens * d_in * d_in < (workspace ? 400000000000 : 30000000000);
 }
 
-// Before both: layers of few 256 x 256 tiles cut these into pieces, with the workspace (plan_split: up to two thirds of the CUs, 512
+// Before these: layers of few 256 x 256 tiles cut them into pieces, with the workspace (plan_split: up to two thirds of the CUs, 512
 // tokens and more each).  us of a call, the kernel chosen otherwise : pieces:
-//   d_in 1024, 1024 tokens: 24.6 : 26.2;  2048: 33.2 : 28.7;  4096: 45 : 32;  8192: 64 : 41;  12288: 78 : 47 (16384: 62 : 53)
-//   d_in 1408, 1024 tokens: 25.2 : 29.2;  2048: 41 : 32.5;  4096: 61 : 37;  6144: 58 : 43;  8192: 60 : 47
-//   d_in 2048, 1024 tokens: 30.4 : 32.2;  2048: 41.6 : 35.6;  4096: 61 : 46;  6144: 64 : 54 (with 252 pieces 73)
+//   d_in 1408, 1024 tokens: 25.2 : 29.2;  2048: 41 : 32.5;  4096: 61 : 36;  6144: 58 : 40;  8192: 60 : 45
+//   d_in 2048, 1024 tokens: 30.4 : 32.2;  2048: 41.6 : 35.6;  4096: 61 : 46;  6144: 64 : 54
 //   d_in 3072, 1024 tokens: 42 : 41;  2048: 56 : 52;  3072: 68 : 60;  4096: 81 : 68
+// The calls of split_bf16 stay there, though pieces would be the faster (d_in 1024, 4096 tokens 45 : 30; 1280, 8192 65 : 39): sixteen
+// chains of additions side by side are closer to 64 bits than the four to sixteen pieces (errors 1 : 1.05 to 1.6).
 bool short_pieces_bf16(int64_t n_tokens, int64_t d_in, size_t ws_bytes) {
     const int64_t n256 = ceil_div(d_in, 256), big = n256 * (n256 + 1) / 2, n_cus = device_cus();
     return d_in >= 1024 && n_tokens >= 1536 && 3 * big <= n_cus && n_cus > 0 &&
@@ -1354,13 +1355,14 @@ onecomp_status gram_accumulate_bf16(const void* X, int64_t n_tokens, int64_t d_i
     // The register-staged kernel takes the smallest calls, rows too far apart for the 32-bit byte offsets that the others
     // have inside a step of tokens, and narrow layers when a shape of wide ones is forced
     const bool far_rows = ldx * 64 >= (int64_t(1) << 31);
-    if (!far_rows && forced_shape() < 0 && !short_pieces_bf16(n_tokens, d_in, ws_bytes)) {
+    if (!far_rows && forced_shape() < 0) {
         if (split_bf16(n_tokens, d_in)) {
             if (!info) return launch_bf16_split(X, n_tokens, d_in, ldx, H, stream);
             *info = GramPlanInfo{B16S_TS, B16S_TS, 1};
             return ONECOMP_OK;
         }
-        if (!staged_bf16(n_tokens, d_in) && few_tokens_bf16(n_tokens, d_in, ws_bytes > 0)) {
+        if (!short_pieces_bf16(n_tokens, d_in, ws_bytes) && !staged_bf16(n_tokens, d_in) &&
+            few_tokens_bf16(n_tokens, d_in, ws_bytes > 0)) {
             if (!info) return launch_bf16_ring<RingSmall, false>(X, X, n_tokens, d_in, ldx, ldx, H, nullptr, 0, stream);
             info->launches = 1;
             return ONECOMP_OK;
