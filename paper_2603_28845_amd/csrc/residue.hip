@@ -23,40 +23,6 @@ namespace {
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef int int16v __attribute__((ext_vector_type(16)));
 
-// Pairwise coprime; 256 needs no reduction, the others are at most 251 so that a value reduced with an error of 2 in the
-// 32-bit quotient's numerator (convert_piece) still fits 8 bits.
-constexpr int MOD[MODULI] = {256, 251, 249, 247, 245, 241, 239, 233, 229, 227, 223, 211, 199, 197};   // 2^109.94
-constexpr int BOUND_EXP = 109;            // BOUND = 2^108.8 = 0.8705 2^109
-constexpr double BOUND_MANT = 0.87;
-
-struct Tables {
-    float inv[MODULI];                  // 1 / m
-    int c1[MODULI], c2[MODULI];         // 2^18 and 2^36 mod m, balanced
-    double hi[MODULI], lo[MODULI];      // q / m in two parts, q the inverse of M / m: x / M = sum r q / m mod 1
-    double M;
-};
-constexpr int balanced(int64_t x, int m) { return int(x % m) > m / 2 ? int(x % m) - m : int(x % m); }
-constexpr Tables make_tables() {
-    Tables t{};
-    t.M = 1.0;
-    for (int i = 0; i < MODULI; ++i) {
-        const int m = MOD[i];
-        t.inv[i] = 1.0f / float(m);
-        t.c1[i] = balanced(int64_t(1) << 18, m);
-        t.c2[i] = balanced(int64_t(1) << 36, m);
-        int64_t p = 1;
-        for (int j = 0; j < MODULI; ++j)
-            if (j != i) p = p * MOD[j] % m;
-        int64_t q = 1;
-        while (p * q % m != 1) ++q;
-        // the upper part in units of 2^-40, so that MODULI products with 8-bit residues add up exactly in 53 bits
-        t.hi[i] = double((q << 40) / m) * 0x1p-40;
-        t.lo[i] = double((q << 40) % m) / m * 0x1p-40;
-        t.M *= m;
-    }
-    return t;
-}
-constexpr Tables TAB = make_tables();
 struct DeviceTables {
     int m[MODULI];
     float inv[MODULI];
@@ -71,42 +37,13 @@ constexpr DeviceTables device_tables() {
 }
 __constant__ DeviceTables d_tab = device_tables();   // where the modulus is known at run time only
 
-// the scale of a row of squared norm s
-__device__ __forceinline__ int32_t shift_of(double s) {
-    if (!(s < __builtin_inf())) return NO_SHIFT;
-    if (!(s > 0.0)) return s == 0.0 ? 0 : NO_SHIFT;
-    int e;
-    const double f = __builtin_frexp(s, &e);          // s = f 2^e, f in [0.5, 1)
-    const int d = BOUND_EXP - e;                      // f 2^(e + 2 shift) <= BOUND_MANT 2^BOUND_EXP
-    return (d & 1) ? (d - 1) / 2 : f <= BOUND_MANT ? d / 2 : d / 2 - 1;
-}
-
-// a c + b, 24-bit factors: two of these are what the compiler makes two products and a sum of three of
-__device__ __forceinline__ int mad24(int a, int c, int b) {
-    int r;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(c), "v"(b));
-    return r;
-}
-__device__ __forceinline__ int low_word(double x) { return int(uint32_t(__builtin_bit_cast(uint64_t, x))); }
-
 // 16 entries of one row, scaled by 2^s -> 16 bytes per modulus at dst, dst + plane, ...
-// N = rint(x) = n2 2^36 + n1 2^18 + n0 with |n0|, |n1| <= 2^17 and |n2| < 2^19, each rounded by adding 1.5 2^52, whose sum holds
-// it in its low word; so n2 c2 + n1 c1 + n0 stays below 2^26 and its quotient by m, from fp32, is off by 2 / m at most.
-// 1.5 2^23 + q holds q in its low bits; the offset 2^22 m it brings into the product leaves the low byte alone.
 // Conversions of fp64 to integers and back instead, and the compiler's choice of products: 120 vector instructions an entry,
 // 30 of them fp64 at a quarter of the rate; now 100.
 __device__ __forceinline__ void convert_piece(const double (&x)[16], char* __restrict__ dst, int64_t plane) {
-    constexpr double MAGIC = 0x1.8p52;
     int n0[16], n1[16], n2[16];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const double h = __builtin_fma(x[e], 0x1p-36, MAGIC);
-        const double l = __builtin_fma(-(h - MAGIC), 0x1p36, x[e]);
-        const double g = __builtin_fma(l, 0x1p-18, MAGIC);
-        n2[e] = low_word(h);
-        n1[e] = low_word(g);
-        n0[e] = low_word(__builtin_fma(-(g - MAGIC), 0x1p18, l) + MAGIC);
-    }
+    for (int e = 0; e < 16; ++e) split_entry(x[e], n0[e], n1[e], n2[e]);
 #pragma unroll
     for (int i = 0; i < MODULI; ++i) {
         uint4v w;
@@ -114,15 +51,7 @@ __device__ __forceinline__ void convert_piece(const double (&x)[16], char* __res
         for (int q = 0; q < 4; ++q) {
             uint32_t b[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (MOD[i] == 256) {
-                    b[e] = uint32_t(n0[4 * q + e]);   // 2^18 and 2^36 are zero mod 256
-                } else {
-                    const int v = mad24(n2[4 * q + e], TAB.c2[i], mad24(n1[4 * q + e], TAB.c1[i], n0[4 * q + e]));
-                    const float t = __builtin_fmaf(float(v), TAB.inv[i], 12582912.0f);
-                    b[e] = uint32_t(mad24(int(__float_as_uint(t)), -MOD[i], v));
-                }
-            }
+            for (int e = 0; e < 4; ++e) b[e] = entry_residue(n0[4 * q + e], n1[4 * q + e], n2[4 * q + e], i);
             // the low bytes of the four
             const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
             w[q] = lo | hi;
@@ -339,7 +268,7 @@ constexpr int64_t PIECE_COLS = 2048;
 // eight waves of 128 x 64), so what counts is bytes out of LDS per product: these waves read two thirds of what those did.
 // A factor's products, us, eight waves : four: d_in 28672 91.7 : 87.4 ms (inner ranges of 8192 2171 : 2010, 2048 963 : 950, 1024
 // 494 : 508), 14336 in block form 5785 : 5643.
-// Accumulators start at 2^22 m; |sum| <= 2^14 MAX_K = 2^29 < 2^22 m, so they stay positive and below 2^31.
+// Accumulators start at 2^22 m, so they stay positive and below 2^31 (margins_hold).
 // Workgroup -> tile: patches of 32 tiles, each with one modulus, go round the XCDs (workgroup b runs on XCD b % 8), so that
 // the 32 tiles an XCD works on share their operands in its L2; with a triangular operand the longest patches come first.
 enum : int { FULL = 0, SYRK = 1, LOWER_B = 2, LOWER_A = 3 };
@@ -464,9 +393,6 @@ __global__ __launch_bounds__(256, 1) void product_kernel(ProductArgs g) {
     if (st + 2 < n_st) stage(std::integral_constant<int, 2>{});
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));   // no LDS write may be in flight when the workgroup ends
 
-    // sum mod m in [0, m): the fp32 quotient of a sum below 2^29 is off by 16 / m + 1 / 2 at most, so what it leaves lies within
-    // m / 2 + 17 of zero and is one m short where negative.  1.5 2^23 + q holds q + 2^22 in its low 24 bits, and 2^22 m is
-    // what the accumulator started with.
     const float inv = d_tab.inv[mod];
     const int l32 = lane & 31, lh = lane >> 5;
     uint32_t* const o = reinterpret_cast<uint32_t*>(g.out + mod * g.out_plane) + int64_t(tm * (TILE / 4) + wr * 32 + lh) * g.out_cols +
@@ -479,18 +405,12 @@ __global__ __launch_bounds__(256, 1) void product_kernel(ProductArgs g) {
             for (int q = 0; q < 4; ++q) {
                 uint32_t r[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int s = acc[i][j][4 * q + e];
-                    const float t = __builtin_fmaf(float(s - (m << 22)), inv, 12582912.0f);
-                    const uint32_t v = uint32_t(s - __mul24(int(__float_as_uint(t)), m));
-                    r[e] = min(v, v + uint32_t(m));
-                }
+                for (int e = 0; e < 4; ++e) r[e] = sum_residue(acc[i][j][4 * q + e], m, inv);
                 o[int64_t(i * 8 + 2 * q) * g.out_cols + j * 32] = r[0] | r[1] << 8 | r[2] << 16 | r[3] << 24;
             }
 }
 
-// C = beta C + alpha x from x's residues; a thread has four rows of a column.  x / M mod 1 = sum of r q / m, exactly but for
-// 2^-82: the upper parts of q / m add up without rounding.  copy: see update_columns.
+// C = beta C + alpha x from x's residues; a thread has four rows of a column.  copy: see update_columns.
 __global__ __launch_bounds__(256) void reconstruct_kernel(const char* __restrict__ res, int64_t plane, int res_cols, int rows,
                                                          int cols, const int32_t* __restrict__ sa,
                                                          const int32_t* __restrict__ sb, double* __restrict__ C, int64_t ldc,
@@ -509,15 +429,11 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(const char* __restrict
     for (int e = 0; e < 4; ++e) {
         const int row = row0 + e;
         if (row >= rows) break;
-        double hi = 0.0, lo = 0.0;
+        Fraction f;
 #pragma unroll
-        for (int i = 0; i < MODULI; ++i) {
-            const double r = double((w[i] >> (8 * e)) & 255u);
-            hi = __builtin_fma(r, TAB.hi[i], hi);
-            lo = __builtin_fma(r, TAB.lo[i], lo);
-        }
+        for (int i = 0; i < MODULI; ++i) f.add((w[i] >> (8 * e)) & 255u, i);
         const int32_t ea = sa[row];
-        double v = __builtin_ldexp(((hi - __builtin_rint(hi)) + lo) * scale, -(ea + eb));
+        double v = __builtin_ldexp(f.value() * scale, -(ea + eb));
         if (ea == NO_SHIFT || eb == NO_SHIFT) v = __builtin_nan("");
         v += c[e];
         C[int64_t(row) * ldc + col] = v;

@@ -1,16 +1,13 @@
 // Products of fp64 matrices from 8-bit integer matrix instructions (residue.hip).
 #pragma once
 #include "common.hpp"
+#include "residue_math.hpp"
 
 namespace onecomp {
 namespace residue {
 
-constexpr int MODULI = 14;
 constexpr int TILE = 256;     // rows and columns of a product tile
-constexpr int MAX_K = 1 << 15;   // longest inner range, see product_kernel
 constexpr int K_STEP = 64;    // inner ranges begin and end on multiples of this
-// shift of a row whose entries no scale fits: every product with it is NaN
-constexpr int32_t NO_SHIFT = INT32_MIN;
 
 inline int64_t pad_rows(int64_t n) { return ceil_div(n, TILE) * TILE; }
 inline int64_t pad_k(int64_t k) { return ceil_div(k, K_STEP) * K_STEP; }
