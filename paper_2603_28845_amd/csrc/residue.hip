@@ -432,9 +432,7 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(const char* __restrict
         Fraction f;
 #pragma unroll
         for (int i = 0; i < MODULI; ++i) f.add((w[i] >> (8 * e)) & 255u, i);
-        const int32_t ea = sa[row];
-        double v = __builtin_ldexp(f.value() * scale, -(ea + eb));
-        if (ea == NO_SHIFT || eb == NO_SHIFT) v = __builtin_nan("");
+        double v = unscaled(f.value() * scale, sa[row], eb);
         v += c[e];
         C[int64_t(row) * ldc + col] = v;
         if (copy && row >= 128 && row < 256 && col < 128) copy[(row - 128) * 128 + col] = v;

@@ -166,6 +166,12 @@ struct Fraction {
     }
     ONECOMP_RES double value() const { return (hi - __builtin_rint(hi)) + lo; }
 };
+// a product of rows with scales ea and eb without them
+ONECOMP_RES double unscaled(double v, int32_t ea, int32_t eb) {
+    const bool none = ea == NO_SHIFT || eb == NO_SHIFT;   // sums with NO_SHIFT overflow
+    v = __builtin_ldexp(v, none ? 0 : -(ea + eb));
+    return none ? __builtin_nan("") : v;
+}
 
 }  // namespace residue
 }  // namespace onecomp

@@ -93,6 +93,14 @@ int main() {
     }
     REQUIRE(shift_of(0.0) == 0, "scale of zero");
     for (double s : {-1.0, double(INFINITY), double(NAN)}) REQUIRE(shift_of(s) == NO_SHIFT, "scale of %a", s);
+
+    // rows without a scale, beside each other and beside ordinary ones, give NaN; no exponent is formed of theirs
+    for (int32_t a : {NO_SHIFT, -640, -1, 0, 1, 640})
+        for (int32_t b : {NO_SHIFT, -640, -1, 0, 1, 640}) {
+            const double v = unscaled(0.75, a, b);
+            if (a == NO_SHIFT || b == NO_SHIFT) REQUIRE(std::isnan(v), "%d, %d", a, b);
+            else REQUIRE(v == std::ldexp(0.75, -(a + b)), "%d, %d", a, b);
+        }
     std::printf("ok %ld\n", checked);
     return 0;
 }
