@@ -598,7 +598,7 @@ def test_factor_against_oracle(d_in, act):
 
 @pytest.mark.parametrize("d_in", [
     144, 192, 464, 1104, 3088,   # 64-wide tiles at every level of the inverse, ragged last tiles, a short last pair
-    12304,                       # 128-wide tiles at the top level, 64-wide below
+    12304,                       # top levels by residues but for a last pair of 16 rows; 64-wide tiles below
 ])
 def test_factor_inverse_levels(d_in):
     _announce(f"factor d_in={d_in}: every level of the triangular inverse")
@@ -623,7 +623,7 @@ def test_factor_inverse_levels(d_in):
 @pytest.mark.parametrize("d_in", [
     272,           # a last block of one sub-block
     5120, 5136,    # the inverse along with the factorization up to 40 blocks, by doubling from 41
-    7184, 7312,    # 57 and 58 blocks: trailing updates with lag 2, narrow ones once fewer than 56 columns trail
+    7184, 7312,    # 57 and 58 blocks in slabs of four, the last one of a short block or two (lagged updates: test_factor_beyond_residues)
 ])
 def test_factor_schedules(d_in):
     """U and the block form at the widths where the factor's launches change: the bound of test_factor_inverse_levels (the
@@ -652,6 +652,54 @@ def test_factor_schedules(d_in):
         off = blk[:, None] < blk[None, :]
         assert torch.all((F.double() - Fx)[off].abs() <= 2.0 ** -23 * Fx[off].abs() + 1e-12 * Fx[off].abs().max())
         assert torch.equal(F[blk[:, None] == blk[None, :]], U[blk[:, None] == blk[None, :]])
+
+
+def test_factor_beyond_residues():
+    """Wider than 32768 the whole factor is 64-bit: trailing updates with lag 4, then 2, then 1, 128-wide tiles in the inverse's
+    products.  H = 64 + X X^T with X of 16 columns of -1, 0 and 1 is exact in fp32, and its factors are known from matrices of 16 x 16
+    (q and p below), so every entry of both forms is checked: rounded once to fp32, the 64-bit work before it far below."""
+    n, k, c = 32896, 16, 64.0
+    _announce(f"factor d_in={n}: 64-bit throughout")
+    rng = np.random.default_rng(5)
+    Xn = rng.integers(-1, 2, size=(n, k)).astype(np.float64)
+    # U^T U = H^-1 = (I - X N X^T) / c, eliminated from the first row on; R R^T = H from the last one
+    N = np.linalg.inv(c * np.eye(k) + Xn.T @ Xn) / c
+    M = np.eye(k)
+    q, u, p, r = np.empty((n, k)), np.empty(n), np.empty((n, k)), np.empty(n)
+    for j in range(n):
+        v = N @ Xn[j]
+        u[j] = math.sqrt(1.0 / c - Xn[j] @ v)
+        q[j] = v / u[j]
+        N += np.outer(q[j], q[j])
+    for j in range(n - 1, -1, -1):
+        v = M @ Xn[j]
+        r[j] = math.sqrt(c + Xn[j] @ v)
+        p[j] = v / r[j]
+        M -= np.outer(p[j], p[j])
+    assert np.allclose(u * r, 1.0, rtol=1e-11)
+    X, q, u, p, r = (torch.from_numpy(a).to(DEV) for a in (Xn, q, u, p, r))
+    H = X.float() @ X.float().t()
+    H.diagonal().add_(c)
+    U = torch.empty_like(H)
+    ws = torch.empty(og.onecomp_factor_workspace_bytes(n), dtype=torch.uint8, device=DEV)
+    col = torch.arange(n, device=DEV)
+    for form in ("inverse", "block"):
+        og.onecomp_hessian_factor(H, 0.0, form=form, U=U, info=(info := torch.zeros(1, dtype=torch.int32, device=DEV)), workspace=ws)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        for a in range(0, n, 1024):
+            row = torch.arange(a, min(n, a + 1024), device=DEV)
+            ref = -(q[row] @ X.t())
+            if form == "block":
+                off = row[:, None] // 128 != col[None, :] // 128
+                ref = torch.where(off, -u[row, None] * (X[row] @ p.t()) / r[None, :], ref)
+            ref[col[None, :] <= row[:, None]] = 0.0
+            E = U[row].double()
+            assert torch.all(E[col[None, :] < row[:, None]] == 0.0)
+            assert float((E[torch.arange(row.numel()), row] / u[row] - 1.0).abs().max()) <= 2.0 ** -23
+            E[torch.arange(row.numel()), row] = 0.0
+            # per entry: half a unit of fp32, and some 2^-53 sqrt(n) times the condition number, 2^8.5, of the largest entries
+            assert torch.all((E - ref).abs() <= 2.0 ** -24 * ref.abs() + 2.0 ** -37 * ref.abs().max()), (form, a)
 
 
 @pytest.mark.parametrize("d_in,tokens", [
