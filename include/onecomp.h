@@ -157,8 +157,10 @@ onecomp_status onecomp_accumulate_describe(onecomp_dtype x_dtype, int64_t n_toke
  *             act_order == 0.
  *   U         [d_in x d_in] fp32 row-major, out: upper triangular with positive diagonal and
  *             U^T U = (H_d)^-1 for the (permuted) damped matrix H_d; the strict lower
- *             triangle is written as zeros.  Computed in fp64 (long products of wide factors in integers of 54 bits),
- *             rounded once to fp32.
+ *             triangle is written as zeros.  Computed in fp64, rounded once to fp32.  Widths of
+ *             6656 to 32768 take their long products from integers, multiples of 2^-54 of a row's
+ *             norm: entries below about 1e-6 of their row's norm may then be right to that norm
+ *             (some 1e-16 of it times the condition number) and not to their own size.
  *   info      device int32, out: 0 on success, k > 0 if the matrix is not positive definite
  *             (k is in 1..d_in and names the pivot, counted from the END of the
  *             permuted order, at which the factorization first met a non-positive value);

@@ -17,7 +17,8 @@
 //     V[C,A] = -V[C,C] (L[C,A] V[A,A]); every level is two batched GEMMs, so the whole inverse is
 //     ~2 log2(n/128) large launches instead of n/128 skinny ones.
 //   * wide factors (factor_slabs): left-looking over slabs of columns, whose updates, and the inverse's long products, are
-//     taken from 8-bit residues on the integer matrix cores (residue.hip) with no more rounding than in fp64.
+//     taken from 8-bit residues on the integer matrix cores (residue.hip), rounded against the norms of rows and columns as
+//     little as in fp64 (an entry's own size does not count: residue.hip).
 //   * ordering by rank counting (stable, deterministic), no floating-point atomics anywhere.
 #include "common.hpp"
 #include "planner.hpp"

@@ -751,6 +751,49 @@ def test_factor_by_residues(d_in, tokens):
         assert wrong <= 2.0 ** -15.5 * d_in * (d_in + 1) / 2
 
 
+@pytest.mark.parametrize("kind,damp", [("half rank", 1e-4), ("low rank and noise", 1e-4), ("exponential", 1e-2), ("band", 1e-2)])
+def test_factor_by_residues_structured(kind, damp):
+    """Wide factors of badly conditioned Gram matrices and of matrices whose factors decay away from the diagonal, where entries lie far
+    below the norms that the products' integers are measured by.  Every entry: half a unit of fp32, and the 64-bit work's error, 2^-53
+    sqrt(d_in) times the condition number of its row's norm (torch's own included).  Rows in the norm: their rounding."""
+    n = 8192
+    _announce(f"factor by residues, {kind}")
+    g = torch.Generator(device=DEV).manual_seed(31)
+    i = torch.arange(n, device=DEV)
+    if kind == "half rank":
+        X = torch.randn((n // 2, n), generator=g, device=DEV)
+    elif kind == "low rank and noise":
+        X = torch.randn((4096, 64), generator=g, device=DEV) @ torch.randn((64, n), generator=g, device=DEV)
+        X += 0.05 * torch.randn((4096, n), generator=g, device=DEV)
+    if kind == "exponential":
+        H = 4.0 * torch.pow(torch.tensor(0.9, device=DEV), (i[:, None] - i[None, :]).abs().float())
+    elif kind == "band":
+        H = torch.clamp(1.0 - (i[:, None] - i[None, :]).abs().float() / 32.0, min=0.0)
+    else:
+        H = X.t() @ X
+        H = (torch.triu(H) + torch.triu(H, 1).t()).contiguous()
+    Hd = H.double()
+    Hd.diagonal().add_(float(np.float32(damp)) * Hd.diagonal().mean())
+    v = torch.ones(n, dtype=torch.float64, device=DEV) + 0.1 * torch.randn(n, generator=g, device=DEV, dtype=torch.float64)
+    for _ in range(40):
+        v = Hd @ (v / v.norm())
+    cond = float(v.norm() / (damp * H.diagonal().double().mean()))   # at most: the damping is the least eigenvalue or below it
+    R = torch.linalg.cholesky(Hd.flip(0, 1)).flip(0, 1).contiguous()
+    N = torch.linalg.solve_triangular(R, torch.eye(n, dtype=torch.float64, device=DEV), upper=True)
+    blk = i // 128
+    for form in ("inverse", "block"):
+        if form == "block":
+            N = torch.where(blk[:, None] == blk[None, :], N, -R / R.diagonal()[None, :] / R.diagonal()[:, None])
+        U, _, info = og.onecomp_hessian_factor(H, damp, form=form)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        norm = N.norm(dim=1, keepdim=True)
+        E = (U.double() - N).abs()
+        _announce(f"   {form}: condition {cond:.1e}, rows {float((E.norm(dim=1, keepdim=True) / norm).max()):.1e}")
+        assert torch.all(E <= 2.0 ** -24 * N.abs() + 2.0 ** -53 * n ** 0.5 * cond * norm)
+        assert torch.all(E.norm(dim=1, keepdim=True) <= 2.0 ** -24 * norm)
+
+
 @pytest.mark.parametrize("entries,want", [
     ([(20, 20, -1.0)], 21),                                     # first slab
     ([(3000, 3000, -1.0)], 3001),                               # later slab: no scale fits its row
