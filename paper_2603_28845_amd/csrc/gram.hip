@@ -572,6 +572,10 @@ __global__ __launch_bounds__(Ring<C>::THREADS, C::MIN_WAVES) void gram_bf16_ring
         }
     };
 
+    // The paced loop has to begin 24 or 28 bytes into a 32-byte window: a call of 262144 tokens at d_in 14336 takes 42.4 ms there, 43.4 at
+    // 20 and 44.1 to 44.3 at 0 to 16.  (The loop without pauses takes the same anywhere.)  What the compiler places between here and
+    // the loop counts along: the ISA test looks where it begins.
+    if constexpr (PACED) asm volatile(".p2align 5\n\t.rept 6\n\ts_nop 0\n\t.endr");
     int s0 = 0;   // slot of step st
 #pragma unroll 1
     for (int64_t st = 0; st < n_st2; st += 2) {

@@ -51,6 +51,29 @@ def test_wide_gram_loop_is_straight_line(tmp_path):
     assert found == 3        # the symmetric kernel, its paced form and the cross kernel
 
 
+def test_paced_gram_loop_is_placed(tmp_path):
+    """The paced loop's place in the 32-byte windows of the instruction fetch is 4 % of the widest calls: 24 or 28 bytes into one."""
+    hipcc, objdump = shutil.which("hipcc") or "/opt/rocm/bin/hipcc", "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(hipcc) or not os.path.exists(objdump):
+        pytest.skip("no hipcc or llvm-objdump")
+    from paper_2603_28845_amd import build
+    out = tmp_path / "gram.co"
+    subprocess.run([hipcc, *build.HIPCC_FLAGS, *build.EXTRA_FLAGS.get("gram.hip", []), "-c", "--cuda-device-only", "--no-gpu-bundle-output",
+                    os.path.join(build.CSRC, "gram.hip"), "-o", str(out)], check=True, capture_output=True)
+    text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(out)], check=True, capture_output=True, text=True).stdout
+    body = re.search(r"^[0-9a-f]+ <\S*gram_bf16_ring_kernelINS\d+_8RingWideELb0ELb1E\S*>:\n(.*?)^\n", text + "\n", re.S | re.M).group(1)
+    ins = [(int(m.group(2), 16), m.group(1)) for m in re.finditer(r"^\s+(.*?)\s*// ([0-9A-F]+):", body, re.M)]
+    first, last = [a for a, i in ins if i.startswith("v_mfma")][::47]
+    starts = set()
+    for a, i in ins:
+        m = re.match(r"s_cbranch\S* (\d+)", i)
+        if m and a > last:
+            to = a + 4 + 4 * (int(m.group(1)) - (65536 if int(m.group(1)) >= 32768 else 0))
+            if first - 512 < to <= first:
+                starts.add(to)
+    assert len(starts) == 1 and starts.pop() % 32 in (24, 28)
+
+
 @pytest.fixture(scope="module")
 def isa(tmp_path_factory):
     return _isa(tmp_path_factory.mktemp("isa"))
