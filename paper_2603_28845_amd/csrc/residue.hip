@@ -161,7 +161,8 @@ __global__ __launch_bounds__(256) void convert_columns_kernel(const double* __re
 }
 
 // Rows of a matrix whose norms are known, a workgroup per 32 rows and 512 columns.  lower: entries right of the diagonal
-// count as zero and are not read; columns that no product tile of these rows takes are not written.  inner, here and below:
+// count as zero whatever they hold (up to the end of the rows' 256-wide tile they are read all the same); columns that no
+// product tile of these rows takes are not written.  inner, here and below:
 // column k of the left operand counts 2^inner[k] times, row k of the right one 2^-inner[k] times (nullptr: 1).
 constexpr int CV_CHUNK = 512;
 __global__ __launch_bounds__(256) void convert_rows_kernel(const double* __restrict__ src, int64_t ld, int rows, int k_len,
