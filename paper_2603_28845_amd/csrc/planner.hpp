@@ -143,7 +143,7 @@ ONECOMP_HD bool syrk_narrow_tile(int bid, int n_t, int inv_cols, int& tm, int& t
     tc = v + 2 - tm * (tm + 1);
     return true;
 }
-// Launches inside a slab of a left-looking factorization (factor_run), which has `cols` >= 1 block columns left: the tiles
+// Launches inside a slab of a left-looking factorization (factor_slabs), which has `cols` >= 1 block columns left: the tiles
 // above of the first 2 cols columns only.
 ONECOMP_HD int syrk_slab_tiles(int n_t, int cols) {
     const int c = imin(cols, n_t);

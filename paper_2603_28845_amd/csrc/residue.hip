@@ -9,8 +9,9 @@
 // in the root mean square whatever the length, less than a chain of fp64 additions leaves (measured against 80-bit sums:
 // 0.23 to 0.67 of its error at lengths of 1024 to 8192).  That is an error against the norms: a sum far below them, whose terms are
 // too, keeps fewer of its own digits than in fp64.  Gram matrices are no such case: entries of U that are not the rounded exact
-// ones, in fp64 : so, d_in 8192, half rank, damping 1e-2 1.6e-5 : 0.9e-5, 1e-4 9.4e-4 : 5.3e-4, 2e-5 3.9e-3 : 2.3e-3; full rank, channels of
-// log-normal scales 3.9e-7 : 4.8e-7.  Factors that decay away from the diagonal are: H = 0.9^|i - j| has as many digits in every
+// ones, in fp64 : so, activations with outlier channels, damping 1e-2, d_in 8192 1.9e-6 : 1.2e-6, 14336 2.4e-6 : 1.4e-6, 28672
+// 3.3e-6 : 1.9e-6 (block form 1.3e-6 : 0.8e-6); 8192, half rank, damping 1e-2 1.6e-5 : 0.9e-5, 1e-4 9.4e-4 : 5.3e-4, 2e-5
+// 3.9e-3 : 2.3e-3; full rank, channels of log-normal scales 3.9e-7 : 4.8e-7.  Factors that decay away from the diagonal are: H = 0.9^|i - j| has as many digits in every
 // entry above 1e-6 of its row's norm, wrong ones further down (all entries: 4.6 % : 7.5 % not the rounded ones).
 //
 // Why: the fp64 matrix rate is 77 TFLOP/s; 14 products at the 8-bit rate (3.6 POP/s in registers, 2.3 in a product out of
@@ -270,8 +271,9 @@ constexpr int64_t PIECE_COLS = 2048;
 // per SIMD (256 accumulators in AGPRs); both operands are in operand order, so a load is 1 KB of memory -> 1 KB of LDS and a
 // fragment is one conflict-free 16-byte read.  Steps of 64 through a ring of four slots of 32 KB; the operands of a step's first
 // half are read before the barrier that publishes the next step's, and reads and loads stand one by one behind MFMAs, so that
-// with a single wave per SIMD no MFMA waits for them.  The chip's power is the bound (MFMAs busy 73 % of the cycles at 1.49 GHz with
-// eight waves of 128 x 64), so what counts is bytes out of LDS per product: these waves read two thirds of what those did.
+// with a single wave per SIMD no MFMA waits for them.  In long launches the chip's power is the bound (4.3 ms at d_in 28672: MFMAs busy
+// 82 % of the cycles at 1.48 GHz, 2.54 POP/s; 0.3 ms: 43 to 60 % at 2.0 to 1.85 GHz, 1.9 to 2.35 POP/s, which start and end of a tile
+// take), so what counts is bytes out of LDS per product: these waves read two thirds of what eight of 128 x 64 did.
 // A factor's products, us, eight waves : four: d_in 28672 91.7 : 87.4 ms (inner ranges of 8192 2171 : 2010, 2048 963 : 950, 1024
 // 494 : 508), 14336 in block form 5785 : 5643.
 // Accumulators start at 2^22 m, so they stay positive and below 2^31 (margins_hold).

@@ -48,10 +48,11 @@ onecomp_status inner_exponents(const double* V, int n, int32_t* inner, hipStream
 
 // ---- C = alpha A B with one triangular operand ---------------------------------------------------------------------------
 // A m x k, B k x n, C m x n, row-major; lower_b: B is lower triangular (k == n), else A is (m == k); what lies above
-// counts as zero whatever it holds, but is read in part, so it has to be there and at rest.  C may be B.  alpha = +-1.  inner: nullptr, or powers of two by which the k terms of a sum are balanced between the
-// operands: column k of A counts 2^inner[k] times, row k of B 2^-inner[k] times, so that what the channels' own scales do to the
-// rows of one and the columns of the other cancels.  operands: operand_bytes bytes of scratch (an upper bound on the columns taken at a
-// time follows from it); product: product_len bytes of scratch; shift_a, shift_b: m and n entries.
+// counts as zero whatever it holds, but is read in part, so it has to be there and at rest.  C may be B.  alpha = +-1.
+// inner: nullptr, or powers of two by which the k terms of a sum are balanced between the operands: column k of A counts
+// 2^inner[k] times, row k of B 2^-inner[k] times, so that what the channels' own scales do to the rows of one and the columns of
+// the other cancels.  operands: operand_len bytes of scratch (an upper bound on the columns taken at a time follows from
+// it); product: product_len bytes of scratch; shift_a, shift_b: m and n entries.
 onecomp_status triangular_product(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int m,
                                   int n, int k, bool lower_b, double alpha, void* operands, size_t operand_len, void* product,
                                   size_t product_len, const int32_t* inner, int32_t* shift_a, int32_t* shift_b, hipStream_t stream);

@@ -1450,8 +1450,9 @@ __global__ __launch_bounds__(256) void operands_kernel(const float* __restrict__
 // Tiles are ranked so that each XCD (blockIdx % 8) owns a contiguous run, m fastest inside bands of 8 row tiles:
 // the workgroups resident on one XCD share their Dt and Un panels through its L2.
 // ------------------------------------------------------------------------------------------
-// The same with a 64 x 128 tile (32 x 64 per wave, 12 KB a step, six slots) for launches of few tiles, see launch_trailing.  An entry's products are added in the same order.  Rows of 64 left-operand entries are 128 bytes, eight
-// chunks: their position is c ^ ((r & 2) << 1).
+// The same with a 64 x 128 tile (32 x 64 per wave, 12 KB a step, six slots) for launches of few tiles, see launch_trailing.
+// An entry's products are added in the same order.  Rows of 64 left-operand entries are 128 bytes, eight chunks: their
+// position is c ^ ((r & 2) << 1).
 template <int MT_, int NT_, int NBUF_>   // 32 x 32 tiles of a wave, slots of the LDS ring
 struct TrailShape {
     static constexpr int MT = MT_, NT = NT_, NBUF = NBUF_, TM = 64 * MT, TN = 64 * NT, KT = 16;
@@ -1627,7 +1628,8 @@ __device__ __forceinline__ void trailing_tile(const TrailArgs& a, const int bid,
     for (int r = 0; r < N_FRAGS; ++r) rd(Fc, r, 0);
     __syncthreads();   // slot 0 is overwritten by the loads of the first half-iteration
 
-    // the MFMAs of one k-step: per row tile m the products lo*hi, hi*lo, hi*hi against the column tiles, consecutive MFMAs on different accumulators; `between(i)` is placed behind MFMA i
+    // the MFMAs of one k-step: per row tile m the products lo*hi, hi*lo, hi*hi against the column tiles, consecutive MFMAs on
+    // different accumulators; `between(i)` is placed behind MFMA i
     auto mma = [&](const Frags& f, auto&& between) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < N_MMA; ++i) {
@@ -2100,8 +2102,9 @@ onecomp_status sweep_run(const void* W, onecomp_dtype w_dtype, int64_t d_out, in
     const int n_u = int(d_in < PREP_WGS ? d_in : PREP_WGS), n_w = int(d_out < PREP_WGS ? d_out : PREP_WGS);
     float *const max_u = reinterpret_cast<float*>(w.Dh), *const max_w = max_u + PREP_WGS;   // the panels write Dh later
     auto prepare = [&](auto* W_) {
-        hipLaunchKernelGGL((prepare_kernel<std::remove_const_t<std::remove_pointer_t<decltype(W_)>>>), dim3(unsigned(n_u + n_w)), dim3(256), 0, stream, U, int(d_in), n_u, max_u, W_, d_out, perm,
-                           w.rowloss, max_w, w.W0p);
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(W_)>>;
+        hipLaunchKernelGGL(prepare_kernel<T>, dim3(unsigned(n_u + n_w)), dim3(256), 0, stream, U, int(d_in), n_u, max_u, W_, d_out,
+                           perm, w.rowloss, max_w, w.W0p);
     };
     if (w_dtype == ONECOMP_BF16) prepare(static_cast<const uint16_t*>(W));
     else prepare(static_cast<const float*>(W));
