@@ -224,7 +224,7 @@ ONECOMP_HD void cross_tile_from_rank(int v, int n_rt, int n_ct, int& ti, int& tk
 // tiles of that range in n_piece pieces of the token axis each, an eighth of all pieces per XCD; on an XCD the pieces run tile
 // after tile for one range of tokens, then for the next.  Returns false for a workgroup with nothing to do.
 // (With an eighth of the tiles and all their pieces instead, 36 tiles in 7 pieces are 35 workgroups on seven XCDs of 32 CUs and 7 on
-// the last: a second round.  us of a call, so : pieces dealt: d_in 1024, 8192 tokens 41.5 : 34.8; 1408, 32768 148 : 98; 2048, 32768
+// the last: a second round.  us of a call, so : pieces dealt: d_in 1408, 32768 tokens 148 : 98; 2048, 32768
 // 236 : 153; 3072, 32768 411 : 376; 3584, 16384 307 : 264; 8192, 98304 5960 : 5540.)
 struct RingWork {
     int v;         // tile rank in the order of the tile map
