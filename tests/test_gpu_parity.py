@@ -751,6 +751,25 @@ def test_factor_by_residues(d_in, tokens):
         assert wrong <= 2.0 ** -15.5 * d_in * (d_in + 1) / 2
 
 
+@pytest.mark.parametrize("d_in", [6784, 8320])
+def test_factor_by_residues_in_column_order(d_in):
+    """Wide factors under a column order are, bit for bit, those of the matrix in that order."""
+    _announce(f"factor by residues, ordered, d_in={d_in}")
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    X = torch.randn((2048, d_in), generator=g, device=DEV) * (0.5 + torch.rand(d_in, generator=g, device=DEV))
+    H = X.t() @ X
+    H = (torch.triu(H) + torch.triu(H, 1).t()).contiguous()
+    H.diagonal().add_(100.0)
+    for form in ("inverse", "block"):
+        U, perm, info = og.onecomp_hessian_factor(H, 0.0, act_order=True, form=form)
+        perm = perm.long()
+        assert torch.equal(perm, torch.argsort(H.diagonal(), descending=True, stable=True))
+        plain, _, _ = og.onecomp_hessian_factor(H[perm][:, perm].contiguous(), 0.0, form=form)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        assert torch.equal(U, plain)
+
+
 @pytest.mark.parametrize("kind,damp", [("half rank", 1e-4), ("low rank and noise", 1e-4), ("exponential", 1e-2), ("band", 1e-2)])
 def test_factor_by_residues_structured(kind, damp):
     """Wide factors of badly conditioned Gram matrices and of matrices whose factors decay away from the diagonal, where entries lie far
